@@ -38,7 +38,7 @@ STAGE_KERNEL = {
     "gemm_down": "gemm_mfma_kernel<0, 0, true, true, false",
     "gemm_dgrad_down_dswiglu": "gemm_mfma_kernel<0, 2, true, false, false",
     "gemm_dgrad_gate_up": "gemm_mfma_kernel<0, 0, true, false, false",
-    "wgrad_down": "gemm_mfma_kernel<1, 0, false, false, true",
+    "wgrad": "gemm_mfma_kernel<1, 0, false, false, true",
     "permute": "permute_kernel",
     "combine": "combine_kernel",
 }
@@ -91,9 +91,7 @@ def stage_model(cfg, rho_rows):
         "gemm_dgrad_down_dswiglu": (mm, 2.0 * R * d * f),
         "gating_bwd": ("hbm", T * M * 4 * 2 + R * 4 * 4),
         "gemm_dgrad_gate_up": (mm, 4.0 * R * d * f),
-        "wgrad_down": (mm, 2.0 * rho_rows * d * f),
-        "wgrad_gate": (mm, 2.0 * rho_rows * d * f),
-        "wgrad_up": (mm, 2.0 * rho_rows * d * f),
+        "wgrad": (mm, 6.0 * rho_rows * d * f),
         "router_wgrad": ("hbm", T * d * s + T * M * 4 + M * d * 4),
         "router_dgrad": ("hbm", T * M * 2 + M * d * s + T * d * s),          # bf16 storage only: its own small GEMM
         # sum of the k permuted gradient rows plus the router part (read as a precomputed row in bf16 storage)

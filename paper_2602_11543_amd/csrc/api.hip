@@ -330,21 +330,17 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     memcpy(g.group_expert, train_list, n_train);
     g.offset = at<int>(ctx, L.pub.offset);
     g.c_f32 = 1; g.accumulate = accumulate;
-    // dW_d[d,f] = dy[token]^T (gate * h) over the expert's rows
-    g.A[0] = dy; g.a_ms = 1; g.a_ks = d; g.a_rows = at<int>(ctx, L.row_token); g.a_elems = (long)T * d;
-    g.B[0] = at<void>(ctx, L.hg); g.b_ns = 1; g.b_ks = f; g.b_elems = R * f;
-    g.Mdim = d; g.Ndim = f; g.C[0] = d_w_down; g.c_ms = f; g.c_gs = (long)d * f;
+    // dW_d[d,f] = dy[token]^T (gate * h), dW_g[f,d] = da^T xp, dW_u[f,d] = db^T xp over the expert's rows, as one launch:
+    // a layer of a few thousand tokens has fewer tiles per matrix than the chip has CUs
+    g.n_sets = 3;
+    g.k_rows = at<int>(ctx, L.row_token);
+    g.a_ms = 1; g.b_ns = 1; g.Mdim = d; g.Ndim = f; g.c_gs = (long)d * f;
+    const long x_elems = (long)T * d, h_elems = R * f;
+    g.set[0] = {dy, at<void>(ctx, L.hg), d_w_down, x_elems, h_elems, d, f, f, d, f, 1, 0};
+    g.set[1] = {at<void>(ctx, L.da), x, d_w_gate, h_elems, x_elems, f, d, d, f, d, 0, 1};
+    g.set[2] = {at<void>(ctx, L.db), x, d_w_up, h_elems, x_elems, f, d, d, f, d, 0, 1};
     SPES_TRY(expert_gemm(dt, kGroupedK, kEpiStore, false, false, g, s));
-    prof_mark(1, "wgrad_down", s);
-    // dW_g[f,d] = da^T xp ; dW_u[f,d] = db^T xp
-    g.B[0] = x; g.b_rows = at<int>(ctx, L.row_token); g.b_ns = 1; g.b_ks = d; g.b_elems = (long)T * d;
-    g.a_ms = 1; g.a_ks = f; g.a_rows = nullptr; g.a_elems = R * f; g.Mdim = f; g.Ndim = d; g.c_ms = d; g.c_gs = (long)f * d;
-    g.A[0] = at<void>(ctx, L.da); g.C[0] = d_w_gate;
-    SPES_TRY(expert_gemm(dt, kGroupedK, kEpiStore, false, false, g, s));
-    prof_mark(1, "wgrad_gate", s);
-    g.A[0] = at<void>(ctx, L.db); g.C[0] = d_w_up;
-    SPES_TRY(expert_gemm(dt, kGroupedK, kEpiStore, false, false, g, s));
-    prof_mark(1, "wgrad_up", s);
+    prof_mark(1, "wgrad", s);
   }
   // dW_r[M,d] = dlogits^T x; the token axis is cut into chunks whose partial products are then added in a fixed order
   {

@@ -30,8 +30,7 @@ struct GemmArgs {
   const void* B[2];
   long a_elems, b_elems;  // matrix-core path: elements addressable from A[i] and from B[i] (reads beyond return zero)
   long a_ms, a_ks;        // element strides of A along m, k
-  const int* a_rows;      // optional gather: kRaggedM reads row a_rows[m] in place of m; kGroupedK reads row a_rows[k] in place of k
-  const int* b_rows;      // optional gather, kGroupedK with K-strided B only: B reads row b_rows[k] in place of k
+  const int* a_rows;      // optional gather, kRaggedM: A reads row a_rows[m] in place of m
   const float* row_scale; // kEpiDSwiglu: per-row factor (the gate of the routed pair)
   float* rowdot;          // kEpiDSwiglu: [gridDim.x, rowdot_stride] partial gate gradients
   long rowdot_stride;
@@ -58,6 +57,17 @@ struct GemmArgs {
   // kGroupedK
   int n_groups;
   int kchunk;             // offset == nullptr: group g contracts k in [g*kchunk, min(Kdim,(g+1)*kchunk))
+  // several contractions over the same groups in one launch (kGroupedK, kEpiStore into fp32, both operands K-strided):
+  // n_sets > 0 replaces A, B, C, their element counts and k strides, c_ms and Mdim / Ndim (which hold set 0's extents;
+  // the other sets have the same or the transposed shape)
+  int n_sets;
+  const int* k_rows;      // operands with a_gather / b_gather read row k_rows[k] in place of k
+  struct Set {
+    const void *A, *B;
+    void* C;
+    long a_elems, b_elems, a_ks, b_ks, c_ms;
+    int Mdim, Ndim, a_gather, b_gather;
+  } set[3];
   unsigned char group_expert[64];  // offset != nullptr: group g contracts rows [offset[e], offset[e+1]), e = group_expert[g]
 };
 

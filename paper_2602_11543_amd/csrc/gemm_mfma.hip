@@ -60,11 +60,6 @@ struct Cfg {
                                                             // permuted instead (kc_unit below)
   static constexpr int RP = 256 / CH;                       // rows staged per pass (K-contiguous operand)
   static constexpr int NA = BM / RP, NB = BN / RP;          // staging registers (uint4) per thread, K-contiguous
-  static constexpr int KPA_ = BM / 8 + 4, KPB_ = BN / 8 + 4;
-  // an operand's LDS region holds either layout: [row][k] with a padded row, or [k][row] (below) with a padded k-row
-  static constexpr int A_VEC = BM * PITCH > BK * KPA_ ? BM * PITCH : BK * KPA_;
-  static constexpr int B_VEC = BN * PITCH > BK * KPB_ ? BN * PITCH : BK * KPB_;
-  static constexpr int STAGE_VEC = A_VEC + B_VEC;
   // K-strided operand: [k][row] in LDS; a k-row of the tile is BM/8 (BN/8) chunks and 64 bytes of padding, so that
   // the four k-rows one transposing read touches start 16 banks apart
   static constexpr int KPA = BM / 8 + 4, KPB = BN / 8 + 4;  // k-row pitch in 16-byte units
@@ -72,7 +67,9 @@ struct Cfg {
   static constexpr int NAS = BK / KRA, NBS = BK / KRB;      // staging registers per thread, K-strided
   static constexpr int RA = NA > NAS ? NA : NAS;            // staging register counts covering both kinds
   static constexpr int RB = NB > NBS ? NB : NBS;
-  static_assert(BK * KPA <= A_VEC && BK * KPB <= B_VEC, "the [k][row] layout must fit the operand's LDS region");
+  // 16-byte units of an operand's LDS region: [row][k], or [k][row] (above) with a padded k-row
+  static constexpr int a_vec(bool kc) { return kc ? BM * PITCH : BK * KPA; }
+  static constexpr int b_vec(bool kc) { return kc ? BN * PITCH : BK * KPB; }
 };
 
 // Position (in 16-byte units) of chunk c of row `row` in the [row][k] LDS layout of a K-contiguous operand with CH
@@ -117,12 +114,15 @@ __device__ __forceinline__ uint2 lds_read_tr(const bf16_t* p) {
 constexpr int kGroupRows = 4;      // row tiles per group of the tile order (ragged-row GEMMs) ...
 constexpr int kGroupMinCols = 8;   // ... used when the output has at least this many column tiles
 
-// A_KG / B_KG: the K-strided operand A / B takes its k-rows through the index table a_rows / b_rows (the dy rows,
-// or the input rows, of an expert's routed pairs)
-template <int MODE, int EPI, bool A_KC, bool B_KC, bool A_KG, bool B_KG, typename C>
+// SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
+// and result; either operand of a set may take its k-rows through the index table k_rows (the dy rows, or the input
+// rows, of an expert's routed pairs)
+template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C>
 __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs g) {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, TM = C::TM, TN = C::TN, CH = C::CH, RP = C::RP;
-  __shared__ uint4 smem[2 * C::STAGE_VEC];
+  constexpr int A_VEC = C::a_vec(A_KC), STAGE_VEC = A_VEC + C::b_vec(B_KC);
+  constexpr int EP_VEC = 32 * (TN * 16 + 4);               // the four wavefronts' epilogue slabs (32 padded float rows each)
+  __shared__ uint4 smem[2 * STAGE_VEC > EP_VEC ? 2 * STAGE_VEC : EP_VEC];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, lq = lane >> 4;          // an MFMA operand: lane holds row l16, k = lq*8 .. lq*8+7 of a 32-wide k-step
   const int wm = wave >> 1, wn = wave & 1;
@@ -130,9 +130,11 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
 
   // ---- which tile ----
   const int n_base = MODE == kRaggedM ? g.n_base : 0;
-  const int gx = cdiv(g.Ndim - n_base, BNO);
+  int Mdim = g.Mdim, Ndim = g.Ndim;
+  int gx = cdiv(Ndim - n_base, BNO);
   long total;
-  if (MODE == kRaggedM) total = (long)(*g.n_tiles) * gx; else total = (long)g.n_groups * cdiv(g.Mdim, BM) * gx;
+  if (MODE == kRaggedM) total = (long)(*g.n_tiles) * gx; else total = (long)g.n_groups * cdiv(Mdim, BM) * gx;
+  if (SETS) total *= g.n_sets;
   long logical;
   if (MODE == kGroupedK && g.offset != nullptr) {
     // ragged contraction lengths: tiles are taken in block order (round-robin over the XCDs) and the groups are
@@ -145,6 +147,23 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     logical = (long)(blockIdx.x % kXcds) * per_xcd + slot;
     if (slot >= per_xcd || logical >= total) return;
   }
+  int set = 0;
+  if (SETS) {
+    // the sets of a group stand side by side, all of the longest group's tiles first; a set whose result is the
+    // transposed shape has the same number of (square) tiles
+    const long per_set = (long)cdiv(Mdim, BM) * gx;
+    const long pos = logical / per_set;
+    set = (int)(pos % g.n_sets);
+    logical = (pos / g.n_sets) * per_set + logical % per_set;
+    Mdim = g.set[set].Mdim; Ndim = g.set[set].Ndim;
+    gx = cdiv(Ndim, BNO);
+  }
+  const void* const opA0 = SETS ? g.set[set].A : g.A[0];
+  const void* const opB0 = SETS ? g.set[set].B : g.B[0];
+  void* const opC0 = SETS ? g.set[set].C : g.C[0];
+  const long a_ks = SETS ? g.set[set].a_ks : g.a_ks, b_ks = SETS ? g.set[set].b_ks : g.b_ks;
+  const long c_ms = SETS ? g.set[set].c_ms : g.c_ms;
+  const bool a_gather = SETS && g.set[set].a_gather, b_gather = SETS && g.set[set].b_gather;
   int nt;
   long mt_all;
   if (MODE == kRaggedM && gx >= kGroupMinCols) {
@@ -174,10 +193,10 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     k_begin = 0; k_end = g.Kdim;
     b_group = (long)e * g.b_gs;
   } else {
-    const int my = cdiv(g.Mdim, BM);
+    const int my = cdiv(Mdim, BM);
     int grp = (int)(mt_all / my);
     m0 = (mt_all % my) * BM;
-    m_end = min((long)g.Mdim, m0 + BM);
+    m_end = min((long)Mdim, m0 + BM);
     if (g.offset != nullptr) {
       // grp counts positions in descending order of length; find the group that holds this position
       // (lane j < n_groups owns group j; ties go to the lower group, so the order is a permutation)
@@ -202,10 +221,11 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   // lane that is fixed for the whole tile, and a uniform offset that moves with the K-tile.  Nothing in the loop
   // computes an address, and no clamp is needed for memory safety: a read inside the tensor but outside the tile
   // returns data that is never used (masked k tail, rows that are not stored), a read beyond the tensor returns zero.
-  const unsigned a_bytes = (unsigned)(g.a_elems * 2), b_bytes = (unsigned)((g.b_elems - b_group) * 2);
-  const rsrc_t a_rsrc[2] = {make_rsrc(g.A[0], a_bytes), make_rsrc(g.A[1] ? g.A[1] : g.A[0], a_bytes)};
-  const rsrc_t b_rsrc[2] = {make_rsrc(reinterpret_cast<const bf16_t*>(g.B[0]) + b_group, b_bytes),
-                            make_rsrc(reinterpret_cast<const bf16_t*>(g.B[1] ? g.B[1] : g.B[0]) + b_group, b_bytes)};
+  const unsigned a_bytes = (unsigned)((SETS ? g.set[set].a_elems : g.a_elems) * 2);
+  const unsigned b_bytes = (unsigned)(((SETS ? g.set[set].b_elems : g.b_elems) - b_group) * 2);
+  const rsrc_t a_rsrc[2] = {make_rsrc(opA0, a_bytes), make_rsrc(!SETS && g.A[1] ? g.A[1] : opA0, a_bytes)};
+  const rsrc_t b_rsrc[2] = {make_rsrc(reinterpret_cast<const bf16_t*>(opB0) + b_group, b_bytes),
+                            make_rsrc(reinterpret_cast<const bf16_t*>(!SETS && g.B[1] ? g.B[1] : opB0) + b_group, b_bytes)};
   // K-contiguous operands: byte offset of this thread's chunk in K-tile 0, per staging register
   unsigned aoff[A_KC ? C::NA : 1];
   unsigned boff[B_KC ? C::NB : 1];
@@ -260,28 +280,23 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   int l_step = 0, l_kq = 0, l_pass = 0;           // tile number, k of the tile relative to the group, pass
   const int klen32 = (int)(k_end - k_begin);
   // K-strided operands: byte offset of this thread's chunk in k-row 0 of K-tile 0
-  const unsigned a_ks_off = (unsigned)(((long)(tid / (BM / 8)) * g.a_ks + m0 + (tid % (BM / 8)) * 8) * 2);
-  const unsigned b_ks_off = (unsigned)(((long)(tid / (BN / 8)) * g.b_ks + n0 + (tid % (BN / 8)) * 8) * 2);
-  // gathered k-rows of the tile about to be loaded; fetched one tile ahead so that no load waits on an index
+  const unsigned a_ks_off = (unsigned)(((long)(tid / (BM / 8)) * a_ks + m0 + (tid % (BM / 8)) * 8) * 2);
+  const unsigned b_ks_off = (unsigned)(((long)(tid / (BN / 8)) * b_ks + n0 + (tid % (BN / 8)) * 8) * 2);
+  // SETS: k-rows of the tile about to be loaded, from the index table (kidx, fetched one tile ahead so that no load
+  // waits on an index) or in their own order; both operands' tiles have the same k-row per thread and register
   constexpr int ACH = BM / 8, BCH = BN / 8;     // 16-byte chunks per k-row of a K-strided tile
-  int kidx[A_KG ? C::NAS : 1];
-  int kidx_b[B_KG ? C::NBS : 1];
+  int kidx[SETS ? C::NAS : 1];
+  int kdir = 0;
   auto load_kidx = [&](int step) {
-    if (A_KG) {
+    if (SETS) {
       const int st = step < nsteps ? step : nsteps - 1;
       const long k = k_begin + (long)(st % nk) * BK + tid / ACH;
 #pragma unroll
-      for (int j = 0; j < C::NAS; ++j) kidx[j] = g.a_rows[k + j * C::KRA < k_end ? k + j * C::KRA : k_end - 1];
+      for (int j = 0; j < C::NAS; ++j) kidx[j] = g.k_rows[k + j * C::KRA < k_end ? k + j * C::KRA : k_end - 1];
     }
   };
-  auto load_kidx_b = [&](int step) {
-    if (B_KG) {
-      const int st = step < nsteps ? step : nsteps - 1;
-      const long k = k_begin + (long)(st % nk) * BK + tid / BCH;
-#pragma unroll
-      for (int j = 0; j < C::NBS; ++j) kidx_b[j] = g.b_rows[k + j * C::KRB < k_end ? k + j * C::KRB : k_end - 1];
-    }
-  };
+  const unsigned a_pitch = (unsigned)(a_ks * 2), b_pitch = (unsigned)(b_ks * 2);
+  const unsigned a_col = (unsigned)((m0 + (tid % ACH) * 8) * 2), b_col = (unsigned)((n0 + (tid % BCH) * 8) * 2);
   // registers 0..n-1 of a K-strided operand hold k-rows inside the contraction range
   // (first_kq = k of the thread's first register relative to the group; rows_per_pass is a power of two)
   auto keep_bits = [&](int first_kq, int rows_per_pass, int nreg) -> unsigned {
@@ -294,6 +309,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     l_pass = step / nk;
     l_step = step;
     l_kq = (step - l_pass * nk) * BK;
+    if (SETS) kdir = (int)k_begin + l_kq + tid / ACH;
     if (A_KC) {
       a_keep_n = (l_kq + (tid % CH) * 8 < klen32) ? 0xffu : 0u;
     } else {
@@ -310,11 +326,11 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     const rsrc_t rs = l_pass ? a_rsrc[1] : a_rsrc[0];
     if (A_KC) {
       ra[idx] = buffer_load16(rs, aoff[idx], (unsigned)((k_begin + l_kq) * 2));
-    } else if (A_KG) {
-      ra[idx] = buffer_load16(rs, (unsigned)kidx[idx] * (unsigned)(g.a_ks * 2) + (unsigned)((m0 + (tid % ACH) * 8) * 2), 0u);
-      if (idx == C::NAS - 1) load_kidx(l_step + 1);
+    } else if (SETS) {
+      const unsigned row = (unsigned)(a_gather ? kidx[idx] : kdir + idx * C::KRA);
+      ra[idx] = buffer_load16(rs, row * a_pitch + a_col, 0u);
     } else {
-      ra[idx] = buffer_load16(rs, a_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRA) * g.a_ks * 2));
+      ra[idx] = buffer_load16(rs, a_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRA) * a_ks * 2));
     }
   };
   auto load_b = [&](int idx) {
@@ -322,19 +338,19 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
       // (the register -> matrix assignment of the fused SwiGLU is the same for every thread)
       const bool second = (EPI == kEpiSwiglu) ? (((RP * idx) % SW_W) / SW_H) != 0 : l_pass != 0;
       rb[idx] = buffer_load16(second ? b_rsrc[1] : b_rsrc[0], boff[idx], (unsigned)((k_begin + l_kq) * 2));
-    } else if (B_KG) {
-      rb[idx] = buffer_load16(l_pass ? b_rsrc[1] : b_rsrc[0],
-                              (unsigned)kidx_b[idx] * (unsigned)(g.b_ks * 2) + (unsigned)((n0 + (tid % BCH) * 8) * 2), 0u);
-      if (idx == C::NBS - 1) load_kidx_b(l_step + 1);
+    } else if (SETS) {
+      const unsigned row = (unsigned)(b_gather ? kidx[idx] : kdir + idx * C::KRB);
+      rb[idx] = buffer_load16(b_rsrc[0], row * b_pitch + b_col, 0u);
+      if (idx == C::NBS - 1) load_kidx(l_step + 1);      // the last use of this tile's indices
     } else {
-      rb[idx] = buffer_load16(l_pass ? b_rsrc[1] : b_rsrc[0], b_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRB) * g.b_ks * 2));
+      rb[idx] = buffer_load16(l_pass ? b_rsrc[1] : b_rsrc[0], b_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRB) * b_ks * 2));
     }
   };
   // `masked`: the tile may reach beyond the contraction range and its k tail is zeroed on the way into LDS.  Only the
   // last K-tile of a pass can need that; every other tile goes to LDS as it came (the four selects per register are
   // most of the vector-ALU work of an iteration, and the matrix pipe waits while they issue).
   auto write_a = [&](int stage, int idx, bool masked) {
-    uint4* ta = smem + stage * C::STAGE_VEC;
+    uint4* ta = smem + stage * STAGE_VEC;
     if (A_KC) {
       ta[kc_unit<CH>(tid / CH + RP * idx, tid % CH)] = masked ? sel4(a_keep != 0, ra[idx]) : copy4(ra[idx]);
     } else {
@@ -342,7 +358,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     }
   };
   auto write_b = [&](int stage, int idx, bool masked) {
-    uint4* tb = smem + stage * C::STAGE_VEC + C::A_VEC;
+    uint4* tb = smem + stage * STAGE_VEC + A_VEC;
     if (B_KC) {
       tb[kc_unit<CH>(tid / CH + RP * idx, tid % CH)] = masked ? sel4(b_keep != 0, rb[idx]) : copy4(rb[idx]);
     } else {
@@ -364,7 +380,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   const int tr_k = lq * 8 + (lane & 15) / 4;                     // k-row (within a k-step) this lane points the transposing read at
   const int tr_r = (lane & 3) * 4;                               // row (within a 16-row MFMA tile) likewise
   auto read_frag_a = [&](int stage, int ks, int set, int i) {
-    const uint4* ta = smem + stage * C::STAGE_VEC;
+    const uint4* ta = smem + stage * STAGE_VEC;
     if (A_KC) {
       fa[set][i] = __builtin_bit_cast(bf16x8, ta[kc_unit<CH>(wm * (BM / 2) + i * 16 + l16, ks * 4 + lq)]);
     } else {
@@ -374,7 +390,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     }
   };
   auto read_frag_b = [&](int stage, int ks, int set, int j) {
-    const uint4* tb = smem + stage * C::STAGE_VEC + C::A_VEC;
+    const uint4* tb = smem + stage * STAGE_VEC + A_VEC;
     if (B_KC) {
       fb[set][j] = __builtin_bit_cast(bf16x8, tb[kc_unit<CH>(wn * (BN / 2) + j * 16 + l16, ks * 4 + lq)]);
     } else {
@@ -397,7 +413,6 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   if (nsteps > 0) {
     // prologue: tile 0 -> registers -> LDS stage 0, tile 1 -> registers
     load_kidx(0);
-    load_kidx_b(0);
     set_load_tile(0);
 #pragma unroll
     for (int p = 0; p < NP; ++p) piece(p, 0, false, true, true);
@@ -479,7 +494,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   // output addresses are a per-tile base (uniform) plus a 32-bit element offset: row within the tile times the row
   // stride plus the column; rows are compared with the tile's valid row count in 32 bits as well
   const int e_rows = (int)(m_end - m0);
-  const long e_tile = c_group + m0 * g.c_ms;
+  const long e_tile = c_group + m0 * c_ms;
   const int e_r0 = wm * (BM / 2);
   // dSwiGLU epilogue: lanes lie along the columns (DS_CPR lanes per row, eight columns each, so that the bf16
   // results leave in 16-byte stores); the saved fp32 projections come in batches of half a 32-row slab
@@ -487,10 +502,10 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   const int ds_c8 = lane % DS_CPR;
   const long ds_n = n0 + wn * (BN / 2) + ds_c8 * 8;
   // addresses are a per-tile base (uniform) plus a 32-bit offset: one register per address instead of two
-  const long ds_tile = m0 * g.c_ms;
+  const long ds_tile = m0 * c_ms;
   const int ds_rows = (int)(m_end - m0);                        // valid rows of the tile
   const int ds_r0 = wm * (BM / 2) + lane / DS_CPR;
-  const bool ds_nin = ds_n < g.Ndim;
+  const bool ds_nin = ds_n < Ndim;
   const unsigned ds_ncl = ds_nin ? (unsigned)ds_n : 0u;
   const bf16_t* ds_a = reinterpret_cast<const bf16_t*>(g.E[0]) + ds_tile;
   const bf16_t* ds_b = reinterpret_cast<const bf16_t*>(g.E[1]) + ds_tile;
@@ -504,7 +519,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
 #pragma unroll
       for (int q = 0; q < DS_HALF; ++q) {
         const int rt = ds_r0 + i * 32 + (hf * DS_HALF + q) * DS_RPI;     // row within the tile
-        const unsigned ci = (unsigned)(rt < ds_rows ? rt : ds_rows - 1) * (unsigned)g.c_ms + ds_ncl;
+        const unsigned ci = (unsigned)(rt < ds_rows ? rt : ds_rows - 1) * (unsigned)c_ms + ds_ncl;
         av[q] = *reinterpret_cast<const uint4*>(ds_a + ci);
         bv[q] = *reinterpret_cast<const uint4*>(ds_b + ci);
         dv[q] = *reinterpret_cast<const uint4*>(ds_d + ci);
@@ -512,6 +527,27 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     }
   };
   load_ab(0, 0);
+  // fp32 store epilogue: lanes along the columns, four of them per lane.  When the result is added to what is there,
+  // the old values of a whole 32-row slab are requested before the previous slab is stored (see load_ab: a load behind
+  // a store waits for that store, and one load, add, store chain per two rows would be 64 round trips a tile; with the
+  // three matrices in one launch this took a step of gradient accumulation at 4096 tokens, 2048 x 2048, 8 of 32 experts
+  // from 1619 to 1471 us)
+  constexpr int F_CPR = ECOLS / 4, F_RPI = 64 / F_CPR, F_NST = 32 / F_RPI;
+  const long f_n = n0 + wn * (BN / 2) + (lane % F_CPR) * 4;
+  float* const f_ct = reinterpret_cast<float*>(opC0) + e_tile;
+  const bool f_add = EPI == kEpiStore && g.c_f32 && g.accumulate;
+  float4 f_old[EPI == kEpiStore ? F_NST : 1];
+  auto load_old = [&](int i) {
+    if (EPI == kEpiStore) {
+#pragma unroll
+      for (int st = 0; st < F_NST; ++st) {
+        const int rt = e_r0 + i * 32 + st * F_RPI + lane / F_CPR;
+        f_old[st] = *reinterpret_cast<const float4*>(
+            f_ct + ((unsigned)(rt < e_rows ? rt : e_rows - 1) * (unsigned)c_ms + (unsigned)(f_n < Ndim ? f_n : 0)));
+      }
+    }
+  };
+  if (f_add) load_old(0);
   __syncthreads();                                   // the staging tiles are dead from here on
 #pragma unroll
   for (int i = 0; i < TS; ++i) {
@@ -529,8 +565,8 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
       constexpr int CPR = ECOLS / 8, RPI = 64 / CPR;   // lanes per row (eight columns each), rows per access
       const int c8 = lane % CPR;
       const long n = n0 + wn * (BN / 2) + c8 * 8;
-      const bool n_in = n < g.Ndim;
-      bf16_t* ct = reinterpret_cast<bf16_t*>(g.C[0]) + e_tile;
+      const bool n_in = n < Ndim;
+      bf16_t* ct = reinterpret_cast<bf16_t*>(opC0) + e_tile;
 #pragma unroll
       for (int st = 0; st < 32 / RPI; ++st) {
         const int row = st * RPI + lane / CPR;
@@ -538,7 +574,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
         const uint2 hi = *reinterpret_cast<const uint2*>(eb + row * BPITCH + c8 * 16 + 8);
         const int rt = e_r0 + i * 32 + row;
         if (rt < e_rows && n_in)
-          *reinterpret_cast<uint4*>(ct + ((unsigned)rt * (unsigned)g.c_ms + (unsigned)n)) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+          *reinterpret_cast<uint4*>(ct + ((unsigned)rt * (unsigned)c_ms + (unsigned)n)) = make_uint4(lo.x, lo.y, hi.x, hi.y);
       }
       continue;
     }
@@ -557,22 +593,20 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
             make_float4(acc[j][2 * i + ii][0], acc[j][2 * i + ii][1], acc[j][2 * i + ii][2], acc[j][2 * i + ii][3]);
       }
     if (EPI == kEpiStore) {
-      constexpr int CPR = ECOLS / 4, RPI = 64 / CPR;   // lanes per row, rows per access
-      const int c4 = lane % CPR;
-      const long n = n0 + wn * (BN / 2) + c4 * 4;
-      const bool n_in = n < g.Ndim;
-      float* ct = reinterpret_cast<float*>(g.C[0]) + e_tile;
+      const bool n_in = f_n < Ndim;
+      float4 out[F_NST];
 #pragma unroll
-      for (int st = 0; st < 32 / RPI; ++st) {
-        const int row = st * RPI + lane / CPR;
-        const float4 v = *reinterpret_cast<const float4*>(ep + row * EPITCH + c4 * 4);
-        const int rt = e_r0 + i * 32 + row;
-        if (rt < e_rows && n_in) {
-          float4* c = reinterpret_cast<float4*>(ct + ((unsigned)rt * (unsigned)g.c_ms + (unsigned)n));
-          float4 o = v;
-          if (g.accumulate) { const float4 old = *c; o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w; }
-          *c = o;
-        }
+      for (int st = 0; st < F_NST; ++st) {
+        out[st] = *reinterpret_cast<const float4*>(ep + (st * F_RPI + lane / F_CPR) * EPITCH + (lane % F_CPR) * 4);
+        if (f_add) { out[st].x += f_old[st].x; out[st].y += f_old[st].y; out[st].z += f_old[st].z; out[st].w += f_old[st].w; }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (f_add && i + 1 < TS) load_old(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int st = 0; st < F_NST; ++st) {
+        const int rt = e_r0 + i * 32 + st * F_RPI + lane / F_CPR;
+        if (rt < e_rows && n_in) *reinterpret_cast<float4*>(f_ct + ((unsigned)rt * (unsigned)c_ms + (unsigned)f_n)) = out[st];
       }
     } else if (EPI == kEpiSwiglu) {
       // LDS columns [0, ECOLS/2) hold the gate projection, [ECOLS/2, ECOLS) the up projection of the same output columns,
@@ -582,7 +616,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
       static_assert(EPI != kEpiSwiglu || (TN == 8 && ECOLS == 128), "lane layout of the SwiGLU epilogue");
       const int c8 = lane & 7, rsel = lane >> 3;
       const long n = n0 + wn * (BN / 4) + c8 * 8;
-      const bool n_in = n < g.Ndim;
+      const bool n_in = n < Ndim;
       bf16_t* cat = reinterpret_cast<bf16_t*>(g.C[0]) + e_tile;
       bf16_t* cbt = reinterpret_cast<bf16_t*>(g.C[1]) + e_tile;
       bf16_t* cht = reinterpret_cast<bf16_t*>(g.C[2]) + e_tile;
@@ -595,7 +629,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
         const float4 b0 = *reinterpret_cast<const float4*>(rp + ECOLS / 2), b1 = *reinterpret_cast<const float4*>(rp + 3 * ECOLS / 4);
         const int rt = e_r0 + i * 32 + row;
         if (rt < e_rows && n_in) {
-          const unsigned ci = (unsigned)rt * (unsigned)g.c_ms + (unsigned)n;
+          const unsigned ci = (unsigned)rt * (unsigned)c_ms + (unsigned)n;
           const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w}, b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
           // The backward needs a and b only to bf16 accuracy, but h = SiLU(a) b nearly to fp32 accuracy (its gate
           // gradient is a difference of nearly equal sums when experts are near copies).  Saved are therefore a and b
@@ -678,7 +712,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
         for (int q = 0; q < DS_HALF; ++q) {
           const int rt = ds_r0 + i * 32 + (hf * DS_HALF + q) * DS_RPI;
           if (rt < ds_rows && ds_nin) {
-            const unsigned ci = (unsigned)rt * (unsigned)g.c_ms + ds_ncl;
+            const unsigned ci = (unsigned)rt * (unsigned)c_ms + ds_ncl;
             *reinterpret_cast<uint4*>(ds_c0 + ci) = oa[q];
             *reinterpret_cast<uint4*>(ds_c1 + ci) = ob[q];
             if (ds_store2) *reinterpret_cast<uint4*>(ds_c2 + ci) = oh[q];
@@ -702,21 +736,26 @@ typedef Cfg<128, 256, 64, 1> TileShort;
 // and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's
 typedef Cfg<128, 128, 64, 2> TileSmall;
 
-template <int MODE, int EPI, bool A_KC, bool B_KC, bool A_KG = false, bool B_KG = false, typename C = Tile>
+template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false>
 int launch(const GemmArgs& g, hipStream_t s) {
-  static_assert(!A_KG || !A_KC, "k-row gather: K-strided A only");
-  static_assert(!B_KG || (!B_KC && MODE == kGroupedK), "k-row gather of B: K-strided B of a grouped contraction only");
-  static_assert(!(A_KG && B_KG), "one gathered operand per launch");
-  if (B_KG && g.npairs != 1) return SPES_EINVAL;
+  static_assert(!SETS || (MODE == kGroupedK && !A_KC && !B_KC && C::BM == C::BN), "operand sets: K-strided, square tiles");
   // operands are addressed with 32-bit byte offsets from their base
-  if (g.a_elems <= 0 || g.b_elems <= 0) return SPES_EINVAL;
-  if (g.a_elems >= (1L << 31) || g.b_elems >= (1L << 31)) return SPES_ESHAPE;
+  if (SETS) {
+    for (int i = 0; i < g.n_sets; ++i) {
+      if (g.set[i].a_elems <= 0 || g.set[i].b_elems <= 0) return SPES_EINVAL;
+      if (g.set[i].a_elems >= (1L << 31) || g.set[i].b_elems >= (1L << 31)) return SPES_ESHAPE;
+    }
+  } else {
+    if (g.a_elems <= 0 || g.b_elems <= 0) return SPES_EINVAL;
+    if (g.a_elems >= (1L << 31) || g.b_elems >= (1L << 31)) return SPES_ESHAPE;
+  }
   const int bno = (EPI == kEpiSwiglu) ? C::BN / 2 : C::BN;
   const int gx = cdiv(g.Ndim - (MODE == kRaggedM ? g.n_base : 0), bno);
   long total = (MODE == kRaggedM) ? (long)g.max_tiles * gx : (long)g.n_groups * cdiv(g.Mdim, C::BM) * gx;
+  if (SETS) total *= g.n_sets;
   if (total <= 0) return SPES_OK;
   total = (total + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL((gemm_mfma_kernel<MODE, EPI, A_KC, B_KC, A_KG, B_KG, C>), dim3((unsigned)total), dim3(256), 0, s, g);
+  hipLaunchKernelGGL((gemm_mfma_kernel<MODE, EPI, A_KC, B_KC, SETS, C>), dim3((unsigned)total), dim3(256), 0, s, g);
   return hipGetLastError() == hipSuccess ? SPES_OK : SPES_EHIP;
 }
 
@@ -732,6 +771,12 @@ static bool few_tiles_narrow(int ndim, int est_tiles) {
   return rounds_full <= 4 && 0.6 * rounds_half < 0.95 * rounds_full;
 }
 
+// Weight gradients: at most this many 256 x 256 tiles over all sets go to 128 x 128 tiles, two blocks per CU.  A launch
+// of that few full tiles is one round, or little more, of tiles that are mostly prologue and epilogue; measured on a
+// whole step, all three gradients in one launch of small tiles against three of full ones: 96 full tiles (1531 tokens,
+// 512 x 352) 350 -> 238 us, 90 tiles (3777 tokens, 1536 x 1280) 447 -> 396 us, 288 tiles (768 x 2048) 590 -> 555 us.
+constexpr long kSmallTilesBelow = 320;
+
 int mfma_row_tile() { return Tile::BM; }
 // number of gate-gradient partials per row that the kEpiDSwiglu epilogue writes for ndim columns (two per column tile)
 int mfma_rowdot_parts(int ndim, int est_tiles) {
@@ -741,7 +786,7 @@ int mfma_rowdot_parts(int ndim, int est_tiles) {
 // bf16 operands only.  a_kcontig / b_kcontig: the contraction index is the fast memory axis of that operand.
 int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
   if (mode == kRaggedM) {
-    if (!a_kcontig || g.b_rows) return SPES_EINVAL;
+    if (!a_kcontig) return SPES_EINVAL;
     // A last column tile that is at most half full goes to a launch of its own on the half-width tile (which costs
     // 0.6 of a full one) instead of running a full-width tile on half-empty operands.
     const int tail = g.Ndim % Tile::BN;
@@ -753,15 +798,15 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
       rest.rowdot_slot0 = 2 * (head.Ndim / Tile::BN);
       const int rc = launch_gemm_mfma(mode, epi, a_kcontig, b_kcontig, head, s);
       if (rc != SPES_OK) return rc;
-      if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, false, false, TileNarrow>(rest, s);
-      if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, false, false, TileNarrow>(rest, s);
-      if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, false, false, TileNarrow>(rest, s);
+      if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, TileNarrow>(rest, s);
+      if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, TileNarrow>(rest, s);
+      if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, TileNarrow>(rest, s);
       return SPES_EINVAL;
     }
     if (epi != kEpiSwiglu && g.n_base == 0 && few_tiles_narrow(g.Ndim, g.est_tiles)) {
-      if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, false, false, TileNarrow>(g, s);
-      if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, false, false, TileNarrow>(g, s);
-      if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, false, false, TileNarrow>(g, s);
+      if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, TileNarrow>(g, s);
+      if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, TileNarrow>(g, s);
+      if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, TileNarrow>(g, s);
       return SPES_EINVAL;
     }
     if (epi == kEpiSwiglu && b_kcontig) return launch<kRaggedM, kEpiSwiglu, true, true>(g, s);
@@ -772,16 +817,19 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
   }
   if (epi != kEpiStore) return SPES_EINVAL;
   if (a_kcontig && b_kcontig)
-    return g.Ndim <= TileNarrow::BN ? launch<kGroupedK, kEpiStore, true, true, false, false, TileNarrow>(g, s)
+    return g.Ndim <= TileNarrow::BN ? launch<kGroupedK, kEpiStore, true, true, TileNarrow>(g, s)
                                     : launch<kGroupedK, kEpiStore, true, true>(g, s);
   if (a_kcontig && !b_kcontig)
-    return (g.kchunk <= TileSmall::BK && g.n_groups == 1) ? launch<kGroupedK, kEpiStore, true, false, false, false, TileSmall>(g, s)
+    return (g.kchunk <= TileSmall::BK && g.n_groups == 1) ? launch<kGroupedK, kEpiStore, true, false, TileSmall>(g, s)
                                                           : launch<kGroupedK, kEpiStore, true, false>(g, s);
-  if (g.b_rows && (a_kcontig || b_kcontig || g.a_rows)) return SPES_EINVAL;
   if (!a_kcontig && !b_kcontig) {
-    if (g.a_rows) return launch<kGroupedK, kEpiStore, false, false, true>(g, s);
-    if (g.b_rows) return launch<kGroupedK, kEpiStore, false, false, false, true>(g, s);
-    if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, false, false, TileShort>(g, s);
+    if (g.n_sets > 0) {
+      // 128 x 128 tiles, two blocks per CU, where the 256 x 256 ones would not give every CU one
+      const long tiles = (long)g.n_sets * g.n_groups * cdiv(g.Mdim, Tile::BM) * cdiv(g.Ndim, Tile::BN);
+      if (tiles <= kSmallTilesBelow) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
+      return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
+    }
+    if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);
     return launch<kGroupedK, kEpiStore, false, false>(g, s);
   }
   return SPES_EINVAL;

@@ -33,6 +33,14 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   const int tx = tid & 15, ty = tid >> 4;
   const int n0 = blockIdx.x * BN;
 
+  // operand set of this block (kGroupedK with several contractions over the same groups)
+  const bool sets = MODE == kGroupedK && g.n_sets > 0;
+  const GemmArgs::Set& st = g.set[sets ? blockIdx.z % g.n_sets : 0];
+  const int Mdim = sets ? st.Mdim : g.Mdim, Ndim = sets ? st.Ndim : g.Ndim;
+  const long a_ks = sets ? st.a_ks : g.a_ks, b_ks = sets ? st.b_ks : g.b_ks, c_ms = sets ? st.c_ms : g.c_ms;
+  void* const C0 = sets ? st.C : g.C[0];
+  if (MODE == kGroupedK && n0 >= Ndim) return;
+
   long m0, m_end;        // rows of A / C covered by this block
   long k_begin, k_end;   // contraction range
   long b_group = 0, c_group = 0;
@@ -46,9 +54,10 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
     k_begin = 0; k_end = g.Kdim;
     b_group = (long)e * g.b_gs;
   } else {
-    const int grp = blockIdx.z;
+    const int grp = sets ? blockIdx.z / g.n_sets : blockIdx.z;
     m0 = (long)blockIdx.y * BM;
-    m_end = min((long)g.Mdim, m0 + BM);
+    if (m0 >= Mdim) return;
+    m_end = min((long)Mdim, m0 + BM);
     if (g.offset != nullptr) {
       const int e = g.group_expert[grp];
       k_begin = g.offset[e]; k_end = g.offset[e + 1];
@@ -77,7 +86,7 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
       for (int j = 0; j < 4; ++j) total[p][i][j] = 0.f;
   int since_flush = 0;
 
-  const bool a_kfast = (g.a_ks == 1), b_kfast = (g.b_ks == 1);
+  const bool a_kfast = (a_ks == 1), b_kfast = (b_ks == 1);
   const int npass = DUAL ? 1 : g.npairs;
   const long ktiles = k_end > k_begin ? (k_end - k_begin + BK - 1) / BK : 0;
   const long ntiles = ktiles * npass;              // K-tiles of all (A,B) pairs, pair after pair
@@ -93,7 +102,7 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   auto fetch = [&](long t) {
     const int pass = (int)(t / ktiles);
     const long kk = k_begin + (t - pass * ktiles) * BK;
-    const void* Ap = g.A[pass];
+    const void* Ap = sets ? st.A : g.A[pass];
 #pragma unroll
     for (int i = 0; i < kPerA; ++i) {
       const int ml = a_kfast ? a_row : a_row + i, kl = a_kfast ? a_k + i : a_k;
@@ -102,25 +111,25 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
       if (m < m_end && k < k_end) {
         if (MODE == kRaggedM) {
           const long row = g.a_rows ? (long)g.a_rows[m] : m;
-          v = ld<TA>(Ap, row * g.a_ms + k * g.a_ks);
+          v = ld<TA>(Ap, row * g.a_ms + k * a_ks);
         } else {
-          const long row = g.a_rows ? (long)g.a_rows[k] : k;
-          v = ld<TA>(Ap, m * g.a_ms + row * g.a_ks);
+          const long row = sets && st.a_gather ? (long)g.k_rows[k] : k;
+          v = ld<TA>(Ap, m * g.a_ms + row * a_ks);
         }
       }
       ra[i] = v;
     }
 #pragma unroll
     for (int p = 0; p < (DUAL ? 2 : 1); ++p) {
-      const void* Bp = g.B[DUAL ? p : pass];
+      const void* Bp = sets ? st.B : g.B[DUAL ? p : pass];
 #pragma unroll
       for (int i = 0; i < kPerB; ++i) {
         const int nl = b_kfast ? b_row : b_row + i, kl = b_kfast ? b_k + i : b_k;
         const long n = n0 + nl, k = kk + kl;
         float v = 0.f;
-        if (n < g.Ndim && k < k_end) {
-          const long row = (MODE == kGroupedK && g.b_rows) ? (long)g.b_rows[k] : k;
-          v = ld<TB>(Bp, b_group + n * g.b_ns + row * g.b_ks);
+        if (n < Ndim && k < k_end) {
+          const long row = sets && st.b_gather ? (long)g.k_rows[k] : k;
+          v = ld<TB>(Bp, b_group + n * g.b_ns + row * b_ks);
         }
         rb[p][i] = v;
       }
@@ -182,14 +191,14 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const long n = n0 + tx * 4 + j;
-      if (n >= g.Ndim) continue;
-      const long ci = c_group + m * g.c_ms + n;
+      if (n >= Ndim) continue;
+      const long ci = c_group + m * c_ms + n;
       if (EPI == kEpiStore) {
         if (g.c_f32) {
-          float* c = reinterpret_cast<float*>(g.C[0]) + ci;
+          float* c = reinterpret_cast<float*>(C0) + ci;
           *c = g.accumulate ? (*c + acc[0][i][j]) : acc[0][i][j];
         } else {
-          Elem<TB>::store(reinterpret_cast<TB*>(g.C[0]) + ci, acc[0][i][j]);
+          Elem<TB>::store(reinterpret_cast<TB*>(C0) + ci, acc[0][i][j]);
         }
       } else if (EPI == kEpiSwiglu) {
         const float a = acc[0][i][j], b = acc[DUAL ? 1 : 0][i][j];
@@ -230,7 +239,9 @@ int launch_tile(const GemmArgs& g, hipStream_t s) {
   if (MODE == kRaggedM) {
     grid = dim3(cdiv(g.Ndim, BN), g.max_tiles * (kRowTile / BM), 1);
   } else {
-    grid = dim3(cdiv(g.Ndim, BN), cdiv(g.Mdim, BM), g.n_groups);
+    // sets of the transposed shape share the grid: blocks beyond a set's own extent leave at once
+    const int ext = g.n_sets > 0 ? (g.Mdim > g.Ndim ? g.Mdim : g.Ndim) : 0;
+    grid = dim3(cdiv(ext ? ext : g.Ndim, BN), cdiv(ext ? ext : g.Mdim, BM), g.n_groups * (g.n_sets > 0 ? g.n_sets : 1));
   }
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SPES_OK;
   hipLaunchKernelGGL((gemm_simt_kernel<TA, TB, MODE, EPI, TR>), grid, dim3(256), 0, s, g);
@@ -241,7 +252,7 @@ int launch_tile(const GemmArgs& g, hipStream_t s) {
 // is bound by its own serial K loop, so more, shorter blocks finish sooner)
 template <typename TA, typename TB, int MODE, int EPI>
 int launch(const GemmArgs& g, hipStream_t s) {
-  const long rows64 = (MODE == kRaggedM) ? g.max_tiles : (long)cdiv(g.Mdim, kRowTile) * g.n_groups;
+  const long rows64 = (MODE == kRaggedM) ? g.max_tiles : (long)cdiv(g.Mdim, kRowTile) * g.n_groups * (g.n_sets > 0 ? g.n_sets : 1);
   const long blocks64 = rows64 * cdiv(g.Ndim, BN);
   if (blocks64 >= 512) return launch_tile<TA, TB, MODE, EPI, 4>(g, s);
   if (blocks64 >= 256) return launch_tile<TA, TB, MODE, EPI, 2>(g, s);
