@@ -16,7 +16,7 @@ constexpr int kRouterSplit = 64;   // chunks of the token axis in the router wei
 struct Layout {
   spes_moe_ctx_layout pub;
   size_t block_counts, tab_simt, tab_mfma, row_token, row_gate, hcorr, dgate_part, da, db, hg, dxp, wr_part, dlogits_bf, dxr, aux, aux_part;
-  int max_tiles, max_tiles_mfma, est_tiles_mfma, max_col_tiles;
+  int max_tiles, row_tile_mfma, max_tiles_mfma, est_tiles_mfma, max_col_tiles;
 };
 
 bool shape_ok(const spes_moe_shape* s) {
@@ -49,8 +49,9 @@ Layout make_layout(const spes_moe_shape* s) {
   const size_t T = s->T, d = s->d_model, M = s->n_experts, f = s->d_ff, k = s->top_k;
   const size_t R = T * k, es = s->dtype == SPES_F32 ? 4 : 2;
   L.max_tiles = (int)(R / 64 + M + 1);
-  L.max_tiles_mfma = (int)(R / 256 + M + 1);
-  L.est_tiles_mfma = (int)(R / 256 + (M + 1) / 2);   // expected count: half of the experts end in a partly filled tile
+  L.row_tile_mfma = mfma_row_tile((long)R, s->n_experts, s->d_model, s->d_ff);
+  L.max_tiles_mfma = (int)(R / L.row_tile_mfma + M + 1);
+  L.est_tiles_mfma = (int)(R / L.row_tile_mfma + (M + 1) / 2);   // expected count: half of the experts end in a partly filled tile
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };
   L.pub.logits = take(kLogitSplit * T * M * 4);   // partial score matrices; the first one ends up holding the scores
@@ -104,6 +105,7 @@ void ragged_tables(GemmArgs& g, void* ctx, const Layout& L, int dt) {
   g.tile_row0 = tab + 1 + L.max_tiles;
   g.offset = at<int>(ctx, L.pub.offset);
   g.max_tiles = dt == SPES_BF16 ? L.max_tiles_mfma : L.max_tiles;   // launch bound on the number of row tiles
+  g.row_tile = L.row_tile_mfma;
   g.est_tiles = dt == SPES_BF16 ? L.est_tiles_mfma : 0;
 }
 
@@ -198,7 +200,7 @@ SPES_API int spes_moe_fwd(const spes_moe_shape* shape, const void* x, const void
                                  at<int>(ctx, L.row_token), at<float>(ctx, L.row_gate),
                                  // only the row-tile table of the GEMM path this storage type runs on is built
                                  dt == SPES_BF16 ? 0 : simt_row_tile(), at<int>(ctx, L.tab_simt),
-                                 dt == SPES_BF16 ? mfma_row_tile() : 0, at<int>(ctx, L.tab_mfma), L.max_tiles,
+                                 dt == SPES_BF16 ? L.row_tile_mfma : 0, at<int>(ctx, L.tab_mfma), L.max_tiles,
                                  at<float>(ctx, L.aux), s));
   prof_mark(0, "hist_scan_rank", s);
   // a = xp W_g^T, b = xp W_u^T, h = SiLU(a) * b with xp[r,:] = x[token of row r,:]: the GEMM reads its operand rows
@@ -287,7 +289,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
   // u = dy[token] W_d per routed row; its epilogue yields the gate gradient <u, h> (per column tile) and,
   // through the SwiGLU, da and db of the gate-scaled upstream gradient
   const long R = (long)T * k;
-  const int n_part = dt == SPES_BF16 ? mfma_rowdot_parts(f, L.est_tiles_mfma) : cdiv(f, simt_col_tile());
+  const int n_part = dt == SPES_BF16 ? mfma_rowdot_parts(f, L.row_tile_mfma, L.est_tiles_mfma) : cdiv(f, simt_col_tile());
   // bf16 storage: the two router contractions run on the matrix cores from a bf16 copy of dlogits
   const bool router_mfma = dt == SPES_BF16 && M % 8 == 0;
   prof_begin(1, s);

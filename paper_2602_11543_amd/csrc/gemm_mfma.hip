@@ -730,11 +730,14 @@ typedef Cfg<256, 256, 64, 1> Tile;
 // narrow outputs (the router's M <= 64 expert columns: half the matrix work on padding), the half-full last column
 // tile of a ragged-row GEMM, and launches of few tiles
 typedef Cfg<256, 128, 64, 1> TileNarrow;
-// few output rows (the router's weight gradient has M <= 64 of them)
+// few output rows (the router's weight gradient has M <= 64 of them, experts of up to a hundred routed rows)
 typedef Cfg<128, 256, 64, 1> TileShort;
 // a contraction of a single K-tile (the router's input gradient contracts over the M <= 64 experts) is all prologue
 // and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's
 typedef Cfg<128, 128, 64, 2> TileSmall;
+// experts of few routed rows (mfma_row_tile below): bound by the stream of the expert weights, two blocks per CU
+typedef Cfg<64, 256, 64, 2> Rows64;
+typedef Cfg<64, 128, 64, 2> Rows64Narrow;
 
 template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false>
 int launch(const GemmArgs& g, hipStream_t s) {
@@ -777,16 +780,47 @@ static bool few_tiles_narrow(int ndim, int est_tiles) {
 // 512 x 352) 350 -> 238 us, 90 tiles (3777 tokens, 1536 x 1280) 447 -> 396 us, 288 tiles (768 x 2048) 590 -> 555 us.
 constexpr long kSmallTilesBelow = 320;
 
-int mfma_row_tile() { return Tile::BM; }
+// Rows per tile of the kRaggedM launches.  A 256-row tile of an expert with a few dozen rows computes padding, one block
+// per CU, while the weights it streams are the only work that is needed; 64- and 128-row tiles run two blocks per CU
+// (all but the 128-row SwiGLU one), take any width in 128-column tiles and fill the chip with fewer rows.  They feed
+// fewer MFMAs per byte read, so full tiles win again once experts fill them.  Measured, us of a whole step with
+// 256 / 128 / 64 rows, at a mean of n rows per expert:
+//   32 experts of 2048 x 2048   n = 20: 563 / 537 / 502   n = 60: 592 / 573 / 589   n = 112: 617 / 653 / 694
+//   64 experts of 1408 x 1408   n = 40: 731 / 512 / 498   n = 96: 778 / 562 / 610
+//   16 experts of 4096 x 2048   n = 40: 573 / 554 / 521   n = 80: 594 / 577 / 641   n = 112: 610 / 690 / 721
+// A short contraction is mostly prologue and epilogue, which two blocks per CU overlap, and the lines lie higher:
+//   16 experts of 768 x 2048    n = 128: 283 / 209 / 199  n = 256: 293 / 291 / 276  n = 320: 310 / 325 / 325
+//   64 experts of 512 x 352     n = 192: 239 / 182 / 173  n = 512: 316 / 275 / 278
+// (the down projection contracts over d_ff: measured up to d_ff = 4 d_model)
+int mfma_row_tile(long rows, int n_experts, int d_model, int d_ff) {
+  const bool narrow = d_ff <= 4L * d_model;
+  const long short_to = narrow && d_model <= 640 ? 512 : narrow && d_model <= 896 ? 256 : 48;
+  if (rows <= short_to * n_experts) return Rows64::BM;
+  return short_to == 48 && rows <= 96L * n_experts ? TileShort::BM : Tile::BM;
+}
 // number of gate-gradient partials per row that the kEpiDSwiglu epilogue writes for ndim columns (two per column tile)
-int mfma_rowdot_parts(int ndim, int est_tiles) {
+int mfma_rowdot_parts(int ndim, int row_tile, int est_tiles) {
+  if (row_tile != Tile::BM) return 2 * cdiv(ndim, Rows64Narrow::BN);
   return few_tiles_narrow(ndim, est_tiles) ? 2 * (ndim / TileNarrow::BN) : 2 * cdiv(ndim, Tile::BN);
+}
+
+// kRaggedM on row tiles shorter than 256.  W: the fused SwiGLU (gate and up columns side by side), N: everything else
+template <typename W, typename N>
+static int launch_short(int epi, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
+  if (epi == kEpiSwiglu && b_kcontig) return launch<kRaggedM, kEpiSwiglu, true, true, W>(g, s);
+  if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, N>(g, s);
+  if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, N>(g, s);
+  if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, N>(g, s);
+  return SPES_EINVAL;
 }
 
 // bf16 operands only.  a_kcontig / b_kcontig: the contraction index is the fast memory axis of that operand.
 int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
   if (mode == kRaggedM) {
     if (!a_kcontig) return SPES_EINVAL;
+    if (g.row_tile == TileShort::BM) return launch_short<TileShort, TileSmall>(epi, b_kcontig, g, s);
+    if (g.row_tile == Rows64::BM) return launch_short<Rows64, Rows64Narrow>(epi, b_kcontig, g, s);
+    if (g.row_tile != Tile::BM) return SPES_EINVAL;
     // A last column tile that is at most half full goes to a launch of its own on the half-width tile (which costs
     // 0.6 of a full one) instead of running a full-width tile on half-empty operands.
     const int tail = g.Ndim % Tile::BN;
