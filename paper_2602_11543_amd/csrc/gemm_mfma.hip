@@ -791,12 +791,18 @@ constexpr long kSmallTilesBelow = 320;
 // A short contraction is mostly prologue and epilogue, which two blocks per CU overlap, and the lines lie higher:
 //   16 experts of 768 x 2048    n = 128: 283 / 209 / 199  n = 256: 293 / 291 / 276  n = 320: 310 / 325 / 325
 //   64 experts of 512 x 352     n = 192: 239 / 182 / 173  n = 512: 316 / 275 / 278
-// (the down projection contracts over d_ff: measured up to d_ff = 4 d_model)
+// (the down projection contracts over d_ff: measured up to d_ff = 4 d_model).  Above the line of 64 rows such a layer
+// takes 128 where one to three rounds of 256 concurrent full tiles would end in a round that is at most 0.6 full: full
+// tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512 (2.5 rounds) 473 / 385 / 428, 24 experts of
+// 768 x 768 at n = 562 (1.1) 279 / 268 / 282, and lose nothing to a round that is nearly full (n = 320 above, 1.75).
+// The same rule cost up to 15 % at 904 and 1000 columns, where the full tiles' column tail has a launch of its own.
 int mfma_row_tile(long rows, int n_experts, int d_model, int d_ff) {
-  const bool narrow = d_ff <= 4L * d_model;
-  const long short_to = narrow && d_model <= 640 ? 512 : narrow && d_model <= 896 ? 256 : 48;
-  if (rows <= short_to * n_experts) return Rows64::BM;
-  return short_to == 48 && rows <= 96L * n_experts ? TileShort::BM : Tile::BM;
+  const bool short_k = d_model <= 896 && d_ff <= 4L * d_model;
+  const long to64 = !short_k ? 48 : d_model <= 640 ? 512 : 256;
+  if (rows <= to64 * n_experts) return Rows64::BM;
+  if (!short_k) return rows <= 96L * n_experts ? TileShort::BM : Tile::BM;
+  const long full = (rows / Tile::BM + (n_experts + 1) / 2) * cdiv(d_ff, Tile::BN / 2);   // SwiGLU tiles to expect
+  return full >= 256 && full < 3 * 256 && full % 256 <= 154 ? TileShort::BM : Tile::BM;
 }
 // number of gate-gradient partials per row that the kEpiDSwiglu epilogue writes for ndim columns (two per column tile)
 int mfma_rowdot_parts(int ndim, int row_tile, int est_tiles) {

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     dict(T=260, d=1032, M=8, f=328, k=4, n_trainable=3),                              # 256 rows, column tails of 8 and 72
     dict(T=300, d=1024, M=8, f=512, k=4, n_trainable=3),                              # 256 rows, half-width launches
     dict(T=512, d=896, M=4, f=200, k=2, n_trainable=2),                               # short contraction, 256 a head
+    dict(T=1100, d=264, M=16, f=1048, k=8, n_trainable=2),                            # 128 rows: 378 full tiles, 1.48 rounds
+    dict(T=1040, d=256, M=8, f=1024, k=4, n_trainable=2),                             # 256 rows: 160 full tiles
     dict(T=1023, d=640, M=4, f=136, k=2, n_trainable=2),                              # shorter one, 511.5 a head
     dict(T=64, d=136, M=8, f=552, k=2, n_trainable=8, bias="normal", bias_scale=8.0),    # d_ff > 4 d_model
 ])
