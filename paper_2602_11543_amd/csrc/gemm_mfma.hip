@@ -793,8 +793,8 @@ constexpr long kSmallTilesBelow = 320;
 //   64 experts of 512 x 352     n = 192: 239 / 182 / 173  n = 512: 316 / 275 / 278
 // (the down projection contracts over d_ff: measured up to d_ff = 4 d_model).  Above the line of 64 rows such a layer
 // takes 128 where one to three rounds of 256 concurrent full tiles would end in a round that is at most 0.6 full: full
-// tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512 (2.5 rounds) 473 / 385 / 428, 24 experts of
-// 768 x 768 at n = 562 (1.1) 279 / 268 / 282, and lose nothing to a round that is nearly full (n = 320 above, 1.75).
+// tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512 (2.5 rounds,
+// unevenly loaded) 473 / 385 / 428, 24 experts of 768 x 768 at n = 562 (1.1) 279 / 268 / 282, and lose nothing to a round that is nearly full (n = 320 above, 1.75).
 // The same rule cost up to 15 % at 904 and 1000 columns, where the full tiles' column tail has a launch of its own.
 int mfma_row_tile(long rows, int n_experts, int d_model, int d_ff) {
   const bool short_k = d_model <= 896 && d_ff <= 4L * d_model;
