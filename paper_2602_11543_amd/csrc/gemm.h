@@ -35,7 +35,7 @@ struct GemmArgs {
   float* rowdot;          // kEpiDSwiglu: [gridDim.x, rowdot_stride] partial gate gradients
   long rowdot_stride;
   long b_ns, b_ks, b_gs;  // element strides of B along n, k, and per expert (kRaggedM)
-  int npairs;             // kEpiStore/kEpiDSwiglu: (A,B) pairs accumulated into one result
+  int npairs;             // kRaggedM, kEpiStore/kEpiDSwiglu: (A,B) pairs accumulated into one result; 1 for kGroupedK
   int Kdim;               // contraction length of each pair (kRaggedM) / total K (kGroupedK, uniform chunks)
   void* C[4];
   const void* E[3];

@@ -7,6 +7,8 @@
 // K advanced 32 at a time through LDS; the next K-tile is requested into registers
 // before the current one is multiplied, so its memory latency hides behind the FMAs
 // (the shapes this path serves put one block on a CU, where nothing else would).
+#include <type_traits>
+
 #include "gemm.h"
 
 namespace spes {
@@ -20,7 +22,11 @@ __device__ __forceinline__ float ld(const void* base, long idx) {
   return Elem<T>::load(reinterpret_cast<const T*>(base) + idx);
 }
 
-template <typename TA, typename TB, int MODE, int EPI, int TR>
+// SETS (kGroupedK only): several contractions over the same groups in one launch, each with its own operands and result.
+// A template parameter, because operands chosen at run time slow every contraction that has none of this: the fp32
+// warm-up of 8 experts of 1024 x 4096 (its Gram matrix runs here) took 939 us with the choice in all kernels, 841 with
+// kernels of their own (886 before there were sets).
+template <typename TA, typename TB, int MODE, int EPI, bool SETS, int TR>
 __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   constexpr bool DUAL = (EPI == kEpiSwiglu);
   constexpr int BM = 16 * TR;
@@ -31,15 +37,15 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
 
   const int tid = threadIdx.x;
   const int tx = tid & 15, ty = tid >> 4;
+
   const int n0 = blockIdx.x * BN;
 
-  // operand set of this block (kGroupedK with several contractions over the same groups)
-  const bool sets = MODE == kGroupedK && g.n_sets > 0;
-  const GemmArgs::Set& st = g.set[sets ? blockIdx.z % g.n_sets : 0];
-  const int Mdim = sets ? st.Mdim : g.Mdim, Ndim = sets ? st.Ndim : g.Ndim;
-  const long a_ks = sets ? st.a_ks : g.a_ks, b_ks = sets ? st.b_ks : g.b_ks, c_ms = sets ? st.c_ms : g.c_ms;
-  void* const C0 = sets ? st.C : g.C[0];
-  if (MODE == kGroupedK && n0 >= Ndim) return;
+  // operand set of this block
+  const GemmArgs::Set st = g.set[SETS ? blockIdx.z % g.n_sets : 0];
+  const int Mdim = SETS ? st.Mdim : g.Mdim, Ndim = SETS ? st.Ndim : g.Ndim;
+  const long a_ks = SETS ? st.a_ks : g.a_ks, b_ks = SETS ? st.b_ks : g.b_ks, c_ms = SETS ? st.c_ms : g.c_ms;
+  void* const C0 = SETS ? st.C : g.C[0];
+  if (SETS && n0 >= Ndim) return;
 
   long m0, m_end;        // rows of A / C covered by this block
   long k_begin, k_end;   // contraction range
@@ -54,9 +60,9 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
     k_begin = 0; k_end = g.Kdim;
     b_group = (long)e * g.b_gs;
   } else {
-    const int grp = sets ? blockIdx.z / g.n_sets : blockIdx.z;
+    const int grp = SETS ? blockIdx.z / g.n_sets : blockIdx.z;
     m0 = (long)blockIdx.y * BM;
-    if (m0 >= Mdim) return;
+    if (SETS && m0 >= Mdim) return;
     m_end = min((long)Mdim, m0 + BM);
     if (g.offset != nullptr) {
       const int e = g.group_expert[grp];
@@ -87,7 +93,8 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   int since_flush = 0;
 
   const bool a_kfast = (a_ks == 1), b_kfast = (b_ks == 1);
-  const int npass = DUAL ? 1 : g.npairs;
+  constexpr bool ONE_PAIR = DUAL || MODE == kGroupedK;   // a division per K-tile less
+  const int npass = ONE_PAIR ? 1 : g.npairs;
   const long ktiles = k_end > k_begin ? (k_end - k_begin + BK - 1) / BK : 0;
   const long ntiles = ktiles * npass;              // K-tiles of all (A,B) pairs, pair after pair
 
@@ -100,9 +107,9 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   float ra[kPerA], rb[DUAL ? 2 : 1][kPerB];
   // requests K-tile t (of all pairs) into ra / rb; elements outside the tile's rows, columns or contraction range are 0
   auto fetch = [&](long t) {
-    const int pass = (int)(t / ktiles);
+    const int pass = ONE_PAIR ? 0 : (int)(t / ktiles);
     const long kk = k_begin + (t - pass * ktiles) * BK;
-    const void* Ap = sets ? st.A : g.A[pass];
+    const void* Ap = SETS ? st.A : g.A[pass];
 #pragma unroll
     for (int i = 0; i < kPerA; ++i) {
       const int ml = a_kfast ? a_row : a_row + i, kl = a_kfast ? a_k + i : a_k;
@@ -113,7 +120,7 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
           const long row = g.a_rows ? (long)g.a_rows[m] : m;
           v = ld<TA>(Ap, row * g.a_ms + k * a_ks);
         } else {
-          const long row = sets && st.a_gather ? (long)g.k_rows[k] : k;
+          const long row = SETS && st.a_gather ? (long)g.k_rows[k] : k;
           v = ld<TA>(Ap, m * g.a_ms + row * a_ks);
         }
       }
@@ -121,14 +128,14 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
     }
 #pragma unroll
     for (int p = 0; p < (DUAL ? 2 : 1); ++p) {
-      const void* Bp = sets ? st.B : g.B[DUAL ? p : pass];
+      const void* Bp = SETS ? st.B : g.B[DUAL ? p : pass];
 #pragma unroll
       for (int i = 0; i < kPerB; ++i) {
         const int nl = b_kfast ? b_row : b_row + i, kl = b_kfast ? b_k + i : b_k;
         const long n = n0 + nl, k = kk + kl;
         float v = 0.f;
         if (n < Ndim && k < k_end) {
-          const long row = sets && st.b_gather ? (long)g.k_rows[k] : k;
+          const long row = SETS && st.b_gather ? (long)g.k_rows[k] : k;
           v = ld<TB>(Bp, b_group + n * g.b_ns + row * b_ks);
         }
         rb[p][i] = v;
@@ -232,31 +239,33 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   }
 }
 
-template <typename TA, typename TB, int MODE, int EPI, int TR>
+template <typename TA, typename TB, int MODE, int EPI, bool SETS, int TR>
 int launch_tile(const GemmArgs& g, hipStream_t s) {
   constexpr int BM = 16 * TR;
   dim3 grid;
   if (MODE == kRaggedM) {
     grid = dim3(cdiv(g.Ndim, BN), g.max_tiles * (kRowTile / BM), 1);
-  } else {
+  } else if (SETS) {
     // sets of the transposed shape share the grid: blocks beyond a set's own extent leave at once
-    const int ext = g.n_sets > 0 ? (g.Mdim > g.Ndim ? g.Mdim : g.Ndim) : 0;
-    grid = dim3(cdiv(ext ? ext : g.Ndim, BN), cdiv(ext ? ext : g.Mdim, BM), g.n_groups * (g.n_sets > 0 ? g.n_sets : 1));
+    const int ext = g.Mdim > g.Ndim ? g.Mdim : g.Ndim;
+    grid = dim3(cdiv(ext, BN), cdiv(ext, BM), g.n_groups * g.n_sets);
+  } else {
+    grid = dim3(cdiv(g.Ndim, BN), cdiv(g.Mdim, BM), g.n_groups);
   }
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SPES_OK;
-  hipLaunchKernelGGL((gemm_simt_kernel<TA, TB, MODE, EPI, TR>), grid, dim3(256), 0, s, g);
+  hipLaunchKernelGGL((gemm_simt_kernel<TA, TB, MODE, EPI, SETS, TR>), grid, dim3(256), 0, s, g);
   return hipGetLastError() == hipSuccess ? SPES_OK : SPES_EHIP;
 }
 
 // 64-row tiles when they give every CU two blocks or more, otherwise 32- or 16-row tiles (a block of a small problem
 // is bound by its own serial K loop, so more, shorter blocks finish sooner)
-template <typename TA, typename TB, int MODE, int EPI>
+template <typename TA, typename TB, int MODE, int EPI, bool SETS = false>
 int launch(const GemmArgs& g, hipStream_t s) {
-  const long rows64 = (MODE == kRaggedM) ? g.max_tiles : (long)cdiv(g.Mdim, kRowTile) * g.n_groups * (g.n_sets > 0 ? g.n_sets : 1);
+  const long rows64 = (MODE == kRaggedM) ? g.max_tiles : (long)cdiv(g.Mdim, kRowTile) * g.n_groups * (SETS ? g.n_sets : 1);
   const long blocks64 = rows64 * cdiv(g.Ndim, BN);
-  if (blocks64 >= 512) return launch_tile<TA, TB, MODE, EPI, 4>(g, s);
-  if (blocks64 >= 256) return launch_tile<TA, TB, MODE, EPI, 2>(g, s);
-  return launch_tile<TA, TB, MODE, EPI, 1>(g, s);
+  if (blocks64 >= 512) return launch_tile<TA, TB, MODE, EPI, SETS, 4>(g, s);
+  if (blocks64 >= 256) return launch_tile<TA, TB, MODE, EPI, SETS, 2>(g, s);
+  return launch_tile<TA, TB, MODE, EPI, SETS, 1>(g, s);
 }
 
 template <typename TA, typename TB>
@@ -266,7 +275,11 @@ int dispatch(int mode, int epi, const GemmArgs& g, hipStream_t s) {
     if (epi == kEpiSwiglu) return launch<TA, TB, kRaggedM, kEpiSwiglu>(g, s);
     return launch<TA, TB, kRaggedM, kEpiDSwiglu>(g, s);
   }
-  if (epi == kEpiStore) return launch<TA, TB, kGroupedK, kEpiStore>(g, s);
+  if (epi != kEpiStore) return SPES_EINVAL;
+  if (g.n_sets == 0) return launch<TA, TB, kGroupedK, kEpiStore>(g, s);
+  // operand sets: the expert weight gradients of fp32 storage
+  if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value)
+    return launch<TA, TB, kGroupedK, kEpiStore, true>(g, s);
   return SPES_EINVAL;
 }
 
