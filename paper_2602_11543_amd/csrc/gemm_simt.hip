@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "plan.h"
 
 namespace spes {
 namespace {
@@ -38,14 +39,14 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   const int tid = threadIdx.x;
   const int tx = tid & 15, ty = tid >> 4;
 
-  const int n0 = blockIdx.x * BN;
-
-  // operand set of this block
+  // operand set, column tile and row tile of this block; the sets of a group stand side by side, and a set with fewer
+  // tiles than the largest one leaves its last blocks idle
   const GemmArgs::Set st = g.set[SETS ? blockIdx.z % g.n_sets : 0];
   const int Mdim = SETS ? st.Mdim : g.Mdim, Ndim = SETS ? st.Ndim : g.Ndim;
   const long a_ks = SETS ? st.a_ks : g.a_ks, b_ks = SETS ? st.b_ks : g.b_ks, c_ms = SETS ? st.c_ms : g.c_ms;
   void* const C0 = SETS ? st.C : g.C[0];
-  if (SETS && n0 >= Ndim) return;
+  const int col_tiles = SETS ? cdiv(Ndim, BN) : 1;
+  const int n0 = (SETS ? blockIdx.x % col_tiles : blockIdx.x) * BN;
 
   long m0, m_end;        // rows of A / C covered by this block
   long k_begin, k_end;   // contraction range
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
     b_group = (long)e * g.b_gs;
   } else {
     const int grp = SETS ? blockIdx.z / g.n_sets : blockIdx.z;
-    m0 = (long)blockIdx.y * BM;
+    m0 = (long)(SETS ? blockIdx.x / col_tiles : blockIdx.y) * BM;
     if (SETS && m0 >= Mdim) return;
     m_end = min((long)Mdim, m0 + BM);
     if (g.offset != nullptr) {
@@ -246,9 +247,11 @@ int launch_tile(const GemmArgs& g, hipStream_t s) {
   if (MODE == kRaggedM) {
     grid = dim3(cdiv(g.Ndim, BN), g.max_tiles * (kRowTile / BM), 1);
   } else if (SETS) {
-    // sets of the transposed shape share the grid: blocks beyond a set's own extent leave at once
-    const int ext = g.Mdim > g.Ndim ? g.Mdim : g.Ndim;
-    grid = dim3(cdiv(ext, BN), cdiv(ext, BM), g.n_groups * g.n_sets);
+    int rows[3], cols[3];
+    for (int i = 0; i < g.n_sets; ++i) { rows[i] = g.set[i].Mdim; cols[i] = g.set[i].Ndim; }
+    const long tiles = plan::set_grid_tiles(rows, cols, g.n_sets, BM, BN);
+    if (tiles * 256 >= (1L << 32)) return SPES_ESHAPE;   // work-items along a grid dimension
+    grid = dim3((unsigned)tiles, 1, g.n_groups * g.n_sets);
   } else {
     grid = dim3(cdiv(g.Ndim, BN), cdiv(g.Mdim, BM), g.n_groups);
   }

@@ -14,6 +14,11 @@ pytestmark = pytest.mark.gpu
     dict(T=300, d=776, M=16, f=520, k=2, n_trainable=16),                            # 576 tiles of 256 x 256
     dict(T=200, d=128, M=8, f=384, k=1, n_trainable=8, bias="normal", bias_scale=8.0),   # experts without a row
     dict(T=300, d=136, M=8, f=264, k=2, n_trainable=3, dtype="f32"),
+    # fp32 results far from square; the transposed sets have fewer tiles and leave the last blocks of the grid idle
+    dict(T=70, d=72, M=4, f=24, k=2, n_trainable=3, dtype="f32"),
+    dict(T=64, d=1032, M=4, f=8, k=1, n_trainable=4, dtype="f32"),
+    dict(T=200, d=8, M=4, f=1504, k=2, n_trainable=4, dtype="f32"),                  # 32-row tiles
+    dict(T=130, d=128, M=16, f=3080, k=2, n_trainable=16, dtype="f32"),              # 64-row tiles
 ])
 def test_wgrad_sets(kw, device):
     kw = {"dtype": "bf16", "router_sigma": 0.3, "trainable": "random", **kw}
