@@ -331,6 +331,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     g.n_groups = n_train;
     memcpy(g.group_expert, train_list, n_train);
     g.offset = at<int>(ctx, L.pub.offset);
+    g.mean_k = cdiv(R, M); g.max_k = T;
     g.c_f32 = 1; g.accumulate = accumulate;
     // dW_d[d,f] = dy[token]^T (gate * h), dW_g[f,d] = da^T xp, dW_u[f,d] = db^T xp over the expert's rows, as one launch:
     // a layer of a few thousand tokens has fewer tiles per matrix than the chip has CUs

@@ -57,6 +57,7 @@ struct GemmArgs {
   unsigned long long c2_skip;  // kEpiDSwiglu: bit e set = nothing reads C[2] for expert e's rows; the matrix-core path leaves them unwritten
   // kGroupedK
   int n_groups;
+  int mean_k, max_k;      // offset != nullptr: mean and largest possible contraction length (the lengths are only known on the device)
   int kchunk;             // offset == nullptr: group g contracts k in [g*kchunk, min(Kdim,(g+1)*kchunk))
   // several contractions over the same groups in one launch (kGroupedK, kEpiStore into fp32, both operands K-strided):
   // n_sets > 0 replaces A, B, C, their element counts and k strides, c_ms and Mdim / Ndim (which hold set 0's extents;

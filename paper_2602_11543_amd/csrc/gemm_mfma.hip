@@ -40,6 +40,7 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "plan.h"
 
 namespace spes {
 namespace {
@@ -774,12 +775,6 @@ static bool few_tiles_narrow(int ndim, int est_tiles) {
   return rounds_full <= 4 && 0.6 * rounds_half < 0.95 * rounds_full;
 }
 
-// Weight gradients: at most this many 256 x 256 tiles over all sets go to 128 x 128 tiles, two blocks per CU.  A launch
-// of that few full tiles is one round, or little more, of tiles that are mostly prologue and epilogue; measured on a
-// whole step, all three gradients in one launch of small tiles against three of full ones: 96 full tiles (1531 tokens,
-// 512 x 352) 350 -> 238 us, 90 tiles (3777 tokens, 1536 x 1280) 447 -> 396 us, 288 tiles (768 x 2048) 590 -> 555 us.
-constexpr long kSmallTilesBelow = 320;
-
 // Rows per tile of the kRaggedM launches.  A 256-row tile of an expert with a few dozen rows computes padding, one block
 // per CU, while the weights it streams are the only work that is needed; 64- and 128-row tiles run two blocks per CU
 // (all but the 128-row SwiGLU one), take any width in 128-column tiles and fill the chip with fewer rows.  They feed
@@ -864,9 +859,8 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
                                                           : launch<kGroupedK, kEpiStore, true, false>(g, s);
   if (!a_kcontig && !b_kcontig) {
     if (g.n_sets > 0) {
-      // 128 x 128 tiles, two blocks per CU, where the 256 x 256 ones would not give every CU one
-      const long tiles = (long)g.n_sets * g.n_groups * cdiv(g.Mdim, Tile::BM) * cdiv(g.Ndim, Tile::BN);
-      if (tiles <= kSmallTilesBelow) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
+      const long full = (long)g.n_sets * g.n_groups * plan::tiles(g.Mdim, g.Ndim, Tile::BM, Tile::BN);
+      if (plan::wgrad_small_tiles(full, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
       return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
     }
     if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);
