@@ -5,6 +5,7 @@
 #include <mutex>
 
 #include "kernels.h"
+#include "plan.h"
 
 using namespace spes;
 
@@ -49,7 +50,7 @@ Layout make_layout(const spes_moe_shape* s) {
   const size_t T = s->T, d = s->d_model, M = s->n_experts, f = s->d_ff, k = s->top_k;
   const size_t R = T * k, es = s->dtype == SPES_F32 ? 4 : 2;
   L.max_tiles = (int)(R / 64 + M + 1);
-  L.row_tile_mfma = mfma_row_tile((long)R, s->n_experts, s->d_model, s->d_ff);
+  L.row_tile_mfma = plan::row_tile((long)R, s->n_experts, s->d_model, s->d_ff);
   L.max_tiles_mfma = (int)(R / L.row_tile_mfma + M + 1);
   L.est_tiles_mfma = (int)(R / L.row_tile_mfma + (M + 1) / 2);   // expected count: half of the experts end in a partly filled tile
   size_t off = 0;
@@ -289,7 +290,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
   // u = dy[token] W_d per routed row; its epilogue yields the gate gradient <u, h> (per column tile) and,
   // through the SwiGLU, da and db of the gate-scaled upstream gradient
   const long R = (long)T * k;
-  const int n_part = dt == SPES_BF16 ? mfma_rowdot_parts(f, L.row_tile_mfma, L.est_tiles_mfma) : cdiv(f, simt_col_tile());
+  const int n_part = dt == SPES_BF16 ? plan::rowdot_parts(f, L.row_tile_mfma, L.est_tiles_mfma) : cdiv(f, simt_col_tile());
   // bf16 storage: the two router contractions run on the matrix cores from a bf16 copy of dlogits
   const bool router_mfma = dt == SPES_BF16 && M % 8 == 0;
   prof_begin(1, s);

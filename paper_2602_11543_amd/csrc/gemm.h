@@ -52,7 +52,7 @@ struct GemmArgs {
   const int* n_tiles;
   const int* offset;      // [M+1] first routed row of each expert
   int max_tiles;
-  int row_tile;           // rows per tile of that table (matrix-core path: mfma_row_tile)
+  int row_tile;           // rows per tile of that table (matrix-core path: plan::row_tile)
   int est_tiles;          // expected number of row tiles (the count itself is only known on the device); 0: unknown
   unsigned long long c2_skip;  // kEpiDSwiglu: bit e set = nothing reads C[2] for expert e's rows; the matrix-core path leaves them unwritten
   // kGroupedK
@@ -80,7 +80,5 @@ int launch_gemm_simt(int dtype_a, int dtype_b, int mode, int epi, const GemmArgs
 int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s);
 int simt_row_tile();
 int simt_col_tile();
-int mfma_row_tile(long rows, int n_experts, int d_model, int d_ff);   // rows per tile of the kRaggedM launches
-int mfma_rowdot_parts(int ndim, int row_tile, int est_tiles);
 
 }  // namespace spes

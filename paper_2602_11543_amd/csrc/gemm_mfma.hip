@@ -725,20 +725,25 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   }
 }
 
-// one tile configuration: 256 x 256 x 64, one block per CU (144 KB of LDS, 256 accumulators per lane in AGPRs)
+// the full tile: 256 x 256 x 64, one block per CU (128 to 144 KB of LDS by operand layout, 256 accumulators per lane in AGPRs)
 typedef Cfg<256, 256, 64, 1> Tile;
 
 // narrow outputs (the router's M <= 64 expert columns: half the matrix work on padding), the half-full last column
 // tile of a ragged-row GEMM, and launches of few tiles
 typedef Cfg<256, 128, 64, 1> TileNarrow;
-// few output rows (the router's weight gradient has M <= 64 of them, experts of up to a hundred routed rows)
+// few output rows (the router's weight gradient has M <= 64 of them), and the fused SwiGLU on 128-row tiles (plan::row_tile)
 typedef Cfg<128, 256, 64, 1> TileShort;
 // a contraction of a single K-tile (the router's input gradient contracts over the M <= 64 experts) is all prologue
-// and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's
+// and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's; also the other
+// ragged-row GEMMs on 128-row tiles, and weight gradients of few full tiles (plan::wgrad_small_tiles)
 typedef Cfg<128, 128, 64, 2> TileSmall;
-// experts of few routed rows (mfma_row_tile below): bound by the stream of the expert weights, two blocks per CU
+// ragged-row GEMMs on 64-row tiles (plan::row_tile), two blocks per CU: experts of few routed rows, bound by the stream of
+// their weights, and narrow models with few tiles, bound by prologue and epilogue
 typedef Cfg<64, 256, 64, 2> Rows64;
 typedef Cfg<64, 128, 64, 2> Rows64Narrow;
+static_assert(Tile::BM == plan::kFullRows && TileShort::BM == plan::kHalfRows && TileSmall::BM == plan::kHalfRows && Rows64::BM == plan::kQuarterRows &&
+              Tile::BN == plan::kFullCols && TileNarrow::BN == plan::kHalfCols && TileSmall::BN == plan::kHalfCols && Rows64Narrow::BN == plan::kHalfCols,
+              "the tiles that the plan counts");
 
 template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false>
 int launch(const GemmArgs& g, hipStream_t s) {
@@ -765,46 +770,6 @@ int launch(const GemmArgs& g, hipStream_t s) {
 
 }  // namespace
 
-// Few tiles: a launch costs its number of rounds of 256 concurrent tiles, the last of them partly empty.  Half-width
-// tiles cost 0.6 of a full one each and fill the rounds better; they are taken where that arithmetic says so (a layer
-// of a few thousand tokens), never for a launch of many rounds.  est_tiles: expected number of row tiles (0: unknown).
-static bool few_tiles_narrow(int ndim, int est_tiles) {
-  if (est_tiles <= 0 || ndim % Tile::BN != 0) return false;
-  const long full = (long)est_tiles * (ndim / Tile::BN);
-  const long rounds_full = (full + 255) / 256, rounds_half = (2 * full + 255) / 256;
-  return rounds_full <= 4 && 0.6 * rounds_half < 0.95 * rounds_full;
-}
-
-// Rows per tile of the kRaggedM launches.  A 256-row tile of an expert with a few dozen rows computes padding, one block
-// per CU, while the weights it streams are the only work that is needed; 64- and 128-row tiles run two blocks per CU
-// (all but the 128-row SwiGLU one), take any width in 128-column tiles and fill the chip with fewer rows.  They feed
-// fewer MFMAs per byte read, so full tiles win again once experts fill them.  Measured, us of a whole step with
-// 256 / 128 / 64 rows, at a mean of n rows per expert:
-//   32 experts of 2048 x 2048   n = 20: 563 / 537 / 502   n = 60: 592 / 573 / 589   n = 112: 617 / 653 / 694
-//   64 experts of 1408 x 1408   n = 40: 731 / 512 / 498   n = 96: 778 / 562 / 610
-//   16 experts of 4096 x 2048   n = 40: 573 / 554 / 521   n = 80: 594 / 577 / 641   n = 112: 610 / 690 / 721
-// A short contraction is mostly prologue and epilogue, which two blocks per CU overlap, and the lines lie higher:
-//   16 experts of 768 x 2048    n = 128: 283 / 209 / 199  n = 256: 293 / 291 / 276  n = 320: 310 / 325 / 325
-//   64 experts of 512 x 352     n = 192: 239 / 182 / 173  n = 512: 316 / 275 / 278
-// (the down projection contracts over d_ff: measured up to d_ff = 4 d_model).  Above the line of 64 rows such a layer
-// takes 128 where one to three rounds of 256 concurrent full tiles would end in a round that is at most 0.6 full: full
-// tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512 (2.5 rounds,
-// unevenly loaded) 473 / 385 / 428, 24 experts of 768 x 768 at n = 562 (1.1) 279 / 268 / 282, and lose nothing to a round that is nearly full (n = 320 above, 1.75).
-// The same rule cost up to 15 % at 904 and 1000 columns, where the full tiles' column tail has a launch of its own.
-int mfma_row_tile(long rows, int n_experts, int d_model, int d_ff) {
-  const bool short_k = d_model <= 896 && d_ff <= 4L * d_model;
-  const long to64 = !short_k ? 48 : d_model <= 640 ? 512 : 256;
-  if (rows <= to64 * n_experts) return Rows64::BM;
-  if (!short_k) return rows <= 96L * n_experts ? TileShort::BM : Tile::BM;
-  const long full = (rows / Tile::BM + (n_experts + 1) / 2) * cdiv(d_ff, Tile::BN / 2);   // SwiGLU tiles to expect
-  return full >= 256 && full < 3 * 256 && full % 256 <= 154 ? TileShort::BM : Tile::BM;
-}
-// number of gate-gradient partials per row that the kEpiDSwiglu epilogue writes for ndim columns (two per column tile)
-int mfma_rowdot_parts(int ndim, int row_tile, int est_tiles) {
-  if (row_tile != Tile::BM) return 2 * cdiv(ndim, Rows64Narrow::BN);
-  return few_tiles_narrow(ndim, est_tiles) ? 2 * (ndim / TileNarrow::BN) : 2 * cdiv(ndim, Tile::BN);
-}
-
 // kRaggedM on row tiles shorter than 256.  W: the fused SwiGLU (gate and up columns side by side), N: everything else
 template <typename W, typename N>
 static int launch_short(int epi, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
@@ -824,8 +789,8 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
     if (g.row_tile != Tile::BM) return SPES_EINVAL;
     // A last column tile that is at most half full goes to a launch of its own on the half-width tile (which costs
     // 0.6 of a full one) instead of running a full-width tile on half-empty operands.
-    const int tail = g.Ndim % Tile::BN;
-    if (epi != kEpiSwiglu && g.n_base == 0 && g.Ndim > Tile::BN && tail > 0 && tail <= TileNarrow::BN) {
+    const int tail = plan::column_tail(g.Ndim);
+    if (epi != kEpiSwiglu && g.n_base == 0 && tail > 0) {
       GemmArgs head = g, rest = g;
       head.Ndim = g.Ndim - tail;
       head.est_tiles = 0;            // both parts keep the slot numbering of full-width tiles
@@ -838,7 +803,7 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
       if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, TileNarrow>(rest, s);
       return SPES_EINVAL;
     }
-    if (epi != kEpiSwiglu && g.n_base == 0 && few_tiles_narrow(g.Ndim, g.est_tiles)) {
+    if (epi != kEpiSwiglu && g.n_base == 0 && plan::few_tiles_narrow(g.Ndim, g.est_tiles)) {
       if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, TileNarrow>(g, s);
       if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, TileNarrow>(g, s);
       if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, TileNarrow>(g, s);

@@ -5,6 +5,9 @@
 namespace spes {
 namespace plan {
 
+// sides of the matrix-core tiles
+constexpr int kFullRows = 256, kHalfRows = 128, kQuarterRows = 64, kFullCols = 256, kHalfCols = 128;
+
 inline long tiles(long rows, long cols, int bm, int bn) { return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); }
 
 // Blocks per operand set of a launch over several results of different shapes: the sets share one grid extent, the tile
@@ -17,6 +20,65 @@ inline long set_grid_tiles(const int* rows, const int* cols, int n_sets, int bm,
     if (t > most) most = t;
   }
   return most;
+}
+
+// Columns of a ragged-row GEMM on full tiles that run as a launch of their own, on half-width tiles: a last column tile
+// that is at most half full.
+inline int column_tail(int ndim) {
+  const int tail = ndim % kFullCols;
+  return ndim > kFullCols && tail <= kHalfCols ? tail : 0;
+}
+
+// Few tiles: a launch costs its number of rounds of 256 concurrent tiles, the last of them partly empty.  Half-width
+// tiles cost 0.6 of a full one each and fill the rounds better; they are taken where that arithmetic says so (a layer
+// of a few thousand tokens), never for a launch of many rounds.  est_tiles: expected number of row tiles (0: unknown).
+inline bool few_tiles_narrow(int ndim, int est_tiles) {
+  if (est_tiles <= 0 || ndim % kFullCols != 0) return false;
+  const long full = (long)est_tiles * (ndim / kFullCols);
+  const long rounds_full = (full + 255) / 256, rounds_half = (2 * full + 255) / 256;
+  return rounds_full <= 4 && 0.6 * rounds_half < 0.95 * rounds_full;
+}
+
+// Rows per tile of the ragged-row GEMMs.  A 256-row tile of an expert with a few dozen rows computes padding, one block
+// per CU, while the weights it streams are the only work that is needed; 64- and 128-row tiles run two blocks per CU
+// (all but the 128-row SwiGLU one), take any width in 128-column tiles and fill the chip with fewer rows.  They feed
+// fewer MFMAs per byte read, so full tiles win again once experts fill them.  Measured, us of a whole step with
+// 256 / 128 / 64 rows, at a mean of n rows per expert, even load:
+//   32 experts of 2048 x 2048   n = 20: 563 / 537 / 502   n = 60: 592 / 573 / 589   n = 112: 617 / 653 / 694
+//   64 experts of 1408 x 1408   n = 40: 731 / 512 / 498   n = 96: 778 / 562 / 610   n = 112: 706 / 502 / 560
+//   16 experts of 4096 x 2048   n = 40: 573 / 554 / 521   n = 80: 594 / 577 / 641   n = 112: 610 / 690 / 721
+// (above 96 rows the best height changes with the width and the load; there full tiles stay, also where 128 would win).
+// A short contraction is mostly prologue and epilogue, which two blocks per CU overlap, and the line of 64 rows lies higher:
+//   16 experts of 768 x 2048    n = 128: 234 / 203 / 190  n = 256: 293 / 291 / 276  n = 320: 310 / 325 / 325
+//   64 experts of 512 x 352     n = 192: 239 / 182 / 173  n = 512: 316 / 275 / 278
+// (the down projection contracts over d_ff: measured up to d_ff = 4 d_model) -- as long as the launch is short of blocks.
+// Many full tiles overlap nothing less by themselves, and the longer the contraction, the fewer are many:
+//   48 experts of 384 x 1536    n = 192 (720 tiles): 408 / 292 / 262    48 of 768 x 2048 (960) 474 / 500 / 542
+//   64 experts of 768 x 1024    n = 192 (640 tiles): 340 / 345 / 384    64 of 704 x 2560, n = 224 (1760) 682 / 803 / 944
+// From there on the lines are those of the long contractions, except that a width with a column tail, for which full tiles
+// pay a second launch, keeps 128 rows (64 experts of 640 x 1280, n = 224: 468 / 417 / 466).
+// Above its line of 64 rows a narrow layer takes 128 where one to three rounds of 256 concurrent full tiles would end
+// in one that is at most 0.6 full: full tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512
+// (2.5 rounds, unevenly loaded) 473 / 385 / 428, 24 experts of 768 x 768 at n = 562 (1.1) 279 / 268 / 282.  They lose
+// nothing to a round that is nearly full (n = 320 above, 1.75).
+// The load is not known here; an uneven one moves every line.  Over 2407 measured cells (34 fixed and 422 random
+// shapes under even, normal and Gumbel load) the choice is more than 2 % slower than full tiles in 18, at worst 14 %
+// (64 experts of 464 x 496 at n = 476 under Gumbel load), 0.74 of their time on average, and in 297 at least 10 % off the best of the three.
+inline int row_tile(long rows, int n_experts, int d_model, int d_ff) {
+  if (rows <= 48L * n_experts) return kQuarterRows;
+  const bool narrow = d_model <= 896 && d_ff <= 4L * d_model;
+  const long full = (rows / kFullRows + (n_experts + 1) / 2) * ((d_ff + kHalfCols - 1) / kHalfCols);   // SwiGLU tiles to expect
+  const bool below = narrow && rows <= (d_model <= 640 ? 512L : 256L) * n_experts;
+  if (below && full * d_model <= 448 * 1024) return kQuarterRows;
+  if (rows <= 96L * n_experts || (below && column_tail(d_model) > 0)) return kHalfRows;
+  if (narrow && full >= 256 && full < 3 * 256 && full % 256 <= 154) return kHalfRows;
+  return kFullRows;
+}
+
+// number of gate-gradient partials per row that the kEpiDSwiglu epilogue writes for ndim columns (two per column tile)
+inline int rowdot_parts(int ndim, int row_tile, int est_tiles) {
+  if (row_tile != kFullRows || few_tiles_narrow(ndim, est_tiles)) return 2 * ((ndim + kHalfCols - 1) / kHalfCols);
+  return 2 * ((ndim + kFullCols - 1) / kFullCols);
 }
 
 // Weight gradients, all three matrices in one launch: 128 x 128 tiles, two blocks per CU, or 256 x 256 tiles, one per CU.

@@ -7,21 +7,32 @@ from test_gpu_layer import _full_parity
 
 pytestmark = pytest.mark.gpu
 
+# case, rows per tile, and how full tiles cut the columns of the down projection: a tail of that many columns on half-width
+# tiles, half-width tiles throughout, or full ones (test_plan.py checks both)
+CASES = [
+    (dict(T=1, d=904, M=4, f=8, k=1, n_trainable=2), 64, "short"),                                   # one row in the launch
+    (dict(T=96, d=904, M=8, f=136, k=4, n_trainable=3), 64, "short"),                                # 48 a head: the last 64-row case
+    (dict(T=97, d=904, M=8, f=264, k=4, n_trainable=3, bias="normal", bias_scale=2.0), 128, "short"),    # full and ragged tiles
+    (dict(T=192, d=1032, M=8, f=72, k=4, n_trainable=3, bias="normal", bias_scale=8.0), 128, "short"),   # 96 a head, experts without a row
+    (dict(T=193, d=904, M=8, f=136, k=4, n_trainable=3), 256, "full"),
+    (dict(T=260, d=1032, M=8, f=328, k=4, n_trainable=3), 256, 8),                                   # column tails of 8 and 72
+    (dict(T=300, d=1024, M=8, f=512, k=4, n_trainable=3), 256, "half"),                              # half-width launches
+    (dict(T=300, d=1152, M=6, f=640, k=2, n_trainable=2), 256, 128),                                 # tails exactly half a tile wide
+    (dict(T=300, d=1088, M=6, f=576, k=2, renorm=1, n_trainable=3), 256, 64),                        # a quarter
+    (dict(T=512, d=896, M=4, f=200, k=2, n_trainable=2), 64, "short"),                               # short contraction, 256 a head
+    (dict(T=1100, d=264, M=16, f=1048, k=8, n_trainable=2), 128, "short"),                           # 378 full tiles, 1.48 rounds
+    (dict(T=1040, d=256, M=8, f=1024, k=4, n_trainable=2), 256, "half"),                             # 160 full tiles
+    (dict(T=1023, d=640, M=4, f=136, k=2, n_trainable=2), 64, "short"),                              # shorter one, 511.5 a head
+    (dict(T=64, d=136, M=8, f=552, k=2, n_trainable=8, bias="normal", bias_scale=8.0), 64, "short"),     # d_ff > 4 d_model
+    (dict(T=400, d=136, M=8, f=544, k=2, n_trainable=2), 64, "short"),                               # 100 a head, d_ff = 4 d_model ...
+    (dict(T=400, d=136, M=8, f=552, k=2, n_trainable=2), 256, "full"),                               # ... and beyond
+    (dict(T=1536, d=768, M=8, f=1024, k=2, n_trainable=2), 256, "half"),                             # 128 full tiles
+    (dict(T=1600, d=520, M=64, f=2080, k=4, n_trainable=2), 128, "short"),                           # many full tiles, d_model with a column tail
+    (dict(T=1600, d=768, M=64, f=1792, k=4, n_trainable=2), 256, "full"),                            # ... without one
+]
 
-@pytest.mark.parametrize("kw", [
-    dict(T=1, d=904, M=4, f=8, k=1, n_trainable=2),                                   # one row in the launch
-    dict(T=96, d=904, M=8, f=136, k=4, n_trainable=3),                                # 48 a head: the last 64-row case
-    dict(T=97, d=904, M=8, f=264, k=4, n_trainable=3, bias="normal", bias_scale=2.0),    # 128 rows, full and ragged tiles
-    dict(T=192, d=1032, M=8, f=72, k=4, n_trainable=3, bias="normal", bias_scale=8.0),   # 96 a head, experts without a row
-    dict(T=193, d=904, M=8, f=136, k=4, n_trainable=3),                               # 256 rows
-    dict(T=260, d=1032, M=8, f=328, k=4, n_trainable=3),                              # 256 rows, column tails of 8 and 72
-    dict(T=300, d=1024, M=8, f=512, k=4, n_trainable=3),                              # 256 rows, half-width launches
-    dict(T=512, d=896, M=4, f=200, k=2, n_trainable=2),                               # short contraction, 256 a head
-    dict(T=1100, d=264, M=16, f=1048, k=8, n_trainable=2),                            # 128 rows: 378 full tiles, 1.48 rounds
-    dict(T=1040, d=256, M=8, f=1024, k=4, n_trainable=2),                             # 256 rows: 160 full tiles
-    dict(T=1023, d=640, M=4, f=136, k=2, n_trainable=2),                              # shorter one, 511.5 a head
-    dict(T=64, d=136, M=8, f=552, k=2, n_trainable=8, bias="normal", bias_scale=8.0),    # d_ff > 4 d_model
-])
-def test_row_tiles(kw, device):
+
+@pytest.mark.parametrize("kw,rows,down", CASES)
+def test_row_tiles(kw, rows, down, device):
     kw = {"dtype": "bf16", "router_sigma": 0.3, "trainable": "random", **kw}
-    _full_parity(layer_inputs(custom_config(**kw)), device, "row tiles")
+    _full_parity(layer_inputs(custom_config(**kw)), device, f"{rows}-row tiles")

@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_row_tiles import CASES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SHIM = """
@@ -13,6 +15,10 @@ using namespace spes;
 extern "C" {
 long set_grid_tiles(const int* m, const int* n, int sets, int bm, int bn) { return plan::set_grid_tiles(m, n, sets, bm, bn); }
 int wgrad_small_tiles(long full, int mean, int most) { return plan::wgrad_small_tiles(full, mean, most); }
+int row_tile(long rows, int experts, int d, int f) { return plan::row_tile(rows, experts, d, f); }
+int rowdot_parts(int n, int row_tile, int est) { return plan::rowdot_parts(n, row_tile, est); }
+int column_tail(int n) { return plan::column_tail(n); }
+int few_tiles_narrow(int n, int est) { return plan::few_tiles_narrow(n, est); }
 }
 """
 
@@ -26,6 +32,7 @@ def plan(tmp_path_factory):
                     os.path.join(ROOT, "paper_2602_11543_amd", "csrc"), str(src), "-o", str(lib)], check=True)
     p = ctypes.CDLL(str(lib))
     p.set_grid_tiles.restype = ctypes.c_long
+    p.row_tile.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     p.wgrad_small_tiles.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return p
 
@@ -46,3 +53,51 @@ def test_sets_share_the_grid_of_the_largest(plan, d, f, bm):
 ])
 def test_weight_gradient_tiles(plan, full, mean, most, small):
     assert plan.wgrad_small_tiles(full, mean, most) == small
+
+
+def test_row_tile_lines(plan):
+    rt = lambda mean, M, d, f, more=0: plan.row_tile(mean * M + more, M, d, f)
+    # long contractions: 48 and 96 rows a head, whatever the width
+    for d, f in ((2048, 2048), (897, 512), (904, 3616), (768, 3080)):
+        assert [rt(48, 16, d, f), rt(48, 16, d, f, 1), rt(96, 16, d, f), rt(96, 16, d, f, 1), rt(2000, 16, d, f)] == [64, 128, 128, 256, 256]
+    # narrow layers with few tiles: 256 rows, 512 up to 640 columns
+    assert [rt(256, 4, 896, 512), rt(256, 4, 896, 512, 1), rt(512, 4, 640, 512), rt(512, 4, 640, 512, 1)] == [64, 256, 64, 256]
+    assert rt(100, 8, 136, 544) == 64 and rt(100, 8, 136, 552) == 256           # d_ff up to 4 d_model
+    # many full tiles (d_model times their number beyond 458752): full tiles again, or 128 rows for a width with a column tail
+    assert [rt(100, 64, 768, f) for f in (1280, 1408, 1792)] == [64, 128, 256]  # 570, 627 and 798 tiles; the line is at 597
+    assert [rt(n, 64, 704, 2560) for n in (48, 49, 96, 97, 224)] == [64, 128, 128, 256, 256]
+    assert [rt(n, 64, 640, 1280) for n in (49, 224, 512)] == [64, 128, 128]
+    assert rt(192, 48, 384, 1536) == 64                                         # 720 tiles of a short contraction
+    # one to three rounds of full tiles, the last one at most 0.6 full
+    rounds = lambda M, d, f, mean: ((mean * M // 256 + (M + 1) // 2) * -(-f // 128), rt(mean, M, d, f))
+    assert rounds(16, 768, 2048, 320) == (448, 256)
+    assert rounds(16, 768, 2048, 400) == (528, 128)
+    assert rounds(16, 768, 2048, 512) == (640, 128)
+    assert rounds(16, 768, 2048, 688) == (816, 256)                             # more than three rounds
+
+
+def test_gate_gradient_partials(plan):
+    """Two per column tile; the layout reserves ceil(f/64) + 1 of them, which every height and width has to stay within."""
+    for f in range(8, 6145, 8):
+        for rows in (64, 128, 256):
+            for est in (0, 1, 16, 100, 2000):
+                n = plan.rowdot_parts(f, rows, est)
+                halves = rows < 256 or plan.few_tiles_narrow(f, est)
+                assert n == 2 * -(-f // (128 if halves else 256)) and n <= -(-f // 64) + 1
+        tail = plan.column_tail(f)
+        assert tail == (f % 256 if f > 256 and f % 256 <= 128 else 0)
+
+
+@pytest.mark.parametrize("kw,rows,down", CASES)
+def test_the_layer_cases_take_the_tiles_they_are_for(plan, kw, rows, down):
+    """What the GPU cases say of themselves: row tile, and how the down projection's columns are cut."""
+    M, d, f = kw["M"], kw["d"], kw["f"]
+    R = kw["T"] * kw["k"]
+    assert plan.row_tile(R, M, d, f) == rows
+    if rows < 256:
+        got = "short"
+    elif plan.column_tail(d):
+        got = plan.column_tail(d)
+    else:
+        got = "half" if plan.few_tiles_narrow(d, R // 256 + (M + 1) // 2) else "full"
+    assert got == down
