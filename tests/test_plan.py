@@ -68,12 +68,14 @@ def test_row_tile_lines(plan):
     assert [rt(n, 64, 704, 2560) for n in (48, 49, 96, 97, 224)] == [64, 128, 128, 256, 256]
     assert [rt(n, 64, 640, 1280) for n in (49, 224, 512)] == [64, 128, 128]
     assert rt(192, 48, 384, 1536) == 64                                         # 720 tiles of a short contraction
-    # one to three rounds of full tiles, the last one at most 0.6 full
+    # two or three rounds of full tiles, the last one partly and at most 0.6 full
     rounds = lambda M, d, f, mean: ((mean * M // 256 + (M + 1) // 2) * -(-f // 128), rt(mean, M, d, f))
     assert rounds(16, 768, 2048, 320) == (448, 256)
+    assert rounds(16, 768, 2048, 384) == (512, 256)                             # two rounds, both full
     assert rounds(16, 768, 2048, 400) == (528, 128)
     assert rounds(16, 768, 2048, 512) == (640, 128)
     assert rounds(16, 768, 2048, 688) == (816, 256)                             # more than three rounds
+    assert rounds(8, 512, 2048, 900) == (512, 128)                              # full rounds of the shortest contractions
 
 
 def test_gate_gradient_partials(plan):
