@@ -42,7 +42,7 @@ struct GemmArgs {
   long c_ms;              // row stride of C and E (n stride is 1)
   long c_gs;              // per-group stride of C (kGroupedK)
   int c_f32;              // C is float whatever the storage type
-  int accumulate;
+  int accumulate;         // C += (fp32 results; matrix-core path: launches over operand sets only)
   int Mdim, Ndim;         // extent of m (kGroupedK) and of n
   int n_base;             // kRaggedM: first column this launch computes (columns n_base .. Ndim-1); 0 unless a launch is split
   int rowdot_slot0;       // kEpiDSwiglu: first partial slot this launch writes

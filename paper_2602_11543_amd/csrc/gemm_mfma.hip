@@ -532,14 +532,16 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   // the old values of a whole 32-row slab are requested before the previous slab is stored (see load_ab: a load behind
   // a store waits for that store, and one load, add, store chain per two rows would be 64 round trips a tile; with the
   // three matrices in one launch this took a step of gradient accumulation at 4096 tokens, 2048 x 2048, 8 of 32 experts
-  // from 1619 to 1471 us)
+  // from 1619 to 1471 us).  Only launches over operand sets add; the others keep neither the registers nor the code of it,
+  // with which the down projection and the router GEMMs took 1 to 7 % longer (32768 tokens 4096 x 1408: 2955 -> 2923,
+  // 77 -> 72 and 105 -> 102 us)
   constexpr int F_CPR = ECOLS / 4, F_RPI = 64 / F_CPR, F_NST = 32 / F_RPI;
   const long f_n = n0 + wn * (BN / 2) + (lane % F_CPR) * 4;
   float* const f_ct = reinterpret_cast<float*>(opC0) + e_tile;
-  const bool f_add = EPI == kEpiStore && g.c_f32 && g.accumulate;
-  float4 f_old[EPI == kEpiStore ? F_NST : 1];
+  const bool f_add = SETS && g.accumulate;
+  float4 f_old[SETS ? F_NST : 1];
   auto load_old = [&](int i) {
-    if (EPI == kEpiStore) {
+    if (SETS) {
 #pragma unroll
       for (int st = 0; st < F_NST; ++st) {
         const int rt = e_r0 + i * 32 + st * F_RPI + lane / F_CPR;
@@ -595,19 +597,29 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
       }
     if (EPI == kEpiStore) {
       const bool n_in = f_n < Ndim;
-      float4 out[F_NST];
+      if (SETS) {
+        float4 out[F_NST];
 #pragma unroll
-      for (int st = 0; st < F_NST; ++st) {
-        out[st] = *reinterpret_cast<const float4*>(ep + (st * F_RPI + lane / F_CPR) * EPITCH + (lane % F_CPR) * 4);
-        if (f_add) { out[st].x += f_old[st].x; out[st].y += f_old[st].y; out[st].z += f_old[st].z; out[st].w += f_old[st].w; }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (f_add && i + 1 < TS) load_old(i + 1);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int st = 0; st < F_NST; ++st) {
+          out[st] = *reinterpret_cast<const float4*>(ep + (st * F_RPI + lane / F_CPR) * EPITCH + (lane % F_CPR) * 4);
+          if (f_add) { out[st].x += f_old[st].x; out[st].y += f_old[st].y; out[st].z += f_old[st].z; out[st].w += f_old[st].w; }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (f_add && i + 1 < TS) load_old(i + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int st = 0; st < F_NST; ++st) {
-        const int rt = e_r0 + i * 32 + st * F_RPI + lane / F_CPR;
-        if (rt < e_rows && n_in) *reinterpret_cast<float4*>(f_ct + ((unsigned)rt * (unsigned)c_ms + (unsigned)f_n)) = out[st];
+        for (int st = 0; st < F_NST; ++st) {
+          const int rt = e_r0 + i * 32 + st * F_RPI + lane / F_CPR;
+          if (rt < e_rows && n_in) *reinterpret_cast<float4*>(f_ct + ((unsigned)rt * (unsigned)c_ms + (unsigned)f_n)) = out[st];
+        }
+      } else {
+        // results that nothing is ever added to: stored as they are read
+#pragma unroll
+        for (int st = 0; st < F_NST; ++st) {
+          const int row = st * F_RPI + lane / F_CPR, rt = e_r0 + i * 32 + row;
+          const float4 v = *reinterpret_cast<const float4*>(ep + row * EPITCH + (lane % F_CPR) * 4);
+          if (rt < e_rows && n_in) *reinterpret_cast<float4*>(f_ct + ((unsigned)rt * (unsigned)c_ms + (unsigned)f_n)) = v;
+        }
       }
     } else if (EPI == kEpiSwiglu) {
       // LDS columns [0, ECOLS/2) hold the gate projection, [ECOLS/2, ECOLS) the up projection of the same output columns,
@@ -755,7 +767,7 @@ int launch(const GemmArgs& g, hipStream_t s) {
       if (g.set[i].a_elems >= (1L << 31) || g.set[i].b_elems >= (1L << 31)) return SPES_ESHAPE;
     }
   } else {
-    if (g.a_elems <= 0 || g.b_elems <= 0) return SPES_EINVAL;
+    if (g.a_elems <= 0 || g.b_elems <= 0 || g.accumulate) return SPES_EINVAL;
     if (g.a_elems >= (1L << 31) || g.b_elems >= (1L << 31)) return SPES_ESHAPE;
   }
   const int bno = (EPI == kEpiSwiglu) ? C::BN / 2 : C::BN;
