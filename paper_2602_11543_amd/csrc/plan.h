@@ -55,24 +55,26 @@ inline bool few_tiles_narrow(int ndim, int est_tiles) {
 // Many full tiles overlap nothing less by themselves, and the longer the contraction, the fewer are many:
 //   48 experts of 384 x 1536    n = 192 (720 tiles): 408 / 292 / 262    48 of 768 x 2048 (960) 474 / 500 / 542
 //   64 experts of 768 x 1024    n = 192 (640 tiles): 340 / 345 / 384    64 of 704 x 2560, n = 224 (1760) 682 / 803 / 944
-// From there on the lines are those of the long contractions, except that a width with a column tail, for which full tiles
-// pay a second launch, keeps 128 rows (64 experts of 640 x 1280, n = 224: 468 / 417 / 466).
+// From there on 64-row tiles end at 64 rows; 128-row ones go on as far as some more tiles (48 experts of 704 x 2752,
+// n = 104, 946 tiles: 564 / 474 / 496), or wherever full tiles pay a second launch for a column tail (64 experts of
+// 640 x 1280, n = 224: 468 / 417 / 466).
 // Above its line of 64 rows a narrow layer takes 128 where two or three rounds of 256 concurrent full tiles would end
 // in one that is partly and at most 0.6 full: full tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512
 // (2.5 rounds, unevenly loaded) 473 / 385 / 428, 24 experts of 768 x 768 at n = 562 (1.1) 279 / 268 / 282.  A round that is
 // full, or nearly, is lost by them: n = 384 at 768 x 2048 (2.0) 324 / 336 / 341, n = 320 above (1.75), unless
 // the load spills into a third (n = 384, normal load: 364 / 323 / 334); only the shortest contractions gain under any
 // load (8 experts of 512 x 2048, n = 900, 2.0: 287 / 271 / 280).
-// The load is not known here; an uneven one moves every line.  Over 2407 measured cells (34 fixed and 422 random
-// shapes under even, normal and Gumbel load) the choice is more than 2 % slower than full tiles in 18, at worst 14 %
-// (64 experts of 464 x 496 at n = 476 under Gumbel load), 0.74 of their time on average, and in 297 at least 10 % off the best of the three.
+// The load is not known here; an uneven one moves every line.  Over 5062 measured cells (34 fixed and 1307 random
+// shapes under even, normal and Gumbel load) the choice takes 0.73 of the time of full tiles on average, is more than 2 %
+// slower than they are in 53, 26 of them under Gumbel load (at worst 21 %), and at least 10 % off the best height in 627.
 inline int row_tile(long rows, int n_experts, int d_model, int d_ff) {
   if (rows <= 48L * n_experts) return kQuarterRows;
   const bool narrow = d_model <= 896 && d_ff <= 4L * d_model;
   const long full = (rows / kFullRows + (n_experts + 1) / 2) * ((d_ff + kHalfCols - 1) / kHalfCols);   // SwiGLU tiles to expect
   const bool below = narrow && rows <= (d_model <= 640 ? 512L : 256L) * n_experts;
-  if (below && full * d_model <= 448 * 1024) return kQuarterRows;
-  if (rows <= 96L * n_experts || (below && column_tail(d_model) > 0)) return kHalfRows;
+  if (below && (full * d_model <= 448 * 1024 || rows <= 64L * n_experts)) return kQuarterRows;
+  if (rows <= 96L * n_experts) return kHalfRows;
+  if (below && (full * d_model <= 688 * 1024 || column_tail(d_model) > 0)) return kHalfRows;
   const long last = full % 256;                       // tiles of the last round, 0 if it is full
   if (narrow && full >= 256 && full < 3 * 256 && last <= 154 && (last > 0 || d_model <= 640)) return kHalfRows;
   return kFullRows;

@@ -27,8 +27,9 @@ CASES = [
     (dict(T=400, d=136, M=8, f=544, k=2, n_trainable=2), 64, "short"),                               # 100 a head, d_ff = 4 d_model ...
     (dict(T=400, d=136, M=8, f=552, k=2, n_trainable=2), 256, "full"),                               # ... and beyond
     (dict(T=1536, d=768, M=8, f=1024, k=2, n_trainable=2), 256, "half"),                             # 128 full tiles
-    (dict(T=1600, d=520, M=64, f=2080, k=4, n_trainable=2), 128, "short"),                           # many full tiles, d_model with a column tail
-    (dict(T=1600, d=768, M=64, f=1792, k=4, n_trainable=2), 256, "full"),                            # ... without one
+    (dict(T=1040, d=768, M=64, f=1664, k=4, n_trainable=2), 128, "short"),                           # 624 full tiles, 65 a head
+    (dict(T=3072, d=520, M=64, f=2080, k=4, n_trainable=2), 128, "short"),                           # 1360, d_model with a column tail
+    (dict(T=1600, d=768, M=64, f=2304, k=4, n_trainable=2), 256, "full"),                            # 1026, none
 ]
 
 

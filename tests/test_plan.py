@@ -63,10 +63,11 @@ def test_row_tile_lines(plan):
     # narrow layers with few tiles: 256 rows, 512 up to 640 columns
     assert [rt(256, 4, 896, 512), rt(256, 4, 896, 512, 1), rt(512, 4, 640, 512), rt(512, 4, 640, 512, 1)] == [64, 256, 64, 256]
     assert rt(100, 8, 136, 544) == 64 and rt(100, 8, 136, 552) == 256           # d_ff up to 4 d_model
-    # many full tiles (d_model times their number beyond 458752): full tiles again, or 128 rows for a width with a column tail
-    assert [rt(100, 64, 768, f) for f in (1280, 1408, 1792)] == [64, 128, 256]  # 570, 627 and 798 tiles; the line is at 597
-    assert [rt(n, 64, 704, 2560) for n in (48, 49, 96, 97, 224)] == [64, 128, 128, 256, 256]
-    assert [rt(n, 64, 640, 1280) for n in (49, 224, 512)] == [64, 128, 128]
+    # many full tiles: 128-row ones (d_model times their number beyond 448 K), then full ones (beyond 688 K, but not for a
+    # width with a column tail)
+    assert [rt(100, 64, 768, f) for f in (1280, 1408, 2048, 2304)] == [64, 128, 128, 256]   # 570, 627, 912, 1026 tiles; 597, 917
+    assert [rt(n, 64, 704, 2560) for n in (48, 64, 65, 96, 97, 224)] == [64, 64, 128, 128, 256, 256]
+    assert [rt(n, 64, 640, 2560) for n in (64, 65, 97, 224, 512)] == [64, 128, 128, 128, 128]
     assert rt(192, 48, 384, 1536) == 64                                         # 720 tiles of a short contraction
     # two or three rounds of full tiles, the last one partly and at most 0.6 full
     rounds = lambda M, d, f, mean: ((mean * M // 256 + (M + 1) // 2) * -(-f // 128), rt(mean, M, d, f))
