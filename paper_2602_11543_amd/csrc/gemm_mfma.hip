@@ -152,10 +152,10 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   if (SETS) {
     // the sets of a group stand side by side, all of the longest group's tiles first; a set whose result is the
     // transposed shape has the same number of (square) tiles
-    const long per_set = (long)cdiv(Mdim, BM) * gx;
-    const long pos = logical / per_set;
-    set = (int)(pos % g.n_sets);
-    logical = (pos / g.n_sets) * per_set + logical % per_set;
+    const unsigned per_set = (unsigned)cdiv(Mdim, BM) * (unsigned)gx, at = (unsigned)logical;
+    const unsigned pos = at / per_set, grp_pos = pos / 3u;       // three sets (see launch); 32-bit: a grid has fewer blocks
+    set = (int)(pos - grp_pos * 3u);
+    logical = grp_pos * per_set + (at - pos * per_set);
     Mdim = g.set[set].Mdim; Ndim = g.set[set].Ndim;
     gx = cdiv(Ndim, BNO);
   }
@@ -283,17 +283,19 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   // K-strided operands: byte offset of this thread's chunk in k-row 0 of K-tile 0
   const unsigned a_ks_off = (unsigned)(((long)(tid / (BM / 8)) * a_ks + m0 + (tid % (BM / 8)) * 8) * 2);
   const unsigned b_ks_off = (unsigned)(((long)(tid / (BN / 8)) * b_ks + n0 + (tid % (BN / 8)) * 8) * 2);
-  // SETS: k-rows of the tile about to be loaded, from the index table (kidx, fetched one tile ahead so that no load
-  // waits on an index) or in their own order; both operands' tiles have the same k-row per thread and register
+  // SETS: k-rows of the tile about to be loaded, from the index table (kidx) or in their own order; both operands' tiles have
+  // the same k-row per thread and register.  Index j of the next tile is requested behind the last use of this tile's,
+  // the j-th load of B, with the other loads of B between it and its use: with all eight behind the last load of B, the first
+  // load of A drained the memory queue in every K-tile (weight gradients of 8 of 64 experts of 4096 x 1408 at 32768
+  // tokens 938 us, now 877; 31 experts of 3848 x 1160 at 488 rows 1016, now 965)
   constexpr int ACH = BM / 8, BCH = BN / 8;     // 16-byte chunks per k-row of a K-strided tile
   int kidx[SETS ? C::NAS : 1];
   int kdir = 0;
-  auto load_kidx = [&](int step) {
+  auto load_kidx = [&](int step, int j) {
     if (SETS) {
       const int st = step < nsteps ? step : nsteps - 1;
-      const long k = k_begin + (long)(st % nk) * BK + tid / ACH;
-#pragma unroll
-      for (int j = 0; j < C::NAS; ++j) kidx[j] = g.k_rows[k + j * C::KRA < k_end ? k + j * C::KRA : k_end - 1];
+      const int k = (int)k_begin + st * BK + tid / ACH + j * C::KRA;
+      kidx[j] = g.k_rows[k < (int)k_end ? k : (int)k_end - 1];
     }
   };
   const unsigned a_pitch = (unsigned)(a_ks * 2), b_pitch = (unsigned)(b_ks * 2);
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     } else if (SETS) {
       const unsigned row = (unsigned)(b_gather ? kidx[idx] : kdir + idx * C::KRB);
       rb[idx] = buffer_load16(b_rsrc[0], row * b_pitch + b_col, 0u);
-      if (idx == C::NBS - 1) load_kidx(l_step + 1);      // the last use of this tile's indices
+      load_kidx(l_step + 1, idx);      // the last use of this tile's index
     } else {
       rb[idx] = buffer_load16(l_pass ? b_rsrc[1] : b_rsrc[0], b_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRB) * b_ks * 2));
     }
@@ -413,7 +415,8 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
 
   if (nsteps > 0) {
     // prologue: tile 0 -> registers -> LDS stage 0, tile 1 -> registers
-    load_kidx(0);
+#pragma unroll
+    for (int j = 0; j < (SETS ? C::NAS : 0); ++j) load_kidx(0, j);
     set_load_tile(0);
 #pragma unroll
     for (int p = 0; p < NP; ++p) piece(p, 0, false, true, true);
@@ -762,6 +765,7 @@ int launch(const GemmArgs& g, hipStream_t s) {
   static_assert(!SETS || (MODE == kGroupedK && !A_KC && !B_KC && C::BM == C::BN), "operand sets: K-strided, square tiles");
   // operands are addressed with 32-bit byte offsets from their base
   if (SETS) {
+    if (g.npairs != 1 || g.n_sets != 3) return SPES_EINVAL;
     for (int i = 0; i < g.n_sets; ++i) {
       if (g.set[i].a_elems <= 0 || g.set[i].b_elems <= 0) return SPES_EINVAL;
       if (g.set[i].a_elems >= (1L << 31) || g.set[i].b_elems >= (1L << 31)) return SPES_ESHAPE;
