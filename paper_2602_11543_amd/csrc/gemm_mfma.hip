@@ -840,8 +840,9 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
                                                           : launch<kGroupedK, kEpiStore, true, false>(g, s);
   if (!a_kcontig && !b_kcontig) {
     if (g.n_sets > 0) {
-      const long full = (long)g.n_sets * g.n_groups * plan::tiles(g.Mdim, g.Ndim, Tile::BM, Tile::BN);
-      if (plan::wgrad_small_tiles(full, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
+      const long n = (long)g.n_sets * g.n_groups, full = n * plan::tiles(g.Mdim, g.Ndim, Tile::BM, Tile::BN),
+                 small = n * plan::tiles(g.Mdim, g.Ndim, TileSmall::BM, TileSmall::BN);
+      if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
       return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
     }
     if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);

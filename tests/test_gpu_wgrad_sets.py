@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("kw", [
     dict(T=300, d=136, M=8, f=264, k=2, n_trainable=8),                              # 128 x 128 tiles, 8 columns / rows over
     dict(T=300, d=776, M=16, f=520, k=2, n_trainable=16),                            # 576 tiles of 256 x 256
-    dict(T=600, d=776, M=4, f=520, k=4, n_trainable=4),                              # 144 tiles of 256 x 256, 600 rows a head
+    dict(T=600, d=776, M=4, f=1000, k=4, n_trainable=4),                             # 192 tiles of 256 x 256, 600 rows a head
+    dict(T=600, d=776, M=4, f=520, k=4, n_trainable=4),                              # 420 of 128 x 128 (144 full ones)
     dict(T=200, d=128, M=8, f=384, k=1, n_trainable=8, bias="normal", bias_scale=8.0),   # experts without a row
     dict(T=300, d=136, M=8, f=264, k=2, n_trainable=3, dtype="f32"),
     # fp32 results far from square; the transposed sets have fewer tiles and leave the last blocks of the grid idle

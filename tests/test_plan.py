@@ -14,7 +14,7 @@ SHIM = """
 using namespace spes;
 extern "C" {
 long set_grid_tiles(const int* m, const int* n, int sets, int bm, int bn) { return plan::set_grid_tiles(m, n, sets, bm, bn); }
-int wgrad_small_tiles(long full, int mean, int most) { return plan::wgrad_small_tiles(full, mean, most); }
+int wgrad_small_tiles(long full, long small, int mean, int most) { return plan::wgrad_small_tiles(full, small, mean, most); }
 int row_tile(long rows, int experts, int d, int f) { return plan::row_tile(rows, experts, d, f); }
 int rowdot_parts(int n, int row_tile, int est) { return plan::rowdot_parts(n, row_tile, est); }
 int column_tail(int n) { return plan::column_tail(n); }
@@ -33,7 +33,7 @@ def plan(tmp_path_factory):
     p = ctypes.CDLL(str(lib))
     p.set_grid_tiles.restype = ctypes.c_long
     p.row_tile.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
-    p.wgrad_small_tiles.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int]
+    p.wgrad_small_tiles.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return p
 
 
@@ -45,14 +45,14 @@ def test_sets_share_the_grid_of_the_largest(plan, d, f, bm):
     assert got == max(-(-d // bm) * -(-f // 64), -(-f // bm) * -(-d // 64))
 
 
-@pytest.mark.parametrize("full,mean,most,small", [
-    (1, 1, 1, 1), (128, 16384, 16384, 1),                    # CUs without a full tile, at any contraction length
-    (129, 512, 512, 1), (129, 513, 513, 0), (256, 513, 1026, 0), (256, 513, 1027, 1), (240, 16384, 16384, 0),   # one round of them
-    (257, 16384, 16384, 1), (320, 16384, 16384, 1),          # a second one that is nearly empty
-    (321, 64, 64, 0), (1536, 64, 512, 0),
+@pytest.mark.parametrize("full,small,mean,most,want", [
+    (1, 1, 1, 1, 1), (128, 512, 16384, 16384, 1), (162, 510, 13797, 27593, 1),     # one round of small tiles, at any contraction length
+    (162, 513, 512, 512, 1), (162, 513, 513, 513, 0), (256, 1024, 513, 1026, 0), (256, 1024, 513, 1027, 1), (240, 960, 16384, 16384, 0),   # one of full ones
+    (257, 1028, 16384, 16384, 1), (320, 1280, 16384, 16384, 1),                    # a second one that is nearly empty
+    (321, 1284, 64, 64, 0), (1536, 6144, 64, 512, 0),
 ])
-def test_weight_gradient_tiles(plan, full, mean, most, small):
-    assert plan.wgrad_small_tiles(full, mean, most) == small
+def test_weight_gradient_tiles(plan, full, small, mean, most, want):
+    assert plan.wgrad_small_tiles(full, small, mean, most) == want
 
 
 def test_row_tile_lines(plan):
