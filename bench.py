@@ -62,7 +62,8 @@ def profiled_traffic(cfg_name: str, stage: str):
             in_table = False
         elif in_table and line.startswith(kernel):
             cols = line.split()
-            fetch, write = float(cols[-2]), float(cols[-1])
+            # a stage may be two launches (a column tail): their rows are added
+            fetch, write = (fetch or 0.0) + float(cols[-2]), (write or 0.0) + float(cols[-1])
         elif line.startswith("# scale factors:"):
             nums = [float(t.lstrip("x").rstrip(",")) for t in line.split() if t.startswith("x")]
             if len(nums) == 2:
