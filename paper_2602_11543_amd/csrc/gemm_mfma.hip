@@ -6,29 +6,25 @@
 // power is what bounds these kernels: on the same operand values a register-resident loop of it
 // sustains about 2.1 PFLOP/s at 2.1 GHz where the 32x32x16 form sustains 1.85 PFLOP/s at
 // 1.83 GHz (it moves half as many accumulator registers per multiply-add).
-// Operand tiles are staged global -> registers -> LDS with two LDS stages:
-//   * a register is written to LDS (K-tile t+1) and at once reloaded from global
-//     memory (K-tile t+2), so every load has a whole iteration to land;
-//   * those writes and loads are issued one at a time between MFMAs, and the main
-//     loop is a single basic block, so the matrix pipe never waits behind a burst
-//     of memory instructions and the compiler's wait counts are exact;
-//   * MFMA fragments are double-buffered in registers: the reads of k-step s+1 are
-//     issued before the MFMAs of k-step s, and the first fragments of the next K-tile
-//     are read (after the block barrier) under the last MFMAs of the current one.
-// An operand whose contraction index is the fast memory axis lives in LDS as [row][k]
-// without padding; the 16-byte chunks of a row are permuted by the row number (kc_unit)
-// so that both the fragment reads (16 rows x one chunk) and the staging writes (2 rows x
-// 8 chunks) of a group of sixteen lanes cover all banks.
-// An operand whose contraction index is the slow memory axis (the weights in the
-// input-gradient GEMMs, both operands of the weight-gradient GEMMs) keeps its memory
-// order in LDS, [k][row] with a pitch of rows*2+64 bytes: it is loaded in 512-byte
-// runs along a k-row, and the MFMA fragments (eight consecutive k of one row per lane)
-// come out of LDS through the transposing read ds_read_b64_tr_b16, four k at a time.
-// Operands are read through buffer resources (uniform base and byte count, a per-lane
-// 32-bit offset fixed for the whole tile, a uniform offset that moves with the K-tile):
-// the loop computes no addresses, and loads are unconditional - a read beyond the tensor
-// returns zero, a read beyond the tile returns data that is never used (the k tail is
-// zeroed by select on its way into LDS, surplus rows are never stored).
+// Operand tiles go from memory straight into LDS (buffer loads with an LDS destination), K-tiles of 64:
+//   * A wavefront issues an instruction every four cycles and an MFMA takes sixteen, and with one wavefront on a SIMD whatever
+//     does not fit between two MFMAs is lost.  So fragment reads, loads and the scalars of the next tiles are dealt out over
+//     the 128 gaps of a K-tile, one or two to a gap, and the loop is one basic block.
+//   * The loads are spread evenly over the whole iteration: the vector-memory path takes a CU's 64 KB of a K-tile at 64 bytes a
+//     clock, half an iteration, and a wavefront whose load finds it busy stands still.  Cycles per K-tile of gate + up at 32768
+//     tokens 4096 x 1408, 64 experts, 2048 of them MFMAs: a load every second gap 3340, every fourth 2750, every
+//     fifth 2560, every eighth 2390 (no load at all 2300).
+//   * That leaves a load little time in two LDS slots, so the A operand has a third one where LDS has room (256 x 256 tiles: all
+//     160 KB).  With two for both the same loop takes 2740 cycles.
+//   * MFMA fragments are double-buffered in registers: the reads of k-step s+1 are issued before the MFMAs of k-step s.
+// Against staging through registers (a load, then a write to LDS, for every 16 bytes of a lane) this takes the sixteen LDS
+// writes, 64 registers and the waits for them out of a K-tile: 3000 to 3200 cycles before.  The clock under the power cap
+// falls as the cycles do (1.82 to 1.73 GHz), so the time gains less: gate + up above 5.48 -> 4.75 ms, its dgrad 5.44 -> 4.65,
+// the step 19.3 -> 17.7.
+// An operand whose contraction index is the fast memory axis lives in LDS as [row][k], one whose contraction index is the slow
+// axis (the weights in the input-gradient GEMMs, both operands of the weight-gradient GEMMs) as [k][row], loaded in
+// runs along a k-row; its MFMA fragments (eight consecutive k of one row per lane) come out of LDS through the
+// transposing read ds_read_b64_tr_b16, four k at a time.  Both are permuted within a row against bank conflicts (below).
 //
 // The MFMA operands are swapped (weights tile as the "A" input) so that each lane ends
 // up holding runs of four consecutive output columns of one row: epilogues then work
@@ -50,56 +46,43 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kXcds = 8;
 
-template <int BM_, int BN_, int BK_, int MINB_>
+template <int BM_, int BN_, int NSA_, int NSB_, int MINB_>
 struct Cfg {
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, MINB = MINB_;
+  static constexpr int BM = BM_, BN = BN_, MINB = MINB_;
+  static constexpr int NSA = NSA_, NSB = NSB_;              // LDS slots of each operand, one K-tile each
+  static constexpr int BK = 64, KSTEPS = 2;                 // k per K-tile; one MFMA contracts 32
   static constexpr int TM = BM / 32, TN = BN / 32;          // 16 x 16 MFMA tiles per wavefront along m, n
   static constexpr int TS = BM / 64;                        // 32-row slabs of a wavefront's sub-tile (epilogues)
-  static constexpr int KSTEPS = BK / 32;                    // one MFMA contracts 32 k
-  static constexpr int CH = BK / 8;                         // 16-byte chunks of data per LDS row
-  static constexpr int PITCH = CH;                          // row pitch in 16-byte units: no padding, the chunks of a row are
-                                                            // permuted instead (kc_unit below)
-  static constexpr int RP = 256 / CH;                       // rows staged per pass (K-contiguous operand)
-  static constexpr int NA = BM / RP, NB = BN / RP;          // staging registers (uint4) per thread, K-contiguous
-  // K-strided operand: [k][row] in LDS; a k-row of the tile is BM/8 (BN/8) chunks and 64 bytes of padding, so that
-  // the four k-rows one transposing read touches start 16 banks apart
-  static constexpr int KPA = BM / 8 + 4, KPB = BN / 8 + 4;  // k-row pitch in 16-byte units
-  static constexpr int KRA = 256 / (BM / 8), KRB = 256 / (BN / 8);   // k-rows staged per pass
-  static constexpr int NAS = BK / KRA, NBS = BK / KRB;      // staging registers per thread, K-strided
-  static constexpr int RA = NA > NAS ? NA : NAS;            // staging register counts covering both kinds
-  static constexpr int RB = NB > NBS ? NB : NBS;
-  // 16-byte units of an operand's LDS region: [row][k], or [k][row] (above) with a padded k-row
-  static constexpr int a_vec(bool kc) { return kc ? BM * PITCH : BK * KPA; }
-  static constexpr int b_vec(bool kc) { return kc ? BN * PITCH : BK * KPB; }
+  static constexpr int NA = BM / 32, NB = BN / 32;          // 1 KB loads per wavefront and K-tile
+  static constexpr int KRA = 2048 / BM, KRB = 2048 / BN;    // k-rows the four wavefronts load at a time, K-strided operand
+  static constexpr int A_VEC = BM * 8, B_VEC = BN * 8;      // 16-byte units of a slot
+  static constexpr int LDS_VEC = NSA * A_VEC + NSB * B_VEC;
 };
 
-// Position (in 16-byte units) of chunk c of row `row` in the [row][k] LDS layout of a K-contiguous operand with CH
-// chunks per row: the chunk index is XORed with bits 1.. of the row.  Sixteen units span all 64 banks; the unit of
-// (row, c) modulo 16 is (row & 1) * 8 + (c ^ (row >> 1) & 7), so the sixteen rows one group of lanes reads at a
-// common chunk (a fragment read), and the two rows times eight chunks one group of lanes writes, each cover all banks.
-template <int CH>
-__device__ __forceinline__ int kc_unit(int row, int c) { return row * CH + (c ^ ((row >> 1) & (CH - 1))); }
-
-__device__ __forceinline__ uint4 zero4() { return make_uint4(0, 0, 0, 0); }
-// branch-free: the main loop must stay one basic block so that the compiler counts outstanding loads exactly
-__device__ __forceinline__ uint4 sel4(bool keep, const uint4& v) {
-  const uint32_t m = keep ? 0xffffffffu : 0u;
-  return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
-}
-// element-wise copy (an aggregate copy of a staging register keeps the whole register array in scratch memory)
-__device__ __forceinline__ uint4 copy4(const uint4& v) { return make_uint4(v.x, v.y, v.z, v.w); }
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return pack_bf16x2(a, b); }
 
-// raw buffer resource over `bytes` bytes from `base`; loads at byte offsets at or beyond `bytes` return zero
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+// raw buffer resource over `bytes` bytes from `base`: loads at byte offsets at or beyond `bytes` deliver zero
+typedef __attribute__((ext_vector_type(4))) unsigned int rsrc_t;
+__device__ __forceinline__ unsigned uniform(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ rsrc_t make_rsrc(unsigned long base, unsigned bytes) {
+  return rsrc_t{(unsigned)base, (unsigned)(base >> 32), bytes, 0x00020000u};
 }
-// 16 bytes at base + lane_off + uniform_off
-__device__ __forceinline__ uint4 buffer_load16(rsrc_t rs, unsigned lane_off, unsigned uniform_off) {
-  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_off, (int)uniform_off, 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
+constexpr unsigned kOutOfRange = 0xfffffff0u;     // at or beyond any resource: operands have less than 2^31 elements of two bytes
+// One load per wavefront of 64 x 16 bytes straight into LDS: lane l's bytes, from its own offset into the resource, land at
+// the address in M0 + 16 l.  Written as assembly because the compiler makes every LDS read that may follow such a load wait for all of them;
+// here the waits stand in the loop.  (The load has no result register, and address and resource are read when it issues.
+// The scalar write of M0 needs one instruction between it and the load that reads it.)
+__device__ __forceinline__ void set_lds_dest(unsigned lds) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds) : "memory"); }
+__device__ __forceinline__ void load_to_lds(const rsrc_t& rs, unsigned lane_off) {
+  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(lane_off), "s"(rs) : "memory");
+}
+__device__ __forceinline__ void one_instruction() { asm volatile("s_nop 0" ::: "memory"); }
+__device__ __forceinline__ void pin(unsigned& v) { asm volatile("" : "+s"(v)); }       // computed here and not elsewhere
+// wait until at most N vector-memory operations of this wavefront are outstanding and all of its LDS reads have returned, then
+// meet the block's other wavefronts
+template <int N>
+__device__ __forceinline__ void wait_and_meet() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -115,19 +98,23 @@ __device__ __forceinline__ uint2 lds_read_tr(const bf16_t* p) {
 constexpr int kGroupRows = 4;      // row tiles per group of the tile order (ragged-row GEMMs) ...
 constexpr int kGroupMinCols = 8;   // ... used when the output has at least this many column tiles
 
+// result type of kEpiStore: the router scores and the weight gradients are fp32, the rest has the storage type
+constexpr bool f32_out(int mode, bool a_kc, bool b_kc) { return mode == kGroupedK && !(a_kc && !b_kc); }
+
 // SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
 // and result; either operand of a set may take its k-rows through the index table k_rows (the dy rows, or the input
 // rows, of an expert's routed pairs)
 template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C>
 __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs g) {
-  constexpr int BM = C::BM, BN = C::BN, BK = C::BK, TM = C::TM, TN = C::TN, CH = C::CH, RP = C::RP;
-  constexpr int A_VEC = C::a_vec(A_KC), STAGE_VEC = A_VEC + C::b_vec(B_KC);
+  constexpr int BM = C::BM, BN = C::BN, BK = C::BK, TM = C::TM, TN = C::TN, NSA = C::NSA, NSB = C::NSB;
+  constexpr int A_VEC = C::A_VEC, B_VEC = C::B_VEC;
   constexpr int EP_VEC = 32 * (TN * 16 + 4);               // the four wavefronts' epilogue slabs (32 padded float rows each)
-  __shared__ uint4 smem[2 * STAGE_VEC > EP_VEC ? 2 * STAGE_VEC : EP_VEC];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ uint4 smem[C::LDS_VEC > EP_VEC ? C::LDS_VEC : EP_VEC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform(tid >> 6);
   const int l16 = lane & 15, lq = lane >> 4;          // an MFMA operand: lane holds row l16, k = lq*8 .. lq*8+7 of a 32-wide k-step
   const int wm = wave >> 1, wn = wave & 1;
   constexpr int BNO = (EPI == kEpiSwiglu) ? BN / 2 : BN;   // output columns per tile
+  constexpr bool F32_OUT = f32_out(MODE, A_KC, B_KC);
 
   // ---- which tile ----
   const int n_base = MODE == kRaggedM ? g.n_base : 0;
@@ -164,7 +151,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   void* const opC0 = SETS ? g.set[set].C : g.C[0];
   const long a_ks = SETS ? g.set[set].a_ks : g.a_ks, b_ks = SETS ? g.set[set].b_ks : g.b_ks;
   const long c_ms = SETS ? g.set[set].c_ms : g.c_ms;
-  const bool a_gather = SETS && g.set[set].a_gather, b_gather = SETS && g.set[set].b_gather;
+  const bool a_gather = SETS && g.set[set].a_gather, b_gather = SETS && !a_gather;      // one of the two
   int nt;
   long mt_all;
   if (MODE == kRaggedM && gx >= kGroupMinCols) {
@@ -218,36 +205,65 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   }
   const long n0 = n_base + (long)nt * BNO;
 
-  // ---- operands are read through buffer resources: a base (uniform) with a byte count, a 32-bit byte offset per
-  // lane that is fixed for the whole tile, and a uniform offset that moves with the K-tile.  Nothing in the loop
-  // computes an address, and no clamp is needed for memory safety: a read inside the tensor but outside the tile
-  // returns data that is never used (masked k tail, rows that are not stored), a read beyond the tensor returns zero.
-  const unsigned a_bytes = (unsigned)((SETS ? g.set[set].a_elems : g.a_elems) * 2);
-  const unsigned b_bytes = (unsigned)(((SETS ? g.set[set].b_elems : g.b_elems) - b_group) * 2);
-  const rsrc_t a_rsrc[2] = {make_rsrc(opA0, a_bytes), make_rsrc(!SETS && g.A[1] ? g.A[1] : opA0, a_bytes)};
-  const rsrc_t b_rsrc[2] = {make_rsrc(reinterpret_cast<const bf16_t*>(opB0) + b_group, b_bytes),
-                            make_rsrc(reinterpret_cast<const bf16_t*>(!SETS && g.B[1] ? g.B[1] : opB0) + b_group, b_bytes)};
-  // K-contiguous operands: byte offset of this thread's chunk in K-tile 0, per staging register
-  unsigned aoff[A_KC ? C::NA : 1];
-  unsigned boff[B_KC ? C::NB : 1];
+  // ---- operands are read through buffer resources whose base moves with the K-tile; a lane's byte offsets are fixed for the
+  // whole tile (but for gathered k-rows).  The resource ends where the operand does, or, for a K-strided one, where the contraction
+  // range does, so k beyond the range, rows beyond the tensor and whole K-tiles beyond the last one come back as zeros
+  // without a fetch.  Rows inside the tensor but outside the tile bring data that is never stored.
+  const int klen = (int)uniform((unsigned)(k_end - k_begin));
+  const int npass = (EPI == kEpiSwiglu) ? 1 : g.npairs;
+  const int nk = klen > 0 ? (klen + BK - 1) / BK : 1;       // an empty range: one K-tile of zeros
+  const int nsteps = nk * npass;
+  const unsigned a_step = uniform(A_KC ? 2u : a_gather ? 0u : (unsigned)(a_ks * 2));       // bytes per k
+  const unsigned b_step = uniform(B_KC ? 2u : b_gather ? 0u : (unsigned)(b_ks * 2));
+  auto base_of = [&](const void* p, long elems) -> unsigned long {
+    const unsigned long v = reinterpret_cast<unsigned long>(p) + (unsigned long)(elems * 2);
+    return (unsigned long)uniform((unsigned)(v >> 32)) << 32 | uniform((unsigned)v);
+  };
+  const long a_first = A_KC ? k_begin : a_gather ? 0 : k_begin * a_ks, b_first = b_group + (B_KC ? k_begin : b_gather ? 0 : k_begin * b_ks);
+  const unsigned long a_base0 = base_of(opA0, a_first), a_base1 = base_of(!SETS && g.A[1] ? g.A[1] : opA0, a_first);
+  const unsigned long b_base0 = base_of(opB0, b_first), b_base1 = base_of(!SETS && g.B[1] ? g.B[1] : opB0, b_first);
+  const unsigned a_bytes = uniform(A_KC || a_gather ? (unsigned)(((SETS ? g.set[set].a_elems : g.a_elems) - a_first) * 2) : (unsigned)klen * a_step);
+  const unsigned b_bytes = uniform(B_KC || b_gather ? (unsigned)(((SETS ? g.set[set].b_elems : g.b_elems) - b_first) * 2) : (unsigned)klen * b_step);
+
+  // LDS layout of a K-contiguous operand: [row][k], 128 bytes a row, the eight 16-byte chunks of a row permuted by the row
+  // number (chunk c of row r at position c ^ (r >> 1 & 7)), so that the sixteen rows a group of sixteen lanes reads at a common
+  // chunk cover all banks.  The permutation is made on the way in: a load's lanes are eight rows by eight positions, and each
+  // lane asks for the chunk that belongs at its position.
+  const int kc_chunk = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+  // A K-strided operand keeps its memory order, [k][row] without padding; the chunks of a k-row are permuted by twice the
+  // low two bits of k, so that the four k-rows of 32 bytes that one group of lanes reads with the transposing read cover all banks.
+  constexpr int ACH = BM / 8, BCH = BN / 8;       // 16-byte chunks per k-row
+  const int a_krow = wave * (512 / BM) + lane / ACH, b_krow = wave * (512 / BN) + lane / BCH;
+  const unsigned a_col = (unsigned)((m0 + (((lane % ACH) ^ (2 * (a_krow & 3))) * 8)) * 2);
+  const unsigned b_col = (unsigned)((n0 + (((lane % BCH) ^ (2 * (b_krow & 3))) * 8)) * 2);
+  auto ks_off = [](unsigned long o) { return o < kOutOfRange ? (unsigned)o : kOutOfRange; };   // k-rows beyond a short, wide operand
+  unsigned aoff[C::NA], boff[C::NB];
   if (A_KC) {
+    int m_row[C::NA];
 #pragma unroll
     for (int i = 0; i < C::NA; ++i) {
-      long m = m0 + tid / CH + RP * i;
-      if (MODE == kRaggedM && g.a_rows) m = g.a_rows[m < m_end ? m : m_end - 1];       // the index table is only that long
-      aoff[i] = (unsigned)((m * g.a_ms + (tid % CH) * 8) * 2);
+      const long m = m0 + wave * 8 + (lane >> 3) + 32 * i;
+      m_row[i] = (int)m;
+      if (MODE == kRaggedM && g.a_rows) m_row[i] = g.a_rows[m < m_end ? m : m_end - 1];       // the index table is only that long
     }
-  }
-  // fused SwiGLU: staging register i holds rows of the gate matrix (B[0]) or of the up matrix (B[1]); tile row nl ->
-  // wave column, then (BN/4) gate columns followed by the matching (BN/4) up columns
-  constexpr int SW_W = BN / 2, SW_H = BN / 4;
-  static_assert(EPI != kEpiSwiglu || (SW_H % RP == 0), "a staging register must not straddle the gate / up boundary");
-  if (B_KC) {
 #pragma unroll
-    for (int i = 0; i < C::NB; ++i) {
-      const int nl = tid / CH + RP * i;
+    for (int i = 0; i < C::NA; ++i) aoff[i] = (unsigned)((m_row[i] * g.a_ms + kc_chunk * 8) * 2);
+  } else {
+#pragma unroll
+    for (int i = 0; i < C::NA; ++i) aoff[i] = ks_off((a_krow + i * C::KRA) * a_ks * 2 + a_col);
+  }
+  // fused SwiGLU: load i brings rows of the gate matrix (B[0]) or of the up matrix (B[1]); tile row nl -> wave column, then
+  // (BN/4) gate columns followed by the matching (BN/4) up columns
+  constexpr int SW_W = BN / 2, SW_H = BN / 4;
+  static_assert(EPI != kEpiSwiglu || (SW_H % 32 == 0), "a load must not straddle the gate / up boundary");
+#pragma unroll
+  for (int i = 0; i < C::NB; ++i) {
+    if (B_KC) {
+      const int nl = wave * 8 + (lane >> 3) + 32 * i;
       const long col = (EPI == kEpiSwiglu) ? n0 + (nl / SW_W) * SW_H + (nl % SW_H) : n0 + nl;
-      boff[i] = (unsigned)((col * g.b_ns + (tid % CH) * 8) * 2);
+      boff[i] = (unsigned)((col * g.b_ns + kc_chunk * 8) * 2);
+    } else {
+      boff[i] = ks_off((b_krow + i * C::KRB) * b_ks * 2 + b_col);
     }
   }
 
@@ -259,233 +275,265 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[j][i][r] = 0.f;
+  // (zeros that the compiler takes for different values: from one common zero it starts the loop with accumulators that it then
+  // moves to their places in every iteration)
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (C::MINB == 1) asm("" : "+a"(acc[j][i]));
+      else asm("" : "+v"(acc[j][i]));
+    }
 
-  const int npass = (EPI == kEpiSwiglu) ? 1 : g.npairs;
-  const long klen = k_end - k_begin;
-  const int nk = (int)((klen + BK - 1) / BK);
-  const int nsteps = nk * npass;
-
-  // ---- staging registers and the pieces of the global -> register -> LDS pipeline ----
-  // The loads and LDS writes of one K-tile are cut into pieces that the main loop issues one at a time between
-  // MFMAs: a wavefront that issues sixteen 1 KB loads (or writes) back to back sits behind the memory queues for
-  // well over a thousand cycles with its matrix pipe idle, while one piece every few MFMAs is absorbed for free.
-  // Piece i = write staging register i to LDS (tile t+1), then reload it (tile t+2).
-  uint4 ra[C::RA], rb[C::RB];
-  unsigned a_keep = 0, b_keep = 0;       // k inside the contraction range, for the tile held in ra / rb (K-strided: bit i for register i)
-  unsigned a_keep_n = 0, b_keep_n = 0;   // the same for the tile being loaded
-  constexpr int NPA = A_KC ? C::NA : C::NAS;
-  constexpr int NPB = B_KC ? C::NB : C::NBS;
-  constexpr int NP = NPA + NPB;
-
-  // scalar coordinates of the K-tile being loaded
-  int l_step = 0, l_kq = 0, l_pass = 0;           // tile number, k of the tile relative to the group, pass
-  const int klen32 = (int)(k_end - k_begin);
-  // K-strided operands: byte offset of this thread's chunk in k-row 0 of K-tile 0
-  const unsigned a_ks_off = (unsigned)(((long)(tid / (BM / 8)) * a_ks + m0 + (tid % (BM / 8)) * 8) * 2);
-  const unsigned b_ks_off = (unsigned)(((long)(tid / (BN / 8)) * b_ks + n0 + (tid % (BN / 8)) * 8) * 2);
-  // SETS: k-rows of the tile about to be loaded, from the index table (kidx) or in their own order; both operands' tiles have
-  // the same k-row per thread and register.  Index j of the next tile is requested behind the last use of this tile's,
-  // the j-th load of B, with the other loads of B between it and its use: with all eight behind the last load of B, the first
-  // load of A drained the memory queue in every K-tile (weight gradients of 8 of 64 experts of 4096 x 1408 at 32768
-  // tokens 938 us, now 877; 31 experts of 3848 x 1160 at 488 rows 1016, now 965)
-  constexpr int ACH = BM / 8, BCH = BN / 8;     // 16-byte chunks per k-row of a K-strided tile
-  int kidx[SETS ? C::NAS : 1];
-  int kdir = 0;
-  auto load_kidx = [&](int step, int j) {
+  // ---- the K-tiles being loaded (numbers la, lb; the tiles of all passes in a row) ----
+  constexpr int NA = C::NA, NB = C::NB, NP = NA + NB;
+  constexpr bool TWO_PASS = MODE == kRaggedM && EPI == kEpiStore && !B_KC;      // the one launch with two operand pairs
+  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) uint4*)smem + (unsigned)wave * 1024u;
+  struct Src { unsigned lo, hi, bytes, left, dst; };     // resource base and size; k left from the tile's first one on; LDS address
+  Src as = {0, 0, 0, 0, 0}, bs = as;
+  // K-tile that a block begins with: it goes round from there.  On 64-row tiles the time is the stream of the weights, a row
+  // tile or two per expert, and all blocks that start together would walk down the same 128 bytes of every row, which with
+  // rows a power of two apart are the same few memory channels.  Each XCD starts an eighth further on; blocks of one XCD share
+  // panels in its L2 and stay together.  200 tokens, 32 experts of 2048 x 2048, top-4: gate + up 104 to 148 us (by where the
+  // buffers lie) -> 101, down 88 -> 50 (5.3 TB/s), the forward pass 228 -> 176; a start of its own for every block is 1 to 5 %
+  // slower at d_model = 640 and 3000.  Taller tiles share panels among many blocks that drift apart by themselves: no gain.
+  const int k_rot = MODE == kRaggedM && BM == 64 ? (int)uniform(((blockIdx.x % kXcds) * (unsigned)nk) / kXcds) : 0;
+  unsigned b1_lo = 0, b1_hi = 0;                         // fused SwiGLU: the base in the second matrix
+  // in steps, so that the main loop can deal them out: 0 the k, 1 the base, 2 the size, 3 where to
+  auto next_src = [&](Src& x, int step, int lt, unsigned per_k, unsigned long base0, unsigned long base1, unsigned bytes, unsigned dst) {
+    const bool second = TWO_PASS && lt >= nk;
+    if (step == 0) {
+      int kt = lt - (second ? nk : 0) + k_rot;
+      if (MODE == kRaggedM && BM == 64) kt -= kt >= nk ? nk : 0;
+      x.left = (unsigned)(klen - kt * BK);
+      pin(x.left);
+    } else if (step == 1) {
+      const unsigned long at = (second ? base1 : base0) + ((unsigned)klen - x.left) * per_k;
+      x.lo = (unsigned)at; x.hi = (unsigned)(at >> 32);
+      pin(x.lo); pin(x.hi);
+    } else if (step == 2) {
+      x.bytes = lt < nsteps ? bytes - ((unsigned)klen - x.left) * per_k : 0u;
+      pin(x.bytes);
+    } else {
+      x.dst = dst;
+      pin(x.dst);
+    }
+  };
+  auto next_a = [&](int step, int la, int slot) {
+    next_src(as, step, la, a_step, a_base0, a_base1, a_bytes, lds0 + (unsigned)slot * (A_VEC * 16u));
+  };
+  auto next_b = [&](int step, int lb, int slot) {
+    next_src(bs, step, lb, b_step, b_base0, b_base1, b_bytes, lds0 + NSA * A_VEC * 16u + (unsigned)slot * (B_VEC * 16u));
+    if (EPI == kEpiSwiglu && step == 1) {
+      const unsigned long at = b_base1 + ((unsigned)klen - bs.left) * b_step;
+      b1_lo = (unsigned)at; b1_hi = (unsigned)(at >> 32);
+      pin(b1_lo); pin(b1_hi);
+    }
+  };
+  // k-rows of the tile to be loaded next, from the index table: requested while the tile before is being loaded, turned into
+  // offsets (rows beyond the range: out of the resource) behind the wait that empties the memory queue in any case
+  int kidx[SETS ? NA : 1];
+  auto load_kidx = [&](int lt, int j) {
     if (SETS) {
-      const int st = step < nsteps ? step : nsteps - 1;
-      const int k = (int)k_begin + st * BK + tid / ACH + j * C::KRA;
-      kidx[j] = g.k_rows[k < (int)k_end ? k : (int)k_end - 1];
+      const int k = (int)k_begin + lt * BK + a_krow + j * C::KRA;
+      kidx[j] = g.k_rows[max(0, min(k, (int)k_end - 1))];
     }
   };
-  const unsigned a_pitch = (unsigned)(a_ks * 2), b_pitch = (unsigned)(b_ks * 2);
-  const unsigned a_col = (unsigned)((m0 + (tid % ACH) * 8) * 2), b_col = (unsigned)((n0 + (tid % BCH) * 8) * 2);
-  // registers 0..n-1 of a K-strided operand hold k-rows inside the contraction range
-  // (first_kq = k of the thread's first register relative to the group; rows_per_pass is a power of two)
-  auto keep_bits = [&](int first_kq, int rows_per_pass, int nreg) -> unsigned {
-    const int left = klen32 - first_kq;
-    int n = (left + rows_per_pass - 1) >> __builtin_ctz(rows_per_pass);      // arithmetic shift: negative stays negative
-    n = max(0, min(n, nreg));
-    return (1u << n) - 1u;
-  };
-  auto set_load_tile = [&](int step) {
-    l_pass = step / nk;
-    l_step = step;
-    l_kq = (step - l_pass * nk) * BK;
-    if (SETS) kdir = (int)k_begin + l_kq + tid / ACH;
-    if (A_KC) {
-      a_keep_n = (l_kq + (tid % CH) * 8 < klen32) ? 0xffu : 0u;
-    } else {
-      a_keep_n = keep_bits(l_kq + tid / ACH, C::KRA, C::NAS);
-    }
-    if (B_KC) {
-      b_keep_n = (l_kq + (tid % CH) * 8 < klen32) ? 0xffu : 0u;
-    } else {
-      b_keep_n = keep_bits(l_kq + tid / BCH, C::KRB, C::NBS);
+  const unsigned g_pitch = (unsigned)((a_gather ? a_ks : b_ks) * 2), g_col = a_gather ? a_col : b_col;
+  auto take_kidx = [&](int j) {
+    if (SETS) {
+      // (beyond the range: all ones from bit 4 up, which is kOutOfRange; arithmetic, because a select becomes a branch)
+      const unsigned off = ((unsigned)kidx[j] * g_pitch + g_col) | ((unsigned)(((int)as.left - 1 - a_krow - j * C::KRA) >> 31) & kOutOfRange);
+      aoff[j] = a_gather ? off : aoff[j];
+      boff[j] = a_gather ? boff[j] : off;
     }
   };
-
-  auto load_a = [&](int idx) {   // idx: staging register
-    const rsrc_t rs = l_pass ? a_rsrc[1] : a_rsrc[0];
-    if (A_KC) {
-      ra[idx] = buffer_load16(rs, aoff[idx], (unsigned)((k_begin + l_kq) * 2));
-    } else if (SETS) {
-      const unsigned row = (unsigned)(a_gather ? kidx[idx] : kdir + idx * C::KRA);
-      ra[idx] = buffer_load16(rs, row * a_pitch + a_col, 0u);
+  // load p of a K-tile, B first, in two steps; `masked`: the tile may reach beyond the contraction range of K-contiguous operands
+  auto aim = [&](int p) { set_lds_dest(p < NB ? bs.dst + (unsigned)p * 4096u : as.dst + (unsigned)(p - NB) * 4096u); };
+  auto load = [&](int p, bool masked) {
+    if (p < NB) {
+      const unsigned off = B_KC && masked && kc_chunk * 8 >= (int)bs.left ? kOutOfRange : boff[p];
+      // (the load -> matrix assignment of the fused SwiGLU is the same for every thread)
+      const bool up = EPI == kEpiSwiglu && ((32 * p) % SW_W) / SW_H != 0;
+      load_to_lds(rsrc_t{up ? b1_lo : bs.lo, up ? b1_hi : bs.hi, bs.bytes, 0x00020000u}, off);
     } else {
-      ra[idx] = buffer_load16(rs, a_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRA) * a_ks * 2));
-    }
-  };
-  auto load_b = [&](int idx) {
-    if (B_KC) {
-      // (the register -> matrix assignment of the fused SwiGLU is the same for every thread)
-      const bool second = (EPI == kEpiSwiglu) ? (((RP * idx) % SW_W) / SW_H) != 0 : l_pass != 0;
-      rb[idx] = buffer_load16(second ? b_rsrc[1] : b_rsrc[0], boff[idx], (unsigned)((k_begin + l_kq) * 2));
-    } else if (SETS) {
-      const unsigned row = (unsigned)(b_gather ? kidx[idx] : kdir + idx * C::KRB);
-      rb[idx] = buffer_load16(b_rsrc[0], row * b_pitch + b_col, 0u);
-      load_kidx(l_step + 1, idx);      // the last use of this tile's index
-    } else {
-      rb[idx] = buffer_load16(l_pass ? b_rsrc[1] : b_rsrc[0], b_ks_off, (unsigned)((k_begin + l_kq + idx * C::KRB) * b_ks * 2));
-    }
-  };
-  // `masked`: the tile may reach beyond the contraction range and its k tail is zeroed on the way into LDS.  Only the
-  // last K-tile of a pass can need that; every other tile goes to LDS as it came (the four selects per register are
-  // most of the vector-ALU work of an iteration, and the matrix pipe waits while they issue).
-  auto write_a = [&](int stage, int idx, bool masked) {
-    uint4* ta = smem + stage * STAGE_VEC;
-    if (A_KC) {
-      ta[kc_unit<CH>(tid / CH + RP * idx, tid % CH)] = masked ? sel4(a_keep != 0, ra[idx]) : copy4(ra[idx]);
-    } else {
-      ta[(tid / ACH + idx * C::KRA) * C::KPA + tid % ACH] = masked ? sel4((a_keep >> idx) & 1u, ra[idx]) : copy4(ra[idx]);
-    }
-  };
-  auto write_b = [&](int stage, int idx, bool masked) {
-    uint4* tb = smem + stage * STAGE_VEC + A_VEC;
-    if (B_KC) {
-      tb[kc_unit<CH>(tid / CH + RP * idx, tid % CH)] = masked ? sel4(b_keep != 0, rb[idx]) : copy4(rb[idx]);
-    } else {
-      tb[(tid / BCH + idx * C::KRB) * C::KPB + tid % BCH] = masked ? sel4((b_keep >> idx) & 1u, rb[idx]) : copy4(rb[idx]);
-    }
-  };
-  // piece p of the pipeline step "tile t+1 to LDS stage `stage`, tile t+2 into registers"
-  auto piece = [&](int p, int stage, bool do_write, bool do_load, bool masked) {
-    if (p < NPA) {
-      if (do_write) write_a(stage, p, masked);
-      if (do_load) load_a(p);
-    } else {
-      if (do_write) write_b(stage, p - NPA, masked);
-      if (do_load) load_b(p - NPA);
+      const unsigned off = A_KC && masked && kc_chunk * 8 >= (int)as.left ? kOutOfRange : aoff[p - NB];
+      load_to_lds(rsrc_t{as.lo, as.hi, as.bytes, 0x00020000u}, off);
     }
   };
 
   bf16x8 fa[2][TM], fb[2][TN];
-  const int tr_k = lq * 8 + (lane & 15) / 4;                     // k-row (within a k-step) this lane points the transposing read at
-  const int tr_r = (lane & 3) * 4;                               // row (within a 16-row MFMA tile) likewise
-  auto read_frag_a = [&](int stage, int ks, int set, int i) {
-    const uint4* ta = smem + stage * STAGE_VEC;
+  // fragment addresses within a slot: K-contiguous, chunk ks*4 + lq of row l16 (+ 16 i); K-strided, k-row ks*32 + lq*8 + l16/4
+  // (+ 4), columns (lane&3)*4 of the 16-row group u = first group + i, which stands at position u ^ (l16/4) of its four
+  const int kc_pos = lq ^ (l16 >> 1);
+  const uint4* const a_kc = smem + (wm * (BM / 2) + l16) * 8;
+  const uint4* const b_kc = smem + NSA * A_VEC + (wn * (BN / 2) + l16) * 8;
+  const bf16_t* const a_tr = reinterpret_cast<const bf16_t*>(smem) + (lq * 8 + (l16 >> 2)) * BM + (lane & 3) * 4 + wm * (BM / 2);
+  const bf16_t* const b_tr = reinterpret_cast<const bf16_t*>(smem + NSA * A_VEC) + (lq * 8 + (l16 >> 2)) * BN + (lane & 3) * 4 + wn * (BN / 2);
+  static_assert((A_KC || BM >= 128) && (B_KC || BN >= 128), "a wavefront's groups of a K-strided operand start at a multiple of four");
+  auto tr_pos = [&](int i) { return (i & ~3) * 16 + ((i & 3) ^ (l16 >> 2)) * 16; };
+  auto read_frag_a = [&](int slot, int ks, int set_, int i) {
     if (A_KC) {
-      fa[set][i] = __builtin_bit_cast(bf16x8, ta[kc_unit<CH>(wm * (BM / 2) + i * 16 + l16, ks * 4 + lq)]);
+      fa[set_][i] = __builtin_bit_cast(bf16x8, a_kc[slot * A_VEC + i * 128 + (kc_pos ^ (ks * 4))]);
     } else {
-      const bf16_t* p = reinterpret_cast<const bf16_t*>(ta + (ks * 32 + tr_k) * C::KPA) + wm * (BM / 2) + i * 16 + tr_r;
-      const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * C::KPA * 8);
-      fa[set][i] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+      const bf16_t* p = a_tr + slot * (A_VEC * 8) + ks * 32 * BM + tr_pos(i);
+      const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * BM);
+      fa[set_][i] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
   };
-  auto read_frag_b = [&](int stage, int ks, int set, int j) {
-    const uint4* tb = smem + stage * STAGE_VEC + A_VEC;
+  auto read_frag_b = [&](int slot, int ks, int set_, int j) {
     if (B_KC) {
-      fb[set][j] = __builtin_bit_cast(bf16x8, tb[kc_unit<CH>(wn * (BN / 2) + j * 16 + l16, ks * 4 + lq)]);
+      fb[set_][j] = __builtin_bit_cast(bf16x8, b_kc[slot * B_VEC + j * 128 + (kc_pos ^ (ks * 4))]);
     } else {
-      const bf16_t* p = reinterpret_cast<const bf16_t*>(tb + (ks * 32 + tr_k) * C::KPB) + wn * (BN / 2) + j * 16 + tr_r;
-      const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * C::KPB * 8);
-      fb[set][j] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+      const bf16_t* p = b_tr + slot * (B_VEC * 8) + ks * 32 * BN + tr_pos(j);
+      const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * BN);
+      fb[set_][j] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
   };
   // fragment w of a k-step in the order the MFMAs first need them: B0, A0 .. A(TM-1), B1 .. B(TN-1)
-  auto read_frag = [&](int stage, int ks, int set, int w) {
-    if (w == 0) read_frag_b(stage, ks, set, 0);
-    else if (w <= TM) read_frag_a(stage, ks, set, w - 1);
-    else read_frag_b(stage, ks, set, w - TM);
-  };
-  auto read_frags = [&](int stage, int ks, int set) {
-#pragma unroll
-    for (int w = 0; w < TM + TN; ++w) read_frag(stage, ks, set, w);
+  auto read_frag = [&](int sa, int sb, int ks, int set_, int w) {
+    if (w == 0) read_frag_b(sb, ks, set_, 0);
+    else if (w <= TM) read_frag_a(sa, ks, set_, w - 1);
+    else read_frag_b(sb, ks, set_, w - TM);
   };
 
-  if (nsteps > 0) {
-    // prologue: tile 0 -> registers -> LDS stage 0, tile 1 -> registers
-#pragma unroll
-    for (int j = 0; j < (SETS ? C::NAS : 0); ++j) load_kidx(0, j);
-    set_load_tile(0);
-#pragma unroll
-    for (int p = 0; p < NP; ++p) piece(p, 0, false, true, true);
-    a_keep = a_keep_n; b_keep = b_keep_n;
-    set_load_tile(nsteps > 1 ? 1 : 0);
-#pragma unroll
-    for (int p = 0; p < NP; ++p) piece(p, 0, true, true, true);
-    a_keep = a_keep_n; b_keep = b_keep_n;
-    __syncthreads();
-    read_frags(0, 0, 0);
+  // ---- schedule: positions are gaps between the 2 MF MFMAs of a K-tile ----
+  constexpr int MF = TM * TN;                       // MFMAs per k-step
+  constexpr int NF = TM + TN;                       // fragments per k-step
+  constexpr bool WIDE = MF >= 32 && !SETS;          // room for a second meeting point
+  constexpr int F0 = MF >= 64 ? 2 : 1;              // gaps per fragment
+  constexpr int QF = NF * F0 + 8 < MF ? NF * F0 + 8 : MF;          // K-tile t is in registers: its slots may be overwritten
+  constexpr int QL = WIDE ? 2 * MF - NF * F0 - (MF >= 64 ? 12 : 6) : QF;    // K-tile t+1 is in LDS: its first fragments may be read
+  // gaps per load: spread over the whole iteration (A's loads run on into the next one, up to its QF), B's done at its end
+  constexpr int DG_ALL = (2 * MF - (SETS ? QF : 0)) / NP, DG_B = (2 * MF - QF) / NB, DG = DG_ALL < DG_B ? DG_ALL : DG_B;
+  constexpr int R0 = QL < MF ? MF : QL;             // the first fragments of K-tile t+1 follow, once their registers are free
+  constexpr int F1 = (2 * MF - R0) / NF < 4 ? (2 * MF - R0) / NF : 4;
+  constexpr int SS = MF >= 32 ? 2 : 1;              // gaps per step of the scalars of the tiles to be loaded
+  static_assert(DG >= 1 && F1 >= 1 && QF + NB * DG <= 2 * MF && R0 + NF * F1 <= 2 * MF && QF >= 4 * SS && NB * DG >= 4 * SS, "more fragments or loads than MFMA gaps");
+  constexpr int LATE = QF + NP * DG > 2 * MF ? (QF + NP * DG - 2 * MF + DG - 1) / DG : 0;      // loads of an iteration that the next one issues
+  constexpr int LOADED = QL > QF ? ((QL - QF) / DG < NP ? (QL - QF) / DG : NP) : 0;     // loads an iteration has issued before QL
+  // loads that may be outstanding at QL, counted back from the last one of K-tile t+1 (B: NSB tiles ahead, A: NSA, behind it)
+  constexpr int AFTER_A = (NSA - 2) * NP, AFTER_B = NA + (NSB - 2) * NP;
+  constexpr int AHEAD = (AFTER_A < AFTER_B ? AFTER_A : AFTER_B);
+  static_assert(AHEAD + NP < 64, "the counter of outstanding loads");
 
-    constexpr int MF = TM * TN;                       // MFMAs per k-step
-    constexpr int NF = TM + TN;                       // fragments per k-step
-    static_assert(C::KSTEPS == 2 && NP == NF, "the schedule below deals one staging register per fragment over a K-tile of two k-steps");
-    constexpr int FR = MF / NF;                       // MFMA gaps per fragment in the first k-step
-    constexpr int R1 = FR > 1 ? 1 : 0, R2 = FR > 2 ? 2 : FR - 1;
-    constexpr int QB = MF - 2 * NF >= 0 ? MF / 4 : 0; // the barrier sits before this MFMA of the second k-step ...
-    constexpr int RT = (MF - QB) / NF;                // ... and the next K-tile's fragments follow it, one every RT gaps
-    static_assert(FR >= 1 && RT >= 1, "more fragments than MFMA gaps");
-    // One iteration: MFMAs of K-tile t from LDS stage t&1, K-tile t+1 from registers to the other stage, K-tile t+2
-    // from memory to registers.  No branches in here: past the last K-tile the pipeline keeps running on clamped
-    // tiles whose results are never used (a spare LDS write, a repeated load).
-    // Everything besides the MFMAs is dealt out over the gaps between them, at most one memory instruction per gap
-    // where the tile is large enough.  First k-step, gaps w*FR .. w*FR+2: fragment w of the second k-step, the LDS
-    // write of staging register w (K-tile t+1), its reload (K-tile t+2).  Second k-step: the block barrier that
-    // publishes K-tile t+1, then the fragments of its first k-step.
-    auto iteration = [&](int t, auto masked_c) __attribute__((always_inline)) {
-      constexpr bool MASKED = decltype(masked_c)::value;
-      const int cur = t & 1;
-      set_load_tile(t + 2 < nsteps ? t + 2 : nsteps - 1);
-      __builtin_amdgcn_sched_barrier(0);
+  // prologue: the first NSA and NSB K-tiles, in the order in which the iterations -NS .. -1 would have loaded them
+  if (SETS) {
+    static_assert(!SETS || (NSA == 2 && NSB == 2), "the indices of the first two K-tiles");
+    int k1[NA];
 #pragma unroll
-      for (int q = 0; q < MF; ++q) {
-        const int j = q / TM, i = q % TM;
-        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][j], fa[0][i], acc[j][i], 0, 0, 0);
-        const int w = q / FR, r = q % FR;
-        if (w < NF) {
-          if (r == 0) read_frag(cur, 1, 1, w);
-          if (r == R1) piece(w, cur ^ 1, true, false, MASKED);
-          if (r == R2) piece(w, cur ^ 1, false, true, MASKED);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int j = 0; j < NA; ++j) load_kidx(1, j);
+#pragma unroll
+    for (int j = 0; j < NA; ++j) k1[j] = kidx[j];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) load_kidx(0, j);
+#pragma unroll
+    for (int j = 0; j < NA; ++j) asm volatile("" : "+v"(k1[j]), "+v"(kidx[j]));    // both sets are here before the first operand load
+#pragma unroll
+    for (int lt = 0; lt < 2; ++lt) {
+#pragma unroll
+      for (int st = 0; st < 4; ++st) { next_a(st, lt, lt); next_b(st, lt, lt); }
+#pragma unroll
+      for (int j = 0; j < NA; ++j) {
+        if (lt == 1) kidx[j] = k1[j];
+        take_kidx(j);
       }
 #pragma unroll
-      for (int q = 0; q < MF; ++q) {
-        const int j = q / TM, i = q % TM;
-        if (q == QB) {
-          a_keep = a_keep_n; b_keep = b_keep_n;
-          __syncthreads();
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[1][j], fa[1][i], acc[j][i], 0, 0, 0);
-        if (q >= QB && (q - QB) % RT == 0 && (q - QB) / RT < NF) read_frag(cur ^ 1, 0, 0, (q - QB) / RT);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int p = 0; p < NP; ++p) { aim(p); one_instruction(); load(p, true); }
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) load_kidx(2, j);
+  } else {
+    constexpr int NS = NSA > NSB ? NSA : NSB;
+#pragma unroll
+    for (int u = -NS; u < 0; ++u) {
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        if (u + NSB >= 0) next_b(st, u + NSB, u + NSB);
+        if (u + NSA >= 0) next_a(st, u + NSA, u + NSA);
       }
-    };
-    // The body exists twice: an inner loop without the k-tail selects for the tiles in the middle of a pass, and one
-    // straight-line copy with them for the iteration that writes the last tile of a pass (and for the final iteration,
-    // whose write is the spare one).  w = t + 1 is the tile written in iteration t.
-    int w = 1, pass_end = nk - 1;
-    while (true) {
-      const int stop = pass_end < nsteps ? pass_end : nsteps;
-      for (; w < stop; ++w) iteration(w - 1, std::false_type{});
-      iteration(w - 1, std::true_type{});
-      ++w;
-      pass_end += nk;
-      if (w > nsteps) break;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        if ((p < NB ? u + NSB < 0 : u + NSA < 0) || (u == -1 && p >= NP - LATE)) continue;
+        aim(p); one_instruction(); load(p, true);
+      }
     }
   }
+  if (LATE > 0) aim(NP - LATE);
+  wait_and_meet<AHEAD + NP - LATE>();
+#pragma unroll
+  for (int w = 0; w < NF; ++w) read_frag(0, 0, 0, 0, w);
+
+  // One iteration: the MFMAs of K-tile t, whose first fragments are in registers.  Before QF: the fragments of its second k-step,
+  // and the scalars of the tiles to be loaded.  At QF the wavefronts meet: K-tile t is in registers everywhere, and its slots are
+  // loaded anew, one load every DG gaps.  At QL they meet again: K-tile t+1 is in LDS everywhere; its first fragments follow.
+  // A wavefront issues an instruction every four cycles and an MFMA takes sixteen, so a gap has room for three others: they are
+  // dealt out one or two to a gap.  No branches in here: past the last K-tile the loads bring zeros, and the fragments are
+  // never used.
+  auto iteration = [&](int t, int sa, int sb, int sa1, int sb1, auto masked_c) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 2 * MF; ++q) {
+      const int ks = q / MF, j = (q % MF) / TM, i = q % TM;
+      if (q == QF) {
+        wait_and_meet<(WIDE ? 63 : AHEAD)>();
+        if (SETS) {
+#pragma unroll
+          for (int x = 0; x < NA; ++x) asm volatile("" : "+v"(kidx[x]));     // (nothing is outstanding here)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (WIDE && q == QL) {
+        wait_and_meet<AHEAD + LOADED>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[j][i], 0, 0, 0);
+      if (q < MF && q % F0 == 0 && q / F0 < NF) read_frag(sa, sb, 1, 1, q / F0);
+      if (q >= R0 && (q - R0) % F1 == 0 && (q - R0) / F1 < NF) read_frag(sa1, sb1, 0, 0, (q - R0) / F1);
+      if (q >= QF - 4 * SS && q < QF && (QF - 1 - q) % SS == 0) next_b((q - (QF - 4 * SS)) / SS, t + NSB, sb);
+      if (q >= QF && q < QF + 4 * SS && (q - QF) % SS == 0) next_a((q - QF) / SS, t + NSA, sa);
+      {
+        const int at = q >= QF ? q - QF : q - QF + 2 * MF, p = at / DG;
+        if (p < NP && (q >= QF || p >= NP - LATE)) {
+          if (at % DG == (DG > 1 ? DG - 2 : 0)) {
+            if (SETS && p < NA) take_kidx(p);
+            aim(p);
+          }
+          if (DG == 1) one_instruction();
+          if (at % DG == DG - 1) {
+            load(p, MASKED);
+            if (SETS && p >= NA) load_kidx(t + NSA + 1, p - NA);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // The iterations that load the last K-tile of a pass of K-contiguous operands zero what lies beyond the range; they run in a copy of
+  // their own, so that the others carry no selects.
+  int t = 0, sa = 0, sb = 0;
+  auto step = [&](auto masked_c) __attribute__((always_inline)) {
+    const int sa1 = sa + 1 == NSA ? 0 : sa + 1, sb1 = sb + 1 == NSB ? 0 : sb + 1;
+    iteration(t, sa, sb, sa1, sb1, masked_c);
+    sa = sa1; sb = sb1;
+    ++t;
+  };
+  if constexpr (A_KC || B_KC) {
+    constexpr int FAR = NSA > NSB ? NSA : NSB, NEAR = NSA > NSB ? NSB : NSA;
+    int last = klen % BK != 0 ? nk - 1 - k_rot : nsteps + FAR;        // the next K-tile that needs it
+    while (last + 1 < NEAR) last += nk;
+    while (true) {
+      const int stop = last - FAR < nsteps ? last - FAR : nsteps;
+      while (t < stop) step(std::false_type{});
+      if (t >= nsteps) break;
+      step(std::true_type{});
+      if (t > last - NEAR + 1) last += nk;
+    }
+  } else {
+    do step(std::false_type{}); while (t < nsteps);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no load may still write the LDS that the epilogue uses
 
   // ---- epilogue ----
   // The MFMA leaves each lane with 4-column runs of one row per register group, which would scatter 32-byte
@@ -557,7 +605,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   __syncthreads();                                   // the staging tiles are dead from here on
 #pragma unroll
   for (int i = 0; i < TS; ++i) {
-    if (EPI == kEpiStore && !g.c_f32) {
+    if (EPI == kEpiStore && !F32_OUT) {
       // bf16 output: round first, so that half as many bytes make the trip through LDS; rows of ECOLS bf16 with a
       // pitch of ECOLS*2+8 bytes (the 32 rows one write instruction touches fall into different banks)
       constexpr int BPITCH = ECOLS * 2 + 8;
@@ -741,21 +789,23 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
 }
 
 // the full tile: 256 x 256 x 64, one block per CU (128 to 144 KB of LDS by operand layout, 256 accumulators per lane in AGPRs)
-typedef Cfg<256, 256, 64, 1> Tile;
+typedef Cfg<256, 256, 3, 2, 1> Tile;
+typedef Cfg<256, 256, 2, 2, 1> TileSets;
+typedef Cfg<128, 128, 2, 2, 2> TileSmallSets;
 
 // narrow outputs (the router's M <= 64 expert columns: half the matrix work on padding), the half-full last column
 // tile of a ragged-row GEMM, and launches of few tiles
-typedef Cfg<256, 128, 64, 1> TileNarrow;
+typedef Cfg<256, 128, 3, 3, 1> TileNarrow;
 // few output rows (the router's weight gradient has M <= 64 of them), and the fused SwiGLU on 128-row tiles (plan::row_tile)
-typedef Cfg<128, 256, 64, 1> TileShort;
+typedef Cfg<128, 256, 3, 3, 1> TileShort;
 // a contraction of a single K-tile (the router's input gradient contracts over the M <= 64 experts) is all prologue
 // and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's; also the other
 // ragged-row GEMMs on 128-row tiles, and weight gradients of few full tiles (plan::wgrad_small_tiles)
-typedef Cfg<128, 128, 64, 2> TileSmall;
+typedef Cfg<128, 128, 3, 2, 2> TileSmall;
 // ragged-row GEMMs on 64-row tiles (plan::row_tile), two blocks per CU: experts of few routed rows, bound by the stream of
 // their weights, and narrow models with few tiles, bound by prologue and epilogue
-typedef Cfg<64, 256, 64, 2> Rows64;
-typedef Cfg<64, 128, 64, 2> Rows64Narrow;
+typedef Cfg<64, 256, 2, 2, 2> Rows64;
+typedef Cfg<64, 128, 3, 3, 2> Rows64Narrow;
 static_assert(Tile::BM == plan::kFullRows && TileShort::BM == plan::kHalfRows && TileSmall::BM == plan::kHalfRows && Rows64::BM == plan::kQuarterRows &&
               Tile::BN == plan::kFullCols && TileNarrow::BN == plan::kHalfCols && TileSmall::BN == plan::kHalfCols && Rows64Narrow::BN == plan::kHalfCols,
               "the tiles that the plan counts");
@@ -763,6 +813,7 @@ static_assert(Tile::BM == plan::kFullRows && TileShort::BM == plan::kHalfRows &&
 template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false>
 int launch(const GemmArgs& g, hipStream_t s) {
   static_assert(!SETS || (MODE == kGroupedK && !A_KC && !B_KC && C::BM == C::BN), "operand sets: K-strided, square tiles");
+  if (EPI == kEpiStore && (g.c_f32 != 0) != f32_out(MODE, A_KC, B_KC)) return SPES_EINVAL;
   // operands are addressed with 32-bit byte offsets from their base
   if (SETS) {
     if (g.npairs != 1 || g.n_sets != 3) return SPES_EINVAL;
@@ -842,8 +893,8 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
     if (g.n_sets > 0) {
       const long n = (long)g.n_sets * g.n_groups, full = n * plan::tiles(g.Mdim, g.Ndim, Tile::BM, Tile::BN),
                  small = n * plan::tiles(g.Mdim, g.Ndim, TileSmall::BM, TileSmall::BN);
-      if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
-      return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
+      if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmallSets, true>(g, s);
+      return launch<kGroupedK, kEpiStore, false, false, TileSets, true>(g, s);
     }
     if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);
     return launch<kGroupedK, kEpiStore, false, false>(g, s);

@@ -1,0 +1,49 @@
+"""The main loop of the expert GEMMs: contractions of one to a few K-tiles with and without a remainder on each row tile, and
+nothing from beyond a contraction range, a tile or an expert in any result."""
+import numpy as np
+import pytest
+import torch
+
+from spes_workloads import custom_config, layer_inputs
+
+from harness import DeviceLayer
+from test_gpu_layer import _full_parity
+
+pytestmark = pytest.mark.gpu
+
+# tokens, d_model, experts, d_ff, top-k: both widths are contraction lengths (forward and backward), 64 to a K-tile
+CASES = [
+    # 64-row tiles: blocks begin at K-tile 0 to 7 eighths of the contraction; 1, 2, 3, 5, 8, 9 and 13 K-tiles
+    (40, 64, 4, 128, 2), (40, 72, 4, 184, 2), (60, 320, 8, 512, 2), (60, 520, 8, 576, 2), (60, 776, 8, 832, 2),
+    # 128-row tiles
+    (96, 64, 2, 128, 2), (150, 328, 4, 136, 2), (150, 1000, 4, 200, 2),
+    # 256-row tiles, full and half-width columns
+    (300, 960, 2, 64, 2), (300, 968, 2, 136, 2), (300, 1024, 2, 320, 2), (700, 1096, 3, 72, 2),
+]
+
+
+@pytest.mark.parametrize("T,d,M,f,k", CASES)
+def test_contraction_lengths(T, d, M, f, k, device):
+    kw = dict(T=T, d=d, M=M, f=f, k=k, n_trainable=min(3, M), trainable="random", dtype="bf16", router_sigma=0.3)
+    _full_parity(layer_inputs(custom_config(**kw)), device, "contraction lengths")
+
+
+@pytest.mark.parametrize("T,d,f", [(60, 136, 200), (200, 1000, 136), (700, 960, 328), (700, 520, 520)])
+def test_values_stay_with_their_expert(T, d, f, device):
+    """NaN weights of one expert: every result of tokens and experts that have nothing to do with it stays bit for bit."""
+    cfg = custom_config(T=T, d=d, M=5, f=f, k=2, n_trainable=5, dtype="bf16", router_sigma=0.3)
+    L = DeviceLayer(layer_inputs(cfg), device)
+    outs = []
+    for poisoned in (False, True):
+        if poisoned:
+            for w in (L.w_gate, L.w_up, L.w_down):
+                w[2] = float("nan")
+        L.fwd(); L.bwd(); torch.cuda.synchronize()
+        outs.append([t.detach().clone() for t in (L.y, L.dx, L.d_w_gate, L.d_w_up, L.d_w_down)])
+    clean = ~(L.idx == 2).any(dim=1).to(outs[0][0].device)
+    others = torch.tensor([0, 1, 3, 4], device=device)
+    assert clean.any() and not clean.all()
+    for i, (a, b) in enumerate(zip(*outs)):
+        pick = clean if i < 2 else others
+        assert torch.equal(a[pick].view(torch.uint8), b[pick].view(torch.uint8)), i
+        assert torch.isfinite(b[pick].float()).all(), i
