@@ -81,6 +81,24 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int lane) {
   return inc - v;
 }
 
+// Row-tile tables of one wavefront whose lane e owns expert e (`total` rows from `off` on).  Layout: [0] = number of tiles,
+// [1 .. max_tiles] expert of each tile, [1+max_tiles ..] first row
+__device__ __forceinline__ void write_tile_tables(int e, int total, int off, int bm0, int* __restrict__ tab0, int bm1, int* __restrict__ tab1,
+                                                  int max_tiles) {
+  for (int which = 0; which < 2; ++which) {
+    const int bm = which ? bm1 : bm0;
+    int* tab = which ? tab1 : tab0;
+    if (bm <= 0 || tab == nullptr) continue;
+    const int nt = (total + bm - 1) / bm;
+    const int t0 = wave_exclusive_scan(nt, e);
+    for (int i = 0; i < nt; ++i) {
+      tab[1 + t0 + i] = e;
+      tab[1 + max_tiles + t0 + i] = off + i * bm;
+    }
+    if (e == 63) tab[0] = t0 + nt;
+  }
+}
+
 // One wavefront: lane e owns expert e.  Turns per-block counts into per-block
 // first positions, and writes counts, offsets and the row-tile tables.
 __global__ __launch_bounds__(64) void scan_kernel(int* __restrict__ block_counts, int nblk, int M, int* __restrict__ expert_count,
@@ -114,19 +132,7 @@ __global__ __launch_bounds__(64) void scan_kernel(int* __restrict__ block_counts
   }
   if (e < M) { expert_count[e] = total; offset[e] = off; }
   if (e == M - 1) offset[M] = off + total;
-  // table layout: [0] = number of tiles, [1 .. max_tiles] expert of each tile, [1+max_tiles ..] first row
-  for (int which = 0; which < 2; ++which) {
-    const int bm = which ? bm1 : bm0;
-    int* tab = which ? tab1 : tab0;
-    if (bm <= 0 || tab == nullptr) continue;
-    const int nt = (total + bm - 1) / bm;
-    const int t0 = wave_exclusive_scan(nt, e);
-    for (int i = 0; i < nt; ++i) {
-      tab[1 + t0 + i] = e;
-      tab[1 + max_tiles + t0 + i] = off + i * bm;
-    }
-    if (e == 63) tab[0] = t0 + nt;
-  }
+  write_tile_tables(e, total, off, bm0, tab0, bm1, tab1, max_tiles);
 }
 
 __global__ __launch_bounds__(256) void scatter_kernel(const int* __restrict__ idx, const float* __restrict__ gate, int R, int k,
@@ -175,6 +181,73 @@ __global__ __launch_bounds__(256) void scatter_kernel(const int* __restrict__ id
   }
 }
 
+// Count, scan and scatter in one launch: every block counts all pairs for itself, those ahead of its own chunk apart, so nothing
+// has to pass between blocks.  Pairs of other chunks are counted with LDS atomics (integer sums: any order gives the same);
+// the block's own are ranked as in scatter_kernel.  Same tables, bit for bit, as the three kernels above.
+constexpr int kOneChunk = 1024;                     // pairs per block, one per thread
+constexpr int kOneLaunchPairs = 32 * kOneChunk;
+__global__ __launch_bounds__(kOneChunk) void route_tables_kernel(const int* __restrict__ idx, const float* __restrict__ gate, int R, int M,
+                                                                 int k, int* __restrict__ expert_count, int* __restrict__ offset,
+                                                                 int* __restrict__ perm, int* __restrict__ inv, int* __restrict__ row_token,
+                                                                 float* __restrict__ row_gate, int bm0, int* __restrict__ tab0, int bm1,
+                                                                 int* __restrict__ tab1, int max_tiles, float* __restrict__ aux) {
+  constexpr int W = kOneChunk / 64;
+  __shared__ int ahead[kMaxExperts], behind[kMaxExperts];       // pairs per expert in the chunks of earlier and of later blocks
+  __shared__ int own[W][kMaxExperts];                           // this block's, per wavefront; then each wavefront's first row
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (w == 0) { ahead[lane] = 0; behind[lane] = 0; }
+  own[w][lane] = 0;
+  __syncthreads();
+  const int first = blockIdx.x * kOneChunk, mine = first + tid;     // this thread's pair
+  const int e_own = mine < R ? idx[mine] : 0;
+  const int nvec = R / 4;
+  for (int v = tid; v < nvec; v += kOneChunk) {
+    const int4 q = reinterpret_cast<const int4*>(idx)[v];
+    const int at = v * 4;
+    if (at >= first && at < first + kOneChunk) continue;
+    int* h = at < first ? ahead : behind;
+    atomicAdd(&h[q.x], 1); atomicAdd(&h[q.y], 1); atomicAdd(&h[q.z], 1); atomicAdd(&h[q.w], 1);
+  }
+  if (tid < R - nvec * 4 && nvec * 4 >= first + kOneChunk) atomicAdd(&behind[idx[nvec * 4 + tid]], 1);
+  // pairs of this wavefront with the same expert
+  const bool valid = mine < R;
+  unsigned long long peers = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    const bool bit = (e_own >> b) & 1;
+    const unsigned long long m = __ballot(valid && bit);
+    peers &= bit ? m : ~m;
+  }
+  const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+  if (valid && rank == 0) own[w][e_own] = __popcll(peers);
+  __syncthreads();
+  // lane e of wavefront 0: totals, first row of each expert, and this block's first row per wavefront
+  if (w == 0) {
+    int n[W], total = ahead[lane] + behind[lane];
+#pragma unroll
+    for (int i = 0; i < W; ++i) { n[i] = own[i][lane]; total += n[i]; }
+    const int off = wave_exclusive_scan(total, lane);
+    int run = off + ahead[lane];
+#pragma unroll
+    for (int i = 0; i < W; ++i) { own[i][lane] = run; run += n[i]; }
+    if (blockIdx.x == 0) {
+      aux[lane] = 0.f;                              // see scan_kernel
+      if (lane < kAuxExtra) aux[kMaxExperts + lane] = 0.f;
+      if (lane < M) { expert_count[lane] = total; offset[lane] = off; }
+      if (lane == M - 1) offset[M] = off + total;
+      write_tile_tables(lane, total, off, bm0, tab0, bm1, tab1, max_tiles);
+    }
+  }
+  __syncthreads();
+  if (valid) {
+    const int r = own[w][e_own] + rank;
+    perm[r] = mine;
+    inv[mine] = r;
+    row_token[r] = mine / k;
+    row_gate[r] = gate[mine];
+  }
+}
+
 // dlogits from dgate (one wavefront per token).  renorm=0: softmax Jacobian on
 // the sparse dp; renorm=1: the renormalised gates are a softmax over the
 // selected scores alone.
@@ -187,18 +260,29 @@ __global__ __launch_bounds__(256) void gating_bwd_kernel(const float* __restrict
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
+  const float lse_t = lse[t];
+  const float score = (lane < M) ? logits[(long)t * M + lane] : 0.f;      // requested ahead of the chain below
   // lane j < k holds selected pair j
   int sel = -1; float g = 0.f, dg = 0.f;
   if (lane < k) {
     sel = topk_idx[(long)t * k + lane];
     g = topk_gate[(long)t * k + lane];
     const long r = inv[(long)t * k + lane];
-    for (int p = 0; p < n_part; ++p) dg += dgate_part[p * part_stride + r];   // column-tile partials, fixed order
+    // column-tile partials in a fixed order, eight requested at a time
+    const float* q = dgate_part + r;
+    int p = 0;
+    for (; p + 8 <= n_part; p += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = q[(p + u) * part_stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) dg += v[u];
+    }
+    for (; p < n_part; ++p) dg += q[p * part_stride];
     dgate[(long)t * k + lane] = dg;
   }
   float out = 0.f;
-  const float lse_t = lse[t];
-  const float p = (lane < M) ? expf(logits[(long)t * M + lane] - lse_t) : 0.f;
+  const float p = (lane < M) ? expf(score - lse_t) : 0.f;
   // Every term below has the shape v_e * (u_e - sum_j u_j v_j) with sum_j v_j = 1.  When routing collapses onto one
   // expert (v -> 1 for the top score) that difference cancels completely in fp32 although the true value is about
   // u * (1 - v).  Only the top entry can come close to 1, so it alone is written as
@@ -324,6 +408,14 @@ int launch_topk_gate(float* logits, int n_part, const float* bias, int T, int M,
 int launch_routing_tables(const int* idx, const float* gate, int R, int M, int k, int* block_counts, int* expert_count,
                           int* offset, int* perm, int* inv, int* row_token, float* row_gate, int bm0, int* tab0, int bm1,
                           int* tab1, int max_tiles, float* aux, hipStream_t s) {
+  // One launch as long as a block's own count of all pairs costs less than two more launches.  Kernel times, one launch against
+  // the three (which leave two gaps besides): 1024 pairs 4.5 / 15.4 us, 12248 7.4 / 18.2, 16384 7.4 / 21.0, 131072 23.8 / 22.2,
+  // 262144 51 / 28.  The line lies where it wins also when every pair goes to one expert and the counts queue at one address.
+  if (R <= kOneLaunchPairs) {
+    hipLaunchKernelGGL(route_tables_kernel, dim3(cdiv(R, kOneChunk)), dim3(kOneChunk), 0, s, idx, gate, R, M, k, expert_count, offset, perm,
+                       inv, row_token, row_gate, bm0, tab0, bm1, tab1, max_tiles, aux);
+    return hipGetLastError() == hipSuccess ? SPES_OK : SPES_EHIP;
+  }
   const int nblk = routing_blocks(R);
   hipLaunchKernelGGL(count_kernel, dim3(nblk), dim3(256), 0, s, idx, R, block_counts);
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(64), 0, s, block_counts, nblk, M, expert_count, offset, bm0, tab0, bm1, tab1,
