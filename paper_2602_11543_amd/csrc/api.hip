@@ -17,7 +17,8 @@ constexpr int kRouterSplit = 64;   // chunks of the token axis in the router wei
 struct Layout {
   spes_moe_ctx_layout pub;
   size_t block_counts, tab_simt, tab_mfma, row_token, row_gate, hcorr, dgate_part, da, db, hg, dxp, wr_part, dlogits_bf, dxr, aux, aux_part;
-  int max_tiles, row_tile_mfma, max_tiles_mfma, est_tiles_mfma, max_col_tiles;
+  bool f32_mfma;                                    // fp32 storage on the matrix cores
+  int max_tiles, row_tile_f32, est_tiles_f32, row_tile_mfma, max_tiles_mfma, est_tiles_mfma, max_col_tiles;
 };
 
 bool shape_ok(const spes_moe_shape* s) {
@@ -49,7 +50,10 @@ Layout make_layout(const spes_moe_shape* s) {
   Layout L;
   const size_t T = s->T, d = s->d_model, M = s->n_experts, f = s->d_ff, k = s->top_k;
   const size_t R = T * k, es = s->dtype == SPES_F32 ? 4 : 2;
-  L.max_tiles = (int)(R / 64 + M + 1);
+  L.f32_mfma = s->dtype == SPES_F32 && plan::f32_on_matrix_cores((long)T, (long)R, s->d_model, s->d_ff);
+  L.row_tile_f32 = L.f32_mfma ? plan::f32_row_tile((long)R, s->n_experts, s->d_model, s->d_ff) : simt_row_tile();
+  L.est_tiles_f32 = (int)(R / L.row_tile_f32 + (M + 1) / 2);
+  L.max_tiles = (int)(R / (s->dtype == SPES_F32 ? L.row_tile_f32 : 64) + M + 1);
   L.row_tile_mfma = plan::row_tile((long)R, s->n_experts, s->d_model, s->d_ff);
   L.max_tiles_mfma = (int)(R / L.row_tile_mfma + M + 1);
   L.est_tiles_mfma = (int)(R / L.row_tile_mfma + (M + 1) / 2);   // expected count: half of the experts end in a partly filled tile
@@ -75,7 +79,8 @@ Layout make_layout(const spes_moe_shape* s) {
   L.pub.yp = take(R * d * es);
   L.pub.dlogits = take(T * M * 4);
   L.pub.dgate = take(T * k * 4);
-  L.max_col_tiles = cdiv((long)f, 64) + 1;   // covers both GEMM paths: f/64 (vector ALU) and 2*ceil(f/128) (matrix core)
+  // gate-gradient partials: f/64 (vector ALUs), f/32 (fp32 on the matrix cores), 2*ceil(f/128) (bf16)
+  L.max_col_tiles = L.f32_mfma ? cdiv((long)f, plan::kF32RowdotCols) : cdiv((long)f, 64) + 1;
   L.dgate_part = take((size_t)L.max_col_tiles * R * 4);
   L.da = take(R * f * es);
   L.db = take(R * f * es);
@@ -93,8 +98,9 @@ Layout make_layout(const spes_moe_shape* s) {
 template <typename T>
 T* at(void* base, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(base) + off); }
 
-// bf16 storage runs the expert GEMMs on the matrix cores, fp32 storage on the vector ALUs
-int expert_gemm(int dt, int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
+// the expert GEMMs run on the matrix cores, those of the very largest fp32 layers on the vector ALUs
+int expert_gemm(const Layout& L, int dt, int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
+  if (L.f32_mfma) return launch_gemm_f32(mode, epi, a_kcontig, b_kcontig, g, s);
   if (dt == SPES_BF16) return launch_gemm_mfma(mode, epi, a_kcontig, b_kcontig, g, s);
   return launch_gemm_simt(dt, dt, mode, epi, g, s);
 }
@@ -106,8 +112,8 @@ void ragged_tables(GemmArgs& g, void* ctx, const Layout& L, int dt) {
   g.tile_row0 = tab + 1 + L.max_tiles;
   g.offset = at<int>(ctx, L.pub.offset);
   g.max_tiles = dt == SPES_BF16 ? L.max_tiles_mfma : L.max_tiles;   // launch bound on the number of row tiles
-  g.row_tile = L.row_tile_mfma;
-  g.est_tiles = dt == SPES_BF16 ? L.est_tiles_mfma : 0;
+  g.row_tile = dt == SPES_BF16 ? L.row_tile_mfma : L.row_tile_f32;
+  g.est_tiles = dt == SPES_BF16 ? L.est_tiles_mfma : L.est_tiles_f32;
 }
 
 GemmArgs blank() {
@@ -188,6 +194,8 @@ SPES_API int spes_moe_fwd(const spes_moe_shape* shape, const void* x, const void
       g.kchunk = (cdiv(d, kLogitSplit) + 63) / 64 * 64; g.n_groups = cdiv(d, g.kchunk); g.c_gs = (long)T * M;
       logit_parts = g.n_groups;
       SPES_TRY(launch_gemm_mfma(kGroupedK, kEpiStore, true, true, g, s));
+    } else if (L.f32_mfma) {
+      SPES_TRY(launch_gemm_f32(kGroupedK, kEpiStore, true, true, g, s));
     } else {
       SPES_TRY(launch_gemm_simt(dt, dt, kGroupedK, kEpiStore, g, s));
     }
@@ -200,7 +208,7 @@ SPES_API int spes_moe_fwd(const spes_moe_shape* shape, const void* x, const void
                                  at<int>(ctx, L.pub.offset), at<int>(ctx, L.pub.perm), at<int>(ctx, L.pub.inv),
                                  at<int>(ctx, L.row_token), at<float>(ctx, L.row_gate),
                                  // only the row-tile table of the GEMM path this storage type runs on is built
-                                 dt == SPES_BF16 ? 0 : simt_row_tile(), at<int>(ctx, L.tab_simt),
+                                 dt == SPES_BF16 ? 0 : L.row_tile_f32, at<int>(ctx, L.tab_simt),
                                  dt == SPES_BF16 ? L.row_tile_mfma : 0, at<int>(ctx, L.tab_mfma), L.max_tiles,
                                  at<float>(ctx, L.aux), s));
   prof_mark(0, "hist_scan_rank", s);
@@ -214,7 +222,7 @@ SPES_API int spes_moe_fwd(const spes_moe_shape* shape, const void* x, const void
     g.C[0] = at<void>(ctx, L.pub.a); g.C[1] = at<void>(ctx, L.pub.b); g.C[2] = at<void>(ctx, L.pub.h); g.c_ms = f;
     g.C[3] = at<void>(ctx, L.hcorr);
     ragged_tables(g, ctx, L, dt);
-    SPES_TRY(expert_gemm(dt, kRaggedM, kEpiSwiglu, true, true, g, s));
+    SPES_TRY(expert_gemm(L, dt, kRaggedM, kEpiSwiglu, true, true, g, s));
   }
   prof_mark(0, "gemm_gate_up_swiglu", s);
   // yp = h W_d^T
@@ -225,7 +233,7 @@ SPES_API int spes_moe_fwd(const spes_moe_shape* shape, const void* x, const void
     g.Kdim = f; g.Ndim = d;
     g.C[0] = at<void>(ctx, L.pub.yp); g.c_ms = d;
     ragged_tables(g, ctx, L, dt);
-    SPES_TRY(expert_gemm(dt, kRaggedM, kEpiStore, true, true, g, s));
+    SPES_TRY(expert_gemm(L, dt, kRaggedM, kEpiStore, true, true, g, s));
   }
   prof_mark(0, "gemm_down", s);
   SPES_TRY(launch_combine(dt, at<void>(ctx, L.pub.yp), at<int>(ctx, L.pub.inv), topk_gate, y, T, d, k, s));
@@ -290,7 +298,8 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
   // u = dy[token] W_d per routed row; its epilogue yields the gate gradient <u, h> (per column tile) and,
   // through the SwiGLU, da and db of the gate-scaled upstream gradient
   const long R = (long)T * k;
-  const int n_part = dt == SPES_BF16 ? plan::rowdot_parts(f, L.row_tile_mfma, L.est_tiles_mfma) : cdiv(f, simt_col_tile());
+  const int n_part = dt == SPES_BF16 ? plan::rowdot_parts(f, L.row_tile_mfma, L.est_tiles_mfma)
+                                      : cdiv(f, L.f32_mfma ? plan::kF32RowdotCols : simt_col_tile());
   // bf16 storage: the two router contractions run on the matrix cores from a bf16 copy of dlogits
   const bool router_mfma = dt == SPES_BF16 && M % 8 == 0;
   prof_begin(1, s);
@@ -307,7 +316,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     for (int e = 0; e < M; ++e)
       if (!trainable_mask[e]) g.c2_skip |= 1ull << e;
     ragged_tables(g, ctx, L, dt);
-    SPES_TRY(expert_gemm(dt, kRaggedM, kEpiDSwiglu, true, false, g, s));
+    SPES_TRY(expert_gemm(L, dt, kRaggedM, kEpiDSwiglu, true, false, g, s));
   }
   prof_mark(1, "gemm_dgrad_down_dswiglu", s);
   SPES_TRY(launch_gating_bwd(at<float>(ctx, L.pub.logits), at<float>(ctx, L.pub.lse), idx, gate, at<float>(ctx, L.dgate_part),
@@ -323,7 +332,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     g.Kdim = f; g.Ndim = d;
     g.C[0] = at<void>(ctx, L.dxp); g.c_ms = d;
     ragged_tables(g, ctx, L, dt);
-    SPES_TRY(expert_gemm(dt, kRaggedM, kEpiStore, true, false, g, s));
+    SPES_TRY(expert_gemm(L, dt, kRaggedM, kEpiStore, true, false, g, s));
   }
   prof_mark(1, "gemm_dgrad_gate_up", s);
   // weight gradients of the trainable experts only, into their compact slots
@@ -343,7 +352,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     g.set[0] = {dy, at<void>(ctx, L.hg), d_w_down, x_elems, h_elems, d, f, f, d, f, 1, 0};
     g.set[1] = {at<void>(ctx, L.da), x, d_w_gate, h_elems, x_elems, f, d, d, f, d, 0, 1};
     g.set[2] = {at<void>(ctx, L.db), x, d_w_up, h_elems, x_elems, f, d, d, f, d, 0, 1};
-    SPES_TRY(expert_gemm(dt, kGroupedK, kEpiStore, false, false, g, s));
+    SPES_TRY(expert_gemm(L, dt, kGroupedK, kEpiStore, false, false, g, s));
     prof_mark(1, "wgrad", s);
   }
   // dW_r[M,d] = dlogits^T x; the token axis is cut into chunks whose partial products are then added in a fixed order
@@ -359,8 +368,14 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
       SPES_TRY(launch_gemm_mfma(kGroupedK, kEpiStore, false, false, g, s));
     } else {
       g.A[0] = at<float>(ctx, L.pub.dlogits);
-      g.kchunk = cdiv(T, kRouterSplit); g.n_groups = cdiv(T, g.kchunk);
-      SPES_TRY(launch_gemm_simt(SPES_F32, dt, kGroupedK, kEpiStore, g, s));
+      if (L.f32_mfma && M % 4 == 0) {       // (its 16-byte vectors lie along the experts)
+        // chunks of at least a K-tile of its deepest tile
+        g.kchunk = cdiv(T, kRouterSplit) > 128 ? (cdiv(T, kRouterSplit) + 127) / 128 * 128 : 128; g.n_groups = cdiv(T, g.kchunk);
+        SPES_TRY(launch_gemm_f32(kGroupedK, kEpiStore, false, false, g, s));
+      } else {
+        g.kchunk = cdiv(T, kRouterSplit); g.n_groups = cdiv(T, g.kchunk);
+        SPES_TRY(launch_gemm_simt(SPES_F32, dt, kGroupedK, kEpiStore, g, s));
+      }
     }
     SPES_TRY(launch_reduce_partials(at<float>(ctx, L.wr_part), g.n_groups, (long)M * d, d_w_router, accumulate, s));
   }
@@ -485,7 +500,9 @@ SPES_API int spes_expert_warmup_merge(int32_t n_experts, int32_t dtype, int32_t 
     g.Kdim = (int)elems_in; g.kchunk = (int)kchunk; g.n_groups = ng;
     g.Mdim = M; g.Ndim = M;
     g.C[0] = scratch; g.c_ms = M; g.c_gs = (long)M * M; g.c_f32 = 1;
-    SPES_TRY(launch_gemm_simt(dtype, dtype, kGroupedK, kEpiStore, g, s));
+    // 32-bit byte offsets over the whole matrix, or the vector ALUs
+    if ((long)n_experts * elems_in < (1L << 30) - 8) SPES_TRY(launch_gemm_f32(kGroupedK, kEpiStore, true, true, g, s));
+    else SPES_TRY(launch_gemm_simt(dtype, dtype, kGroupedK, kEpiStore, g, s));
   }
   SPES_TRY(launch_sim_topk(static_cast<float*>(scratch), ng, M, top_K, sim, nbr, s));
   for (int m = 0; m < n_mats; ++m)

@@ -52,7 +52,7 @@ struct GemmArgs {
   const int* n_tiles;
   const int* offset;      // [M+1] first routed row of each expert
   int max_tiles;
-  int row_tile;           // rows per tile of that table (matrix-core path: plan::row_tile)
+  int row_tile;           // rows per tile of that table (matrix-core paths: plan::row_tile, plan::f32_row_tile)
   int est_tiles;          // expected number of row tiles (the count itself is only known on the device); 0: unknown
   unsigned long long c2_skip;  // kEpiDSwiglu: bit e set = nothing reads C[2] for expert e's rows; the matrix-core path leaves them unwritten
   // kGroupedK
@@ -75,9 +75,10 @@ struct GemmArgs {
 
 __device__ __forceinline__ float sigmoidf_(float a) { return __builtin_amdgcn_rcpf(1.0f + __expf(-a)); }
 
-// launchers (storage type T of A/B/C unless stated); defined in gemm_simt.hip / gemm_mfma.hip
+// launchers (storage type T of A/B/C unless stated); defined in gemm_simt.hip / gemm_mfma.hip / gemm_f32.hip
 int launch_gemm_simt(int dtype_a, int dtype_b, int mode, int epi, const GemmArgs& g, hipStream_t s);
 int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s);
+int launch_gemm_f32(int mode, int epi, bool a_kcontig, bool b_kcontig, const GemmArgs& g, hipStream_t s);
 int simt_row_tile();
 int simt_col_tile();
 

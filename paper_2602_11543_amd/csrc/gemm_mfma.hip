@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "lds_load.h"
 #include "plan.h"
 
 namespace spes {
@@ -60,30 +61,6 @@ struct Cfg {
 };
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return pack_bf16x2(a, b); }
-
-// raw buffer resource over `bytes` bytes from `base`: loads at byte offsets at or beyond `bytes` deliver zero
-typedef __attribute__((ext_vector_type(4))) unsigned int rsrc_t;
-__device__ __forceinline__ unsigned uniform(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ rsrc_t make_rsrc(unsigned long base, unsigned bytes) {
-  return rsrc_t{(unsigned)base, (unsigned)(base >> 32), bytes, 0x00020000u};
-}
-constexpr unsigned kOutOfRange = 0xfffffff0u;     // at or beyond any resource: operands have less than 2^31 elements of two bytes
-// One load per wavefront of 64 x 16 bytes straight into LDS: lane l's bytes, from its own offset into the resource, land at
-// the address in M0 + 16 l.  Written as assembly because the compiler makes every LDS read that may follow such a load wait for all of them;
-// here the waits stand in the loop.  (The load has no result register, and address and resource are read when it issues.
-// The scalar write of M0 needs one instruction between it and the load that reads it.)
-__device__ __forceinline__ void set_lds_dest(unsigned lds) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds) : "memory"); }
-__device__ __forceinline__ void load_to_lds(const rsrc_t& rs, unsigned lane_off) {
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(lane_off), "s"(rs) : "memory");
-}
-__device__ __forceinline__ void one_instruction() { asm volatile("s_nop 0" ::: "memory"); }
-__device__ __forceinline__ void pin(unsigned& v) { asm volatile("" : "+s"(v)); }       // computed here and not elsewhere
-// wait until at most N vector-memory operations of this wavefront are outstanding and all of its LDS reads have returned, then
-// meet the block's other wavefronts
-template <int N>
-__device__ __forceinline__ void wait_and_meet() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
-}
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;

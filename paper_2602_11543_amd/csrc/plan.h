@@ -104,5 +104,24 @@ inline bool wgrad_small_tiles(long full_tiles, long small_tiles, int mean_rows, 
   return full_tiles > 256 || mean_rows <= 512 || max_rows > 2L * mean_rows;
 }
 
+// fp32 layers on the matrix cores: rows per tile, columns per gate-gradient partial (a wavefront's), and the blocks that fill the
+// chip (two per CU)
+constexpr int kF32Rows = 64, kF32ShortRows = 32, kF32RowdotCols = 32;
+constexpr long kF32Blocks = 512;
+
+// Their loads address an operand with 32-bit byte offsets; larger layers stay on the vector ALUs.
+inline bool f32_on_matrix_cores(long tokens, long rows, long d_model, long d_ff) {
+  const long lim = (1L << 30) - 8;
+  return tokens * d_model < lim && rows * d_ff < lim && d_ff * d_model < lim;
+}
+
+// 64-row tiles where the GEMM with fewest columns fills the chip with them (64 columns each, 32 of the fused SwiGLU's two
+// matrices), otherwise 32-row ones, whose blocks share out k as well.
+inline int f32_row_tile(long rows, int n_experts, int d_model, int d_ff) {
+  const long cols_d = (d_model + 63) / 64, cols_f = (d_ff + 31) / 32;
+  const long est = rows / kF32Rows + (n_experts + 1) / 2;
+  return est * (cols_d < cols_f ? cols_d : cols_f) >= kF32Blocks ? kF32Rows : kF32ShortRows;
+}
+
 }  // namespace plan
 }  // namespace spes

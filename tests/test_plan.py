@@ -5,6 +5,7 @@ import subprocess
 
 import pytest
 
+from test_gpu_gemm_f32 import CASES as F32_CASES
 from test_gpu_row_tiles import CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -19,6 +20,8 @@ int row_tile(long rows, int experts, int d, int f) { return plan::row_tile(rows,
 int rowdot_parts(int n, int row_tile, int est) { return plan::rowdot_parts(n, row_tile, est); }
 int column_tail(int n) { return plan::column_tail(n); }
 int few_tiles_narrow(int n, int est) { return plan::few_tiles_narrow(n, est); }
+int f32_row_tile(long rows, int experts, int d, int f) { return plan::f32_row_tile(rows, experts, d, f); }
+int f32_on_matrix_cores(long tokens, long rows, long d, long f) { return plan::f32_on_matrix_cores(tokens, rows, d, f); }
 }
 """
 
@@ -33,6 +36,8 @@ def plan(tmp_path_factory):
     p = ctypes.CDLL(str(lib))
     p.set_grid_tiles.restype = ctypes.c_long
     p.row_tile.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    p.f32_row_tile.argtypes = p.row_tile.argtypes
+    p.f32_on_matrix_cores.argtypes = [ctypes.c_long] * 4
     p.wgrad_small_tiles.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return p
 
@@ -104,3 +109,16 @@ def test_the_layer_cases_take_the_tiles_they_are_for(plan, kw, rows, down):
     else:
         got = "half" if plan.few_tiles_narrow(d, R // 256 + (M + 1) // 2) else "full"
     assert got == down
+
+
+def test_f32_tiles(plan):
+    # 64-row tiles once the GEMM with fewest columns has 512 blocks of them
+    assert [plan.f32_row_tile(r, 8, 512, 512) for r in (59 * 64, 60 * 64)] == [32, 64]        # (60 + 4) * 8
+    assert [plan.f32_row_tile(16384, 16, 8, f) for f in (8, 512)] == [32, 32]
+    for kw, rows in F32_CASES:
+        assert plan.f32_row_tile(kw["T"] * kw["k"], kw["M"], kw["d"], kw["f"]) == rows
+    # 32-bit byte offsets: four bytes an element, less the last 32 bytes
+    lim = (1 << 30) - 8
+    assert plan.f32_on_matrix_cores(1, 1, lim - 8, 1) and not plan.f32_on_matrix_cores(1, 1, lim, 1)
+    assert not plan.f32_on_matrix_cores(lim // 8 + 1, 1, 8, 8) and not plan.f32_on_matrix_cores(1, lim // 8 + 1, 8, 8)
+    assert not plan.f32_on_matrix_cores(1, 1, 1 << 15, 1 << 15)
