@@ -68,7 +68,7 @@ Layout make_layout(const spes_moe_shape* s) {
   L.pub.inv = take(R * 4);
   L.block_counts = take((size_t)routing_blocks((int)R) * kMaxExperts * 4);
   L.tab_simt = take((1 + 2 * (size_t)L.max_tiles) * 4);
-  L.tab_mfma = take((1 + 2 * (size_t)L.max_tiles) * 4);
+  L.tab_mfma = take((2 + 2 * (size_t)L.max_tiles) * 4);
   L.row_token = take(R * 4);
   L.row_gate = take(R * 4);
   // fp32 storage keeps the projections in fp32; bf16 storage keeps them in bf16 plus a bf16 correction of h
@@ -110,6 +110,7 @@ void ragged_tables(GemmArgs& g, void* ctx, const Layout& L, int dt) {
   g.n_tiles = tab;
   g.tile_expert = tab + 1;
   g.tile_row0 = tab + 1 + L.max_tiles;
+  g.n_full = tab + 1 + 2 * L.max_tiles;
   g.offset = at<int>(ctx, L.pub.offset);
   g.max_tiles = dt == SPES_BF16 ? L.max_tiles_mfma : L.max_tiles;   // launch bound on the number of row tiles
   g.row_tile = dt == SPES_BF16 ? L.row_tile_mfma : L.row_tile_f32;

@@ -50,6 +50,7 @@ struct GemmArgs {
   const int* tile_expert;
   const int* tile_row0;
   const int* n_tiles;
+  const int* n_full;      // how many of them are full-height (bf16, 256-row tiles: the others, behind them, are half as high)
   const int* offset;      // [M+1] first routed row of each expert
   int max_tiles;
   int row_tile;           // rows per tile of that table (matrix-core paths: plan::row_tile, plan::f32_row_tile)

@@ -81,12 +81,15 @@ constexpr bool f32_out(int mode, bool a_kc, bool b_kc) { return mode == kGrouped
 // SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
 // and result; either operand of a set may take its k-rows through the index table k_rows (the dy rows, or the input
 // rows, of an expert's routed pairs)
+// 16-byte units of LDS that a tile uses: its operand slots, or the four wavefronts' epilogue slabs (32 padded float rows each)
+template <typename C>
+constexpr int lds_units() { return C::LDS_VEC > 32 * (C::TN * 16 + 4) ? C::LDS_VEC : 32 * (C::TN * 16 + 4); }
+
+// One tile.  block: position in the launch, or in its part with this tile shape; ragged rows: that part's row tiles in the table
 template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C>
-__global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs g) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, const unsigned block, const int mt_first, const int mt_count) {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, TM = C::TM, TN = C::TN, NSA = C::NSA, NSB = C::NSB;
   constexpr int A_VEC = C::A_VEC, B_VEC = C::B_VEC;
-  constexpr int EP_VEC = 32 * (TN * 16 + 4);               // the four wavefronts' epilogue slabs (32 padded float rows each)
-  __shared__ uint4 smem[C::LDS_VEC > EP_VEC ? C::LDS_VEC : EP_VEC];
   const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform(tid >> 6);
   const int l16 = lane & 15, lq = lane >> 4;          // an MFMA operand: lane holds row l16, k = lq*8 .. lq*8+7 of a 32-wide k-step
   const int wm = wave >> 1, wn = wave & 1;
@@ -98,18 +101,18 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   int Mdim = g.Mdim, Ndim = g.Ndim;
   int gx = cdiv(Ndim - n_base, BNO);
   long total;
-  if (MODE == kRaggedM) total = (long)(*g.n_tiles) * gx; else total = (long)g.n_groups * cdiv(Mdim, BM) * gx;
+  if (MODE == kRaggedM) total = (long)mt_count * gx; else total = (long)g.n_groups * cdiv(Mdim, BM) * gx;
   if (SETS) total *= g.n_sets;
   long logical;
   if (MODE == kGroupedK && g.offset != nullptr) {
     // ragged contraction lengths: tiles are taken in block order (round-robin over the XCDs) and the groups are
     // visited longest first, so the long tiles start early and the short ones fill in behind them
-    logical = blockIdx.x;
+    logical = block;
     if (logical >= total) return;
   } else {
     const long per_xcd = (total + kXcds - 1) / kXcds;
-    const long slot = blockIdx.x / kXcds;
-    logical = (long)(blockIdx.x % kXcds) * per_xcd + slot;
+    const long slot = block / kXcds;
+    logical = (long)(block % kXcds) * per_xcd + slot;
     if (slot >= per_xcd || logical >= total) return;
   }
   int set = 0;
@@ -147,6 +150,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
     nt = (int)(logical % gx);
     mt_all = logical / gx;
   }
+  if (MODE == kRaggedM) mt_all += mt_first;
 
   long m0, m_end, k_begin, k_end, b_group = 0, c_group = 0;
   bool ds_store2 = true;
@@ -274,7 +278,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   // panels in its L2 and stay together.  200 tokens, 32 experts of 2048 x 2048, top-4: gate + up 104 to 148 us (by where the
   // buffers lie) -> 101, down 88 -> 50 (5.3 TB/s), the forward pass 228 -> 176; a start of its own for every block is 1 to 5 %
   // slower at d_model = 640 and 3000.  Taller tiles share panels among many blocks that drift apart by themselves: no gain.
-  const int k_rot = MODE == kRaggedM && BM == 64 ? (int)uniform(((blockIdx.x % kXcds) * (unsigned)nk) / kXcds) : 0;
+  const int k_rot = MODE == kRaggedM && BM == 64 ? (int)uniform(((block % kXcds) * (unsigned)nk) / kXcds) : 0;
   unsigned b1_lo = 0, b1_hi = 0;                         // fused SwiGLU: the base in the second matrix
   // in steps, so that the main loop can deal them out: 0 the k, 1 the base, 2 the size, 3 where to
   auto next_src = [&](Src& x, int step, int lt, unsigned per_k, unsigned long base0, unsigned long base1, unsigned bytes, unsigned dst) {
@@ -765,6 +769,33 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   }
 }
 
+// C: the tile; CH: the shorter tile of the experts' last rows, or C again.
+// An expert's last full tile holds 128 rows on average, and beside a round of 256 of them a launch of a few thousand tokens has few
+// others.  Last tiles of up to 128 rows are therefore half as high: 0.7 of a full one's time, because each is alone with its
+// panel of the weights.  They come last, where they also shorten the round that is not full: 4096 tokens, 32 experts of 2048 x 2048,
+// top-4, gradient accumulation 1302 -> 1271 us; 16384, 32 of 3584 x 4864, top-2 7561 -> 7291; 12000, 48 of 4096 x 640, top-2
+// 1128 -> 1094; layers whose experts end in few such tiles within 1 %.  In the order of the experts, beside the full tiles
+// whose weights they share, they take 0.6 of one, but a full tile ends the launch: 1295 and 7610 us.
+template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C, typename CH>
+__global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs g) {
+  __shared__ uint4 smem[lds_units<C>() > lds_units<CH>() ? lds_units<C>() : lds_units<CH>()];
+  const int all = MODE == kRaggedM ? *g.n_tiles : 0;
+  if constexpr (C::BM != CH::BM) {
+    static_assert(MODE == kRaggedM && CH::BN == C::BN && CH::BM == plan::kHalfRows, "the table's short tiles, the same columns");
+    // the table has the full tiles first; the blocks of either kind are dealt to the XCDs by themselves
+    const int full = *g.n_full;
+    const unsigned gx = (unsigned)cdiv(g.Ndim - g.n_base, EPI == kEpiSwiglu ? C::BN / 2 : C::BN);
+    const unsigned first_short = ((unsigned)full * gx + kXcds - 1) / kXcds * kXcds;
+    if (blockIdx.x >= first_short) {
+      gemm_tile<MODE, EPI, A_KC, B_KC, SETS, CH>(g, smem, blockIdx.x - first_short, full, all - full);
+      return;
+    }
+    gemm_tile<MODE, EPI, A_KC, B_KC, SETS, C>(g, smem, blockIdx.x, 0, full);
+  } else {
+    gemm_tile<MODE, EPI, A_KC, B_KC, SETS, C>(g, smem, blockIdx.x, 0, all);
+  }
+}
+
 // the full tile: 256 x 256 x 64, one block per CU (128 to 144 KB of LDS by operand layout, 256 accumulators per lane in AGPRs)
 typedef Cfg<256, 256, 3, 2, 1> Tile;
 typedef Cfg<256, 256, 2, 2, 1> TileSets;
@@ -779,6 +810,8 @@ typedef Cfg<128, 256, 3, 3, 1> TileShort;
 // and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's; also the other
 // ragged-row GEMMs on 128-row tiles, and weight gradients of few full tiles (plan::wgrad_small_tiles)
 typedef Cfg<128, 128, 3, 2, 2> TileSmall;
+// the last rows of an expert beside TileNarrow
+typedef Cfg<128, 128, 3, 2, 1> TileNarrowShort;
 // ragged-row GEMMs on 64-row tiles (plan::row_tile), two blocks per CU: experts of few routed rows, bound by the stream of
 // their weights, and narrow models with few tiles, bound by prologue and epilogue
 typedef Cfg<64, 256, 2, 2, 2> Rows64;
@@ -787,7 +820,7 @@ static_assert(Tile::BM == plan::kFullRows && TileShort::BM == plan::kHalfRows &&
               Tile::BN == plan::kFullCols && TileNarrow::BN == plan::kHalfCols && TileSmall::BN == plan::kHalfCols && Rows64Narrow::BN == plan::kHalfCols,
               "the tiles that the plan counts");
 
-template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false>
+template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false, typename CH = C>
 int launch(const GemmArgs& g, hipStream_t s) {
   static_assert(!SETS || (MODE == kGroupedK && !A_KC && !B_KC && C::BM == C::BN), "operand sets: K-strided, square tiles");
   if (EPI == kEpiStore && (g.c_f32 != 0) != f32_out(MODE, A_KC, B_KC)) return SPES_EINVAL;
@@ -807,8 +840,8 @@ int launch(const GemmArgs& g, hipStream_t s) {
   long total = (MODE == kRaggedM) ? (long)g.max_tiles * gx : (long)g.n_groups * cdiv(g.Mdim, C::BM) * gx;
   if (SETS) total *= g.n_sets;
   if (total <= 0) return SPES_OK;
-  total = (total + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL((gemm_mfma_kernel<MODE, EPI, A_KC, B_KC, SETS, C>), dim3((unsigned)total), dim3(256), 0, s, g);
+  total = (total + kXcds - 1) / kXcds * kXcds + (C::BM != CH::BM ? kXcds : 0);      // two kinds of tiles: rounded up twice
+  hipLaunchKernelGGL((gemm_mfma_kernel<MODE, EPI, A_KC, B_KC, SETS, C, CH>), dim3((unsigned)total), dim3(256), 0, s, g);
   return hipGetLastError() == hipSuccess ? SPES_OK : SPES_EHIP;
 }
 
@@ -821,6 +854,15 @@ static int launch_short(int epi, bool b_kcontig, const GemmArgs& g, hipStream_t 
   if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, N>(g, s);
   if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, N>(g, s);
   if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, N>(g, s);
+  return SPES_EINVAL;
+}
+
+// kRaggedM on full-height tiles and, for the last rows of an expert, half-height ones
+template <typename C, typename CH>
+static int launch_mixed(int epi, bool b_kcontig, const GemmArgs& g, hipStream_t s) {
+  if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, C, false, CH>(g, s);
+  if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, C, false, CH>(g, s);
+  if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, C, false, CH>(g, s);
   return SPES_EINVAL;
 }
 
@@ -841,23 +883,12 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
       rest.n_base = g.Ndim - tail;
       rest.rowdot_slot0 = 2 * (head.Ndim / Tile::BN);
       const int rc = launch_gemm_mfma(mode, epi, a_kcontig, b_kcontig, head, s);
-      if (rc != SPES_OK) return rc;
-      if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, TileNarrow>(rest, s);
-      if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, TileNarrow>(rest, s);
-      if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, TileNarrow>(rest, s);
-      return SPES_EINVAL;
+      return rc != SPES_OK ? rc : launch_mixed<TileNarrow, TileNarrowShort>(epi, b_kcontig, rest, s);
     }
-    if (epi != kEpiSwiglu && g.n_base == 0 && plan::few_tiles_narrow(g.Ndim, g.est_tiles)) {
-      if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true, TileNarrow>(g, s);
-      if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false, TileNarrow>(g, s);
-      if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false, TileNarrow>(g, s);
-      return SPES_EINVAL;
-    }
-    if (epi == kEpiSwiglu && b_kcontig) return launch<kRaggedM, kEpiSwiglu, true, true>(g, s);
-    if (epi == kEpiStore && b_kcontig) return launch<kRaggedM, kEpiStore, true, true>(g, s);
-    if (epi == kEpiStore && !b_kcontig) return launch<kRaggedM, kEpiStore, true, false>(g, s);
-    if (epi == kEpiDSwiglu && !b_kcontig) return launch<kRaggedM, kEpiDSwiglu, true, false>(g, s);
-    return SPES_EINVAL;
+    if (epi != kEpiSwiglu && g.n_base == 0 && plan::few_tiles_narrow(g.Ndim, g.est_tiles))
+      return launch_mixed<TileNarrow, TileNarrowShort>(epi, b_kcontig, g, s);
+    if (epi == kEpiSwiglu && b_kcontig) return launch<kRaggedM, kEpiSwiglu, true, true, Tile, false, TileShort>(g, s);
+    return launch_mixed<Tile, TileShort>(epi, b_kcontig, g, s);
   }
   if (epi != kEpiStore) return SPES_EINVAL;
   if (a_kcontig && b_kcontig)

@@ -3,6 +3,7 @@
 // routing, drop-less dispatch).  Integer results are deterministic: no
 // order-dependent atomics decide a position.
 #include "kernels.h"
+#include "plan.h"
 
 namespace spes {
 namespace {
@@ -82,20 +83,33 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int lane) {
 }
 
 // Row-tile tables of one wavefront whose lane e owns expert e (`total` rows from `off` on).  Layout: [0] = number of tiles,
-// [1 .. max_tiles] expert of each tile, [1+max_tiles ..] first row
+// [1 .. max_tiles] expert of each tile, [1+max_tiles ..] first row.  The matrix-core table (tab1) says at [1+2 max_tiles] how many of
+// them are full-height: of 256-row tiles, the last one of an expert is half as high where that holds its rows, and
+// these stand behind the full ones.
 __device__ __forceinline__ void write_tile_tables(int e, int total, int off, int bm0, int* __restrict__ tab0, int bm1, int* __restrict__ tab1,
                                                   int max_tiles) {
   for (int which = 0; which < 2; ++which) {
     const int bm = which ? bm1 : bm0;
     int* tab = which ? tab1 : tab0;
     if (bm <= 0 || tab == nullptr) continue;
-    const int nt = (total + bm - 1) / bm;
+    const int rest = total % bm;
+    const int half = which && bm == plan::kFullRows && rest > 0 && rest <= plan::kHalfRows ? 1 : 0;
+    const int nt = (total + bm - 1) / bm - half;
     const int t0 = wave_exclusive_scan(nt, e);
     for (int i = 0; i < nt; ++i) {
       tab[1 + t0 + i] = e;
       tab[1 + max_tiles + t0 + i] = off + i * bm;
     }
-    if (e == 63) tab[0] = t0 + nt;
+    const int full = __builtin_amdgcn_readlane(t0 + nt, 63);
+    const int h0 = full + wave_exclusive_scan(half, e);
+    if (half) {
+      tab[1 + h0] = e;
+      tab[1 + max_tiles + h0] = off + nt * bm;
+    }
+    if (e == 63) {
+      tab[0] = h0 + half;
+      if (which) tab[1 + 2 * max_tiles] = full;
+    }
   }
 }
 

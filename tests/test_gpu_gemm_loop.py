@@ -28,6 +28,14 @@ def test_contraction_lengths(T, d, M, f, k, device):
     _full_parity(layer_inputs(custom_config(**kw)), device, "contraction lengths")
 
 
+# one expert's rows around the heights of full and half tiles; with whole columns, a column tail, and on half-width tiles
+@pytest.mark.parametrize("T", [128, 129, 256, 257, 384, 385, 641])
+@pytest.mark.parametrize("d,f", [(904, 136), (1032, 328), (1024, 256)])
+def test_last_rows(T, d, f, device):
+    kw = dict(T=T, d=d, M=1, f=f, k=1, n_trainable=1, dtype="bf16", router_sigma=0.3)
+    _full_parity(layer_inputs(custom_config(**kw)), device, "last rows")
+
+
 @pytest.mark.parametrize("T,d,f", [(60, 136, 200), (200, 1000, 136), (700, 960, 328), (700, 520, 520)])
 def test_values_stay_with_their_expert(T, d, f, device):
     """NaN weights of one expert: every result of tokens and experts that have nothing to do with it stays bit for bit."""
