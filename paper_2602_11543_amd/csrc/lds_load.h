@@ -28,4 +28,10 @@ __device__ __forceinline__ void wait_and_meet() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
+// 16 bytes per lane to base + lane_off with the non-temporal hint, nothing for a lane out of the `bytes` bytes
+__device__ __forceinline__ void store_stream16(unsigned long base, unsigned bytes, unsigned lane_off, const uint4& v) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, (int)bytes, 0x00020000);
+  __builtin_amdgcn_raw_buffer_store_b128(rsrc_t{v.x, v.y, v.z, v.w}, rs, (int)lane_off, 0, 2);
+}
+
 }  // namespace spes

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "lds_load.h"
 
 namespace spes {
 namespace {
@@ -220,8 +221,8 @@ __global__ __launch_bounds__(256) void sim_topk_kernel(const float* __restrict__
 // takes the column runs x, x+8, ... with all M experts of a run on consecutive blocks.  The M rows of a run (M x 4 KB)
 // are then in flight on one XCD at the same time and each is fetched from memory once instead of once per reader
 // (measured: 256 MiB fetched per 256 MiB matrix, against 1187 MiB with the experts as the slow grid axis).  What is
-// left is L2 bandwidth: 99 us + 10 us per peer for a 256 MiB matrix.  Staging the M rows of a run in LDS instead
-// (one block per run, peers read from LDS) was measured slower: 130 us + 10 us per peer.
+// left is L2 bandwidth: 99 us + 10 us per peer for a 256 MiB matrix.  For few runs, more than eight peers, and matrices
+// beyond 32-bit offsets; the kernel below takes the others.
 template <typename T>
 __global__ __launch_bounds__(256) void warmup_mix_kernel(const T* __restrict__ src, T* __restrict__ dst,
                                                          const int* __restrict__ nbr, int M, int K, float scale, long nvec, long elems) {
@@ -277,6 +278,91 @@ int flush(const MergeTable& tb, int n, void* dst, long elems, hipStream_t s) {
   const long nvec = elems / Vec16<T>::N;
   hipLaunchKernelGGL(sync_merge_kernel<T>, dim3(stream_grid_x(nvec), n), dim3(256), 0, s, tb, (T*)dst, nvec);
   return ok();
+}
+
+// The same with every source element read from memory once: a block takes a run of columns of all experts into LDS and forms
+// every expert's result from there.  Blocks stay (one per CU, each with every gridDim-th run) and keep three runs of 32 KB in
+// flight ahead of the one they work on, so that loads, LDS reads and stores overlap.  64 experts of 2048 x 1024 in bf16, four peers:
+// 140 -> 112 us per matrix (4.8 TB/s of 5.2 that a copy reaches), eight peers 190 -> 116; the fp32 warm-up of 8 experts of 1024 x
+// 1024 (with its Gram matrix on the matrix cores) 247 -> 72.
+// A run has up to 2048 vectors, four for every thread: M experts by `vc` vectors, whole 128-byte lines.  KU = K peers, their LDS
+// offsets in registers.
+constexpr int kMixSlots = 4, kMixVecs = 2048, kMixItems = kMixVecs / 512;
+template <typename T, int KU>
+__global__ __launch_bounds__(512) void warmup_mix_lds_kernel(const T* __restrict__ src, T* __restrict__ dst, const int* __restrict__ nbr, int M,
+                                                             float scale, int vc, long nvec, int n_runs) {
+  constexpr int N = Vec16<T>::N;
+  __shared__ uint4 smem[kMixSlots * kMixVecs];
+  const int tid = threadIdx.x, wave = (int)uniform(tid >> 6);
+  const unsigned row_bytes = (unsigned)(nvec * 16);
+  unsigned off[kMixItems], pos[kMixItems][KU + 1];   // item: offset in a run of src / dst, LDS offsets of the expert and its peers
+  int col[kMixItems];
+#pragma unroll
+  for (int it = 0; it < kMixItems; ++it) {
+    const int li = it * 512 + tid, row = li / vc;
+    col[it] = li - row * vc;
+    off[it] = row < M ? (unsigned)row * row_bytes + (unsigned)col[it] * 16u : kOutOfRange;
+    pos[it][0] = (unsigned)li;
+#pragma unroll
+    for (int u = 0; u < KU; ++u) pos[it][u + 1] = (unsigned)((row < M ? nbr[row * KU + u] : 0) * vc + col[it]);
+  }
+  const unsigned all_bytes = (unsigned)M * row_bytes;
+  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) uint4*)smem + (unsigned)wave * 1024u;
+  const unsigned long s_base = reinterpret_cast<unsigned long>(src), d_base = reinterpret_cast<unsigned long>(dst);
+  auto left = [&](int run) { return nvec - (long)run * vc; };       // vectors of a row from the run's first one on
+  auto load_run = [&](int run, int slot) {
+    const bool live = run < n_runs;
+    const unsigned at = live ? (unsigned)run * (unsigned)vc * 16u : 0u;
+    const rsrc_t rs = make_rsrc(s_base + at, live ? all_bytes - at : 0u);
+    const long l = live ? left(run) : 0;
+#pragma unroll
+    for (int it = 0; it < kMixItems; ++it) {
+      set_lds_dest(lds0 + (unsigned)(slot * kMixVecs + it * 512) * 16u);
+      one_instruction();
+      load_to_lds(rs, col[it] < l ? off[it] : kOutOfRange);
+    }
+  };
+  // at the wait for run i: the loads of the runs behind it, and the stores of the runs since its own loads
+  constexpr int kBehind = (kMixSlots - 2) * kMixItems + (kMixSlots - 1) * kMixItems;
+  const int step = gridDim.x;
+  int run = blockIdx.x;
+  for (int i = 0; i < kMixSlots - 1; ++i) load_run(run + i * step, i);
+  // (the first runs have fewer stores between loads and wait: one wait for all of their loads)
+  int slot = 0, since = 0;
+  for (; run < n_runs; run += step) {
+    if (since < kMixSlots - 1) { wait_and_meet<0>(); ++since; }
+    else wait_and_meet<kBehind>();
+    const int fill = (slot + kMixSlots - 1) % kMixSlots;            // read by all before they met
+    load_run(run + (kMixSlots - 1) * step, fill);
+    const unsigned at = (unsigned)run * (unsigned)vc * 16u;
+    const long l = left(run);
+    const uint4* const in = smem + slot * kMixVecs;
+#pragma unroll
+    for (int it = 0; it < kMixItems; ++it) {
+      Vec16<T> q;
+      float f0[N], acc[N];
+      q.load(reinterpret_cast<const T*>(in + pos[it][0]));
+      q.unpack(f0);
+#pragma unroll
+      for (int e = 0; e < N; ++e) acc[e] = 0.f;
+#pragma unroll
+      for (int u = 0; u < KU; ++u) {
+        Vec16<T> p;
+        float f[N];
+        p.load(reinterpret_cast<const T*>(in + pos[it][u + 1]));
+        p.unpack(f);
+#pragma unroll
+        for (int e = 0; e < N; ++e) acc[e] += f[e] - f0[e];
+      }
+#pragma unroll
+      for (int e = 0; e < N; ++e) acc[e] = fmaf(scale, acc[e], f0[e]);
+      q.pack(acc);
+      // stores through the resource, never skipped: the wait counts them
+      store_stream16(d_base + at, all_bytes - at, col[it] < l ? off[it] : kOutOfRange, __builtin_bit_cast(uint4, q.raw));
+    }
+    slot = (slot + 1) % kMixSlots;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no load may still write LDS when the block ends
 }
 
 }  // namespace
@@ -341,6 +427,23 @@ int launch_sim_topk(float* partial, int n_partial, int M, int K, float* sim, int
 int launch_warmup_mix(int dtype, int M, long elems, int K, float alpha, const void* src, void* dst, const int* nbr, hipStream_t s) {
   const float scale = alpha / (float)K;
   const long nvec = elems / (dtype == SPES_F32 ? 4 : 8);
+  const int vc = kMixVecs / M / 8 * 8, n_runs = cdiv(nvec, vc);
+  // From LDS where every CU has a few runs to overlap: 512 runs 50.7 against 52.2 us for a whole warm-up (64 experts of 256 x 512, four
+  // peers), 256 of them 41.4 against 40.5; with one peer there is little to save (64 of 512 x 512, 1024 runs: 71.0 against 69.7;
+  // 33 of 2000 x 1000, 4465 runs: 196 against 203)
+  if (K <= 8 && n_runs >= (K == 1 ? 2048 : 512) && (long)M * nvec * 16 < 0xfffffff0L) {
+    const dim3 grid(n_runs < 256 ? n_runs : 256);
+#define SPES_MIX(T, KU) \
+  hipLaunchKernelGGL((warmup_mix_lds_kernel<T, KU>), grid, dim3(512), 0, s, (const T*)src, (T*)dst, nbr, M, scale, vc, nvec, n_runs)
+#define SPES_MIX_K(KU) \
+  case KU: \
+    if (dtype == SPES_F32) SPES_MIX(float, KU); else SPES_MIX(bf16_t, KU); \
+    break;
+    switch (K) { SPES_MIX_K(1) SPES_MIX_K(2) SPES_MIX_K(3) SPES_MIX_K(4) SPES_MIX_K(5) SPES_MIX_K(6) SPES_MIX_K(7) SPES_MIX_K(8) }
+#undef SPES_MIX_K
+#undef SPES_MIX
+    return ok();
+  }
   const long runs8 = (long)cdiv(cdiv(nvec, 256), 8) * 8;         // column runs, rounded up to a whole turn of the XCDs
   const long blocks = runs8 * M;
   if (blocks <= 0) return SPES_OK;

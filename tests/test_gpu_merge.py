@@ -128,6 +128,27 @@ def test_warmup_merge_parity(dtype, M, E, K, alpha, device):
             assert np.array_equal(_host(t), m)
 
 
+@pytest.mark.parametrize("dtype,M,E,K", [
+    # enough column runs for the kernel that mixes from LDS: 512 and more, ragged last run, experts that do not fill a run
+    ("bf16", 64, 8 * (32 * 512 + 3), 4), ("bf16", 33, 8 * (56 * 513 - 1), 8), ("f32", 5, 4 * (408 * 511 + 2), 3), ("f32", 21, 4 * 96 * 700, 5),
+    ("bf16", 64, 8 * (32 * 2048 + 1), 1), ("bf16", 3, 8 * (680 * 512 - 5), 2),
+    ("bf16", 64, 8 * 32 * 511, 2), ("bf16", 33, 8 * 56 * 600, 9)])            # one run short of it; more peers than it takes
+def test_warmup_mix_of_long_matrices(dtype, M, E, K, device):
+    print(f"[case] mix {dtype} M={M} E={E} K={K}", flush=True)
+    dt = S.SPES_F32 if dtype == "f32" else S.SPES_BF16
+    w_in, m = _structured_experts(M, 2048, dtype, 1), np.ascontiguousarray(_structured_experts(M, E, dtype, 2))
+    src, guard = to_dev(m, dtype, device), 64
+    dst = torch.full((M * E + guard,), 7.0, dtype=src.dtype, device=device)
+    nbr = torch.zeros(M, K, dtype=torch.int32, device=device)
+    scratch = torch.empty(S.spes_warmup_scratch_bytes(M, 2048), dtype=torch.uint8, device=device)
+    S.spes_expert_warmup_merge(M, dt, K, 0.3, to_dev(w_in, dtype, device), 2048, [src], [dst], [E], None, nbr, scratch)
+    torch.cuda.synchronize()
+    peers = nbr.cpu().numpy()
+    mag = np.maximum(np.abs(m), np.abs(m[peers]).max(axis=1))
+    assert storage_ulp_excess(_host(dst)[:M * E].reshape(M, E), O.warmup_merge(m, peers, 0.3), mag, dtype, f32_ulps=K + 2.0) <= 0
+    assert torch.all(dst[M * E:] == 7.0)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_warmup_merge_with_a_zero_norm_expert(dtype, device):
     """An all-zero input projection makes Eq. 5 a 0/0: the pair gets similarity 0, peers stay valid experts."""
