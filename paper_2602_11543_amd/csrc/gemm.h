@@ -64,7 +64,8 @@ struct GemmArgs {
   // n_sets > 0 replaces A, B, C, their element counts and k strides, c_ms and Mdim / Ndim (which hold set 0's extents;
   // the other sets have the same or the transposed shape)
   int n_sets;
-  const int* k_rows;      // operands with a_gather / b_gather read row k_rows[k] in place of k
+  const int* k_rows;      // operands with a_gather / b_gather (one of the two in every set) read row k_rows[k] in place of k; the
+                          // matrix-core path reads up to 63 entries beyond the last group's and does not use them
   struct Set {
     const void *A, *B;
     void* C;

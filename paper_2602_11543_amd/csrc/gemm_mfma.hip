@@ -86,7 +86,8 @@ template <typename C>
 constexpr int lds_units() { return C::LDS_VEC > 32 * (C::TN * 16 + 4) ? C::LDS_VEC : 32 * (C::TN * 16 + 4); }
 
 // One tile.  block: position in the launch, or in its part with this tile shape; ragged rows: that part's row tiles in the table
-template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C>
+// GATHER: which operand of a set (1 A, 2 B) takes its k-rows through the index table
+template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C, int GATHER = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, const unsigned block, const int mt_first, const int mt_count) {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, TM = C::TM, TN = C::TN, NSA = C::NSA, NSB = C::NSB;
   constexpr int A_VEC = C::A_VEC, B_VEC = C::B_VEC;
@@ -131,7 +132,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   void* const opC0 = SETS ? g.set[set].C : g.C[0];
   const long a_ks = SETS ? g.set[set].a_ks : g.a_ks, b_ks = SETS ? g.set[set].b_ks : g.b_ks;
   const long c_ms = SETS ? g.set[set].c_ms : g.c_ms;
-  const bool a_gather = SETS && g.set[set].a_gather, b_gather = SETS && !a_gather;      // one of the two
+  static_assert(SETS == (GATHER != 0), "one operand of every set");
+  constexpr bool a_gather = GATHER == 1, b_gather = GATHER == 2;
   int nt;
   long mt_all;
   if (MODE == kRaggedM && gx >= kGroupMinCols) {
@@ -218,6 +220,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const unsigned a_col = (unsigned)((m0 + (((lane % ACH) ^ (2 * (a_krow & 3))) * 8)) * 2);
   const unsigned b_col = (unsigned)((n0 + (((lane % BCH) ^ (2 * (b_krow & 3))) * 8)) * 2);
   auto ks_off = [](unsigned long o) { return o < kOutOfRange ? (unsigned)o : kOutOfRange; };   // k-rows beyond a short, wide operand
+  // k of the k-row that load i of a K-strided operand brings to k-row krow + i*KR of its slot: the same, or, with k-rows from the
+  // index table, in an order (of both operands) in which a wavefront's sixteen are sixteen entries of the table in a row
+  auto ks_k = [](int krow, int i, int kr) { return SETS ? krow * (BK / kr) + i : krow + i * kr; };
   unsigned aoff[C::NA], boff[C::NB];
   if (A_KC) {
     int m_row[C::NA];
@@ -231,7 +236,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     for (int i = 0; i < C::NA; ++i) aoff[i] = (unsigned)((m_row[i] * g.a_ms + kc_chunk * 8) * 2);
   } else {
 #pragma unroll
-    for (int i = 0; i < C::NA; ++i) aoff[i] = ks_off((a_krow + i * C::KRA) * a_ks * 2 + a_col);
+    for (int i = 0; i < C::NA; ++i) aoff[i] = ks_off(ks_k(a_krow, i, C::KRA) * a_ks * 2 + a_col);
   }
   // fused SwiGLU: load i brings rows of the gate matrix (B[0]) or of the up matrix (B[1]); tile row nl -> wave column, then
   // (BN/4) gate columns followed by the matching (BN/4) up columns
@@ -244,7 +249,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       const long col = (EPI == kEpiSwiglu) ? n0 + (nl / SW_W) * SW_H + (nl % SW_H) : n0 + nl;
       boff[i] = (unsigned)((col * g.b_ns + kc_chunk * 8) * 2);
     } else {
-      boff[i] = ks_off((b_krow + i * C::KRB) * b_ks * 2 + b_col);
+      boff[i] = ks_off(ks_k(b_krow, i, C::KRB) * b_ks * 2 + b_col);
     }
   }
 
@@ -311,34 +316,46 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       pin(b1_lo); pin(b1_hi);
     }
   };
-  // k-rows of the tile to be loaded next, from the index table: requested while the tile before is being loaded, turned into
-  // offsets (rows beyond the range: out of the resource) behind the wait that empties the memory queue in any case
-  int kidx[SETS ? NA : 1];
-  auto load_kidx = [&](int lt, int j) {
+  // The index table's entries of a wavefront's sixteen k-rows, in scalar registers: requested an iteration before they are needed,
+  // while no LDS read is outstanding (both count on one counter, out of order), and turned into offsets one load at a time.
+  // Entries beyond the range are there to be read (up to 63, see GemmArgs) and not used: their loads are masked.  (As loads
+  // of each lane's own indices, waited for in order behind the loads into LDS, they emptied the memory queue in every
+  // K-tile, and their 64-bit addresses, clamps and selects were two thirds of 224 vector instructions a K-tile, now 57:
+  // 1024 rows an expert, 3584 x 4864, 4100 -> 3000 cycles per K-tile, the launch 1228 -> 1050 us.)
+  typedef __attribute__((ext_vector_type(16))) int i32x16;
+  typedef __attribute__((address_space(4))) const i32x16 const_i32x16 __attribute__((aligned(4)));
+  i32x16 kidx, kidx_next;
+  auto load_kidx = [&](int lt) {
     if (SETS) {
-      const int k = (int)k_begin + lt * BK + a_krow + j * C::KRA;
-      kidx[j] = g.k_rows[max(0, min(k, (int)k_end - 1))];
+      const int at = (int)uniform((unsigned)k_begin) + (lt < nsteps ? lt : nsteps - 1) * BK + wave * 16;
+      kidx_next = *(const_i32x16*)(unsigned long)(g.k_rows + at);
     }
   };
-  const unsigned g_pitch = (unsigned)((a_gather ? a_ks : b_ks) * 2), g_col = a_gather ? a_col : b_col;
+  auto have_kidx = [&]() {
+    if (SETS) { asm volatile("" : "+s"(kidx_next)); kidx = kidx_next; }
+  };
   auto take_kidx = [&](int j) {
     if (SETS) {
-      // (beyond the range: all ones from bit 4 up, which is kOutOfRange; arithmetic, because a select becomes a branch)
-      const unsigned off = ((unsigned)kidx[j] * g_pitch + g_col) | ((unsigned)(((int)as.left - 1 - a_krow - j * C::KRA) >> 31) & kOutOfRange);
-      aoff[j] = a_gather ? off : aoff[j];
-      boff[j] = a_gather ? boff[j] : off;
+      constexpr int CHK = a_gather ? ACH : BCH, N = a_gather ? NA : NB;
+      int row = kidx[j];
+#pragma unroll
+      for (int h = 1; h < 64 / CHK; ++h) row = lane / CHK == h ? kidx[h * N + j] : row;
+      if (a_gather) aoff[j] = (unsigned)row * (unsigned)(a_ks * 2) + a_col;
+      if (b_gather) boff[j] = (unsigned)row * (unsigned)(b_ks * 2) + b_col;
     }
   };
   // load p of a K-tile, B first, in two steps; `masked`: the tile may reach beyond the contraction range of K-contiguous operands
   auto aim = [&](int p) { set_lds_dest(p < NB ? bs.dst + (unsigned)p * 4096u : as.dst + (unsigned)(p - NB) * 4096u); };
   auto load = [&](int p, bool masked) {
     if (p < NB) {
-      const unsigned off = B_KC && masked && kc_chunk * 8 >= (int)bs.left ? kOutOfRange : boff[p];
+      const int kb = B_KC ? kc_chunk * 8 : ks_k(b_krow, p, C::KRB);
+      const unsigned off = (B_KC || b_gather) && masked && kb >= (int)bs.left ? kOutOfRange : boff[p];
       // (the load -> matrix assignment of the fused SwiGLU is the same for every thread)
       const bool up = EPI == kEpiSwiglu && ((32 * p) % SW_W) / SW_H != 0;
       load_to_lds(rsrc_t{up ? b1_lo : bs.lo, up ? b1_hi : bs.hi, bs.bytes, 0x00020000u}, off);
     } else {
-      const unsigned off = A_KC && masked && kc_chunk * 8 >= (int)as.left ? kOutOfRange : aoff[p - NB];
+      const int ka = A_KC ? kc_chunk * 8 : ks_k(a_krow, p - NB, C::KRA);
+      const unsigned off = (A_KC || a_gather) && masked && ka >= (int)as.left ? kOutOfRange : aoff[p - NB];
       load_to_lds(rsrc_t{as.lo, as.hi, as.bytes, 0x00020000u}, off);
     }
   };
@@ -381,14 +398,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   // ---- schedule: positions are gaps between the 2 MF MFMAs of a K-tile ----
   constexpr int MF = TM * TN;                       // MFMAs per k-step
   constexpr int NF = TM + TN;                       // fragments per k-step
-  constexpr bool WIDE = MF >= 32 && !SETS;          // room for a second meeting point
+  constexpr bool WIDE = MF >= 32;          // room for a second meeting point
   constexpr int F0 = MF >= 64 ? 2 : 1;              // gaps per fragment
   constexpr int QF = NF * F0 + 8 < MF ? NF * F0 + 8 : MF;          // K-tile t is in registers: its slots may be overwritten
   constexpr int QL = WIDE ? 2 * MF - NF * F0 - (MF >= 64 ? 12 : 6) : QF;    // K-tile t+1 is in LDS: its first fragments may be read
   // gaps per load: spread over the whole iteration (A's loads run on into the next one, up to its QF), B's done at its end
-  constexpr int DG_ALL = (2 * MF - (SETS ? QF : 0)) / NP, DG_B = (2 * MF - QF) / NB, DG = DG_ALL < DG_B ? DG_ALL : DG_B;
+  constexpr int DG_ALL = 2 * MF / NP, DG_B = (2 * MF - QF) / NB, DG = DG_ALL < DG_B ? DG_ALL : DG_B;
   constexpr int R0 = QL < MF ? MF : QL;             // the first fragments of K-tile t+1 follow, once their registers are free
   constexpr int F1 = (2 * MF - R0) / NF < 4 ? (2 * MF - R0) / NF : 4;
+  constexpr int KG = MF >= 32 ? 2 : 1;              // gaps per offset of gathered k-rows of A
+  static_assert(!SETS || !WIDE || QF + KG * NA < MF, "before the next indices replace these");
   constexpr int SS = MF >= 32 ? 2 : 1;              // gaps per step of the scalars of the tiles to be loaded
   static_assert(DG >= 1 && F1 >= 1 && QF + NB * DG <= 2 * MF && R0 + NF * F1 <= 2 * MF && QF >= 4 * SS && NB * DG >= 4 * SS, "more fragments or loads than MFMA gaps");
   constexpr int LATE = QF + NP * DG > 2 * MF ? (QF + NP * DG - 2 * MF + DG - 1) / DG : 0;      // loads of an iteration that the next one issues
@@ -399,49 +418,30 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   static_assert(AHEAD + NP < 64, "the counter of outstanding loads");
 
   // prologue: the first NSA and NSB K-tiles, in the order in which the iterations -NS .. -1 would have loaded them
-  if (SETS) {
-    static_assert(!SETS || (NSA == 2 && NSB == 2), "the indices of the first two K-tiles");
-    int k1[NA];
+  constexpr int FAR = NSA > NSB ? NSA : NSB, NEAR = NSA > NSB ? NSB : NSA, NSG = a_gather ? NSA : NSB;
 #pragma unroll
-    for (int j = 0; j < NA; ++j) load_kidx(1, j);
+  for (int u = -FAR; u < 0; ++u) {
+    if (SETS && u + NSG >= 0) {
+      load_kidx(u + NSG);
+      have_kidx();
 #pragma unroll
-    for (int j = 0; j < NA; ++j) k1[j] = kidx[j];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) load_kidx(0, j);
-#pragma unroll
-    for (int j = 0; j < NA; ++j) asm volatile("" : "+v"(k1[j]), "+v"(kidx[j]));    // both sets are here before the first operand load
-#pragma unroll
-    for (int lt = 0; lt < 2; ++lt) {
-#pragma unroll
-      for (int st = 0; st < 4; ++st) { next_a(st, lt, lt); next_b(st, lt, lt); }
-#pragma unroll
-      for (int j = 0; j < NA; ++j) {
-        if (lt == 1) kidx[j] = k1[j];
-        take_kidx(j);
-      }
-#pragma unroll
-      for (int p = 0; p < NP; ++p) { aim(p); one_instruction(); load(p, true); }
+      for (int j = 0; j < (a_gather ? NA : NB); ++j) take_kidx(j);
     }
 #pragma unroll
-    for (int j = 0; j < NA; ++j) load_kidx(2, j);
-  } else {
-    constexpr int NS = NSA > NSB ? NSA : NSB;
+    for (int st = 0; st < 4; ++st) {
+      if (u + NSB >= 0) next_b(st, u + NSB, u + NSB);
+      if (u + NSA >= 0) next_a(st, u + NSA, u + NSA);
+    }
 #pragma unroll
-    for (int u = -NS; u < 0; ++u) {
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        if (u + NSB >= 0) next_b(st, u + NSB, u + NSB);
-        if (u + NSA >= 0) next_a(st, u + NSA, u + NSA);
-      }
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        if ((p < NB ? u + NSB < 0 : u + NSA < 0) || (u == -1 && p >= NP - LATE)) continue;
-        aim(p); one_instruction(); load(p, true);
-      }
+    for (int p = 0; p < NP; ++p) {
+      if ((p < NB ? u + NSB < 0 : u + NSA < 0) || (u == -1 && p >= NP - LATE)) continue;
+      aim(p); one_instruction(); load(p, true);
     }
   }
+  load_kidx(NSG);
   if (LATE > 0) aim(NP - LATE);
   wait_and_meet<AHEAD + NP - LATE>();
+  have_kidx();
 #pragma unroll
   for (int w = 0; w < NF; ++w) read_frag(0, 0, 0, 0, w);
 
@@ -459,10 +459,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       const int ks = q / MF, j = (q % MF) / TM, i = q % TM;
       if (q == QF) {
         wait_and_meet<(WIDE ? 63 : AHEAD)>();
-        if (SETS) {
-#pragma unroll
-          for (int x = 0; x < NA; ++x) asm volatile("" : "+v"(kidx[x]));     // (nothing is outstanding here)
-        }
         __builtin_amdgcn_sched_barrier(0);
       }
       if (WIDE && q == QL) {
@@ -474,17 +470,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       if (q >= R0 && (q - R0) % F1 == 0 && (q - R0) / F1 < NF) read_frag(sa1, sb1, 0, 0, (q - R0) / F1);
       if (q >= QF - 4 * SS && q < QF && (QF - 1 - q) % SS == 0) next_b((q - (QF - 4 * SS)) / SS, t + NSB, sb);
       if (q >= QF && q < QF + 4 * SS && (q - QF) % SS == 0) next_a((q - QF) / SS, t + NSA, sa);
+      // offsets of the gathered operand: B's before its loads begin at QF, A's between the late loads of the tile before and its
+      // own; then the next tile's indices, to be here before the next LDS read
+      if (b_gather && q >= QF - NB && q < QF) take_kidx(q - (QF - NB));
+      if (a_gather && q >= QF && q < QF + KG * NA && (q - QF) % KG == 0) take_kidx((q - QF) / KG);
+      if (SETS && q == (WIDE ? QF + 1 : NF * F0 + 1)) load_kidx(t + 1 + NSG);
+      if (SETS && q == (WIDE ? MF - 1 : QF + NA)) have_kidx();
       {
         const int at = q >= QF ? q - QF : q - QF + 2 * MF, p = at / DG;
         if (p < NP && (q >= QF || p >= NP - LATE)) {
           if (at % DG == (DG > 1 ? DG - 2 : 0)) {
-            if (SETS && p < NA) take_kidx(p);
             aim(p);
           }
           if (DG == 1) one_instruction();
           if (at % DG == DG - 1) {
             load(p, MASKED);
-            if (SETS && p >= NA) load_kidx(t + NSA + 1, p - NA);
           }
         }
       }
@@ -500,8 +500,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     sa = sa1; sb = sb1;
     ++t;
   };
-  if constexpr (A_KC || B_KC) {
-    constexpr int FAR = NSA > NSB ? NSA : NSB, NEAR = NSA > NSB ? NSB : NSA;
+  if constexpr (A_KC || B_KC || SETS) {
     int last = klen % BK != 0 ? nk - 1 - k_rot : nsteps + FAR;        // the next K-tile that needs it
     while (last + 1 < NEAR) last += nk;
     while (true) {
@@ -791,6 +790,11 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
       return;
     }
     gemm_tile<MODE, EPI, A_KC, B_KC, SETS, C>(g, smem, blockIdx.x, 0, full);
+  } else if constexpr (SETS) {
+    // the sets stand side by side, see there
+    const unsigned per_set = (unsigned)cdiv(g.Mdim, C::BM) * (unsigned)cdiv(g.Ndim, C::BN);
+    if (g.set[blockIdx.x / per_set % 3u].a_gather) gemm_tile<MODE, EPI, A_KC, B_KC, SETS, C, 1>(g, smem, blockIdx.x, 0, all);
+    else gemm_tile<MODE, EPI, A_KC, B_KC, SETS, C, 2>(g, smem, blockIdx.x, 0, all);
   } else {
     gemm_tile<MODE, EPI, A_KC, B_KC, SETS, C>(g, smem, blockIdx.x, 0, all);
   }
@@ -798,8 +802,6 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
 
 // the full tile: 256 x 256 x 64, one block per CU (128 to 144 KB of LDS by operand layout, 256 accumulators per lane in AGPRs)
 typedef Cfg<256, 256, 3, 2, 1> Tile;
-typedef Cfg<256, 256, 2, 2, 1> TileSets;
-typedef Cfg<128, 128, 2, 2, 2> TileSmallSets;
 
 // narrow outputs (the router's M <= 64 expert columns: half the matrix work on padding), the half-full last column
 // tile of a ragged-row GEMM, and launches of few tiles
@@ -901,8 +903,8 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
     if (g.n_sets > 0) {
       const long n = (long)g.n_sets * g.n_groups, full = n * plan::tiles(g.Mdim, g.Ndim, Tile::BM, Tile::BN),
                  small = n * plan::tiles(g.Mdim, g.Ndim, TileSmall::BM, TileSmall::BN);
-      if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmallSets, true>(g, s);
-      return launch<kGroupedK, kEpiStore, false, false, TileSets, true>(g, s);
+      if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
+      return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
     }
     if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);
     return launch<kGroupedK, kEpiStore, false, false>(g, s);
