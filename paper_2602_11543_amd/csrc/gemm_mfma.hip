@@ -806,10 +806,11 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
 // the full tile: 256 x 256 x 64, one block per CU (128 to 144 KB of LDS by operand layout, 256 accumulators per lane in AGPRs)
 typedef Cfg<256, 256, 3, 2, 1> Tile;
 
-// narrow outputs (the router's M <= 64 expert columns: half the matrix work on padding), the half-full last column
+// narrow outputs (the router scores of many tokens: half the matrix work on padding), the half-full last column
 // tile of a ragged-row GEMM, and launches of few tiles
 typedef Cfg<256, 128, 3, 3, 1> TileNarrow;
-// few output rows (the router's weight gradient has M <= 64 of them), and the fused SwiGLU on 128-row tiles (plan::row_tile)
+// few output rows (the router's weight gradient over many tokens has M <= 64 of them), the fused SwiGLU on 128-row tiles
+// (plan::row_tile), and the last rows of an expert beside the full tile
 typedef Cfg<128, 256, 3, 3, 1> TileShort;
 // a contraction of a single K-tile (the router's input gradient contracts over the M <= 64 experts) is all prologue
 // and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's; also the other
@@ -897,8 +898,10 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
   }
   if (epi != kEpiStore) return SPES_EINVAL;
   if (a_kcontig && b_kcontig)
-    return g.Ndim <= TileNarrow::BN ? launch<kGroupedK, kEpiStore, true, true, TileNarrow>(g, s)
-                                    : launch<kGroupedK, kEpiStore, true, true>(g, s);
+    // router scores: 256-row tiles read the weights least often, but up to some thousand tokens leave most CUs idle for the
+    // time of one tall tile: 200 / 1531 / 4096 tokens 12.0 / 9.0 / 14.3 us, with 64-row ones 7.1 / 5.1 / 8.7; 16384 18.8 against 20.2
+    return g.Mdim <= 8192 ? launch<kGroupedK, kEpiStore, true, true, Rows64Narrow>(g, s)
+                          : launch<kGroupedK, kEpiStore, true, true, TileNarrow>(g, s);
   if (a_kcontig && !b_kcontig)
     return (g.kchunk <= TileSmall::BK && g.n_groups == 1) ? launch<kGroupedK, kEpiStore, true, false, TileSmall>(g, s)
                                                           : launch<kGroupedK, kEpiStore, true, false>(g, s);
@@ -909,6 +912,9 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
       if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
       return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
     }
+    // router weight gradient: 1531 / 3777 / 4096 tokens 7.2 / 9.2 / 12.4 us on the wider tile, 5.4 / 8.4 / 10.8 on the small one; 16384
+    // 23.6 against 23.1, 32768 87 against 90
+    if (g.Mdim <= TileShort::BM && g.Kdim <= 16384) return launch<kGroupedK, kEpiStore, false, false, TileSmall>(g, s);
     if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);
     return launch<kGroupedK, kEpiStore, false, false>(g, s);
   }
