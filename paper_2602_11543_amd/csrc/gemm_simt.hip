@@ -25,8 +25,8 @@ __device__ __forceinline__ float ld(const void* base, long idx) {
 
 // SETS (kGroupedK only): several contractions over the same groups in one launch, each with its own operands and result.
 // A template parameter, because operands chosen at run time slow every contraction that has none of this: the fp32
-// warm-up of 8 experts of 1024 x 4096 (its Gram matrix runs here) took 939 us with the choice in all kernels, 841 with
-// kernels of their own (886 before there were sets).
+// warm-up of 8 experts of 1024 x 4096 with its Gram matrix from this kernel took 939 us with the choice in all kernels, 841
+// with kernels of their own (886 before there were sets).
 template <typename TA, typename TB, int MODE, int EPI, bool SETS, int TR>
 __global__ __launch_bounds__(256) void gemm_simt_kernel(const GemmArgs g) {
   constexpr bool DUAL = (EPI == kEpiSwiglu);
