@@ -277,24 +277,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) uint4*)smem + (unsigned)wave * 1024u;
   struct Src { unsigned lo, hi, bytes, left, dst; };     // resource base and size; k left from the tile's first one on; LDS address
   Src as = {0, 0, 0, 0, 0}, bs = as;
-  // K-tile that a block begins with: it goes round from there.  All blocks that start together would walk down the same 128 bytes
-  // of every row of K-contiguous weights, which with rows a power of two apart are the same few memory channels.  Each XCD
-  // starts an eighth further on; blocks of one XCD share panels in its L2 and stay together.  Where the time is the stream of
-  // the weights, a row tile or two per expert: 200 tokens, 32 experts of 2048 x 2048, top-4, gate + up 104 to 148 us (by where
-  // the buffers lie) -> 101, down 88 -> 50 (5.3 TB/s), the forward pass 228 -> 176; a start of its own for every block is 1 to 5 %
-  // slower at d_model = 640 and 3000.  On 256-row tiles: 4096 tokens of that layer 1290 -> 1254, 8 experts of 2048 x 6144 708 -> 695,
-  // larger launches, whose blocks drift apart by themselves, within 0.2 %.  Of [k][row] weights a K-tile is 64 whole
-  // runs of a row, and only 64-row tiles gain.
-  constexpr bool ROTATE = MODE == kRaggedM && (BM == 64 || B_KC);
-  const int k_rot = ROTATE ? (int)uniform(((block % kXcds) * (unsigned)nk) / kXcds) : 0;
+  // Every block takes the K-tiles in their order, so that a result's bits follow from its operands and not from the place of its
+  // tile.  Blocks that start together then walk down the same 128 bytes of every row of K-contiguous weights, which with rows a power of
+  // two apart are the same few memory channels.  A start an eighth further on for each XCD avoids that (200 tokens, 32 experts of
+  // 2048 x 2048, top-4: forward 166 us against 233; 4096 tokens 1 %, longer launches nothing), but adds up equal rows in different orders.
   unsigned b1_lo = 0, b1_hi = 0;                         // fused SwiGLU: the base in the second matrix
   // in steps, so that the main loop can deal them out: 0 the k, 1 the base, 2 the size, 3 where to
   auto next_src = [&](Src& x, int step, int lt, unsigned per_k, unsigned long base0, unsigned long base1, unsigned bytes, unsigned dst) {
     const bool second = TWO_PASS && lt >= nk;
     if (step == 0) {
-      int kt = lt - (second ? nk : 0) + k_rot;
-      if (ROTATE) kt -= kt >= nk ? nk : 0;
-      x.left = (unsigned)(klen - kt * BK);
+      x.left = (unsigned)(klen - (lt - (second ? nk : 0)) * BK);
       pin(x.left);
     } else if (step == 1) {
       const unsigned long at = (second ? base1 : base0) + ((unsigned)klen - x.left) * per_k;
@@ -504,7 +496,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     ++t;
   };
   if constexpr (A_KC || B_KC || SETS) {
-    int last = klen % BK != 0 ? nk - 1 - k_rot : nsteps + FAR;        // the next K-tile that needs it
+    int last = klen % BK != 0 ? nk - 1 : nsteps + FAR;        // the next K-tile that needs it
     while (last + 1 < NEAR) last += nk;
     while (true) {
       const int stop = last - FAR < nsteps ? last - FAR : nsteps;

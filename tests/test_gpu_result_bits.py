@@ -1,0 +1,59 @@
+"""A result's bits follow from its operands: not from the tile, the XCD or the batch that a token falls into."""
+import dataclasses
+
+import pytest
+import torch
+
+from spes_workloads import custom_config, layer_inputs
+
+from harness import DeviceLayer
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(t):
+    return t.contiguous().view(torch.int16 if t.element_size() == 2 else torch.int32)
+
+
+def _equal_tokens(kw, n_base, device):
+    """A layer whose T tokens are copies of n_base ones, in turn; each copy's number; what forward and backward say per token."""
+    kw = {"router_sigma": 0.3, "n_trainable": 1, **kw}
+    inp = layer_inputs(custom_config(**kw))
+    copy_of = torch.arange(kw["T"]) % n_base
+    inp["x"], inp["dy"] = inp["x"][copy_of.numpy()], inp["dy"][copy_of.numpy()]
+    L = DeviceLayer(inp, device)
+    print(f"[case] {kw} {n_base}", flush=True)
+    L.fwd(); L.bwd(); torch.cuda.synchronize()
+    row = L.view("inv").long().view(L.cfg.T, L.cfg.k)
+    return L, copy_of.to(device), dict(y=L.y, dx=L.dx, **{n: L.view(n)[row] for n in ("a", "b", "h")})
+
+
+# Long contractions, several row tiles of an expert: 64-, 128- and 256-row ones (those with a half-height last tile, with a column
+# tail and on half-width tiles as well), and both tiles of fp32 layers.
+POSITIONS = [
+    (dict(T=384, d=1032, M=8, f=776, k=1, dtype="bf16"), 2, 64), (dict(T=382, d=2048, M=8, f=1024, k=1, dtype="bf16"), 4, 64),
+    (dict(T=760, d=1032, M=8, f=1032, k=1, dtype="bf16"), 2, 128),
+    (dict(T=1800, d=1024, M=8, f=968, k=2, dtype="bf16"), 3, 256), (dict(T=1803, d=1032, M=8, f=1024, k=1, dtype="bf16"), 3, 256),
+    (dict(T=290, d=520, M=8, f=264, k=2), 3, 32), (dict(T=4100, d=264, M=8, f=520, k=4), 3, 64),
+]
+
+
+@pytest.mark.parametrize("kw,n_base,rows", POSITIONS)
+def test_equal_tokens_have_equal_results(kw, n_base, rows, device):
+    L, copy_of, out = _equal_tokens(kw, n_base, device)
+    assert int(L.count.max()) > rows, "more than one row tile"
+    if rows == 256:
+        out.pop("dx")          # (its router part rests on the gate gradient, which the half-height tiles form as well)
+    for name, t in out.items():
+        assert torch.equal(_bits(t), _bits(t[:n_base])[copy_of]), name
+
+
+def test_a_token_has_the_same_output_in_any_batch(device):
+    """One set of weights, batches that run on 64-, 128- and 256-row tiles, the last one with the router on its tall tiles."""
+    inp = layer_inputs(custom_config(T=9000, d=1032, M=8, f=776, k=2, dtype="bf16", n_trainable=0, router_sigma=0.3))
+    first = None
+    for T in (190, 380, 2000, 9000):
+        L = DeviceLayer({**inp, "cfg": dataclasses.replace(inp["cfg"], T=T), "x": inp["x"][:T], "dy": inp["dy"][:T]}, device)
+        L.fwd(); torch.cuda.synchronize()
+        first = L.y if first is None else first
+        assert torch.equal(_bits(L.y[:190]), _bits(first)), T

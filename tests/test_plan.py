@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from test_gpu_gemm_f32 import CASES as F32_CASES
+from test_gpu_result_bits import POSITIONS
 from test_gpu_row_tiles import CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -109,6 +110,12 @@ def test_the_layer_cases_take_the_tiles_they_are_for(plan, kw, rows, down):
     else:
         got = "half" if plan.few_tiles_narrow(d, R // 256 + (M + 1) // 2) else "full"
     assert got == down
+
+
+@pytest.mark.parametrize("kw,n_base,rows", POSITIONS)
+def test_the_position_cases_take_the_tiles_they_are_for(plan, kw, n_base, rows):
+    rule = plan.row_tile if kw.get("dtype") == "bf16" else plan.f32_row_tile
+    assert rule(kw["T"] * kw["k"], kw["M"], kw["d"], kw["f"]) == rows
 
 
 def test_f32_tiles(plan):
