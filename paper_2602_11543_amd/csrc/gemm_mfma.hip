@@ -55,7 +55,6 @@ struct Cfg {
   static constexpr int TM = BM / 32, TN = BN / 32;          // 16 x 16 MFMA tiles per wavefront along m, n
   static constexpr int TS = BM / 64;                        // 32-row slabs of a wavefront's sub-tile (epilogues)
   static constexpr int NA = BM / 32, NB = BN / 32;          // 1 KB loads per wavefront and K-tile
-  static constexpr int KRA = 2048 / BM, KRB = 2048 / BN;    // k-rows the four wavefronts load at a time, K-strided operand
   static constexpr int A_VEC = BM * 8, B_VEC = BN * 8;      // 16-byte units of a slot
   static constexpr int LDS_VEC = NSA * A_VEC + NSB * B_VEC;
 };
@@ -215,14 +214,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const int kc_chunk = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
   // A K-strided operand keeps its memory order, [k][row] without padding; the chunks of a k-row are permuted by twice the
   // low two bits of k, so that the four k-rows of 32 bytes that one group of lanes reads with the transposing read cover all banks.
+  // The four wavefronts' loads i stand side by side; with k-rows from the index table a wavefront's loads stand one behind the
+  // other, so that its sixteen k-rows are sixteen entries of the table in a row.  Either way k-row r of a slot is the K-tile's k = r: the
+  // sums have one order on every tile, and an expert's gradients do not change with the tile that the number of trainable
+  // experts decides.
   constexpr int ACH = BM / 8, BCH = BN / 8;       // 16-byte chunks per k-row
-  const int a_krow = wave * (512 / BM) + lane / ACH, b_krow = wave * (512 / BN) + lane / BCH;
-  const unsigned a_col = (unsigned)((m0 + (((lane % ACH) ^ (2 * (a_krow & 3))) * 8)) * 2);
-  const unsigned b_col = (unsigned)((n0 + (((lane % BCH) ^ (2 * (b_krow & 3))) * 8)) * 2);
+  constexpr unsigned LOAD_STEP = SETS ? 1024u : 4096u;       // bytes in LDS from one load of a wavefront to its next
+  auto ks_k = [&](int i, int ch, int n) { return SETS ? wave * 16 + i * (16 / n) + lane / ch : wave * (64 / ch) + lane / ch + i * (64 / n); };
+  auto ks_col = [&](int i, int ch, int n, long first) { return (unsigned)((first + (((lane % ch) ^ (2 * (ks_k(i, ch, n) & 3))) * 8)) * 2); };
   auto ks_off = [](unsigned long o) { return o < kOutOfRange ? (unsigned)o : kOutOfRange; };   // k-rows beyond a short, wide operand
-  // k of the k-row that load i of a K-strided operand brings to k-row krow + i*KR of its slot: the same, or, with k-rows from the
-  // index table, in an order (of both operands) in which a wavefront's sixteen are sixteen entries of the table in a row
-  auto ks_k = [](int krow, int i, int kr) { return SETS ? krow * (BK / kr) + i : krow + i * kr; };
   unsigned aoff[C::NA], boff[C::NB];
   if (A_KC) {
     int m_row[C::NA];
@@ -236,7 +236,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     for (int i = 0; i < C::NA; ++i) aoff[i] = (unsigned)((m_row[i] * g.a_ms + kc_chunk * 8) * 2);
   } else {
 #pragma unroll
-    for (int i = 0; i < C::NA; ++i) aoff[i] = ks_off(ks_k(a_krow, i, C::KRA) * a_ks * 2 + a_col);
+    for (int i = 0; i < C::NA; ++i) aoff[i] = ks_off(ks_k(i, ACH, C::NA) * a_ks * 2 + ks_col(i, ACH, C::NA, m0));
   }
   // fused SwiGLU: load i brings rows of the gate matrix (B[0]) or of the up matrix (B[1]); tile row nl -> wave column, then
   // (BN/4) gate columns followed by the matching (BN/4) up columns
@@ -249,7 +249,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       const long col = (EPI == kEpiSwiglu) ? n0 + (nl / SW_W) * SW_H + (nl % SW_H) : n0 + nl;
       boff[i] = (unsigned)((col * g.b_ns + kc_chunk * 8) * 2);
     } else {
-      boff[i] = ks_off(ks_k(b_krow, i, C::KRB) * b_ks * 2 + b_col);
+      boff[i] = ks_off(ks_k(i, BCH, C::NB) * b_ks * 2 + ks_col(i, BCH, C::NB, n0));
     }
   }
 
@@ -274,7 +274,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   // ---- the K-tiles being loaded (numbers la, lb; the tiles of all passes in a row) ----
   constexpr int NA = C::NA, NB = C::NB, NP = NA + NB;
   constexpr bool TWO_PASS = MODE == kRaggedM && EPI == kEpiStore && !B_KC;      // the one launch with two operand pairs
-  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) uint4*)smem + (unsigned)wave * 1024u;
+  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) uint4*)smem + (unsigned)wave * (SETS ? NA * 1024u : 1024u);
   struct Src { unsigned lo, hi, bytes, left, dst; };     // resource base and size; k left from the tile's first one on; LDS address
   Src as = {0, 0, 0, 0, 0}, bs = as;
   // Every block takes the K-tiles in their order, so that a result's bits follow from its operands and not from the place of its
@@ -331,25 +331,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   };
   auto take_kidx = [&](int j) {
     if (SETS) {
-      constexpr int CHK = a_gather ? ACH : BCH, N = a_gather ? NA : NB;
-      int row = kidx[j];
+      constexpr int CHK = a_gather ? ACH : BCH, RPL = 64 / CHK;       // k-rows per load
+      int row = kidx[j * RPL];
 #pragma unroll
-      for (int h = 1; h < 64 / CHK; ++h) row = lane / CHK == h ? kidx[h * N + j] : row;
-      if (a_gather) aoff[j] = (unsigned)row * (unsigned)(a_ks * 2) + a_col;
-      if (b_gather) boff[j] = (unsigned)row * (unsigned)(b_ks * 2) + b_col;
+      for (int h = 1; h < RPL; ++h) row = lane / CHK == h ? kidx[j * RPL + h] : row;
+      if (a_gather) aoff[j] = (unsigned)row * (unsigned)(a_ks * 2) + ks_col(j, ACH, NA, m0);
+      if (b_gather) boff[j] = (unsigned)row * (unsigned)(b_ks * 2) + ks_col(j, BCH, NB, n0);
     }
   };
   // load p of a K-tile, B first, in two steps; `masked`: the tile may reach beyond the contraction range of K-contiguous operands
-  auto aim = [&](int p) { set_lds_dest(p < NB ? bs.dst + (unsigned)p * 4096u : as.dst + (unsigned)(p - NB) * 4096u); };
+  auto aim = [&](int p) { set_lds_dest(p < NB ? bs.dst + (unsigned)p * LOAD_STEP : as.dst + (unsigned)(p - NB) * LOAD_STEP); };
   auto load = [&](int p, bool masked) {
     if (p < NB) {
-      const int kb = B_KC ? kc_chunk * 8 : ks_k(b_krow, p, C::KRB);
+      const int kb = B_KC ? kc_chunk * 8 : ks_k(p, BCH, NB);
       const unsigned off = (B_KC || b_gather) && masked && kb >= (int)bs.left ? kOutOfRange : boff[p];
       // (the load -> matrix assignment of the fused SwiGLU is the same for every thread)
       const bool up = EPI == kEpiSwiglu && ((32 * p) % SW_W) / SW_H != 0;
       load_to_lds(rsrc_t{up ? b1_lo : bs.lo, up ? b1_hi : bs.hi, bs.bytes, 0x00020000u}, off);
     } else {
-      const int ka = A_KC ? kc_chunk * 8 : ks_k(a_krow, p - NB, C::KRA);
+      const int ka = A_KC ? kc_chunk * 8 : ks_k(p - NB, ACH, NA);
       const unsigned off = (A_KC || a_gather) && masked && ka >= (int)as.left ? kOutOfRange : aoff[p - NB];
       load_to_lds(rsrc_t{as.lo, as.hi, as.bytes, 0x00020000u}, off);
     }

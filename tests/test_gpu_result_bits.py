@@ -28,13 +28,14 @@ def _equal_tokens(kw, n_base, device):
     return L, copy_of.to(device), dict(y=L.y, dx=L.dx, **{n: L.view(n)[row] for n in ("a", "b", "h")})
 
 
-# Long contractions, several row tiles of an expert: 64-, 128- and 256-row ones (those with a half-height last tile, with a column
+# Long contractions and experts with several row tiles: 64-, 128- and 256-row ones (those with a half-height last tile, with a column
 # tail and on half-width tiles as well), and both tiles of fp32 layers.
+SKEWED = dict(bias="normal", bias_scale=2.0)
 POSITIONS = [
-    (dict(T=384, d=1032, M=8, f=776, k=1, dtype="bf16"), 2, 64), (dict(T=382, d=2048, M=8, f=1024, k=1, dtype="bf16"), 4, 64),
-    (dict(T=760, d=1032, M=8, f=1032, k=1, dtype="bf16"), 2, 128),
-    (dict(T=1800, d=1024, M=8, f=968, k=2, dtype="bf16"), 3, 256), (dict(T=1803, d=1032, M=8, f=1024, k=1, dtype="bf16"), 3, 256),
-    (dict(T=290, d=520, M=8, f=264, k=2), 3, 32), (dict(T=4100, d=264, M=8, f=520, k=4), 3, 64),
+    (dict(T=384, d=1032, M=8, f=776, k=1, dtype="bf16", **SKEWED), 96, 64), (dict(T=192, d=2048, M=8, f=1024, k=2, dtype="bf16", **SKEWED), 64, 64),
+    (dict(T=760, d=1032, M=8, f=392, k=1, dtype="bf16", **SKEWED), 190, 128),
+    (dict(T=1800, d=1024, M=8, f=968, k=2, dtype="bf16"), 450, 256), (dict(T=1803, d=1032, M=8, f=1024, k=1, dtype="bf16", **SKEWED), 401, 256),
+    (dict(T=290, d=520, M=8, f=264, k=2), 70, 32), (dict(T=4100, d=264, M=8, f=520, k=4), 1000, 64),
 ]
 
 
@@ -57,3 +58,25 @@ def test_a_token_has_the_same_output_in_any_batch(device):
         L.fwd(); torch.cuda.synchronize()
         first = L.y if first is None else first
         assert torch.equal(_bits(L.y[:190]), _bits(first)), T
+
+
+# trainable experts on either side of the line between two tiles of the weight gradients
+MASKS = [(dict(T=1032, d=512, M=16, f=512, k=8, dtype="bf16"), (10, 11))]
+
+
+@pytest.mark.parametrize("kw,numbers", MASKS)
+def test_weight_gradients_under_any_mask(kw, numbers, device):
+    """Expert e's gradients have the same bits whichever others are trainable."""
+    few, more = numbers
+    L = DeviceLayer(layer_inputs(custom_config(router_sigma=0.3, n_trainable=few, **kw)), device)
+    print(f"[case] {kw} {numbers}", flush=True)
+    L.fwd()
+    got = []
+    for n in (few, more, 1):
+        L.set_mask([int(e < n) for e in range(kw["M"])])
+        L.bwd(); torch.cuda.synchronize()
+        got.append([t[:n] for t in (L.d_w_gate, L.d_w_up, L.d_w_down)] + [L.dx.clone(), L.d_w_router.clone()])
+    for other in got[1:]:
+        for i, (a, b) in enumerate(zip(got[0], other)):
+            n = min(len(a), len(b))
+            assert torch.equal(_bits(a[:n]), _bits(b[:n])), i

@@ -6,7 +6,7 @@ import subprocess
 import pytest
 
 from test_gpu_gemm_f32 import CASES as F32_CASES
-from test_gpu_result_bits import POSITIONS
+from test_gpu_result_bits import MASKS, POSITIONS
 from test_gpu_row_tiles import CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -116,6 +116,13 @@ def test_the_layer_cases_take_the_tiles_they_are_for(plan, kw, rows, down):
 def test_the_position_cases_take_the_tiles_they_are_for(plan, kw, n_base, rows):
     rule = plan.row_tile if kw.get("dtype") == "bf16" else plan.f32_row_tile
     assert rule(kw["T"] * kw["k"], kw["M"], kw["d"], kw["f"]) == rows
+
+
+@pytest.mark.parametrize("kw,numbers", MASKS)
+def test_the_mask_cases_lie_on_either_side_of_the_line(plan, kw, numbers):
+    T, d, M, f, k = (kw[n] for n in "TdMfk")
+    tiles = lambda n, side: 3 * n * -(-d // side) * -(-f // side)
+    assert [plan.wgrad_small_tiles(tiles(n, 256), tiles(n, 128), -(-T * k // M), T) for n in numbers] == [1, 0]
 
 
 def test_f32_tiles(plan):
