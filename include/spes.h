@@ -27,6 +27,8 @@
  *  - dtype selects the storage type of parameters and activations (fp32, or
  *    bf16 with round-to-nearest-even on every store); every accumulation is fp32.
  *    Router logits, gates and all weight gradients are fp32 in both modes.
+ *  - Results are reproducible bit for bit.  Within a call, rows with equal operands
+ *    get equal bits wherever they stand.
  */
 #ifndef SPES_H_
 #define SPES_H_

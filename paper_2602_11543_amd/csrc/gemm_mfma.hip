@@ -687,7 +687,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
             const float ar = __uint_as_float((e & 1) ? (ap[e >> 1] & 0xffff0000u) : (ap[e >> 1] << 16));
             const float br = __uint_as_float((e & 1) ? (bp[e >> 1] & 0xffff0000u) : (bp[e >> 1] << 16));
             const float dsl = sg + sl * (1.f - sg);                   // SiLU'(a)
-            dl[e] = dsl * (a[e] - ar) * br + sl * (b[e] - br);
+            // (the second product is the one that is rounded: left to the compiler, that changed with the loop around it)
+            dl[e] = fmaf(dsl * (a[e] - ar), br, sl * (b[e] - br));
           }
           // the saved values are next read by the backward pass: streaming stores (h, which the next GEMM reads, stays plain)
           store_stream(reinterpret_cast<uint4*>(cat + ci), make_uint4(ap[0], ap[1], ap[2], ap[3]));

@@ -1,10 +1,12 @@
 """A result's bits follow from its operands: not from the tile, the XCD or the batch that a token falls into."""
 import dataclasses
 
+import numpy as np
 import pytest
 import torch
 
-from spes_workloads import custom_config, layer_inputs
+import paper_2602_11543_amd as S
+from spes_workloads import bf16_round, custom_config, layer_inputs
 
 from harness import DeviceLayer
 
@@ -13,6 +15,13 @@ pytestmark = pytest.mark.gpu
 
 def _bits(t):
     return t.contiguous().view(torch.int16 if t.element_size() == 2 else torch.int32)
+
+
+def _correction(L):
+    """What bf16 a and b miss of h: the region ahead of h."""
+    at, h = S.spes_moe_ctx_describe(L.shape)["h"], L.view("h")
+    size = -(-h.numel() * 2 // 256) * 256
+    return L.ctx[at - size:][:h.numel() * 2].view(torch.bfloat16).view(h.shape)
 
 
 def _equal_tokens(kw, n_base, device):
@@ -25,7 +34,10 @@ def _equal_tokens(kw, n_base, device):
     print(f"[case] {kw} {n_base}", flush=True)
     L.fwd(); L.bwd(); torch.cuda.synchronize()
     row = L.view("inv").long().view(L.cfg.T, L.cfg.k)
-    return L, copy_of.to(device), dict(y=L.y, dx=L.dx, **{n: L.view(n)[row] for n in ("a", "b", "h")})
+    out = dict(y=L.y, dx=L.dx, **{n: L.view(n) for n in ("dgate", "dlogits")}, **{n: L.view(n)[row] for n in ("a", "b", "h")})
+    if L.cfg.dtype == "bf16":
+        out["correction"] = _correction(L)[row]
+    return L, copy_of.to(device), out
 
 
 # Long contractions and experts with several row tiles: 64-, 128- and 256-row ones (those with a half-height last tile, with a column
@@ -44,7 +56,7 @@ def test_equal_tokens_have_equal_results(kw, n_base, rows, device):
     L, copy_of, out = _equal_tokens(kw, n_base, device)
     assert int(L.count.max()) > rows, "more than one row tile"
     if rows == 256:
-        out.pop("dx")          # (its router part rests on the gate gradient, which the half-height tiles form as well)
+        assert any(n > 256 and 0 < n % 256 <= 128 for n in L.count.tolist()), "a half-height last tile"
     for name, t in out.items():
         assert torch.equal(_bits(t), _bits(t[:n_base])[copy_of]), name
 
@@ -58,6 +70,35 @@ def test_a_token_has_the_same_output_in_any_batch(device):
         L.fwd(); torch.cuda.synchronize()
         first = L.y if first is None else first
         assert torch.equal(_bits(L.y[:190]), _bits(first)), T
+
+
+def _pairs_whose_correction_shows_the_rounding(n):
+    """a in [20, 32) and b in [16, 32), 24 bits each as three times eight, whose (a - bf16 a) bf16 b + a (b - bf16 b) is another bf16 value
+    when the first product is rounded than when the second one is: the first is exact, the second has up to 40 bits."""
+    rng = np.random.default_rng(1)
+    low = 160, 128
+    digits = [np.stack([rng.integers(lo, 256, 1 << 21), rng.integers(0, 256, 1 << 21), rng.integers(0, 256, 1 << 21)]) for lo in low]
+    a, b = (np.ldexp((d[0] * 65536 + d[1] * 256 + d[2]).astype(np.float64), -19) for d in digits)
+    ar, br = bf16_round(a.astype(np.float32)).astype(np.float64), bf16_round(b.astype(np.float32)).astype(np.float64)
+    to_bf16 = lambda v: bf16_round(v.astype(np.float32))
+    second, first = to_bf16((a - ar) * br + (a * (b - br)).astype(np.float32).astype(np.float64)), to_bf16((a - ar) * br + a * (b - br))
+    pick = np.nonzero(first != second)[0][:n]
+    assert len(pick) == n
+    return [d[:, pick] for d in digits], second[pick]
+
+
+@pytest.mark.parametrize("T", [40, 90, 300])        # 64-row, 128-row and 256-row tiles, the last with a half-height one
+def test_the_correction_of_h_rounds_the_second_product(T, device):
+    """Where the gate is saturated (sigmoid and its derivative 1 and 0) one rounding is left, and it is the same on every tile."""
+    f = 64
+    (ga, gb), want = _pairs_whose_correction_shows_the_rounding(f)
+    L = DeviceLayer(layer_inputs(custom_config(T=T, d=904, M=1, f=f, k=1, n_trainable=0, dtype="bf16")), device)
+    L.x.zero_(); L.w_gate.zero_(); L.w_up.zero_()
+    for i in range(3):
+        L.x[:, i] = 2.0 ** (-8 * i)
+        L.w_gate[0, :, i], L.w_up[0, :, i] = (torch.from_numpy(g[i] / 8.0).to(device, torch.bfloat16) for g in (ga, gb))
+    L.fwd(); torch.cuda.synchronize()
+    assert torch.equal(_correction(L).float(), torch.from_numpy(want).to(device).expand(T, f))
 
 
 # trainable experts on either side of the line between two tiles of the weight gradients
