@@ -14,6 +14,8 @@
 // experts, top-2: gate + up 56 -> 16, down 35 -> 9.5, its dgrad 35 -> 15, dgrad gate + up 65 -> 16, weight gradients 29 -> 13, the step
 // 269 -> 90.  Steps of 2000 tokens 768 x 1024, 16 experts, top-8: 5039 -> 1604 (94 TFLOP/s of the 157 that the instruction
 // has); 300 tokens 256 x 1000, 32 experts, top-8: 590 -> 223; 64 tokens 128 x 128, 64 experts: 129 -> 57.
+#include <type_traits>
+
 #include "gemm.h"
 #include "lds_load.h"
 #include "plan.h"
@@ -32,6 +34,8 @@ struct Cfg {
   static constexpr int A_VEC = BM * WK * 8, STAGE_VEC = (BM + BN) * WK * 8;      // 16-byte units
   static_assert((BM / 32) * WN * WK == 4, "four wavefronts");
 };
+
+constexpr int kSetSlices = 4;      // slices of k of the weight gradients, on every tile
 
 template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
@@ -180,11 +184,18 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
   };
 
   // ---- main loop ----
-  f32x4 acc[2][2], total[2][2];        // [column fragment][row fragment]
+  // KS sums side by side, K-tile t into sum t % KS.  Weight gradients: the slices of the tile that shares out k, so that the two tiles,
+  // between which the number of trainable experts decides, add up in the same order.  (With one sum on the wide tile an
+  // expert's gradients changed with the mask; the four cost a step of 1200 tokens 640 x 640 248 -> 255 us, of 2000 tokens 768 x 1024,
+  // top-8, 1885 -> 1915, of 512 tokens 256 x 512 nothing.)
+  constexpr int KS = SETS ? kSetSlices / WK : 1;
+  f32x4 acc[KS][2][2], total[KS][2][2];        // [sum][column fragment][row fragment]
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int c = 0; c < KS; ++c)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) { acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f}; total[j][i] = acc[j][i]; }
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) { acc[c][j][i] = f32x4{0.f, 0.f, 0.f, 0.f}; total[c][j][i] = acc[c][j][i]; }
   const char* const lds = reinterpret_cast<const char*>(smem);
   for (int t = 0; t < NS - 1; ++t) {
     load_kidx(t);
@@ -192,7 +203,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
   }
   load_kidx(NS - 1);
   int slot = 0, fill = NS - 1;         // LDS slot of K-tile t and of the one to be loaded
-  for (int t = 0; t < nsteps; ++t) {
+  auto k_tile = [&](int t, auto sum) __attribute__((always_inline)) {
+    constexpr int c = decltype(sum)::value;
     wait_and_meet<(NS - 2) * NP>();    // K-tile t is here, and K-tile t-1, whose slot is loaded now, has been read by all
     load_tile(t + NS - 1, fill);
     load_kidx(t + NS);
@@ -233,21 +245,35 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][s], fa[i][s], acc[j][i], 0, 0, 0);
-    if ((t & 3) == 3) {                // 128 terms
+        for (int i = 0; i < 2; ++i) acc[c][j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][s], fa[i][s], acc[c][j][i], 0, 0, 0);
+    if ((t / KS & 3) == 3) {           // 128 terms
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) { total[j][i] += acc[j][i]; acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        for (int i = 0; i < 2; ++i) { total[c][j][i] += acc[c][j][i]; acc[c][j][i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
     }
     slot = slot + 1 == NS ? 0 : slot + 1;
     fill = fill + 1 == NS ? 0 : fill + 1;
+  };
+  for (int t = 0; t < nsteps; t += KS) {
+    k_tile(t, std::integral_constant<int, 0>{});
+    if constexpr (KS > 1) {
+      static_assert(KS == 4, "four sums");
+      if (t + 1 < nsteps) k_tile(t + 1, std::integral_constant<int, 1>{});
+      if (t + 2 < nsteps) k_tile(t + 2, std::integral_constant<int, 2>{});
+      if (t + 3 < nsteps) k_tile(t + 3, std::integral_constant<int, 3>{});
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no load may still write LDS: the sums use it, or the next block
+  f32x4 result[2][2];
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) total[j][i] += acc[j][i];
+    for (int i = 0; i < 2; ++i) {
+      result[j][i] = total[0][j][i] + acc[0][j][i];
+#pragma unroll
+      for (int c = 1; c < KS; ++c) result[j][i] += total[c][j][i] + acc[c][j][i];
+    }
 
   // ---- partial sums of the slices, added in order; wavefront wk of a sub-tile goes on with row fragment wk ----
   if (WK > 1) {
@@ -256,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) red[((wave * 2 + i) * 2 + j) * 64 + lane] = total[j][i];
+      for (int i = 0; i < 2; ++i) red[((wave * 2 + i) * 2 + j) * 64 + lane] = result[j][i];
     __syncthreads();
     if (wk >= 2) return;
 #pragma unroll
@@ -264,7 +290,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
       f32x4 sum = red[((((wave - wk) * 2) + wk) * 2 + j) * 64 + lane];
 #pragma unroll
       for (int w = 1; w < WK; ++w) sum += red[(((wave - wk + w) * 2 + wk) * 2 + j) * 64 + lane];
-      total[j][0] = sum;
+      result[j][0] = sum;
     }
   }
 
@@ -277,7 +303,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
     const int i = WK > 1 ? wk : u;
     const long m = m0 + wm * 32 + (A_KC ? 16 * i + l16 : 2 * l16 + i);
     const bool m_in = m < m_end;
-    const f32x4 v0 = total[0][u], v1 = total[1][u];
+    const f32x4 v0 = result[0][u], v1 = result[1][u];
     if (EPI == kEpiSwiglu) {
       const int n = nw + 4 * q;
       if (m_in && n < Ndim) {

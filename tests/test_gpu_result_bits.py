@@ -102,7 +102,8 @@ def test_the_correction_of_h_rounds_the_second_product(T, device):
 
 
 # trainable experts on either side of the line between two tiles of the weight gradients
-MASKS = [(dict(T=1032, d=512, M=16, f=512, k=8, dtype="bf16"), (10, 11))]
+MASKS = [(dict(T=1032, d=512, M=16, f=512, k=8, dtype="bf16"), (10, 11)),
+         (dict(T=3001, d=136, M=32, f=120, k=8), (14, 15)), (dict(T=150, d=128, M=32, f=128, k=4), (21, 22))]
 
 
 @pytest.mark.parametrize("kw,numbers", MASKS)

@@ -122,6 +122,9 @@ def test_the_position_cases_take_the_tiles_they_are_for(plan, kw, n_base, rows):
 def test_the_mask_cases_lie_on_either_side_of_the_line(plan, kw, numbers):
     T, d, M, f, k = (kw[n] for n in "TdMfk")
     tiles = lambda n, side: 3 * n * -(-d // side) * -(-f // side)
+    if "dtype" not in kw:        # fp32: 64 x 64 tiles from 256 of them on
+        assert [tiles(n, 64) >= 256 for n in numbers] == [False, True]
+        return
     assert [plan.wgrad_small_tiles(tiles(n, 256), tiles(n, 128), -(-T * k // M), T) for n in numbers] == [1, 0]
 
 
