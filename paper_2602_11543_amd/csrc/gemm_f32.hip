@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
   const long a_ks = SETS ? st.a_ks : g.a_ks, b_ks = SETS ? st.b_ks : g.b_ks, c_ms = SETS ? st.c_ms : g.c_ms;
   const bool a_gather = SETS && st.a_gather, b_gather = SETS && !a_gather;      // one of the two
   const int col_tiles = cdiv(Ndim, BNO);
-  const int n0 = (SETS ? blockIdx.x % col_tiles : blockIdx.x) * BNO;
+  const int n0 = (MODE == kRaggedM ? blockIdx.x : blockIdx.x % col_tiles) * BNO;
   long m0, m_end, k_begin, k_end, b_group = 0, c_group = 0;
   bool store2 = true;
   if (MODE == kRaggedM) {
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
     b_group = (long)e * g.b_gs;
   } else {
     const int grp = SETS ? blockIdx.z / g.n_sets : blockIdx.z;
-    m0 = (long)(SETS ? blockIdx.x / col_tiles : blockIdx.y) * BM;
+    m0 = (long)(blockIdx.x / col_tiles) * BM;
     if (m0 >= Mdim) return;
     m_end = min((long)Mdim, m0 + BM);
     if (g.offset != nullptr) {
@@ -381,14 +381,13 @@ int launch_tile(const GemmArgs& g, hipStream_t s) {
   dim3 grid;
   if (MODE == kRaggedM) {
     grid = dim3(cdiv(g.Ndim, BNO), g.max_tiles, 1);
-  } else if (SETS) {
-    int rows[3], cols[3];
-    for (int i = 0; i < g.n_sets; ++i) { rows[i] = g.set[i].Mdim; cols[i] = g.set[i].Ndim; }
-    const long tiles = plan::set_grid_tiles(rows, cols, g.n_sets, C::BM, C::BN);
-    if (tiles * 256 >= (1L << 32)) return SPES_ESHAPE;   // work-items along a grid dimension
-    grid = dim3((unsigned)tiles, 1, g.n_groups * g.n_sets);
   } else {
-    grid = dim3(cdiv(g.Ndim, C::BN), cdiv(g.Mdim, C::BM), g.n_groups);
+    // all tiles of a result along x: the router scores of the most tokens have 131072 row tiles, twice what the other dimensions hold
+    int rows[3] = {g.Mdim}, cols[3] = {g.Ndim};
+    for (int i = 0; SETS && i < g.n_sets; ++i) { rows[i] = g.set[i].Mdim; cols[i] = g.set[i].Ndim; }
+    const long tiles = plan::set_grid_tiles(rows, cols, SETS ? g.n_sets : 1, C::BM, C::BN);
+    if (tiles * 256 >= (1L << 32)) return SPES_ESHAPE;   // work-items along a grid dimension
+    grid = dim3((unsigned)tiles, 1, g.n_groups * (SETS ? g.n_sets : 1));
   }
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return SPES_OK;
   hipLaunchKernelGGL((gemm_f32_kernel<MODE, EPI, A_KC, B_KC, SETS, C>), grid, dim3(256), 0, s, g);

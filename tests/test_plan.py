@@ -139,3 +139,16 @@ def test_f32_tiles(plan):
     assert plan.f32_on_matrix_cores(1, 1, lim - 8, 1) and not plan.f32_on_matrix_cores(1, 1, lim, 1)
     assert not plan.f32_on_matrix_cores(lim // 8 + 1, 1, 8, 8) and not plan.f32_on_matrix_cores(1, lim // 8 + 1, 8, 8)
     assert not plan.f32_on_matrix_cores(1, 1, 1 << 15, 1 << 15)
+
+
+def test_grids_of_the_longest_fp32_layers(plan):
+    """T * top_k up to 2^22 - 4224.  A launch has 2^32 work-items along x and 65535 blocks along y and z."""
+    rows, one = 2**22 - 4224, ctypes.c_int * 3
+    for M in (1, 4, 32, 33, 64):
+        # router scores, 64 x 64 and 32 x 32 tiles, the 131000 row tiles of the latter along x
+        for side in (64, 32):
+            tiles = plan.set_grid_tiles(one(rows), one(M), 1, side, side)
+            assert tiles == -(-rows // side) * -(-M // side) and tiles * 256 < 2**32
+        # expert GEMMs: row tiles along y
+        for d, f in ((8, 8), (128, 8), (8, 256), (248, 248)):
+            assert rows // plan.f32_row_tile(rows, M, d, f) + M + 1 <= 65535
