@@ -10,6 +10,12 @@ import paper_2602_11543_amd as S
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def _give_back_memory():
+    yield
+    torch.cuda.empty_cache()
+
+
 def _layer(T, d, M, f, n_trainable, device):
     """Top-1 layer with activations, projections and scores of order one."""
     g = torch.Generator(device=device).manual_seed(T + d + f)
@@ -33,9 +39,10 @@ def _layer(T, d, M, f, n_trainable, device):
 def _check(L):
     T, d = L["x"].shape
     M, f = L["w_gate"].shape[:2]
-    # A sum of n terms, one after the other, is off by 2^-24 sqrt(n / 6) of its size (norm over many sums); at most five such sums stand in a
-    # row (projection, down projection, its gradient, the projections' gradient, and the gate), and the SiLU's exponential and quotient
-    tol = lambda n: 2.0 ** -24 * 5 * math.sqrt(n / 6) + 1e-6
+    # A sum of n terms, one after the other, is off by 2^-24 sqrt(n / 6) of its size (norm over many sums).  The kernels add up 128 at a time
+    # and then those sums, the gate gradient partial sums of 32 columns or more; at most five such sums stand in a row (projection, down
+    # projection, its gradient, the projections' gradient, and the gate), and the SiLU's exponential and quotient
+    tol = lambda n: 2.0 ** -24 * 5 * math.sqrt((128 + n / 32) / 6) + 1e-6
     worst = {}
 
     def compare(name, got, want, n):
@@ -84,3 +91,38 @@ def _check(L):
 def test_more_row_tiles_than_a_grid_dimension_holds(T, M, device):
     """The router scores of more than 2097120 tokens have more than 65535 tiles of 32 rows."""
     _check(_layer(T, 8, M, 8, 2, device))
+
+
+# Operands of 2^30 elements and more: beyond 32-bit byte offsets every fp32 GEMM runs on the vector ALUs, on 64-, 32- or 16-row tiles
+# by the number of its blocks.  The height of the gate + up GEMM and of its gradient, of the down projection and of the other
+# input gradient, and of the weight gradients, as 16 x:
+BEYOND = [
+    (dict(T=8003, d=134184, M=3, f=8, n_trainable=2), (1, 4, 4)), (dict(T=16400, d=65480, M=5, f=8, n_trainable=5), (2, 4, 4)),      # x, dy
+    (dict(T=8003, d=8, M=3, f=134184, n_trainable=1), (4, 1, 4)), (dict(T=16400, d=8, M=5, f=65480, n_trainable=2), (4, 2, 4)),      # a, b, h
+    (dict(T=2097160, d=512, M=12, f=16, n_trainable=12), (4, 4, 2)), (dict(T=2097160, d=512, M=12, f=16, n_trainable=3), (4, 4, 1)),
+    (dict(T=70, d=32776, M=1, f=32776, n_trainable=1), (4, 4, 4)),                                                                    # weights
+]
+
+
+@pytest.mark.parametrize("kw,heights", BEYOND)
+def test_operands_beyond_32_bit_offsets(kw, heights, device):
+    _check(_layer(**kw, device=device))
+
+
+def test_similarity_beyond_32_bit_offsets(device):
+    """The Gram matrix of 64 experts of 2^24 elements, on the vector ALUs."""
+    M, n = 64, 1 << 24
+    w = torch.randn(M, n, device=device, generator=torch.Generator(device=device).manual_seed(1))
+    w[1::2] += 0.5 * w[::2]
+    sim, nbr = torch.empty(M, M, device=device), torch.empty(M, 2, dtype=torch.int32, device=device)
+    scratch = torch.empty(S.spes_warmup_scratch_bytes(M, n), dtype=torch.uint8, device=device)
+    S.spes_expert_warmup_merge(M, S.SPES_F32, 2, 0.1, w, n, [], [], [], sim, nbr, scratch)
+    torch.cuda.synchronize()
+    want = torch.zeros(M, M, dtype=torch.float64, device=device)
+    for part in w.split(1 << 20, dim=1):
+        want += part.double() @ part.double().t()
+    norm = want.diagonal().sqrt()
+    want /= norm[:, None] * norm[None, :]
+    # chunks of 2^15 terms added one after the other, then 512 of them
+    assert float((sim.double() - want).norm() / want.norm()) < 2.0 ** -24 * 2 * math.sqrt(2**15 / 6)
+    assert torch.equal(nbr[:, 0].long(), torch.arange(M, device=device) ^ 1)

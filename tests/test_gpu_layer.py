@@ -71,7 +71,8 @@ def test_layer_parity(name, device):
     dict(T=600, d=320, M=6, f=576, k=2, renorm=1, n_trainable=3, trainable="random", dtype="bf16"),
     # widths that are multiples of 256, 512 rows a head: the last 64-row case of the narrowest layers
     dict(T=1024, d=256, M=4, f=512, k=2, n_trainable=2, dtype="bf16"),
-    # fp32 path with enough 64-row tiles for the tallest of its three tile heights (the cases above use the shorter two)
+    # fp32 tiles of 32 rows whose wavefronts share out k, by twos in the gate + up GEMM and its gradient, by fours in the other two
+    # (64-row ones are in test_gpu_gemm_f32.py, the vector ALUs, which take larger operands, in test_gpu_large_f32.py)
     dict(T=2048, d=128, M=4, f=512, k=2, n_trainable=2),
 ])
 def test_layer_edge_cases(kw, device):

@@ -7,6 +7,7 @@ import pytest
 
 from test_gpu_gemm_f32 import CASES as F32_CASES
 from test_gpu_result_bits import MASKS, POSITIONS
+from test_gpu_large_f32 import BEYOND
 from test_gpu_row_tiles import CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -152,3 +153,13 @@ def test_grids_of_the_longest_fp32_layers(plan):
         # expert GEMMs: row tiles along y
         for d, f in ((8, 8), (128, 8), (8, 256), (248, 248)):
             assert rows // plan.f32_row_tile(rows, M, d, f) + M + 1 <= 65535
+
+
+@pytest.mark.parametrize("kw,heights", BEYOND)
+def test_the_cases_beyond_32_bit_offsets_take_the_tiles_they_are_for(plan, kw, heights):
+    T, d, M, f, n = (kw[k] for k in ("T", "d", "M", "f", "n_trainable"))
+    assert not plan.f32_on_matrix_cores(T, T, d, f)
+    up = lambda a, b: -(-a // b)
+    height = lambda blocks: 4 if blocks >= 512 else 2 if blocks >= 256 else 1        # of 64 x 64
+    rows = T // 64 + M + 1
+    assert (height(rows * up(f, 64)), height(rows * up(d, 64)), height(3 * n * up(d, 64) * up(f, 64))) == heights
