@@ -159,9 +159,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
         const unsigned go = a_krow + i * 4 * KRA < left ? (unsigned)kidx[i] * g_pitch + g_col : kOutOfRange;
         off = a_gather ? go : off;
       }
-      set_lds_dest(dst + (unsigned)i * 4096u);
+      const unsigned m0 = set_lds_dest(dst + (unsigned)i * 4096u);
       one_instruction();
-      load_to_lds(ra, off);
+      load_to_lds(ra, off, m0);
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -171,14 +171,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const GemmArgs g) {
         const unsigned go = a_krow + i * 4 * KRA < left ? (unsigned)kidx[i] * g_pitch + g_col : kOutOfRange;
         off = a_gather ? off : go;
       }
-      set_lds_dest(dst + C::A_VEC * 16u + (unsigned)i * 4096u);
+      const unsigned m0 = set_lds_dest(dst + C::A_VEC * 16u + (unsigned)i * 4096u);
       one_instruction();
       if (EPI == kEpiSwiglu) {
         // a wavefront's eight tile rows are all gate rows or all up rows: rows 0-15 of every 32 are gate rows
         const bool up = (wave & 2) != 0;
-        load_to_lds(rsrc_t{up ? rb1.x : rb.x, up ? rb1.y : rb.y, rb.z, rb.w}, off);
+        load_to_lds(rsrc_t{up ? rb1.x : rb.x, up ? rb1.y : rb.y, rb.z, rb.w}, off, m0);
       } else {
-        load_to_lds(rb, off);
+        load_to_lds(rb, off, m0);
       }
     }
   };

@@ -340,18 +340,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     }
   };
   // load p of a K-tile, B first, in two steps; `masked`: the tile may reach beyond the contraction range of K-contiguous operands
-  auto aim = [&](int p) { set_lds_dest(p < NB ? bs.dst + (unsigned)p * LOAD_STEP : as.dst + (unsigned)(p - NB) * LOAD_STEP); };
+  unsigned lds_dest = 0;
+  auto aim = [&](int p) { lds_dest = set_lds_dest(p < NB ? bs.dst + (unsigned)p * LOAD_STEP : as.dst + (unsigned)(p - NB) * LOAD_STEP); };
   auto load = [&](int p, bool masked) {
     if (p < NB) {
       const int kb = B_KC ? kc_chunk * 8 : ks_k(p, BCH, NB);
       const unsigned off = (B_KC || b_gather) && masked && kb >= (int)bs.left ? kOutOfRange : boff[p];
       // (the load -> matrix assignment of the fused SwiGLU is the same for every thread)
       const bool up = EPI == kEpiSwiglu && ((32 * p) % SW_W) / SW_H != 0;
-      load_to_lds(rsrc_t{up ? b1_lo : bs.lo, up ? b1_hi : bs.hi, bs.bytes, 0x00020000u}, off);
+      load_to_lds(rsrc_t{up ? b1_lo : bs.lo, up ? b1_hi : bs.hi, bs.bytes, 0x00020000u}, off, lds_dest);
     } else {
       const int ka = A_KC ? kc_chunk * 8 : ks_k(p - NB, ACH, NA);
       const unsigned off = (A_KC || a_gather) && masked && ka >= (int)as.left ? kOutOfRange : aoff[p - NB];
-      load_to_lds(rsrc_t{as.lo, as.hi, as.bytes, 0x00020000u}, off);
+      load_to_lds(rsrc_t{as.lo, as.hi, as.bytes, 0x00020000u}, off, lds_dest);
     }
   };
 
@@ -434,7 +435,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     }
   }
   load_kidx(NSG);
-  if (LATE > 0) aim(NP - LATE);
   wait_and_meet<AHEAD + NP - LATE>();
   have_kidx();
 #pragma unroll
@@ -474,13 +474,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       {
         const int at = q >= QF ? q - QF : q - QF + 2 * MF, p = at / DG;
         if (p < NP && (q >= QF || p >= NP - LATE)) {
-          if (at % DG == (DG > 1 ? DG - 2 : 0)) {
-            aim(p);
-          }
-          if (DG == 1) one_instruction();
-          if (at % DG == DG - 1) {
-            load(p, MASKED);
-          }
+          // (a gap ahead of the load, but in the same iteration)
+          const bool alone = DG == 1 || (q == 0 && at % DG == DG - 1);
+          if (alone || (at % DG == DG - 2 && q < 2 * MF - 1)) aim(p);
+          if (alone) one_instruction();
+          if (at % DG == DG - 1) load(p, MASKED);
         }
       }
       __builtin_amdgcn_sched_barrier(0);

@@ -13,11 +13,17 @@ __device__ __forceinline__ rsrc_t make_rsrc(unsigned long base, unsigned bytes) 
 constexpr unsigned kOutOfRange = 0xfffffff0u;     // at or beyond any resource: operands have less than 2^31 elements of two bytes
 // One load per wavefront of 64 x 16 bytes straight into LDS: lane l's bytes, from its own offset into the resource, land at
 // the address in M0 + 16 l.  Written as assembly because the compiler makes every LDS read that may follow such a load wait for all of them;
-// here the waits stand in the loop.  (The load has no result register, and address and resource are read when it issues.
-// The scalar write of M0 needs one instruction between it and the load that reads it.)
-__device__ __forceinline__ void set_lds_dest(unsigned lds) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds) : "memory"); }
-__device__ __forceinline__ void load_to_lds(const rsrc_t& rs, unsigned lane_off) {
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(lane_off), "s"(rs) : "memory");
+// here the waits stand in the loop.  (The load has no result register, and address and resource are read when it issues.)  M0 is handed from
+// the statement that sets it to the load as a value that lives in that register, so the compiler knows of both and keeps its own
+// uses of M0 off it.  Between the two there has to be one instruction, and none of the compiler's copies: they stand in one straight run of
+// code, and tests/test_lds_loads.py looks at every load that is built.
+__device__ __forceinline__ unsigned set_lds_dest(unsigned lds) {
+  unsigned m0;
+  asm volatile("s_mov_b32 %0, %1" : "={m0}"(m0) : "s"(lds) : "memory");
+  return m0;
+}
+__device__ __forceinline__ void load_to_lds(const rsrc_t& rs, unsigned lane_off, unsigned m0) {
+  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(lane_off), "s"(rs), "{m0}"(m0) : "memory");
 }
 __device__ __forceinline__ void one_instruction() { asm volatile("s_nop 0" ::: "memory"); }
 __device__ __forceinline__ void pin(unsigned& v) { asm volatile("" : "+s"(v)); }       // computed here and not elsewhere

@@ -317,9 +317,9 @@ __global__ __launch_bounds__(512) void warmup_mix_lds_kernel(const T* __restrict
     const long l = live ? left(run) : 0;
 #pragma unroll
     for (int it = 0; it < kMixItems; ++it) {
-      set_lds_dest(lds0 + (unsigned)(slot * kMixVecs + it * 512) * 16u);
+      const unsigned m0 = set_lds_dest(lds0 + (unsigned)(slot * kMixVecs + it * 512) * 16u);
       one_instruction();
-      load_to_lds(rs, col[it] < l ? off[it] : kOutOfRange);
+      load_to_lds(rs, col[it] < l ? off[it] : kOutOfRange, m0);
     }
   };
   // at the wait for run i: the loads of the runs behind it, and the stores of the runs since its own loads
