@@ -77,14 +77,14 @@ constexpr int kGroupMinCols = 8;   // ... used when the output has at least this
 // result type of kEpiStore: the router scores and the weight gradients are fp32, the rest has the storage type
 constexpr bool f32_out(int mode, bool a_kc, bool b_kc) { return mode == kGroupedK && !(a_kc && !b_kc); }
 
-// SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
-// and result; either operand of a set may take its k-rows through the index table k_rows (the dy rows, or the input
-// rows, of an expert's routed pairs)
 // 16-byte units of LDS that a tile uses: its operand slots, or the four wavefronts' epilogue slabs (32 padded float rows each)
 template <typename C>
 constexpr int lds_units() { return C::LDS_VEC > 32 * (C::TN * 16 + 4) ? C::LDS_VEC : 32 * (C::TN * 16 + 4); }
 
 // One tile.  block: position in the launch, or in its part with this tile shape; ragged rows: that part's row tiles in the table
+// SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
+// and result; either operand of a set may take its k-rows through the index table k_rows (the dy rows, or the input
+// rows, of an expert's routed pairs)
 // GATHER: which operand of a set (1 A, 2 B) takes its k-rows through the index table
 template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C, int GATHER = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, const unsigned block, const int mt_first, const int mt_count) {
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   }
 }
 
-// the full tile: 256 x 256 x 64, one block per CU (128 to 144 KB of LDS by operand layout, 256 accumulators per lane in AGPRs)
+// the full tile: 256 x 256 x 64, one block per CU (all 160 KB of LDS, 256 accumulators per lane in AGPRs)
 typedef Cfg<256, 256, 3, 2, 1> Tile;
 
 // narrow outputs (the router scores of many tokens: half the matrix work on padding), the half-full last column
@@ -889,8 +889,9 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
   }
   if (epi != kEpiStore) return SPES_EINVAL;
   if (a_kcontig && b_kcontig)
-    // router scores: 256-row tiles read the weights least often, but up to some thousand tokens leave most CUs idle for the
-    // time of one tall tile: 200 / 1531 / 4096 tokens 12.0 / 9.0 / 14.3 us, with 64-row ones 7.1 / 5.1 / 8.7; 16384 18.8 against 20.2
+    // router scores: 256-row tiles read the weights least often, but up to some thousand tokens leave most CUs idle for the time of one
+    // tall tile.  64-row ones relative to them over 90 shapes (512, 1536 and 4096 wide, 8, 32 and 64 experts): 0.47 to 1.00 up to
+    // 4096 tokens, 0.58 to 0.91 at 6000 and 8192; from 12000 on 0.71 to 1.28, on either side of 1 at each width
     return g.Mdim <= 8192 ? launch<kGroupedK, kEpiStore, true, true, Rows64Narrow>(g, s)
                           : launch<kGroupedK, kEpiStore, true, true, TileNarrow>(g, s);
   if (a_kcontig && !b_kcontig)
@@ -903,8 +904,8 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
       if (plan::wgrad_small_tiles(full, small, g.mean_k, g.max_k)) return launch<kGroupedK, kEpiStore, false, false, TileSmall, true>(g, s);
       return launch<kGroupedK, kEpiStore, false, false, Tile, true>(g, s);
     }
-    // router weight gradient: 1531 / 3777 / 4096 tokens 7.2 / 9.2 / 12.4 us on the wider tile, 5.4 / 8.4 / 10.8 on the small one; 16384
-    // 23.6 against 23.1, 32768 87 against 90
+    // router weight gradient: the small tile relative to the wider one over the same shapes 0.79 to 1.00 up to 16384 tokens, beyond 0.78 to
+    // 0.91 at 512 wide and 0.99 to 1.06 at 1536 and 4096
     if (g.Mdim <= TileShort::BM && g.Kdim <= 16384) return launch<kGroupedK, kEpiStore, false, false, TileSmall>(g, s);
     if (g.Mdim <= TileShort::BM) return launch<kGroupedK, kEpiStore, false, false, TileShort>(g, s);
     return launch<kGroupedK, kEpiStore, false, false>(g, s);

@@ -1,7 +1,7 @@
 // Grouped GEMM on the vector ALUs: fp32 FMA, LDS-tiled, any operand strides.
 //
-// What the matrix-core kernels do not take: fp32 operands beyond 32-bit byte offsets (plan::f32_on_matrix_cores), fp32 router
-// gradients of a number of experts that is no multiple of four, the router GEMMs of bf16 layers of an odd number of them.
+// What the matrix-core kernels do not take: fp32 operands beyond 32-bit byte offsets (plan::f32_on_matrix_cores), the router's fp32
+// weight gradient where the number of experts is no multiple of four, and in bf16 layers its scores (four) and weight gradient (eight).
 // (16*TR)x64 output tile per 256-thread block, TR x 4 outputs per thread (TR = 4, 2 or 1: the
 // launcher takes shorter tiles when the taller ones would leave most CUs without a block),
 // K advanced 32 at a time through LDS; the next K-tile is requested into registers

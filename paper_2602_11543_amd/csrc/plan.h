@@ -32,6 +32,9 @@ inline int column_tail(int ndim) {
 // Few tiles: a launch costs its number of rounds of 256 concurrent tiles, the last of them partly empty.  Half-width
 // tiles cost 0.6 of a full one each and fill the rounds better; they are taken where that arithmetic says so (a layer
 // of a few thousand tokens), never for a launch of many rounds.  est_tiles: expected number of row tiles (0: unknown).
+// Step relative to full tiles throughout, mean (range) over 2129 cells of widths that are multiples of 256: 0.89 (0.81 to 1.09) where the
+// rule takes half-width tiles for either width, 0.97 (0.82 to 1.08) where for one; half-width ones for both cost 1.09 (1.00 to 1.16)
+// where it takes none.
 inline bool few_tiles_narrow(int ndim, int est_tiles) {
   if (est_tiles <= 0 || ndim % kFullCols != 0) return false;
   const long full = (long)est_tiles * (ndim / kFullCols);
@@ -42,31 +45,31 @@ inline bool few_tiles_narrow(int ndim, int est_tiles) {
 // Rows per tile of the ragged-row GEMMs.  A 256-row tile of an expert with a few dozen rows computes padding, one block
 // per CU, while the weights it streams are the only work that is needed; 64- and 128-row tiles run two blocks per CU
 // (all but the 128-row SwiGLU one), take any width in 128-column tiles and fill the chip with fewer rows.  They feed
-// fewer MFMAs per byte read, so full tiles win again once experts fill them.  Measured, us of a whole step with
-// 256 / 128 / 64 rows, at a mean of n rows per expert, even load:
-//   32 experts of 2048 x 2048   n = 20: 563 / 537 / 502   n = 60: 592 / 573 / 589   n = 112: 617 / 653 / 694
-//   64 experts of 1408 x 1408   n = 40: 731 / 512 / 498   n = 96: 778 / 562 / 610   n = 112: 706 / 502 / 560
-//   16 experts of 4096 x 2048   n = 40: 573 / 554 / 521   n = 80: 594 / 577 / 641   n = 112: 610 / 690 / 721
-// (above 96 rows the best height changes with the width and the load; there full tiles stay, also where 128 would win).
+// fewer MFMAs per byte read, so full tiles win again once experts fill them.  The lines were drawn with an earlier main loop (operands
+// through registers, no half-height last tiles).  Us of a whole step with 256 / 128 / 64 rows, at a mean of n rows per expert, even
+// load, with the present one:
+//   32 experts of 2048 x 2048   n = 20: 605 / 609 / 590   n = 60: 557 / 568 / 597   n = 112: 629 / 711 / 794
+//   64 experts of 1408 x 1408   n = 40: 621 / 557 / 506   n = 96: 684 / 625 / 633   n = 112: 708 / 643 / 687
+//   16 experts of 4096 x 2048   n = 40: 547 / 551 / 563   n = 80: 571 / 581 / 646   n = 112: 582 / 594 / 652
 // A short contraction is mostly prologue and epilogue, which two blocks per CU overlap, and the line of 64 rows lies higher:
-//   16 experts of 768 x 2048    n = 128: 234 / 203 / 190  n = 256: 293 / 291 / 276  n = 320: 310 / 325 / 325
-//   64 experts of 512 x 352     n = 192: 239 / 182 / 173  n = 512: 316 / 275 / 278
+//   16 experts of 768 x 2048    n = 128: 207 / 196 / 178  n = 256: 262 / 249 / 247  n = 320: 287 / 275 / 289
+//   64 experts of 512 x 352     n = 192: 197 / 150 / 158  n = 512: 310 / 268 / 276
 // (the down projection contracts over d_ff: measured up to d_ff = 4 d_model) -- as long as the launch is short of blocks.
 // Many full tiles overlap nothing less by themselves, and the longer the contraction, the fewer are many:
-//   48 experts of 384 x 1536    n = 192 (720 tiles): 408 / 292 / 262    48 of 768 x 2048 (960) 474 / 500 / 542
-//   64 experts of 768 x 1024    n = 192 (640 tiles): 340 / 345 / 384    64 of 704 x 2560, n = 224 (1760) 682 / 803 / 944
+//   48 experts of 384 x 1536    n = 192 (720 tiles): 408 / 311 / 291    48 of 768 x 2048 (960) 524 / 577 / 597
+//   64 experts of 768 x 1024    n = 192 (640 tiles): 365 / 397 / 424    64 of 704 x 2560, n = 224 (1760) 781 / 902 / 1034
 // From there on 64-row tiles end at 64 rows; 128-row ones go on as far as some more tiles (48 experts of 704 x 2752,
-// n = 104, 946 tiles: 564 / 474 / 496), or wherever full tiles pay a second launch for a column tail (64 experts of
-// 640 x 1280, n = 224: 468 / 417 / 466).
+// n = 104, 946 tiles: 552 / 541 / 551), or wherever full tiles pay a second launch for a column tail (64 experts of
+// 640 x 1280, n = 224: 498 / 472 / 507).
 // Above its line of 64 rows a narrow layer takes 128 where two or three rounds of 256 concurrent full tiles would end
-// in one that is partly and at most 0.6 full: full tiles pay for the whole last round, 16 experts of 768 x 2048 at n = 512
-// (2.5 rounds, unevenly loaded) 473 / 385 / 428, 24 experts of 768 x 768 at n = 562 (1.1) 279 / 268 / 282.  A round that is
-// full, or nearly, is lost by them: n = 384 at 768 x 2048 (2.0) 324 / 336 / 341, n = 320 above (1.75), unless
-// the load spills into a third (n = 384, normal load: 364 / 323 / 334); only the shortest contractions gain under any
-// load (8 experts of 512 x 2048, n = 900, 2.0: 287 / 271 / 280).
-// The load is not known here; an uneven one moves every line.  Over 5062 measured cells (34 fixed and 1307 random
-// shapes under even, normal and Gumbel load) the choice takes 0.73 of the time of full tiles on average, is more than 2 %
-// slower than they are in 53, 26 of them under Gumbel load (at worst 21 %), and at least 10 % off the best height in 627.
+// in one that is partly and at most 0.6 full: 24 experts of 768 x 768 at n = 562 (1.1 rounds) 266 / 251 / 261.  (The half-height last
+// tiles shorten such a round by themselves: at 2.5 rounds, 16 experts of 768 x 2048, n = 512, full tiles are now ahead, 359 / 372 / 392.)
+// A round that is full, or nearly, keeps full tiles: n = 384 at 768 x 2048 (2.0) 298 / 310 / 325; only the shortest contractions gain
+// under any load (8 experts of 512 x 2048, n = 900, 2.0: 251 / 238 / 247).
+// The load is not known here; an uneven one moves every line.  Over 10622 cells of the present loop (24 fixed and 3517 random shapes
+// under even, normal and Gumbel load) the choice takes 0.84 of the time of full tiles on average, is more than 2 % slower than they are
+// in 171 (at worst 22 %), and at least 10 % off the best height in 1928.  Most of those are wide layers beyond the line of 96 rows, where
+// 128-row tiles now take 0.86 of the choice's time up to 192 rows, 0.93 up to 256 and 0.96 up to 512, and 1.06 beyond.
 inline int row_tile(long rows, int n_experts, int d_model, int d_ff) {
   if (rows <= 48L * n_experts) return kQuarterRows;
   const bool narrow = d_model <= 896 && d_ff <= 4L * d_model;
@@ -89,15 +92,17 @@ inline int rowdot_parts(int ndim, int row_tile, int est_tiles) {
 // Weight gradients, all three matrices in one launch: 128 x 128 tiles, two blocks per CU, or 256 x 256 tiles, one per CU.
 // full_tiles, small_tiles: how many of them over all sets.  mean_rows, max_rows: routed rows of an expert (the contraction) in
 // the mean and at most; the lengths themselves are known on the device only.  What decides is the rounds of blocks on 256
-// CUs, and how evenly the experts are loaded.  Backward of a layer, small tiles relative to full ones, mean (range) over
-// 1090 cells of 40 results and three load distributions:
-//   small ones in one round leave fewer CUs idle, and cover less padding: 0.96 (0.78 to 1.00) at any length
+// CUs, and how evenly the experts are loaded.  Backward of a layer, small tiles relative to full ones, mean (range of 96 %) over
+// 7235 cells of random layers under three load distributions, with and without accumulation (which differ by 0.01 on average):
+//   small ones in one round leave fewer CUs idle, and cover less padding: 0.92 (0.75 to 1.00) at any length
 //   up to 256 full tiles are one round, small ones then more than one, and they read twice the operand bytes per FLOP:
-//     1.00 (0.97 to 1.04) up to 700 rows, 1.02 (0.96 to 1.08) to 1500, 1.05 (0.98 to 1.17) from 1500 on -- where no expert can
+//     1.00 (0.92 to 1.04) up to 700 rows, 1.02 (0.97 to 1.08) to 1500, 1.04 (0.94 to 1.15) from 1500 on -- where no expert can
 //     exceed twice the mean.  A round lasts as long as the tiles of its longest expert, which small ones spread over more
-//     CUs: 0.98 (0.74 to 1.11) where an expert can
-//   257 to 320 full tiles end in a round that is nearly empty: 0.96 (0.90 to 1.04)
-//   beyond, that round fills up and the difference goes: 0.97 at 64 rows, 1.00 at 1024, 1.08 at 16384
+//     CUs: 0.98 (0.77 to 1.09) where an expert can
+//   257 to 320 full tiles end in a round that is nearly empty: 0.97 (0.82 to 1.04)
+//   beyond, that round fills up and the difference goes: 0.97 (320 to 1024 tiles) and 1.00 (more) below 200 rows, 1.00 and 1.03 to 700,
+//   1.02 and 1.05 to 1500, 1.04 and 1.12 above
+// The choice is 1 % off the better tile on average, and more than 5 % off it in 280 cells.
 inline bool wgrad_small_tiles(long full_tiles, long small_tiles, int mean_rows, int max_rows) {
   if (small_tiles <= 512) return true;
   if (full_tiles > 320) return false;
