@@ -28,6 +28,14 @@ def test_contraction_lengths(T, d, M, f, k, device):
     _full_parity(layer_inputs(custom_config(**kw)), device, "contraction lengths")
 
 
+# an expert's forward contractions begin at a K-tile of its own: 17 and 18 of them, the last one short, for up to 64 experts on 64-row
+# and on 256-row tiles
+@pytest.mark.parametrize("T,d,M,f,k", [(300, 1096, 64, 1128, 4), (3300, 1096, 33, 136, 8)])
+def test_first_k_tiles_of_many_experts(T, d, M, f, k, device):
+    kw = dict(T=T, d=d, M=M, f=f, k=k, n_trainable=2, trainable="random", dtype="bf16", router_sigma=0.02, bias="normal")
+    _full_parity(layer_inputs(custom_config(**kw)), device, "first K-tiles")
+
+
 # one expert's rows around the heights of full and half tiles; with whole columns, a column tail, and on half-width tiles
 @pytest.mark.parametrize("T", [128, 129, 256, 257, 384, 385, 641])
 @pytest.mark.parametrize("d,f", [(904, 136), (1032, 328), (1024, 256)])
