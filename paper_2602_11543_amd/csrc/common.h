@@ -109,12 +109,32 @@ __device__ __forceinline__ float dpp_move(float v) {
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
+// the value of the lane whose number is `at` / 4, another one in every lane
+__device__ __forceinline__ float lane_value_at(float v, int at) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(at, __builtin_bit_cast(int, v)));
+}
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_move<0xB1>(v);     // quad_perm [1,0,3,2]
   v += dpp_move<0x4E>(v);     // quad_perm [2,3,0,1]
   v += dpp_move<0x141>(v);    // row_half_mirror
   v += dpp_move<0x140>(v);    // row_mirror
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+// sum of each group of 8 or 16 adjacent lanes in all of its lanes: partners 8, 4, 2, 1 apart, in this order
+template <int LANES>
+__device__ __forceinline__ float lane_group_sum(float v) {
+  static_assert(LANES == 8 || LANES == 16, "rows of lanes, or halves of them");
+  if (LANES == 16) {
+    v += dpp_move<0x128>(v);    // row_ror:8; from here on the value repeats with twice the next distance
+    v += dpp_move<0x124>(v);    // row_ror:4
+    v += dpp_move<0x122>(v);    // row_ror:2
+    v += dpp_move<0x121>(v);    // row_ror:1
+  } else {
+    v += dpp_move<0x1B>(dpp_move<0x141>(v));      // row_half_mirror, then quad_perm [3,2,1,0]: the lane 4 apart
+    v += dpp_move<0x4E>(v);     // quad_perm [2,3,0,1]
+    v += dpp_move<0xB1>(v);     // quad_perm [1,0,3,2]
+  }
+  return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp_move<0xB1>(v));

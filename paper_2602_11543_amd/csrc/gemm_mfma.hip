@@ -77,9 +77,13 @@ constexpr int kGroupMinCols = 8;   // ... used when the output has at least this
 // result type of kEpiStore: the router scores and the weight gradients are fp32, the rest has the storage type
 constexpr bool f32_out(int mode, bool a_kc, bool b_kc) { return mode == kGroupedK && !(a_kc && !b_kc); }
 
-// 16-byte units of LDS that a tile uses: its operand slots, or the four wavefronts' epilogue slabs (32 padded float rows each)
+// 16-byte units of LDS that a tile uses: its operand slots, or the four wavefronts' epilogue slabs (32 padded float rows each) and
+// row dots
 template <typename C>
-constexpr int lds_units() { return C::LDS_VEC > 32 * (C::TN * 16 + 4) ? C::LDS_VEC : 32 * (C::TN * 16 + 4); }
+constexpr int lds_units() {
+  constexpr int slabs = 32 * (C::TN * 16 + 4) + C::BM / 2;
+  return C::LDS_VEC > slabs ? C::LDS_VEC : slabs;
+}
 
 // One tile.  block: position in the launch, or in its part with this tile shape; ragged rows: that part's row tiles in the table
 // SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
@@ -403,6 +407,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   };
 
   // ---- schedule: positions are gaps between the 2 MF MFMAs of a K-tile ----
+  // dSwiGLU epilogue: row groups of a wavefront, and how many of them have their a, b and correction requested ahead
+  constexpr int ECOLS = TN * 16, DS_CPR = ECOLS / 8, DS_RPI = 64 / DS_CPR, DS_UNITS = BM / 2 / DS_RPI;
+  constexpr int DS_AHEAD = DS_UNITS < 8 ? DS_UNITS : C::MINB == 1 ? 8 : 4;
+  enum { kPlainLoads, kMaskedLoads, kNextToLast, kLast };          // iterations
   constexpr int MF = TM * TN;                       // MFMAs per k-step
   constexpr int NF = TM + TN;                       // fragments per k-step
   constexpr bool WIDE = MF >= 32;          // room for a second meeting point
@@ -423,6 +431,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   constexpr int AFTER_A = (NSA - 2) * NP, AFTER_B = NA + (NSB - 2) * NP;
   constexpr int AHEAD = (AFTER_A < AFTER_B ? AFTER_A : AFTER_B);
   static_assert(AHEAD + NP < 64, "the counter of outstanding loads");
+  constexpr bool EARLY = EPI == kEpiDSwiglu;        // an epilogue that reads: its first loads before the main loop ends ...
+  constexpr int EG = 4 * MF / (DS_AHEAD * 3);       // ... and the gaps from one of them to the next
 
   // prologue: the first NSA and NSB K-tiles, in the order in which the iterations -NS .. -1 would have loaded them
   constexpr int FAR = NSA > NSB ? NSA : NSB, NEAR = NSA > NSB ? NSB : NSA, NSG = a_gather ? NSA : NSB;
@@ -457,25 +467,32 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   // A wavefront issues an instruction every four cycles and an MFMA takes sixteen, so a gap has room for three others: they are
   // dealt out one or two to a gap.  No branches in here: past the last K-tile the loads bring zeros, and the fragments are
   // never used.
-  auto iteration = [&](int t, int sa, int sb, int sa1, int sb1, auto masked_c) __attribute__((always_inline)) {
-    constexpr bool MASKED = decltype(masked_c)::value;
+  // `behind`: the last two iterations of a launch with EARLY epilogue loads, which load no K-tile but call behind(gap).
+  auto iteration = [&](int t, int sa, int sb, int sa1, int sb1, auto kind_c, auto behind) __attribute__((always_inline)) {
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool MASKED = KIND == kMaskedLoads, LOADS = KIND <= kMaskedLoads;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < 2 * MF; ++q) {
       const int ks = q / MF, j = (q % MF) / TM, i = q % TM;
-      if (q == QF) {
+      if (q == QF && LOADS) {
         wait_and_meet<(WIDE ? 63 : AHEAD)>();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (WIDE && q == QL) {
+      if (WIDE && q == QL && LOADS) {
         wait_and_meet<AHEAD + LOADED>();
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (q == QL && KIND == kNextToLast) {
+        wait_and_meet<(QL + EG - 1) / EG>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
       acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[j][i], 0, 0, 0);
+      if (!LOADS) behind(q);
       if (q < MF && q % F0 == 0 && q / F0 < NF) read_frag(sa, sb, 1, 1, q / F0);
-      if (q >= R0 && (q - R0) % F1 == 0 && (q - R0) / F1 < NF) read_frag(sa1, sb1, 0, 0, (q - R0) / F1);
-      if (q >= QF - 4 * SS && q < QF && (QF - 1 - q) % SS == 0) next_b((q - (QF - 4 * SS)) / SS, t + NSB, sb);
-      if (q >= QF && q < QF + 4 * SS && (q - QF) % SS == 0) next_a((q - QF) / SS, t + NSA, sa);
+      if (KIND != kLast && q >= R0 && (q - R0) % F1 == 0 && (q - R0) / F1 < NF) read_frag(sa1, sb1, 0, 0, (q - R0) / F1);
+      if (LOADS && q >= QF - 4 * SS && q < QF && (QF - 1 - q) % SS == 0) next_b((q - (QF - 4 * SS)) / SS, t + NSB, sb);
+      if (LOADS && q >= QF && q < QF + 4 * SS && (q - QF) % SS == 0) next_a((q - QF) / SS, t + NSA, sa);
       // offsets of the gathered operand: B's before its loads begin at QF, A's between the late loads of the tile before and its
       // own; then the next tile's indices, to be here before the next LDS read
       if (b_gather && q >= QF - NB && q < QF) take_kidx(q - (QF - NB));
@@ -484,7 +501,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
       if (SETS && q == (WIDE ? MF - 1 : QF + NA)) have_kidx();
       {
         const int at = q >= QF ? q - QF : q - QF + 2 * MF, p = at / DG;
-        if (p < NP && (q >= QF || p >= NP - LATE)) {
+        if (LOADS && p < NP && (q >= QF || p >= NP - LATE)) {
           // (a gap ahead of the load, but in the same iteration)
           const bool alone = DG == 1 || (q == 0 && at % DG == DG - 1);
           if (alone || (at % DG == DG - 2 && q < 2 * MF - 1)) aim(p);
@@ -498,33 +515,37 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   // The iterations that load the last K-tile of a pass of K-contiguous operands zero what lies beyond the range; they run in a copy of
   // their own, so that the others carry no selects.
   int t = 0, sa = 0, sb = 0;
-  auto step = [&](auto masked_c) __attribute__((always_inline)) {
+  auto step = [&](auto kind_c, auto behind) __attribute__((always_inline)) {
     const int sa1 = sa + 1 == NSA ? 0 : sa + 1, sb1 = sb + 1 == NSB ? 0 : sb + 1;
-    iteration(t, sa, sb, sa1, sb1, masked_c);
+    iteration(t, sa, sb, sa1, sb1, kind_c, behind);
     sa = sa1; sb = sb1;
     ++t;
   };
+  auto nothing = [](int) {};
+  // the last two iterations of an EARLY launch run behind these (of a single K-tile, the second one multiplies the zeros that follow it):
+  // by then every K-tile has been requested, A's NSA = 3 ahead and B's two or three
+  const int n_main = EARLY ? (nsteps > 2 ? nsteps - 2 : 0) : nsteps;
   if constexpr (A_KC || B_KC || SETS) {
     int last = klen % BK != 0 ? nk - 1 - k_rot : nsteps + FAR;        // the next K-tile that needs it
     while (last + 1 < NEAR) last += nk;
     while (true) {
-      const int stop = last - FAR < nsteps ? last - FAR : nsteps;
-      while (t < stop) step(std::false_type{});
-      if (t >= nsteps) break;
-      step(std::true_type{});
+      const int stop = last - FAR < n_main ? last - FAR : n_main;
+      while (t < stop) step(std::integral_constant<int, kPlainLoads>{}, nothing);
+      if (t >= n_main) break;
+      step(std::integral_constant<int, kMaskedLoads>{}, nothing);
       if (t > last - NEAR + 1) last += nk;
     }
   } else {
-    do step(std::false_type{}); while (t < nsteps);
+    do step(std::integral_constant<int, kPlainLoads>{}, nothing); while (t < nsteps);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no load may still write the LDS that the epilogue uses
+  if (!EARLY) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no load may still write the LDS that the epilogue uses
 
   // ---- epilogue ----
   // The MFMA leaves each lane with 4-column runs of one row per register group, which would scatter 32-byte
   // pieces over 32 rows per store.  Each wavefront therefore turns its sub-tile through a private LDS region,
   // 32 rows at a time, and comes back with lanes laid along the columns: every global access below is a run of
   // 256 to 512 contiguous bytes per row.
-  constexpr int ECOLS = TN * 16, EPITCH = ECOLS + 4; // floats per LDS row
+  constexpr int EPITCH = ECOLS + 4;                  // floats per LDS row
   constexpr int TS = C::TS;                          // 32-row slabs: slab i holds the MFMA row tiles 2i and 2i+1
   float* ep = reinterpret_cast<float*>(smem) + wave * (32 * EPITCH);
   // output addresses are a per-tile base (uniform) plus a 32-bit element offset: row within the tile times the row
@@ -532,37 +553,50 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const int e_rows = (int)(m_end - m0);
   const long e_tile = c_group + m0 * c_ms;
   const int e_r0 = wm * (BM / 2);
-  // dSwiGLU epilogue: lanes lie along the columns (DS_CPR lanes per row, eight columns each, so that the bf16
-  // results leave in 16-byte stores); the saved fp32 projections come in batches of half a 32-row slab
-  constexpr int DS_CPR = ECOLS / 8, DS_RPI = 64 / DS_CPR, DS_NB = 2, DS_HALF = 32 / DS_RPI / DS_NB;
+  // dSwiGLU epilogue: lanes lie along the columns (DS_CPR lanes per row, eight columns each, so that the bf16 results leave in
+  // 16-byte stores), DS_RPI rows at a time.  Its loads and stores go through buffer resources that begin at the tile and end with its
+  // last row: a lane out of the tile asks for an offset beyond them, so all are unconditional, and the compiler, which knows how many are
+  // outstanding, does not wait for stores where it needs a load.  A tile is 5200 vector instructions per wavefront (25 000 cycles), 384 KB in and 256 or
+  // 384 KB out (3.5 and 1.9 us where one CU does it alone, 12 and 7 where all do at once).  The first loads go out before the main
+  // loop ends, and in the middle of the arithmetic one or two at a time; nothing is formed of gate * h for an expert that does not train.  Before (batches of 12 loads
+  // and 12 stores, each load waited for behind the stores before it) the half-width tiles took 22 800 cycles, now 18 600: steps of
+  // 1531 tokens 512 x 352 163 -> 161 us, 4096 tokens 768 x 2048 489 -> 484, 3777 tokens 1536 x 1280 331 -> 327, 16384 tokens 2048 x 1024
+  // 3866 -> 3840.
   const int ds_c8 = lane % DS_CPR;
   const long ds_n = n0 + wn * (BN / 2) + ds_c8 * 8;
-  // addresses are a per-tile base (uniform) plus a 32-bit offset: one register per address instead of two
-  const long ds_tile = m0 * c_ms;
   const int ds_rows = (int)(m_end - m0);                        // valid rows of the tile
   const int ds_r0 = wm * (BM / 2) + lane / DS_CPR;
   const bool ds_nin = ds_n < Ndim;
-  const unsigned ds_ncl = ds_nin ? (unsigned)ds_n : 0u;
-  const bf16_t* ds_a = reinterpret_cast<const bf16_t*>(g.E[0]) + ds_tile;
-  const bf16_t* ds_b = reinterpret_cast<const bf16_t*>(g.E[1]) + ds_tile;
-  const bf16_t* ds_d = reinterpret_cast<const bf16_t*>(g.E[2]) + ds_tile;
-  bf16_t* ds_c0 = reinterpret_cast<bf16_t*>(g.C[0]) + ds_tile;
-  bf16_t* ds_c1 = reinterpret_cast<bf16_t*>(g.C[1]) + ds_tile;
-  bf16_t* ds_c2 = reinterpret_cast<bf16_t*>(g.C[2]) + ds_tile;
-  uint4 av[EPI == kEpiDSwiglu ? DS_HALF : 1], bv[EPI == kEpiDSwiglu ? DS_HALF : 1], dv[EPI == kEpiDSwiglu ? DS_HALF : 1];
-  auto load_ab = [&](int i, int hf) {
-    if (EPI == kEpiDSwiglu) {
+  const unsigned ds_bytes = uniform((unsigned)(((long)(ds_rows - 1) * c_ms + Ndim) * 2)), ds_row_bytes = (unsigned)c_ms * 2;
+  auto ds_rsrc = [&](const void* p, long elems, unsigned bytes) { return tile_rsrc(base_of(p, elems), bytes); };
+  const long ds_tile = m0 * c_ms;
+  __amdgpu_buffer_rsrc_t ds_in[3], ds_out[3];
+  float ds_scale[BM > 128 ? 2 : 1];                             // of row `lane` of the wavefront's, and of the row 64 below
+  if (EPI == kEpiDSwiglu) {
 #pragma unroll
-      for (int q = 0; q < DS_HALF; ++q) {
-        const int rt = ds_r0 + i * 32 + (hf * DS_HALF + q) * DS_RPI;     // row within the tile
-        const unsigned ci = (unsigned)(rt < ds_rows ? rt : ds_rows - 1) * (unsigned)c_ms + ds_ncl;
-        av[q] = *reinterpret_cast<const uint4*>(ds_a + ci);
-        bv[q] = *reinterpret_cast<const uint4*>(ds_b + ci);
-        dv[q] = *reinterpret_cast<const uint4*>(ds_d + ci);
-      }
+    for (int i = 0; i < 3; ++i) {
+      ds_in[i] = ds_rsrc(g.E[i], ds_tile, ds_bytes);
+      ds_out[i] = ds_rsrc(g.C[i], ds_tile, ds_bytes);
     }
+    const auto sc = ds_rsrc(g.row_scale, m0 * 2, (unsigned)ds_rows * 4u);
+#pragma unroll
+    for (int i = 0; i < (BM > 128 ? 2 : 1); ++i) ds_scale[i] = load4(sc, (unsigned)(wm * (BM / 2) + i * 64 + lane) * 4u);
+  }
+  auto ds_off = [&](int unit) {
+    const int rt = ds_r0 + unit * DS_RPI;
+    return rt < ds_rows && ds_nin ? (unsigned)rt * ds_row_bytes + (unsigned)ds_n * 2u : kOutOfRange;
   };
-  load_ab(0, 0);
+  rsrc_t ds_v[DS_AHEAD][3];
+  if constexpr (EARLY) {
+    // The first of these loads are spread over the last two iterations, in registers that the main loop has to spare.
+    auto first_loads = [&](int n) { ds_v[n / 3][n % 3] = load16(ds_in[n % 3], ds_off(n / 3)); };
+    constexpr int N2 = (2 * MF + EG - 1) / EG;             // by the next-to-last one
+    static_assert(NSA == 3 && 2 * N2 >= DS_AHEAD * 3, "every K-tile and every one of these loads is requested");
+    auto at_gap = [&](int q) { if (q % EG == 0 && q / EG < DS_AHEAD * 3) first_loads(q / EG); };
+    step(std::integral_constant<int, kNextToLast>{}, at_gap);
+    step(std::integral_constant<int, kLast>{}, [&](int q) { if (q % EG == 0 && N2 + q / EG < DS_AHEAD * 3) first_loads(N2 + q / EG); });
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(DS_AHEAD * 3) : "memory");      // no load may still write the LDS that the epilogue uses
+  }
   // fp32 store epilogue: lanes along the columns, four of them per lane.  When the result is added to what is there,
   // the old values of a whole 32-row slab are requested before the previous slab is stored (see load_ab: a load behind
   // a store waits for that store, and one load, add, store chain per two rows would be 64 round trips a tile; with the
@@ -587,6 +621,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   };
   if (f_add) load_old(0);
   __syncthreads();                                   // the staging tiles are dead from here on
+  rsrc_t ds_o[2][2];
+  float* const ds_dots = reinterpret_cast<float*>(smem) + 4 * 32 * EPITCH + wave * (BM / 2);
 #pragma unroll
   for (int i = 0; i < TS; ++i) {
     if (EPI == kEpiStore && !F32_OUT) {
@@ -708,66 +744,69 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
         }
       }
     } else {
+      // Two elements of a lane at a time, and behind each pair one or two of the memory instructions of the row groups before and
+      // behind: the path takes a wavefront's 1 KB in sixteen cycles, and a wavefront that issues several in a row stands still for the
+      // other three's.
+      constexpr int UPS = 32 / DS_RPI;              // row groups per slab
+      float4 uu[2][2];
+      float rs[2];
+      auto read_u = [&](int v) {
+        const float* const p = ep + (v * DS_RPI + lane / DS_CPR) * EPITCH + ds_c8 * 4;
+        uu[v & 1][0] = *reinterpret_cast<const float4*>(p);
+        uu[v & 1][1] = *reinterpret_cast<const float4*>(p + ECOLS / 2);
+        const int row = (i * UPS + v) * DS_RPI;
+        rs[v & 1] = lane_value_at(ds_scale[row / 64], (row % 64) * 4 + lane / DS_CPR * 4);
+      };
+      read_u(0);
 #pragma unroll
-      for (int hf = 0; hf < DS_NB; ++hf) {
-        uint4 oa[DS_HALF], ob[DS_HALF], oh[DS_HALF];
-        float dots[DS_HALF];
+      for (int v = 0; v < UPS; ++v) {
+        const int unit = i * UPS + v, far = unit - 1 + DS_AHEAD;
+        const rsrc_t av = ds_v[unit % DS_AHEAD][0], bv = ds_v[unit % DS_AHEAD][1], dv = ds_v[unit % DS_AHEAD][2];
+        const unsigned off_far = ds_off(far), off_prev = ds_off(unit - 1);
+        rsrc_t (&o)[2] = ds_o[unit & 1], (&po)[2] = ds_o[1 - (unit & 1)];
+        float dot = 0.f, h[8];
 #pragma unroll
-        for (int q = 0; q < DS_HALF; ++q) {
-          const int row = (hf * DS_HALF + q) * DS_RPI + lane / DS_CPR;
-          const float4 u0 = *reinterpret_cast<const float4*>(ep + row * EPITCH + ds_c8 * 4);
-          const float4 u1 = *reinterpret_cast<const float4*>(ep + row * EPITCH + ECOLS / 2 + ds_c8 * 4);
-          const int rt = ds_r0 + i * 32 + (hf * DS_HALF + q) * DS_RPI;
-          const float rs = g.row_scale[m0 + (rt < ds_rows ? rt : ds_rows - 1)];
-          const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-          const uint32_t aw[4] = {av[q].x, av[q].y, av[q].z, av[q].w}, bw[4] = {bv[q].x, bv[q].y, bv[q].z, bv[q].w},
-                         dw[4] = {dv[q].x, dv[q].y, dv[q].z, dv[q].w};
-          float a[8], b[8], hc[8];
+        for (int e2 = 0; e2 < 4; ++e2) {
+          float da[2], db[2];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            a[2 * e] = __uint_as_float(aw[e] << 16); a[2 * e + 1] = __uint_as_float(aw[e] & 0xffff0000u);
-            b[2 * e] = __uint_as_float(bw[e] << 16); b[2 * e + 1] = __uint_as_float(bw[e] & 0xffff0000u);
-            hc[2 * e] = __uint_as_float(dw[e] << 16); hc[2 * e + 1] = __uint_as_float(dw[e] & 0xffff0000u);
-          }
-          float da[8], db[8], hg[8], dot = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float sg = sigmoidf_(a[e]);
-            const float as = a[e] * sg;          // SiLU of the saved (bf16) gate projection
-            const float h = as * b[e] + hc[e];   // the forward's h: what the rounded pair gives plus the saved correction
-            dot = fmaf(u[e], h, dot);
-            const float dh = rs * u[e];
-            da[e] = dh * b[e] * (sg + as * (1.f - sg));
+          for (int e = 0; e < 2; ++e) {
+            const float a = __uint_as_float(e ? av[e2] & 0xffff0000u : av[e2] << 16), b = __uint_as_float(e ? bv[e2] & 0xffff0000u : bv[e2] << 16);
+            const float hc = __uint_as_float(e ? dv[e2] & 0xffff0000u : dv[e2] << 16);
+            const float4 u4 = uu[v & 1][e2 / 2];
+            const float u = (e2 & 1) ? (e ? u4.w : u4.z) : (e ? u4.y : u4.x);
+            const float sg = sigmoidf_(a);
+            const float as = a * sg;          // SiLU of the saved (bf16) gate projection
+            h[2 * e2 + e] = as * b + hc;      // the forward's h: what the rounded pair gives plus the saved correction
+            dot = fmaf(u, h[2 * e2 + e], dot);
+            const float dh = rs[v & 1] * u;
+            da[e] = dh * b * (sg + as * (1.f - sg));
             db[e] = dh * as;
-            hg[e] = rs * h;
           }
-          oa[q] = make_uint4(pack2(da[0], da[1]), pack2(da[2], da[3]), pack2(da[4], da[5]), pack2(da[6], da[7]));
-          ob[q] = make_uint4(pack2(db[0], db[1]), pack2(db[2], db[3]), pack2(db[4], db[5]), pack2(db[6], db[7]));
-          oh[q] = make_uint4(pack2(hg[0], hg[1]), pack2(hg[2], hg[3]), pack2(hg[4], hg[5]), pack2(hg[6], hg[7]));
-          if (!(rt < ds_rows && ds_nin)) dot = 0.f;
-          // gate-gradient partial of this row over the wavefront's columns: the CPR lanes of a row sit side by side
-#pragma unroll
-          for (int o = DS_CPR / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, kWave);
-          dots[q] = dot;
-        }
-        // The saved projections of the next half-slab are requested before this one's results are stored: one
-        // in-order counter covers loads and stores, so a load issued after a store would wait for that store to
-        // be acknowledged, and every half-slab would pay a full load and a full store round trip in sequence.
-        __builtin_amdgcn_sched_barrier(0);
-        if (hf + 1 < DS_NB) load_ab(i, hf + 1);
-        else if (i + 1 < TS) load_ab(i + 1, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < DS_HALF; ++q) {
-          const int rt = ds_r0 + i * 32 + (hf * DS_HALF + q) * DS_RPI;
-          if (rt < ds_rows && ds_nin) {
-            const unsigned ci = (unsigned)rt * (unsigned)c_ms + ds_ncl;
-            *reinterpret_cast<uint4*>(ds_c0 + ci) = oa[q];
-            *reinterpret_cast<uint4*>(ds_c1 + ci) = ob[q];
-            if (ds_store2) *reinterpret_cast<uint4*>(ds_c2 + ci) = oh[q];
+          o[0][e2] = pack2(da[0], da[1]); o[1][e2] = pack2(db[0], db[1]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (e2 == 0 && v + 1 < UPS) read_u(v + 1);
+          if (unit > 0) {
+            if (e2 < 3 && far < DS_UNITS) ds_v[far % DS_AHEAD][e2] = load16(ds_in[e2], off_far);
+            if (e2 == 1 || e2 == 3) store16(ds_out[e2 / 2], off_prev, po[e2 / 2]);
           }
-          if (ds_c8 == 0 && rt < ds_rows) g.rowdot[(long)(g.rowdot_slot0 + nt * 2 + wn) * g.rowdot_stride + m0 + rt] = dots[q];
+          __builtin_amdgcn_sched_barrier(0);
         }
+        asm("" : "+v"(dot));                 // (computed by all lanes: else the compiler branches around it)
+        // gate-gradient partial of this row over the wavefront's columns: the CPR lanes of a row sit side by side
+        dot = lane_group_sum<DS_CPR>(ds_off(unit) == kOutOfRange ? 0.f : dot);
+        if (ds_c8 == 0) ds_dots[unit * DS_RPI + lane / DS_CPR] = dot;
+        if (ds_store2) {
+          const float r = rs[v & 1];
+          store16(ds_out[2], ds_off(unit), rsrc_t{pack2(r * h[0], r * h[1]), pack2(r * h[2], r * h[3]), pack2(r * h[4], r * h[5]), pack2(r * h[6], r * h[7])});
+        }
+      }
+      if (i + 1 == TS) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) store16(ds_out[x], ds_off(DS_UNITS - 1), ds_o[(DS_UNITS - 1) & 1][x]);
+        const auto rd = ds_rsrc(g.rowdot, ((g.rowdot_slot0 + nt * 2 + wn) * g.rowdot_stride + m0) * 2, (unsigned)ds_rows * 4u);
+#pragma unroll
+        for (int x = 0; x < BM / 2; x += 64)
+          if (x + lane < BM / 2) store4(rd, (unsigned)(wm * (BM / 2) + x + lane) * 4u, ds_dots[x + lane]);
       }
     }
   }

@@ -34,6 +34,21 @@ __device__ __forceinline__ void wait_and_meet() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
+// Loads and stores of a lane's own through a buffer resource: zero, or nothing, at or beyond its end
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(unsigned long base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ rsrc_t load16(__amdgpu_buffer_rsrc_t rs, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0); }
+__device__ __forceinline__ float load4(__amdgpu_buffer_rsrc_t rs, unsigned off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+}
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t rs, unsigned off, const rsrc_t& v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)off, 0, 0);
+}
+__device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t rs, unsigned off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, (int)off, 0, 0);
+}
+
 // 16 bytes per lane to base + lane_off with the non-temporal hint, nothing for a lane out of the `bytes` bytes
 __device__ __forceinline__ void store_stream16(unsigned long base, unsigned bytes, unsigned lane_off, const uint4& v) {
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, (int)bytes, 0x00020000);
