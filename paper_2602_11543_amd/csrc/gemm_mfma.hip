@@ -85,6 +85,9 @@ constexpr int lds_units() {
   return C::LDS_VEC > slabs ? C::LDS_VEC : slabs;
 }
 
+// an element at an address that is the same for the whole wavefront, of a table that an earlier launch wrote
+__device__ __forceinline__ int scalar_load(const int* p) { return *(__attribute__((address_space(4))) const int*)(unsigned long)p; }
+
 // One tile.  block: position in the launch, or in its part with this tile shape; ragged rows: that part's row tiles in the table
 // SETS: several contractions over the same groups in one launch (the three weight gradients), each with its own operands
 // and result; either operand of a set may take its k-rows through the index table k_rows (the dy rows, or the input
@@ -101,34 +104,40 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   constexpr bool F32_OUT = f32_out(MODE, A_KC, B_KC);
 
   // ---- which tile ----
+  // What is ahead of a tile's first MFMA is a chain of round trips (number of tiles, tile table, expert's end and index table, operands) with
+  // integer divisions between them, and nothing else runs on the CU.  The scalars come in pairs, the divisions are 32-bit, the
+  // weights' first K-tile, which needs no index, is requested before the indices are waited for, and the indices come by
+  // scalar loads, which do not wait in line with it.  From a tile's start to its operand loads 1.3 us, and 2.8 in a launch's first round;
+  // now 0.5 to 1.0, and 0.8.  With the surplus rows' fetches left out as well: steps of 1531 tokens 512 x 352 153 -> 145 us, 4096
+  // tokens 768 x 2048 479 -> 469, 3777 tokens 1536 x 1280 328 -> 318, 16384 tokens 2048 x 1024 3854 -> 3818.
   const int n_base = MODE == kRaggedM ? g.n_base : 0;
   int Mdim = g.Mdim, Ndim = g.Ndim;
-  int gx = cdiv(Ndim - n_base, BNO);
-  long total;
-  if (MODE == kRaggedM) total = (long)mt_count * gx; else total = (long)g.n_groups * cdiv(Mdim, BM) * gx;
-  if (SETS) total *= g.n_sets;
-  long logical;
+  unsigned gx = (unsigned)(Ndim - n_base + BNO - 1) / BNO;
+  // (32-bit: a launch has fewer blocks, and a 64-bit division takes a wavefront some 700 cycles)
+  unsigned total = (MODE == kRaggedM ? (unsigned)mt_count : (unsigned)g.n_groups * ((unsigned)(Mdim + BM - 1) / BM)) * gx;
+  if (SETS) total *= (unsigned)g.n_sets;
+  unsigned logical;
   if (MODE == kGroupedK && g.offset != nullptr) {
     // ragged contraction lengths: tiles are taken in block order (round-robin over the XCDs) and the groups are
     // visited longest first, so the long tiles start early and the short ones fill in behind them
     logical = block;
     if (logical >= total) return;
   } else {
-    const long per_xcd = (total + kXcds - 1) / kXcds;
-    const long slot = block / kXcds;
-    logical = (long)(block % kXcds) * per_xcd + slot;
+    const unsigned per_xcd = (total + kXcds - 1) / kXcds;
+    const unsigned slot = block / kXcds;
+    logical = (block % kXcds) * per_xcd + slot;
     if (slot >= per_xcd || logical >= total) return;
   }
   int set = 0;
   if (SETS) {
     // the sets of a group stand side by side, all of the longest group's tiles first; a set whose result is the
     // transposed shape has the same number of (square) tiles
-    const unsigned per_set = (unsigned)cdiv(Mdim, BM) * (unsigned)gx, at = (unsigned)logical;
+    const unsigned per_set = (unsigned)cdiv(Mdim, BM) * gx, at = logical;
     const unsigned pos = at / per_set, grp_pos = pos / 3u;       // three sets (see launch); 32-bit: a grid has fewer blocks
     set = (int)(pos - grp_pos * 3u);
     logical = grp_pos * per_set + (at - pos * per_set);
     Mdim = g.set[set].Mdim; Ndim = g.set[set].Ndim;
-    gx = cdiv(Ndim, BNO);
+    gx = (unsigned)(Ndim + BNO - 1) / BNO;
   }
   const void* const opA0 = SETS ? g.set[set].A : g.A[0];
   const void* const opB0 = SETS ? g.set[set].B : g.B[0];
@@ -137,41 +146,61 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const long c_ms = SETS ? g.set[set].c_ms : g.c_ms;
   static_assert(SETS == (GATHER != 0), "one operand of every set");
   constexpr bool a_gather = GATHER == 1, b_gather = GATHER == 2;
-  int nt;
-  long mt_all;
+  unsigned nt, mt_all;
   if (MODE == kRaggedM && gx >= kGroupMinCols) {
     // Row tiles are taken kGroupRows at a time and the column tiles run inside such a group, so that the 32 tiles an
     // XCD works on at once are about kGroupRows row panels times 32/kGroupRows column panels: with the plain
     // row-major order a wide output (many column tiles) has every CU of the XCD stream its own weight panel, and the
     // next row tile of the expert streams them all again.
-    const long rows_all = total / gx;
-    const long per_group = (long)kGroupRows * gx;
-    const long grp_i = logical / per_group, within = logical - grp_i * per_group;
-    const long left = rows_all - grp_i * kGroupRows;
-    const int gm = (int)(left < kGroupRows ? left : kGroupRows);
-    nt = (int)(within / gm);
-    mt_all = grp_i * kGroupRows + within % gm;
+    const unsigned per_group = kGroupRows * gx;
+    const unsigned grp_i = logical / per_group, within = logical - grp_i * per_group;
+    const unsigned left = (unsigned)mt_count - grp_i * kGroupRows;
+    if (left >= kGroupRows) {
+      nt = within / kGroupRows;
+      mt_all = grp_i * kGroupRows + within % kGroupRows;
+    } else {
+      nt = within / left;
+      mt_all = grp_i * kGroupRows + (within - nt * left);
+    }
   } else {
-    nt = (int)(logical % gx);
     mt_all = logical / gx;
+    nt = logical - mt_all * gx;
   }
-  if (MODE == kRaggedM) mt_all += mt_first;
+  if (MODE == kRaggedM) mt_all += (unsigned)mt_first;
 
   long m0, m_end, k_begin, k_end, b_group = 0, c_group = 0;
+  // kRaggedM with gathered rows of A (every row read from x or dy): the index table's entries of this wavefront's rows, eight per load of
+  // a K-tile, four loads at a time in scalar registers, where they do not wait in line with the loads into LDS.  (Entries beyond
+  // the tile's last row are there to be read, at worst in the regions of the context behind the table, and not used.)
+  constexpr bool ROWS = MODE == kRaggedM && EPI != kEpiStore;
+  constexpr int ROWB = C::NA < 4 ? C::NA : 4;
+  typedef __attribute__((ext_vector_type(8))) int i32x8;
+  typedef __attribute__((address_space(4))) const i32x8 const_i32x8 __attribute__((aligned(4)));
+  i32x8 row_idx[ROWB];
+  auto request_rows = [&](int first) {
+    if (ROWS) {
+#pragma unroll
+      for (int i = 0; i < ROWB; ++i) row_idx[i] = *(const_i32x8*)(unsigned long)(g.a_rows + (int)uniform((unsigned)m0 + (unsigned)wave * 8 + 32u * (unsigned)(first + i)));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   bool ds_store2 = true;
   unsigned expert = 0;
   if (MODE == kRaggedM) {
-    const int e = g.tile_expert[mt_all];
+    // (each pair of scalar loads together: one round trip)
+    int e = scalar_load(g.tile_expert + mt_all), row0 = scalar_load(g.tile_row0 + mt_all);
+    asm volatile("" : "+s"(e), "+s"(row0));
     expert = uniform((unsigned)e);
     ds_store2 = ((g.c2_skip >> e) & 1ull) == 0;
-    m0 = g.tile_row0[mt_all];
-    m_end = min((long)g.offset[e + 1], m0 + BM);
+    m0 = row0;
+    request_rows(0);
+    m_end = min((long)scalar_load(g.offset + e + 1), m0 + BM);
     k_begin = 0; k_end = g.Kdim;
     b_group = (long)e * g.b_gs;
   } else {
-    const int my = cdiv(Mdim, BM);
+    const unsigned my = (unsigned)cdiv(Mdim, BM);
     int grp = (int)(mt_all / my);
-    m0 = (mt_all % my) * BM;
+    m0 = (long)(mt_all - (unsigned)grp * my) * BM;
     m_end = min((long)Mdim, m0 + BM);
     if (g.offset != nullptr) {
       // grp counts positions in descending order of length; find the group that holds this position
@@ -230,19 +259,30 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   auto ks_col = [&](int i, int ch, int n, long first) { return (unsigned)((first + (((lane % ch) ^ (2 * (ks_k(i, ch, n) & 3))) * 8)) * 2); };
   auto ks_off = [](unsigned long o) { return o < kOutOfRange ? (unsigned)o : kOutOfRange; };   // k-rows beyond a short, wide operand
   unsigned aoff[C::NA], boff[C::NB];
-  if (A_KC) {
-    int m_row[C::NA];
+  // of A: kRaggedM, once the first loads of B are on their way, ROWB loads at a time; surplus rows: zeros, without a fetch
+  auto ragged_rows = [&](int first) {
+    if (ROWS) {
 #pragma unroll
-    for (int i = 0; i < C::NA; ++i) {
-      const long m = m0 + wave * 8 + (lane >> 3) + 32 * i;
-      m_row[i] = (int)m;
-      if (MODE == kRaggedM && g.a_rows) m_row[i] = g.a_rows[m < m_end ? m : m_end - 1];       // the index table is only that long
+      for (int i = 0; i < ROWB; ++i) asm volatile("" : "+s"(row_idx[i]));
     }
 #pragma unroll
-    for (int i = 0; i < C::NA; ++i) aoff[i] = (unsigned)((m_row[i] * g.a_ms + kc_chunk * 8) * 2);
-  } else {
+    for (int i = 0; i < ROWB; ++i) {
+      const int m = (int)m0 + wave * 8 + (lane >> 3) + 32 * (first + i);
+      int row = m;
+      if (ROWS) {
+        row = row_idx[i][0];
+#pragma unroll
+        for (int h = 1; h < 8; ++h) row = lane >> 3 == h ? row_idx[i][h] : row;
+      }
+      aoff[first + i] = m < (int)m_end ? ((unsigned)row * (unsigned)g.a_ms + (unsigned)kc_chunk * 8u) * 2u : kOutOfRange;
+    }
+  };
+  if (!A_KC) {
 #pragma unroll
     for (int i = 0; i < C::NA; ++i) aoff[i] = ks_off(ks_k(i, ACH, C::NA) * a_ks * 2 + ks_col(i, ACH, C::NA, m0));
+  } else if (MODE != kRaggedM) {
+#pragma unroll
+    for (int i = 0; i < C::NA; ++i) aoff[i] = (unsigned)(((m0 + wave * 8 + (lane >> 3) + 32 * i) * g.a_ms + kc_chunk * 8) * 2);
   }
   // fused SwiGLU: load i brings rows of the gate matrix (B[0]) or of the up matrix (B[1]); tile row nl -> wave column, then
   // (BN/4) gate columns followed by the matching (BN/4) up columns
@@ -436,6 +476,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
 
   // prologue: the first NSA and NSB K-tiles, in the order in which the iterations -NS .. -1 would have loaded them
   constexpr int FAR = NSA > NSB ? NSA : NSB, NEAR = NSA > NSB ? NSB : NSA, NSG = a_gather ? NSA : NSB;
+  if (MODE == kRaggedM) {
+#pragma unroll
+    for (int st = 0; st < 4; ++st) next_b(st, 0, 0);
+#pragma unroll
+    for (int p = 0; p < NB; ++p) { aim(p); one_instruction(); load(p, true); }
+#pragma unroll
+    for (int st = 0; st < 4; ++st) next_a(st, 0, 0);
+#pragma unroll
+    for (int first = 0; first < NA; first += ROWB) {
+      ragged_rows(first);
+      if (first + ROWB < NA) request_rows(first + ROWB);
+#pragma unroll
+      for (int p = NB + first; p < NB + first + ROWB; ++p) { aim(p); one_instruction(); load(p, true); }
+    }
+  }
 #pragma unroll
   for (int u = -FAR; u < 0; ++u) {
     if (SETS && u + NSG >= 0) {
@@ -446,12 +501,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     }
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
-      if (u + NSB >= 0) next_b(st, u + NSB, u + NSB);
-      if (u + NSA >= 0) next_a(st, u + NSA, u + NSA);
+      if (u + NSB >= (MODE == kRaggedM ? 1 : 0)) next_b(st, u + NSB, u + NSB);
+      if (u + NSA >= (MODE == kRaggedM ? 1 : 0)) next_a(st, u + NSA, u + NSA);
     }
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      if ((p < NB ? u + NSB < 0 : u + NSA < 0) || (u == -1 && p >= NP - LATE)) continue;
+      if ((p < NB ? u + NSB : u + NSA) < (MODE == kRaggedM ? 1 : 0) || (u == -1 && p >= NP - LATE)) continue;
       aim(p); one_instruction(); load(p, true);
     }
   }
@@ -822,11 +877,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
 template <int MODE, int EPI, bool A_KC, bool B_KC, bool SETS, typename C, typename CH>
 __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs g) {
   __shared__ uint4 smem[lds_units<C>() > lds_units<CH>() ? lds_units<C>() : lds_units<CH>()];
-  const int all = MODE == kRaggedM ? *g.n_tiles : 0;
+  int all = MODE == kRaggedM ? scalar_load(g.n_tiles) : 0, full = C::BM != CH::BM ? scalar_load(g.n_full) : 0;
+  if (MODE == kRaggedM) asm volatile("" : "+s"(all), "+s"(full));          // one round trip
   if constexpr (C::BM != CH::BM) {
     static_assert(MODE == kRaggedM && CH::BN == C::BN && CH::BM == plan::kHalfRows, "the table's short tiles, the same columns");
     // the table has the full tiles first; the blocks of either kind are dealt to the XCDs by themselves
-    const int full = *g.n_full;
     const unsigned gx = (unsigned)cdiv(g.Ndim - g.n_base, EPI == kEpiSwiglu ? C::BN / 2 : C::BN);
     const unsigned first_short = ((unsigned)full * gx + kXcds - 1) / kXcds * kXcds;
     if (blockIdx.x >= first_short) {
@@ -871,6 +926,7 @@ template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS 
 int launch(const GemmArgs& g, hipStream_t s) {
   static_assert(!SETS || (MODE == kGroupedK && !A_KC && !B_KC && C::BM == C::BN), "operand sets: K-strided, square tiles");
   if (EPI == kEpiStore && (g.c_f32 != 0) != f32_out(MODE, A_KC, B_KC)) return SPES_EINVAL;
+  if (MODE == kRaggedM && (g.a_rows != nullptr) != (EPI != kEpiStore)) return SPES_EINVAL;
   // operands are addressed with 32-bit byte offsets from their base
   if (SETS) {
     if (g.npairs != 1 || g.n_sets != 3) return SPES_EINVAL;
