@@ -341,6 +341,8 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     GemmArgs g = blank();
     g.n_groups = n_train;
     memcpy(g.group_expert, train_list, n_train);
+    g.n_experts = M;
+    for (int i = 0; i < n_train; ++i) g.groups |= 1ull << train_list[i];
     g.offset = at<int>(ctx, L.pub.offset);
     g.mean_k = cdiv(R, M); g.max_k = T;
     g.c_f32 = 1; g.accumulate = accumulate;

@@ -72,6 +72,8 @@ struct GemmArgs {
     long a_elems, b_elems, a_ks, b_ks, c_ms;
     int Mdim, Ndim, a_gather, b_gather;
   } set[3];
+  int n_experts;
+  unsigned long long groups;       // the same experts as bits, and how many experts there are (matrix-core path)
   unsigned char group_expert[64];  // offset != nullptr: group g contracts rows [offset[e], offset[e+1]), e = group_expert[g]
 };
 
