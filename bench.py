@@ -94,9 +94,8 @@ def stage_model(cfg, rho_rows):
         "gemm_dgrad_gate_up": (mm, 4.0 * R * d * f),
         "wgrad": (mm, 6.0 * rho_rows * d * f),
         "router_wgrad": ("hbm", T * d * s + T * M * 4 + M * d * 4),
-        "router_dgrad": ("hbm", T * M * 2 + M * d * s + T * d * s),          # bf16 storage only: its own small GEMM
-        # sum of the k permuted gradient rows plus the router part (read as a precomputed row in bf16 storage)
-        "unpermute_sum_router_dgrad": ("hbm", R * d * s + T * d * s + R * 4 + (T * d * s if s == 2 else 0)),
+        # sum of the k permuted gradient rows plus the router part, formed in the same launch (with the sum of dW_r's partial products)
+        "unpermute_sum_router_dgrad": ("hbm", R * d * s + T * d * s + R * 4 + T * M * s + M * d * s),
     }
 
 

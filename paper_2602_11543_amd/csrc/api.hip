@@ -16,7 +16,7 @@ constexpr int kRouterSplit = 64;   // chunks of the token axis in the router wei
 
 struct Layout {
   spes_moe_ctx_layout pub;
-  size_t block_counts, tab_simt, tab_mfma, row_token, row_gate, hcorr, dgate_part, da, db, hg, dxp, wr_part, dlogits_bf, dxr, aux, aux_part;
+  size_t block_counts, tab_simt, tab_mfma, row_token, row_gate, hcorr, dgate_part, da, db, hg, dxp, wr_part, dlogits_bf, aux, aux_part;
   bool f32_mfma;                                    // fp32 storage on the matrix cores
   int max_tiles, row_tile_f32, est_tiles_f32, row_tile_mfma, max_tiles_mfma, est_tiles_mfma, max_col_tiles;
 };
@@ -88,7 +88,6 @@ Layout make_layout(const spes_moe_shape* s) {
   L.dxp = take(R * d * es);
   L.wr_part = take((size_t)kRouterSplit * M * d * 4);
   L.dlogits_bf = take(T * M * 2);
-  L.dxr = take(T * d * es);
   L.aux = take((kMaxExperts + kAuxExtra) * 4);
   L.aux_part = take((size_t)kAuxBlocks * (kMaxExperts + 1) * 4);
   L.pub.total = off;
@@ -359,6 +358,7 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
     prof_mark(1, "wgrad", s);
   }
   // dW_r[M,d] = dlogits^T x; the token axis is cut into chunks whose partial products are then added in a fixed order
+  int wr_parts = 0;
   {
     GemmArgs g = blank();
     g.a_ms = 1; g.a_ks = M; g.a_elems = (long)T * M;
@@ -380,22 +380,12 @@ SPES_API int spes_moe_bwd(const spes_moe_shape* shape, const void* dy, const voi
         SPES_TRY(launch_gemm_simt(SPES_F32, dt, kGroupedK, kEpiStore, g, s));
       }
     }
-    SPES_TRY(launch_reduce_partials(at<float>(ctx, L.wr_part), g.n_groups, (long)M * d, d_w_router, accumulate, s));
+    wr_parts = g.n_groups;
   }
   prof_mark(1, "router_wgrad", s);
-  // router part of the input gradient, dxr[T,d] = dlogits W_r, as its own small GEMM in bf16 mode
-  if (router_mfma) {
-    GemmArgs g = blank();
-    g.A[0] = at<void>(ctx, L.dlogits_bf); g.a_ms = M; g.a_ks = 1; g.a_elems = (long)T * M;
-    g.B[0] = w_router; g.b_ns = 1; g.b_ks = d; g.b_elems = (long)M * d;
-    g.Kdim = M; g.kchunk = (M + 63) / 64 * 64; g.Mdim = T; g.Ndim = d;
-    g.C[0] = at<void>(ctx, L.dxr); g.c_ms = d;
-    SPES_TRY(launch_gemm_mfma(kGroupedK, kEpiStore, true, false, g, s));
-    prof_mark(1, "router_dgrad", s);
-  }
-  // dx = unpermuted sum of dxp + router part
-  SPES_TRY(launch_dx_gather(dt, at<void>(ctx, L.dxp), inv, at<float>(ctx, L.pub.dlogits), w_router,
-                            router_mfma ? at<void>(ctx, L.dxr) : nullptr, dx, T, d, k, M, s));
+  // dx = unpermuted sum of dxp + dlogits W_r; in the same launch the sum of dW_r's partial products
+  SPES_TRY(launch_dx_gather(dt, at<void>(ctx, L.dxp), inv, at<float>(ctx, L.pub.dlogits), router_mfma ? at<bf16_t>(ctx, L.dlogits_bf) : nullptr,
+                            w_router, dx, T, d, k, M, at<float>(ctx, L.wr_part), wr_parts, d_w_router, accumulate, s));
   prof_mark(1, "unpermute_sum_router_dgrad", s);
   return SPES_OK;
 }

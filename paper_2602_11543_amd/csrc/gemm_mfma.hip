@@ -42,9 +42,6 @@
 namespace spes {
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 constexpr int kXcds = 8;
 
 template <int BM_, int BN_, int NSA_, int NSB_, int MINB_>
@@ -61,21 +58,11 @@ struct Cfg {
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return pack_bf16x2(a, b); }
 
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-// Transposing LDS read.  Within each group of 16 lanes, lane s supplies the address of four consecutive 16-bit
-// elements (think of them as row s of a 16 x 4 matrix); lane i receives column i%4 of rows i/4, i/4+4, i/4+8, i/4+12.
-// With lane s pointing at [k0 + s/4][r0 + 4*(s%4)] of a [k][row] tile, lane i gets k0..k0+3 of row r0+i.
-__device__ __forceinline__ uint2 lds_read_tr(const bf16_t* p) {
-  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-  return __builtin_bit_cast(uint2, v);
-}
-
 constexpr int kGroupRows = 4;      // row tiles per group of the tile order (ragged-row GEMMs) ...
 constexpr int kGroupMinCols = 8;   // ... used when the output has at least this many column tiles
 
 // result type of kEpiStore: the router scores and the weight gradients are fp32, the rest has the storage type
-constexpr bool f32_out(int mode, bool a_kc, bool b_kc) { return mode == kGroupedK && !(a_kc && !b_kc); }
+constexpr bool f32_out(int mode) { return mode == kGroupedK; }
 
 // 16-byte units of LDS that a tile uses: its operand slots, or the four wavefronts' epilogue slabs (32 padded float rows each) and
 // row dots
@@ -101,7 +88,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const int l16 = lane & 15, lq = lane >> 4;          // an MFMA operand: lane holds row l16, k = lq*8 .. lq*8+7 of a 32-wide k-step
   const int wm = wave >> 1, wn = wave & 1;
   constexpr int BNO = (EPI == kEpiSwiglu) ? BN / 2 : BN;   // output columns per tile
-  constexpr bool F32_OUT = f32_out(MODE, A_KC, B_KC);
+  constexpr bool F32_OUT = f32_out(MODE);
 
   // ---- which tile ----
   // What is ahead of a tile's first MFMA is a chain of round trips (number of tiles, tile table, expert's end and index table, operands) with
@@ -912,9 +899,8 @@ typedef Cfg<256, 128, 3, 3, 1> TileNarrow;
 // few output rows (the router's weight gradient over many tokens has M <= 64 of them), the fused SwiGLU on 128-row tiles
 // (plan::row_tile), and the last rows of an expert beside the full tile
 typedef Cfg<128, 256, 3, 3, 1> TileShort;
-// a contraction of a single K-tile (the router's input gradient contracts over the M <= 64 experts) is all prologue
-// and epilogue: small tiles, two blocks per CU, so that one block's memory phases overlap the other's; also the other
-// ragged-row GEMMs on 128-row tiles, and weight gradients of few full tiles (plan::wgrad_small_tiles)
+// two blocks per CU, so that one block's memory phases overlap the other's: the ragged-row GEMMs but the fused SwiGLU on 128-row tiles,
+// weight gradients of few full tiles (plan::wgrad_small_tiles), and the router's
 typedef Cfg<128, 128, 3, 2, 2> TileSmall;
 // the last rows of an expert beside TileNarrow
 typedef Cfg<128, 128, 3, 2, 1> TileNarrowShort;
@@ -929,7 +915,7 @@ static_assert(Tile::BM == plan::kFullRows && TileShort::BM == plan::kHalfRows &&
 template <int MODE, int EPI, bool A_KC, bool B_KC, typename C = Tile, bool SETS = false, typename CH = C>
 int launch(const GemmArgs& g, hipStream_t s) {
   static_assert(!SETS || (MODE == kGroupedK && !A_KC && !B_KC && C::BM == C::BN), "operand sets: K-strided, square tiles");
-  if (EPI == kEpiStore && (g.c_f32 != 0) != f32_out(MODE, A_KC, B_KC)) return SPES_EINVAL;
+  if (EPI == kEpiStore && (g.c_f32 != 0) != f32_out(MODE)) return SPES_EINVAL;
   if (MODE == kRaggedM && (g.a_rows != nullptr) != (EPI != kEpiStore)) return SPES_EINVAL;
   // operands are addressed with 32-bit byte offsets from their base
   if (SETS) {
@@ -1004,9 +990,6 @@ int launch_gemm_mfma(int mode, int epi, bool a_kcontig, bool b_kcontig, const Ge
     // 4096 tokens, 0.58 to 0.91 at 6000 and 8192; from 12000 on 0.71 to 1.28, on either side of 1 at each width
     return g.Mdim <= 8192 ? launch<kGroupedK, kEpiStore, true, true, Rows64Narrow>(g, s)
                           : launch<kGroupedK, kEpiStore, true, true, TileNarrow>(g, s);
-  if (a_kcontig && !b_kcontig)
-    return (g.kchunk <= TileSmall::BK && g.n_groups == 1) ? launch<kGroupedK, kEpiStore, true, false, TileSmall>(g, s)
-                                                          : launch<kGroupedK, kEpiStore, true, false>(g, s);
   if (!a_kcontig && !b_kcontig) {
     if (g.n_sets > 0) {
       const long n = (long)g.n_sets * g.n_groups, full = n * plan::tiles(g.Mdim, g.Ndim, Tile::BM, Tile::BN),

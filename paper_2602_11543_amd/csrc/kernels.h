@@ -22,15 +22,15 @@ int launch_router_aux(const float* logits, const float* lse, const int* offset, 
 // movement.hip (dtype = spes_dtype of the storage type)
 int launch_permute(int dtype, const void* x, const int* inv, int k, void* xp, int T, int d, hipStream_t s);
 int launch_combine(int dtype, const void* yp, const int* inv, const float* gate, void* y, int T, int d, int k, hipStream_t s);
-int launch_dx_gather(int dtype, const void* dxp, const int* inv, const float* dlogits, const void* w_router, const void* dxr,
-                     void* dx, int T, int d, int k, int M, hipStream_t s);
+// dx = the sum of each token's k rows of dxp plus dlogits W_r, on the matrix cores where there is a bf16 copy of dlogits; in the same
+// launch d_w_router[M,d] (+)= sum_p partial[p], p ascending
+int launch_dx_gather(int dtype, const void* dxp, const int* inv, const float* dlogits, const bf16_t* dlogits_bf, const void* w_router,
+                     void* dx, int T, int d, int k, int M, const float* partial, int n_partial, float* d_w_router, int accumulate,
+                     hipStream_t s);
 
 // dyp[inv[t*k+j],:] = gate[t,j] * dy[t,:], dgate[t,j] = <dy[t,:], yp[inv[t*k+j],:]> (movement.hip)
 int launch_grad_scatter(int dtype, const void* dy, const void* yp, const int* inv, const float* gate, void* dyp, float* dgate,
                         int T, int d, int k, hipStream_t s);
-
-// out[i] (+)= sum_p partial[p*n + i], p ascending (movement.hip)
-int launch_reduce_partials(const float* partial, int n_partial, long n, float* out, int accumulate, hipStream_t s);
 
 // merge.hip
 int launch_sync_merge(int dtype, int n_experts, long elems, int n_nodes, const void* const* node_store, const int* slot,

@@ -1,4 +1,4 @@
-// Loads from memory straight into LDS, for the GEMM kernels.
+// Loads from memory straight into LDS and transposing reads out of it, for the kernels on the matrix cores.
 #pragma once
 #include "common.h"
 
@@ -33,6 +33,19 @@ template <int N>
 __device__ __forceinline__ void wait_and_meet() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;      // an operand fragment of a 16 x 16 x 32 MFMA
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+// Transposing LDS read.  Within each group of 16 lanes, lane s supplies the address of four consecutive 16-bit
+// elements (think of them as row s of a 16 x 4 matrix); lane i receives column i%4 of rows i/4, i/4+4, i/4+8, i/4+12.
+// With lane s pointing at [k0 + s/4][r0 + 4*(s%4)] of a [k][row] tile, lane i gets k0..k0+3 of row r0+i.
+__device__ __forceinline__ uint2 lds_read_tr(const bf16_t* p) {
+  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+  return __builtin_bit_cast(uint2, v);
+}
+
 
 // Loads and stores of a lane's own through a buffer resource: zero, or nothing, at or beyond its end
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(unsigned long base, unsigned bytes) {

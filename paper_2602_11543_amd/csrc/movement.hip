@@ -3,6 +3,7 @@
 // counterparts.  All traffic is 16-byte vectors along the contiguous feature
 // dimension; sums run in fp32 in a fixed slot order and are rounded once.
 #include "kernels.h"
+#include "lds_load.h"
 
 namespace spes {
 namespace {
@@ -72,16 +73,45 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ yp, 
   }
 }
 
-// dx[t,:] = sum_j dxp[inv[t*k+j], :] + router part; one block per token.  The router part is either the row
-// dxr[t,:] computed beforehand, or sum_e dlogits[t,e] * w_router[e,:] formed here.
+// out[i] (+)= sum_p partial[p*n + i], p ascending: four elements per thread, n a multiple of four.  The partials are requested eight at a
+// time: one after the other, each load waited for, 32 of them took 10 to 12 us for a 32 x 2048 gradient.  (The router weight
+// gradient's sum is the work of a few blocks and has nothing to do with dx: they run ahead of the dx blocks in one launch.  As a launch of its
+// own it was 5 us.)
+struct Partials {
+  const float* partial;
+  float* out;
+  long n;
+  int n_partial, accumulate, blocks;       // 256 threads each
+};
+__device__ __forceinline__ void reduce_partials(const Partials& r) {
+  const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4, n = r.n;
+  if (i >= n) return;
+  constexpr int U = 8;
+  const float4 acc = r.accumulate ? *reinterpret_cast<const float4*>(r.out + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](const float4& v) { sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w; };
+  int p = 0;
+  for (; p + U <= r.n_partial; p += U) {
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(r.partial + (long)(p + u) * n + i);
+#pragma unroll
+    for (int u = 0; u < U; ++u) add(v[u]);
+  }
+  for (; p < r.n_partial; ++p) add(*reinterpret_cast<const float4*>(r.partial + (long)p * n + i));
+  *reinterpret_cast<float4*>(r.out + i) = make_float4(acc.x + sum.x, acc.y + sum.y, acc.z + sum.z, acc.w + sum.w);
+}
+
+// dx[t,:] = sum_j dxp[inv[t*k+j], :] + sum_e dlogits[t,e] * w_router[e,:]; one block per token
 template <typename T>
 __global__ __launch_bounds__(256) void dx_gather_kernel(const T* __restrict__ dxp, const int* __restrict__ inv,
                                                         const float* __restrict__ dlogits, const T* __restrict__ w_router,
-                                                        const T* __restrict__ dxr, T* __restrict__ dx, int d, int k, int M) {
+                                                        T* __restrict__ dx, int d, int k, int M, const Partials red) {
+  if ((int)blockIdx.x < red.blocks) { reduce_partials(red); return; }
   constexpr int N = Vec16<T>::N;
   __shared__ float dl[kMaxExperts];
   __shared__ int rows[kMaxExperts];
-  const long t = blockIdx.x;
+  const long t = (int)blockIdx.x - red.blocks;
   if (threadIdx.x < M) dl[threadIdx.x] = dlogits[t * M + threadIdx.x];
   if (threadIdx.x < k) rows[threadIdx.x] = inv[t * k + threadIdx.x];
   __syncthreads();
@@ -98,27 +128,125 @@ __global__ __launch_bounds__(256) void dx_gather_kernel(const T* __restrict__ dx
 #pragma unroll
       for (int i = 0; i < N; ++i) acc[i] += f[i];
     }
-    if (dxr != nullptr) {
+    for (int e = 0; e < M; ++e) {
       Vec16<T> q;
-      q.load_once(dxr + t * d + c * N);
+      q.load(w_router + (long)e * d + c * N);
       float f[N];
       q.unpack(f);
+      const float s = dl[e];
 #pragma unroll
-      for (int i = 0; i < N; ++i) acc[i] += f[i];
-    } else {
-      for (int e = 0; e < M; ++e) {
-        Vec16<T> q;
-        q.load(w_router + (long)e * d + c * N);
-        float f[N];
-        q.unpack(f);
-        const float s = dl[e];
-#pragma unroll
-        for (int i = 0; i < N; ++i) acc[i] = fmaf(s, f[i], acc[i]);
-      }
+      for (int i = 0; i < N; ++i) acc[i] = fmaf(s, f[i], acc[i]);
     }
     Vec16<T> o;
     o.pack(acc);
     o.store_once(dx + t * d + c * N);
+  }
+}
+
+// The same in bf16 storage with the router part on the matrix cores, from the bf16 copy of dlogits (M a multiple of 8): a wavefront takes 64
+// columns of `tokens` tokens, sixteen at a time.  Its panel of W_r goes through LDS once, into fragments that stay in registers; the
+// product of sixteen tokens is turned through LDS to where a token's row segment, 128 bytes of dxp, belongs to eight lanes.
+// The k rows of a token are all requested before the product is formed (KU > 0: k == KU).  Bound by the bytes of dxp and dx.  (As
+// a GEMM of its own the product was written and read once more, in bf16, and cost a launch, and the sum of dW_r's partials another: steps
+// of 3777 tokens 1536 x 1280 307 -> 296 us, 1531 tokens 512 x 352 151 -> 148, 16384 tokens 2048 x 1024 3727 -> 3667, 32768 tokens 4096 x
+// 1408 16.74 -> 16.63 ms.)
+template <int KU>
+__global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict__ dxp, const int* __restrict__ inv,
+                                                        const bf16_t* __restrict__ dlogits, const bf16_t* __restrict__ w_router,
+                                                        bf16_t* __restrict__ dx, int T, int d, int k, int M, int tokens, int col_blocks, const Partials red) {
+  if ((int)blockIdx.x < red.blocks) { reduce_partials(red); return; }
+  constexpr int WP = 72, OP = 68;                  // pitches: bf16 of a row of W_r's panel, floats of a token's product
+  static_assert(16 * OP * 4 <= 64 * WP * 2, "the products take the panel's place");
+  __shared__ __attribute__((aligned(16))) bf16_t panel[4][64 * WP];
+  const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6), l16 = lane & 15, lq = lane >> 4;
+  const int block = (int)blockIdx.x - red.blocks, tile = block / col_blocks;
+  const int c0 = (block - tile * col_blocks) * 256 + wave * 64, c = c0 + (lane & 7) * 8;
+  if (c0 >= d) return;                             // (the wavefronts of a block never meet)
+  const bool c_in = c < d;
+  bf16_t* const w = panel[wave];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int e = i * 8 + (lane >> 3);
+    *reinterpret_cast<uint4*>(w + e * WP + (lane & 7) * 8) =
+        e < M && c_in ? *reinterpret_cast<const uint4*>(w_router + (long)e * d + c) : make_uint4(0, 0, 0, 0);
+  }
+  __builtin_amdgcn_wave_barrier();
+  bf16x8 fw[4][2];                                 // column l16 of the panel's sixteen columns j, experts s*32 + lq*8 .. +7
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const bf16_t* const p = w + (s * 32 + lq * 8 + (l16 >> 2)) * WP + j * 16 + (lane & 3) * 4;
+      const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * WP);
+      fw[j][s] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    }
+  __builtin_amdgcn_wave_barrier();
+  float* const out = reinterpret_cast<float*>(w);
+  const int t_first = tile * tokens, t_end = t_first + tokens < T ? t_first + tokens : T;
+  for (int t0 = t_first; t0 < t_end; t0 += 16) {
+    // the lane's two tokens, their rows of dxp
+    constexpr int KV = KU > 0 ? KU : 1;
+    Vec16<bf16_t> q[2][KV];
+    long row[2][KV];
+    int tok[2];
+    bool live[2];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      tok[v] = t0 + v * 8 + (lane >> 3);
+      live[v] = tok[v] < t_end && c_in;
+#pragma unroll
+      for (int j = 0; j < KU; ++j) row[v][j] = live[v] ? inv[(long)tok[v] * KU + j] : -1;
+    }
+    bf16x8 fl[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const bool in = t0 + l16 < t_end && s * 32 + lq * 8 < M;
+      fl[s] = __builtin_bit_cast(bf16x8, in ? *reinterpret_cast<const uint4*>(dlogits + (long)(t0 + l16) * M + s * 32 + lq * 8) : make_uint4(0, 0, 0, 0));
+    }
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int j = 0; j < KU; ++j)
+        if (live[v]) q[v][j].load_once(dxp + row[v][j] * d + c); else q[v][j].raw = make_uint4(0, 0, 0, 0);
+    // prod[j][r] = the product of token l16 and column j*16 + lq*4 + r
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f32x4 prod = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 2; ++s) prod = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][s], fl[s], prod, 0, 0, 0);
+      *reinterpret_cast<float4*>(out + l16 * OP + j * 16 + lq * 4) = make_float4(prod[0], prod[1], prod[2], prod[3]);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      float acc[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+      auto add = [&](const Vec16<bf16_t>& x) {
+        float f[8];
+        x.unpack(f);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += f[i];
+      };
+      if (KU > 0) {
+#pragma unroll
+        for (int j = 0; j < KU; ++j) add(q[v][j]);
+      } else if (live[v]) {
+        for (int j = 0; j < k; ++j) {
+          q[v][0].load_once(dxp + (long)inv[(long)tok[v] * k + j] * d + c);
+          add(q[v][0]);
+        }
+      }
+      const float* const p = out + (v * 8 + (lane >> 3)) * OP + (lane & 7) * 8;
+      const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
+      const float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] += r[i];
+      Vec16<bf16_t> o;
+      o.pack(acc);
+      if (live[v]) o.store_once(dx + (long)tok[v] * d + c);
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -190,29 +318,6 @@ __global__ __launch_bounds__(256) void grad_scatter_kernel(const T* __restrict__
   if (tid < k) dgate[t * k + tid] = (part[tid][0] + part[tid][1]) + (part[tid][2] + part[tid][3]);   // fixed order
 }
 
-// One float4 per thread, wavefront-sized blocks (a router gradient is a few thousand float4, which must reach all CUs).  The
-// partials are requested eight at a time: one after the other, each load waited for, 32 of them took 10 to 12 us for a
-// 32 x 2048 gradient (64 of them 17 us for 8 x 256).
-__global__ __launch_bounds__(64) void reduce_partials_kernel(const float* __restrict__ partial, int n_partial, long n,
-                                                             float* __restrict__ out, int accumulate) {
-  const long i = ((long)blockIdx.x * 64 + threadIdx.x) * 4;
-  if (i >= n) return;
-  constexpr int U = 8;
-  const float4 acc = accumulate ? *reinterpret_cast<const float4*>(out + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto add = [&](const float4& v) { sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w; };
-  int p = 0;
-  for (; p + U <= n_partial; p += U) {
-    float4 v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(partial + (long)(p + u) * n + i);
-#pragma unroll
-    for (int u = 0; u < U; ++u) add(v[u]);
-  }
-  for (; p < n_partial; ++p) add(*reinterpret_cast<const float4*>(partial + (long)p * n + i));
-  *reinterpret_cast<float4*>(out + i) = make_float4(acc.x + sum.x, acc.y + sum.y, acc.z + sum.z, acc.w + sum.w);
-}
-
 inline int flat_grid(long total_vec) {
   long b = (total_vec + 255) / 256;       // one vector per thread where the grid allows it
   if (b < 1) b = 1;
@@ -278,19 +383,36 @@ int launch_grad_scatter(int dtype, const void* dy, const void* yp, const int* in
   return ok();
 }
 
-int launch_reduce_partials(const float* partial, int n_partial, long n, float* out, int accumulate, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(cdiv(n, 256)), dim3(64), 0, s, partial, n_partial, n, out, accumulate);
-  return ok();
-}
-
-int launch_dx_gather(int dtype, const void* dxp, const int* inv, const float* dlogits, const void* w_router, const void* dxr,
-                     void* dx, int T, int d, int k, int M, hipStream_t s) {
-  if (dtype == SPES_F32)
-    hipLaunchKernelGGL(dx_gather_kernel<float>, dim3(T), dim3(256), 0, s, (const float*)dxp, inv, dlogits,
-                       (const float*)w_router, (const float*)dxr, (float*)dx, d, k, M);
-  else
-    hipLaunchKernelGGL(dx_gather_kernel<bf16_t>, dim3(T), dim3(256), 0, s, (const bf16_t*)dxp, inv, dlogits,
-                       (const bf16_t*)w_router, (const bf16_t*)dxr, (bf16_t*)dx, d, k, M);
+int launch_dx_gather(int dtype, const void* dxp, const int* inv, const float* dlogits, const bf16_t* dlogits_bf, const void* w_router,
+                     void* dx, int T, int d, int k, int M, const float* partial, int n_partial, float* d_w_router, int accumulate,
+                     hipStream_t s) {
+  const long n = (long)M * d;
+  const Partials red = {partial, d_w_router, n, n_partial, accumulate, cdiv(n, 1024)};
+  if (dlogits_bf != nullptr) {
+    // tokens per wavefront: as many as leave four blocks per CU, so that W_r's panel is read for few of them only where tokens are few
+    const int cols = cdiv(d, 256);
+    int tokens = 64;
+    while (tokens > 16 && (long)cdiv(T, tokens) * cols < 1024) tokens /= 2;
+    const long blocks = (long)cdiv(T, tokens) * cols + red.blocks;
+    if (blocks > 0x7fffffffL) return SPES_ESHAPE;
+#define SPES_DX(KU) \
+  hipLaunchKernelGGL(dx_router_kernel<KU>, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t*)dxp, inv, dlogits_bf, \
+                     (const bf16_t*)w_router, (bf16_t*)dx, T, d, k, M, tokens, cols, red)
+    switch (k) {
+      case 1: SPES_DX(1); break;
+      case 2: SPES_DX(2); break;
+      case 4: SPES_DX(4); break;
+      case 8: SPES_DX(8); break;
+      default: SPES_DX(0);
+    }
+#undef SPES_DX
+  } else if (dtype == SPES_F32) {
+    hipLaunchKernelGGL(dx_gather_kernel<float>, dim3(T + red.blocks), dim3(256), 0, s, (const float*)dxp, inv, dlogits,
+                       (const float*)w_router, (float*)dx, d, k, M, red);
+  } else {
+    hipLaunchKernelGGL(dx_gather_kernel<bf16_t>, dim3(T + red.blocks), dim3(256), 0, s, (const bf16_t*)dxp, inv, dlogits,
+                       (const bf16_t*)w_router, (bf16_t*)dx, d, k, M, red);
+  }
   return ok();
 }
 
