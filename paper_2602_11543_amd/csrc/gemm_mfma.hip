@@ -607,7 +607,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   // loop ends, and in the middle of the arithmetic one or two at a time; nothing is formed of gate * h for an expert that does not train.  Before (batches of 12 loads
   // and 12 stores, each load waited for behind the stores before it) the half-width tiles took 22 800 cycles, now 18 600: steps of
   // 1531 tokens 512 x 352 163 -> 161 us, 4096 tokens 768 x 2048 489 -> 484, 3777 tokens 1536 x 1280 331 -> 327, 16384 tokens 2048 x 1024
-  // 3866 -> 3840.
+  // 3866 -> 3840.  a, b and the correction are read once, by streaming loads: the steps of 512 x 352 and 768 x 2048 0.7 to 1 % less, 2048 x
+  // 1024 3808 -> 3790.  (Streaming stores of its results, of h and of the other GEMMs: within 0.5 % either way.)
   const int ds_c8 = lane % DS_CPR;
   const long ds_n = n0 + wn * (BN / 2) + ds_c8 * 8;
   const int ds_rows = (int)(m_end - m0);                        // valid rows of the tile
@@ -635,7 +636,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   rsrc_t ds_v[DS_AHEAD][3];
   if constexpr (EARLY) {
     // The first of these loads are spread over the last two iterations, in registers that the main loop has to spare.
-    auto first_loads = [&](int n) { ds_v[n / 3][n % 3] = load16(ds_in[n % 3], ds_off(n / 3)); };
+    auto first_loads = [&](int n) { ds_v[n / 3][n % 3] = load16_once(ds_in[n % 3], ds_off(n / 3)); };
     constexpr int N2 = (2 * MF + EG - 1) / EG;             // by the next-to-last one
     static_assert(NSA == 3 && 2 * N2 >= DS_AHEAD * 3, "every K-tile and every one of these loads is requested");
     auto at_gap = [&](int q) { if (q % EG == 0 && q / EG < DS_AHEAD * 3) first_loads(q / EG); };
@@ -832,7 +833,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
           __builtin_amdgcn_sched_barrier(0);
           if (e2 == 0 && v + 1 < UPS) read_u(v + 1);
           if (unit > 0) {
-            if (e2 < 3 && far < DS_UNITS) ds_v[far % DS_AHEAD][e2] = load16(ds_in[e2], off_far);
+            if (e2 < 3 && far < DS_UNITS) ds_v[far % DS_AHEAD][e2] = load16_once(ds_in[e2], off_far);
             if (e2 == 1 || e2 == 3) store16(ds_out[e2 / 2], off_prev, po[e2 / 2]);
           }
           __builtin_amdgcn_sched_barrier(0);

@@ -51,7 +51,9 @@ __device__ __forceinline__ uint2 lds_read_tr(const bf16_t* p) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(unsigned long base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ rsrc_t load16(__amdgpu_buffer_rsrc_t rs, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0); }
+__device__ __forceinline__ rsrc_t load16_once(__amdgpu_buffer_rsrc_t rs, unsigned off) {      // (with the non-temporal hint)
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 2);
+}
 __device__ __forceinline__ float load4(__amdgpu_buffer_rsrc_t rs, unsigned off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
 }
