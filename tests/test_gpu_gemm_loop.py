@@ -44,6 +44,14 @@ def test_last_rows(T, d, f, device):
     _full_parity(layer_inputs(custom_config(**kw)), device, "last rows")
 
 
+# full tiles of the forward launch beyond a whole round of 256, by one expert's rows times the columns: 32 that are cut in two, alone and
+# beside half-height tiles, 167 that are not; the backward has launches of 9, which are cut, and of 144 and 207, which are not
+@pytest.mark.parametrize("T,d,f", [(2248, 256, 4096), (2148, 256, 4608), (2200, 128, 6016)])
+def test_last_round_of_full_tiles(T, d, f, device):
+    kw = dict(T=T, d=d, M=1, f=f, k=1, n_trainable=1, dtype="bf16", router_sigma=0.3)
+    _full_parity(layer_inputs(custom_config(**kw)), device, "last round")
+
+
 @pytest.mark.parametrize("T,d,f", [(60, 136, 200), (200, 1000, 136), (700, 960, 328), (700, 520, 520)])
 def test_values_stay_with_their_expert(T, d, f, device):
     """NaN weights of one expert: every result of tokens and experts that have nothing to do with it stays bit for bit."""
