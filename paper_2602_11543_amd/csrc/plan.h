@@ -34,7 +34,7 @@ inline int column_tail(int ndim) {
 // of a few thousand tokens), never for a launch of many rounds.  est_tiles: expected number of row tiles (0: unknown).
 // Step relative to full tiles throughout, mean (range) over 2129 cells of widths that are multiples of 256: 0.89 (0.81 to 1.09) where the
 // rule takes half-width tiles for either width, 0.97 (0.82 to 1.08) where for one; half-width ones for both cost 1.09 (1.00 to 1.16)
-// where it takes none.
+// where it takes none.  (Full tiles as they were before the last round of them was cut in two where it is at most half full.)
 inline bool few_tiles_narrow(int ndim, int est_tiles) {
   if (est_tiles <= 0 || ndim % kFullCols != 0) return false;
   const long full = (long)est_tiles * (ndim / kFullCols);
@@ -69,7 +69,9 @@ inline bool few_tiles_narrow(int ndim, int est_tiles) {
 // The load is not known here; an uneven one moves every line.  Over 10622 cells of the present loop (24 fixed and 3517 random shapes
 // under even, normal and Gumbel load) the choice takes 0.84 of the time of full tiles on average, is more than 2 % slower than they are
 // in 171 (at worst 22 %), and at least 10 % off the best height in 1928.  Most of those are wide layers beyond the line of 96 rows, where
-// 128-row tiles now take 0.86 of the choice's time up to 192 rows, 0.93 up to 256 and 0.96 up to 512, and 1.06 beyond.
+// 128-row tiles took 0.86 of the choice's time up to 192 rows, 0.93 up to 256 and 0.96 up to 512, and 1.06 beyond.  (All of these figures are
+// from before a last round of full tiles that is at most half full ran on half-height ones, which is what 128-row tiles gained there: 175
+// rows of 4096 x 1408 or 125 of 2048 x 1024 in each of 8 experts, a step 0.81 and 0.84 of its time before.)
 inline int row_tile(long rows, int n_experts, int d_model, int d_ff) {
   if (rows <= 48L * n_experts) return kQuarterRows;
   const bool narrow = d_model <= 896 && d_ff <= 4L * d_model;
