@@ -174,12 +174,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     }
   };
   bool ds_store2 = true;
-  unsigned expert = 0;
   if (MODE == kRaggedM) {
     // (each pair of scalar loads together: one round trip)
     int e = scalar_load(g.tile_expert + mt_all), row0 = scalar_load(g.tile_row0 + mt_all);
     asm volatile("" : "+s"(e), "+s"(row0));
-    expert = uniform((unsigned)e);
     ds_store2 = ((g.c2_skip >> e) & 1ull) == 0;
     m0 = row0 + half * plan::kHalfRows;
     const int end = scalar_load(g.offset + e + 1);
@@ -316,25 +314,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) uint4*)smem + (unsigned)wave * (SETS ? NA * 1024u : 1024u);
   struct Src { unsigned lo, hi, bytes, left, dst; };     // resource base and size; k left from the tile's first one on; LDS address
   Src as = {0, 0, 0, 0, 0}, bs = as;
-  // K-tile that the forward GEMMs begin with: they go round from there, from a place that the expert alone decides (its number with
-  // the bits reversed, in 64ths of the contraction).  Blocks that all began with the first K-tile would walk down the same 128 bytes of
-  // every row of K-contiguous weights, which with rows a power of two apart are the same few memory channels.  The row tiles, column tiles
-  // and batches of an expert share its start, so a token's results have the same bits wherever its tile lies, and the blocks
-  // that share panels in an XCD's L2 stay together.  Where the time is the stream of the weights, 200 tokens, 32 experts of 2048 x 2048,
-  // top-4: forward pass 233 -> 163 us (gate + up 160 -> 107, down 90 -> 50: 5 TB/s); 4096 tokens of that layer, a step 1259 -> 1240;
-  // 8 experts of 2048 x 6144, forward 683 -> 672; launches of many rounds, whose blocks drift apart by themselves, within 0.1 %.  Of
-  // [k][row] weights a K-tile is 64 whole runs of a row: the input gradients begin at 0 (with a start of their own 1 % slower at 3777 tokens
-  // 1536 x 1280, 16 experts).
-  constexpr bool ROTATE = MODE == kRaggedM && B_KC;
-  const int k_rot = ROTATE ? (int)(((__brev(expert) >> 26) * (unsigned)nk) >> 6) : 0;
+  // Every block takes the K-tiles in their order, so that a result's bits follow from its operands and not from the place of its
+  // tile or the number of its expert (copies of an expert, and its gate gradients, stay equal).  Blocks that start together then walk
+  // down the same 128 bytes of every row of K-contiguous weights, which with rows a power of two apart are the same few memory channels.
+  // A start of its own for each XCD or each expert avoids that (200 tokens, 32 experts of 2048 x 2048, top-4: forward 161 us against
+  // 232; 4096 tokens 1 %, longer launches nothing), but adds up equal rows in different orders.
   unsigned b1_lo = 0, b1_hi = 0;                         // fused SwiGLU: the base in the second matrix
   // in steps, so that the main loop can deal them out: 0 the k, 1 the base, 2 the size, 3 where to
   auto next_src = [&](Src& x, int step, int lt, unsigned per_k, unsigned long base0, unsigned long base1, unsigned bytes, unsigned dst) {
     const bool second = TWO_PASS && lt >= nk;
     if (step == 0) {
-      int kt = lt - (second ? nk : 0) + k_rot;
-      if (ROTATE) kt -= kt >= nk ? nk : 0;
-      x.left = (unsigned)(klen - kt * BK);
+      x.left = (unsigned)(klen - (lt - (second ? nk : 0)) * BK);
       pin(x.left);
     } else if (step == 1) {
       const unsigned long at = (second ? base1 : base0) + ((unsigned)klen - x.left) * per_k;
@@ -574,7 +564,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
   // by then every K-tile has been requested, A's NSA = 3 ahead and B's two or three
   const int n_main = EARLY ? (nsteps > 2 ? nsteps - 2 : 0) : nsteps;
   if constexpr (A_KC || B_KC || SETS) {
-    int last = klen % BK != 0 ? nk - 1 - k_rot : nsteps + FAR;        // the next K-tile that needs it
+    int last = klen % BK != 0 ? nk - 1 : nsteps + FAR;        // the next K-tile that needs it
     while (last + 1 < NEAR) last += nk;
     while (true) {
       const int stop = last - FAR < n_main ? last - FAR : n_main;

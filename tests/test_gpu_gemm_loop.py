@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # tokens, d_model, experts, d_ff, top-k: both widths are contraction lengths (forward and backward), 64 to a K-tile
 CASES = [
-    # 64-row tiles: blocks begin at K-tile 0 to 7 eighths of the contraction; 1, 2, 3, 5, 8, 9 and 13 K-tiles
+    # 64-row tiles: 1, 2, 3, 5, 8, 9 and 13 K-tiles
     (40, 64, 4, 128, 2), (40, 72, 4, 184, 2), (60, 320, 8, 512, 2), (60, 520, 8, 576, 2), (60, 776, 8, 832, 2),
     # 128-row tiles
     (96, 64, 2, 128, 2), (150, 328, 4, 136, 2), (150, 1000, 4, 200, 2),
@@ -28,12 +28,11 @@ def test_contraction_lengths(T, d, M, f, k, device):
     _full_parity(layer_inputs(custom_config(**kw)), device, "contraction lengths")
 
 
-# an expert's forward contractions begin at a K-tile of its own: 17 and 18 of them, the last one short, for up to 64 experts on 64-row
-# and on 256-row tiles
+# contractions of 17 and 18 K-tiles, the last one short, for up to 64 experts on 64-row and on 256-row tiles
 @pytest.mark.parametrize("T,d,M,f,k", [(300, 1096, 64, 1128, 4), (3300, 1096, 33, 136, 8)])
 def test_first_k_tiles_of_many_experts(T, d, M, f, k, device):
     kw = dict(T=T, d=d, M=M, f=f, k=k, n_trainable=2, trainable="random", dtype="bf16", router_sigma=0.02, bias="normal")
-    _full_parity(layer_inputs(custom_config(**kw)), device, "first K-tiles")
+    _full_parity(layer_inputs(custom_config(**kw)), device, "many experts")
 
 
 # one expert's rows around the heights of full and half tiles; with whole columns, a column tail, and on half-width tiles

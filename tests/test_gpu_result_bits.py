@@ -72,6 +72,28 @@ def test_a_token_has_the_same_output_in_any_batch(device):
         assert torch.equal(_bits(L.y[:190]), _bits(first)), T
 
 
+# 64-, 128- and 256-row tiles and fp32, several K-tiles with a remainder in both contractions
+@pytest.mark.parametrize("T,dtype", [(90, "bf16"), (180, "bf16"), (700, "bf16"), (180, "f32")])
+def test_equal_experts_have_equal_results(T, dtype, device):
+    """Experts that are copies of one another (an upcycled layer's first step) give a token's rows equal bits, so that its gate gradients are
+    equal, and with renormalised gates nothing but rounding is left of the score gradients."""
+    L = DeviceLayer(layer_inputs(custom_config(T=T, d=1032, M=8, f=776, k=4, renorm=1, n_trainable=2, dtype=dtype, router_sigma=0.3)), device)
+    print(f"[case] {T} {dtype}", flush=True)
+    for w in (L.w_gate, L.w_up, L.w_down):
+        w[1:] = w[:1].clone()
+    L.fwd(); L.bwd(); torch.cuda.synchronize()
+    row = L.view("inv").long().view(T, L.cfg.k)
+    out = {n: L.view(n)[row] for n in ("a", "b", "h", "yp")}
+    if dtype == "bf16":
+        out["correction"] = _correction(L)[row]
+    out["dgate"] = L.view("dgate")
+    for name, t in out.items():
+        assert torch.equal(_bits(t), _bits(t[:, :1]).expand(_bits(t).shape)), name
+    # g_i (D sum_{j != i} g_j - sum_{j != i} D g_j) and g_i (D - D sum_j g_j): products, sums of at most 64 terms by halves, and gates that
+    # add up to 1 but for their own rounding, each at most 2^-24 of D: fewer than 32 of them
+    assert (L.view("dlogits").abs().amax(1) <= 32 * 2.0 ** -24 * L.view("dgate").abs().amax(1)).all()
+
+
 def _pairs_whose_correction_shows_the_rounding(n):
     """a in [20, 32) and b in [16, 32), 24 bits each as three times eight, whose (a - bf16 a) bf16 b + a (b - bf16 b) is another bf16 value
     when the first product is rounded than when the second one is: the first is exact, the second has up to 40 bits."""
