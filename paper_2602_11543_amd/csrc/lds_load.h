@@ -45,7 +45,12 @@ __device__ __forceinline__ uint2 lds_read_tr(const bf16_t* p) {
   const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
   return __builtin_bit_cast(uint2, v);
 }
-
+// Between a wavefront's writes to LDS of its own and its reads of what other lanes wrote: the hardware runs them in the order of the program,
+// and the compiler, whatever types they have, leaves them in it.  No instruction.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // Loads and stores of a lane's own through a buffer resource: zero, or nothing, at or beyond its end
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(unsigned long base, unsigned bytes) {

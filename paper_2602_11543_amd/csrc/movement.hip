@@ -146,8 +146,9 @@ __global__ __launch_bounds__(256) void dx_gather_kernel(const T* __restrict__ dx
 // The same in bf16 storage with the router part on the matrix cores, from the bf16 copy of dlogits (M a multiple of 8): a wavefront takes 64
 // columns of `tokens` tokens, sixteen at a time.  Its panel of W_r goes through LDS once, into fragments that stay in registers; the
 // product of sixteen tokens is turned through LDS to where a token's row segment, 128 bytes of dxp, belongs to eight lanes.
+// The product is rounded to bf16 before it is added: a token's router part is a value of the storage type, as when it was a GEMM's result.
 // The k rows of a token are all requested before the product is formed (KU > 0: k == KU).  Bound by the bytes of dxp and dx.  (As
-// a GEMM of its own the product was written and read once more, in bf16, and cost a launch, and the sum of dW_r's partials another: steps
+// a GEMM of its own the product was written and read once more, and cost a launch, and the sum of dW_r's partials another: steps
 // of 3777 tokens 1536 x 1280 307 -> 296 us, 1531 tokens 512 x 352 151 -> 148, 16384 tokens 2048 x 1024 3727 -> 3667, 32768 tokens 4096 x
 // 1408 16.74 -> 16.63 ms.)
 template <int KU>
@@ -155,8 +156,7 @@ __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict
                                                         const bf16_t* __restrict__ dlogits, const bf16_t* __restrict__ w_router,
                                                         bf16_t* __restrict__ dx, int T, int d, int k, int M, int tokens, int col_blocks, const Partials red) {
   if ((int)blockIdx.x < red.blocks) { reduce_partials(red); return; }
-  constexpr int WP = 72, OP = 68;                  // pitches: bf16 of a row of W_r's panel, floats of a token's product
-  static_assert(16 * OP * 4 <= 64 * WP * 2, "the products take the panel's place");
+  constexpr int WP = 72;                           // pitch of a row of W_r's panel, and of a token's product, which take its place
   __shared__ __attribute__((aligned(16))) bf16_t panel[4][64 * WP];
   const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6), l16 = lane & 15, lq = lane >> 4;
   const int block = (int)blockIdx.x - red.blocks, tile = block / col_blocks;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict
     *reinterpret_cast<uint4*>(w + e * WP + (lane & 7) * 8) =
         e < M && c_in ? *reinterpret_cast<const uint4*>(w_router + (long)e * d + c) : make_uint4(0, 0, 0, 0);
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   bf16x8 fw[4][2];                                 // column l16 of the panel's sixteen columns j, experts s*32 + lq*8 .. +7
 #pragma unroll
   for (int j = 0; j < 4; ++j)
@@ -180,8 +180,7 @@ __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict
       const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * WP);
       fw[j][s] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
-  __builtin_amdgcn_wave_barrier();
-  float* const out = reinterpret_cast<float*>(w);
+  wave_lds_order();
   const int t_first = tile * tokens, t_end = t_first + tokens < T ? t_first + tokens : T;
   for (int t0 = t_first; t0 < t_end; t0 += 16) {
     // the lane's two tokens, their rows of dxp
@@ -214,9 +213,9 @@ __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict
       f32x4 prod = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 2; ++s) prod = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][s], fl[s], prod, 0, 0, 0);
-      *reinterpret_cast<float4*>(out + l16 * OP + j * 16 + lq * 4) = make_float4(prod[0], prod[1], prod[2], prod[3]);
+      *reinterpret_cast<uint2*>(w + l16 * WP + j * 16 + lq * 4) = make_uint2(pack_bf16x2(prod[0], prod[1]), pack_bf16x2(prod[2], prod[3]));
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       float acc[8];
@@ -237,16 +236,14 @@ __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict
           add(q[v][0]);
         }
       }
-      const float* const p = out + (v * 8 + (lane >> 3)) * OP + (lane & 7) * 8;
-      const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
-      const float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += r[i];
+      Vec16<bf16_t> r;
+      r.raw = *reinterpret_cast<const uint4*>(w + (v * 8 + (lane >> 3)) * WP + (lane & 7) * 8);
+      add(r);
       Vec16<bf16_t> o;
       o.pack(acc);
       if (live[v]) o.store_once(dx + (long)tok[v] * d + c);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
   }
 }
 
