@@ -143,32 +143,36 @@ __global__ __launch_bounds__(256) void dx_gather_kernel(const T* __restrict__ dx
   }
 }
 
-// The same in bf16 storage with the router part on the matrix cores, from the bf16 copy of dlogits (M a multiple of 8): a wavefront takes 64
-// columns of `tokens` tokens, sixteen at a time.  Its panel of W_r goes through LDS once, into fragments that stay in registers; the
-// product of sixteen tokens is turned through LDS to where a token's row segment, 128 bytes of dxp, belongs to eight lanes.
-// The product is rounded to bf16 before it is added: a token's router part is a value of the storage type, as when it was a GEMM's result.
-// The k rows of a token are all requested before the product is formed (KU > 0: k == KU).  Bound by the bytes of dxp and dx.  (As
-// a GEMM of its own the product was written and read once more, and cost a launch, and the sum of dW_r's partials another: steps
-// of 3777 tokens 1536 x 1280 307 -> 296 us, 1531 tokens 512 x 352 151 -> 148, 16384 tokens 2048 x 1024 3727 -> 3667, 32768 tokens 4096 x
-// 1408 16.74 -> 16.63 ms.)
-template <int KU>
+// The same in bf16 storage with the router part on the matrix cores, from the bf16 copy of dlogits (M a multiple of 8): a block takes 256
+// columns of `tokens` tokens, sixteen at a time.  A wavefront's 64 columns of W_r go through LDS once, into fragments that stay in registers;
+// its product of sixteen tokens goes through LDS, as a value of the storage type, to the 32 lanes that hold a token's 512 bytes of dxp.
+// Up to eight rows of a token (KU) are all requested before the product is formed, further ones (MORE) eight at a time, with their
+// places in dxp known by then.  Bound by the bytes of dxp and dx.  (As a GEMM of its own the product was written and read once more, and cost a
+// launch, and the sum of dW_r's partials another.)  Where d is no multiple of 64, rows begin within a 128-byte line, and two wavefronts
+// read the line between them: with eight lanes to a row every second one, and a streaming load drops it for the other.  So a row is 32 lanes
+// wide, and such rows (LINES false) come by plain loads, which cost 4 to 15 % where d is a multiple.  The router's products, the sum and dx, in us: as
+// launches of their own / one launch, eight lanes to a row, rows one by one where k is not 1, 2, 4 or 8 / now
+//   64 experts, 20000 tokens x 520   k = 4: 72 / 58 / 47     k = 7: 84 / 107 / 65    k = 8: 85 / 87 / 72     k = 16: 131 / 210 / 129
+//   16384 x 2056                     k = 4: 143 / 169 / 133  k = 7: 190 / 250 / 186  k = 8: 196 / 265 / 193  k = 16: 305 / 418 / 299
+//   16384 x 2048                     k = 4: 128 / 102 / 102  k = 7: 172 / 199 / 147  k = 8: 180 / 161 / 162  k = 16: 279 / 364 / 271
+//   1531 x 512                       k = 4: 24 / 16 / 16     k = 7: 25 / 24 / 18     k = 8: 25 / 18 / 18     k = 16: 27 / 35 / 21
+template <int KU, bool MORE, bool LINES>
 __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict__ dxp, const int* __restrict__ inv,
                                                         const bf16_t* __restrict__ dlogits, const bf16_t* __restrict__ w_router,
                                                         bf16_t* __restrict__ dx, int T, int d, int k, int M, int tokens, int col_blocks, const Partials red) {
   if ((int)blockIdx.x < red.blocks) { reduce_partials(red); return; }
-  constexpr int WP = 72;                           // pitch of a row of W_r's panel, and of a token's product, which take its place
-  __shared__ __attribute__((aligned(16))) bf16_t panel[4][64 * WP];
-  const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6), l16 = lane & 15, lq = lane >> 4;
+  constexpr int WP = 72, OP = 264;                 // pitches of a wavefront's panel of W_r and of a token's product over the block's columns
+  __shared__ __attribute__((aligned(16))) bf16_t lds[4 * 64 * WP];       // the four panels, then two sets of products in turn
+  static_assert(2 * 16 * OP <= 4 * 64 * WP, "the products take the panels' place");
+  const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform(tid >> 6), l16 = lane & 15, lq = lane >> 4;
   const int block = (int)blockIdx.x - red.blocks, tile = block / col_blocks;
-  const int c0 = (block - tile * col_blocks) * 256 + wave * 64, c = c0 + (lane & 7) * 8;
-  if (c0 >= d) return;                             // (the wavefronts of a block never meet)
-  const bool c_in = c < d;
-  bf16_t* const w = panel[wave];
+  const int c0 = (block - tile * col_blocks) * 256, w0 = c0 + wave * 64;
+  bf16_t* const w = lds + wave * 64 * WP;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int e = i * 8 + (lane >> 3);
+    const int e = i * 8 + (lane >> 3), col = w0 + (lane & 7) * 8;
     *reinterpret_cast<uint4*>(w + e * WP + (lane & 7) * 8) =
-        e < M && c_in ? *reinterpret_cast<const uint4*>(w_router + (long)e * d + c) : make_uint4(0, 0, 0, 0);
+        e < M && col < d ? *reinterpret_cast<const uint4*>(w_router + (long)e * d + col) : make_uint4(0, 0, 0, 0);
   }
   wave_lds_order();
   bf16x8 fw[4][2];                                 // column l16 of the panel's sixteen columns j, experts s*32 + lq*8 .. +7
@@ -180,70 +184,91 @@ __global__ __launch_bounds__(256) void dx_router_kernel(const bf16_t* __restrict
       const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * WP);
       fw[j][s] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
-  wave_lds_order();
+  __syncthreads();
+  // lanes to a token's row, as a power of two: 32, in the last columns as few as cover them
+  const int width = d - c0 < 256 ? d - c0 : 256, lanes = width > 128 ? 5 : width > 64 ? 4 : 3;
+  const int cl = (tid & ((1 << lanes) - 1)) * 8, c = c0 + cl;
   const int t_first = tile * tokens, t_end = t_first + tokens < T ? t_first + tokens : T;
   for (int t0 = t_first; t0 < t_end; t0 += 16) {
-    // the lane's two tokens, their rows of dxp
-    constexpr int KV = KU > 0 ? KU : 1;
-    Vec16<bf16_t> q[2][KV];
-    long row[2][KV];
-    int tok[2];
+    bf16_t* const out = lds + ((t0 - t_first) & 16 ? 16 * OP : 0);
+    // the lane's two tokens, KU of their rows of dxp
+    Vec16<bf16_t> q[2][KU];
+    int row[2][KU], tok[2];
     bool live[2];
+    auto find = [&](int first) {
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int j = 0; j < KU; ++j) row[v][j] = live[v] && (!MORE || first + j < k) ? inv[(long)tok[v] * (MORE ? k : KU) + first + j] : -1;
+    };
+    auto request = [&]() {
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int j = 0; j < KU; ++j) {
+          const bf16_t* const p = dxp + (long)row[v][j] * d + c;
+          if (row[v][j] < 0) q[v][j].raw = make_uint4(0, 0, 0, 0);
+          else if (LINES) q[v][j].load_once(p);
+          else q[v][j].load(p);
+        }
+    };
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
-      tok[v] = t0 + v * 8 + (lane >> 3);
-      live[v] = tok[v] < t_end && c_in;
-#pragma unroll
-      for (int j = 0; j < KU; ++j) row[v][j] = live[v] ? inv[(long)tok[v] * KU + j] : -1;
+      const int at = (v << (8 - lanes)) + (tid >> lanes);
+      tok[v] = t0 + at;
+      live[v] = at < 16 && tok[v] < t_end && c < d;
     }
+    find(0);
     bf16x8 fl[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const bool in = t0 + l16 < t_end && s * 32 + lq * 8 < M;
       fl[s] = __builtin_bit_cast(bf16x8, in ? *reinterpret_cast<const uint4*>(dlogits + (long)(t0 + l16) * M + s * 32 + lq * 8) : make_uint4(0, 0, 0, 0));
     }
-#pragma unroll
-    for (int v = 0; v < 2; ++v)
-#pragma unroll
-      for (int j = 0; j < KU; ++j)
-        if (live[v]) q[v][j].load_once(dxp + row[v][j] * d + c); else q[v][j].raw = make_uint4(0, 0, 0, 0);
+    request();
+    if (MORE) find(KU);
     // prod[j][r] = the product of token l16 and column j*16 + lq*4 + r
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       f32x4 prod = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 2; ++s) prod = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][s], fl[s], prod, 0, 0, 0);
-      *reinterpret_cast<uint2*>(w + l16 * WP + j * 16 + lq * 4) = make_uint2(pack_bf16x2(prod[0], prod[1]), pack_bf16x2(prod[2], prod[3]));
+      *reinterpret_cast<uint2*>(out + l16 * OP + wave * 64 + j * 16 + lq * 4) = make_uint2(pack_bf16x2(prod[0], prod[1]), pack_bf16x2(prod[2], prod[3]));
     }
-    wave_lds_order();
+    __syncthreads();                               // (the products' other half is written when all have read it: behind the next of these)
+    float acc[2][8];
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[v][i] = 0.f;
+    auto add = [&](int v, const Vec16<bf16_t>& x) {
+      float f[8];
+      x.unpack(f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[v][i] += f[i];
+    };
+    auto add_rows = [&]() {
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int j = 0; j < KU; ++j) add(v, q[v][j]);
+    };
+    add_rows();
+    if (MORE)
+      for (int first = KU; first < k; first += KU) {
+        request();
+        find(first + KU);
+        add_rows();
+      }
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
-      float acc[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-      auto add = [&](const Vec16<bf16_t>& x) {
-        float f[8];
-        x.unpack(f);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += f[i];
-      };
-      if (KU > 0) {
-#pragma unroll
-        for (int j = 0; j < KU; ++j) add(q[v][j]);
-      } else if (live[v]) {
-        for (int j = 0; j < k; ++j) {
-          q[v][0].load_once(dxp + (long)inv[(long)tok[v] * k + j] * d + c);
-          add(q[v][0]);
-        }
-      }
-      Vec16<bf16_t> r;
-      r.raw = *reinterpret_cast<const uint4*>(w + (v * 8 + (lane >> 3)) * WP + (lane & 7) * 8);
-      add(r);
-      Vec16<bf16_t> o;
-      o.pack(acc);
-      if (live[v]) o.store_once(dx + (long)tok[v] * d + c);
+      if (!live[v]) continue;
+      Vec16<bf16_t> r, o;
+      r.raw = *reinterpret_cast<const uint4*>(out + (tok[v] - t0) * OP + cl);
+      add(v, r);
+      o.pack(acc[v]);
+      o.store_once(dx + (long)tok[v] * d + c);
     }
-    wave_lds_order();
   }
 }
 
@@ -386,21 +411,28 @@ int launch_dx_gather(int dtype, const void* dxp, const int* inv, const float* dl
   const long n = (long)M * d;
   const Partials red = {partial, d_w_router, n, n_partial, accumulate, cdiv(n, 1024)};
   if (dlogits_bf != nullptr) {
-    // tokens per wavefront: as many as leave four blocks per CU, so that W_r's panel is read for few of them only where tokens are few
+    // tokens per block: as many as leave four blocks per CU, so that W_r's panel is read for few of them only where tokens are few
     const int cols = cdiv(d, 256);
     int tokens = 64;
     while (tokens > 16 && (long)cdiv(T, tokens) * cols < 1024) tokens /= 2;
     const long blocks = (long)cdiv(T, tokens) * cols + red.blocks;
     if (blocks > 0x7fffffffL) return SPES_ESHAPE;
-#define SPES_DX(KU) \
-  hipLaunchKernelGGL(dx_router_kernel<KU>, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t*)dxp, inv, dlogits_bf, \
-                     (const bf16_t*)w_router, (bf16_t*)dx, T, d, k, M, tokens, cols, red)
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t*)dxp, inv, dlogits_bf, (const bf16_t*)w_router,
+                         (bf16_t*)dx, T, d, k, M, tokens, cols, red);
+    };
+#define SPES_DX(KU, MORE) \
+  if (d % 64 == 0) launch(dx_router_kernel<KU, MORE, true>); else launch(dx_router_kernel<KU, MORE, false>)
     switch (k) {
-      case 1: SPES_DX(1); break;
-      case 2: SPES_DX(2); break;
-      case 4: SPES_DX(4); break;
-      case 8: SPES_DX(8); break;
-      default: SPES_DX(0);
+      case 1: SPES_DX(1, false); break;
+      case 2: SPES_DX(2, false); break;
+      case 3: SPES_DX(3, false); break;
+      case 4: SPES_DX(4, false); break;
+      case 5: SPES_DX(5, false); break;
+      case 6: SPES_DX(6, false); break;
+      case 7: SPES_DX(7, false); break;
+      case 8: SPES_DX(8, false); break;
+      default: SPES_DX(8, true);
     }
 #undef SPES_DX
   } else if (dtype == SPES_F32) {

@@ -10,8 +10,7 @@ from harness import DeviceLayer
 
 pytestmark = pytest.mark.gpu
 
-# one token, remainders of 16 tokens and of 64 columns, whole and partial sets of 64 experts, 16 and 64 tokens a wavefront, each number
-# of rows per token that has a kernel of its own and one that has none
+# one token, remainders of 16 tokens and of 64 columns, whole and partial sets of 64 experts, 16 and 64 tokens a block
 CASES = [dict(T=1, d=72, M=8, k=1), dict(T=17, d=264, M=24, k=3), dict(T=65, d=520, M=64, k=8), dict(T=250, d=64, M=16, k=2),
          dict(T=1030, d=776, M=40, k=4), dict(T=8200, d=2056, M=32, k=1)]
 
@@ -45,8 +44,9 @@ def _expert_rows(L):
     return L.ctx[at:][:T * k * d * 2].view(torch.bfloat16).view(T * k, d)
 
 
-# 16, 32 and 64 tokens a wavefront, each with a last group that is not whole; fewer experts than rows at a time, and more
-@pytest.mark.parametrize("T,d,M", [(250, 520, 16), (4100, 2056, 24), (8203, 2056, 16)])
+# 16, 32 and 64 tokens a block, each with a last group that is not whole; last columns of 8, 128 and 200, rows of whole lines and others; up to
+# eight rows a token, and one, five and eight more
+@pytest.mark.parametrize("T,d,M", [(250, 520, 16), (300, 384, 16), (1030, 456, 40), (4100, 2056, 24), (8203, 2056, 16)])
 @pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 16])
 def test_expert_rows_and_router_part(T, d, M, k, device):
     """dx is the fp32 sum of a token's rows, slot by slot, plus the bf16 router part, rounded to bf16, bit for bit: with two powers of two in
