@@ -43,7 +43,6 @@ namespace spes {
 namespace {
 
 constexpr int kXcds = 8;
-constexpr unsigned kRound = 256;      // tiles that run at once, one per CU
 
 template <int BM_, int BN_, int NSA_, int NSB_, int MINB_>
 struct Cfg {
@@ -865,14 +864,12 @@ __global__ __launch_bounds__(256, C::MINB) void gemm_mfma_kernel(const GemmArgs 
   if (MODE == kRaggedM) asm volatile("" : "+s"(all), "+s"(full));          // one round trip
   if constexpr (C::BM != CH::BM) {
     static_assert(MODE == kRaggedM && CH::BN == C::BN && CH::BM == plan::kHalfRows, "the table's short tiles, the same columns");
-    // The table has the full tiles first.  A last round of them that is at most half full goes to half-height ones, two for one, where
-    // these and the table's own half-height ones still are one round: 0.65 of a full round instead of a whole one (beyond one round they are
-    // two, 1.3).  Steps: 700 tokens 4096 x 1408, 8 experts top-2 413 -> 335 us, 1200 tokens 1032 x 1000, 12 experts 248 -> 195, 500 tokens 2048 x
+    // The table has the full tiles first; the last round of them is cut in two where plan::tiles_cut says so.  Steps: 700 tokens 4096 x 1408, 8 experts top-2 413 -> 335 us, 1200 tokens 1032 x 1000, 12 experts 248 -> 195, 500 tokens 2048 x
     // 1024, 8 experts 175 -> 147, 3777 tokens 1536 x 1280, 16 experts 298 -> 288, 9000 tokens 2048 x 1024, 8 experts top-1 457 -> 431; eight
     // others 1.00 to 1.07 faster, launches of many rounds within 0.5 %.  Results are the same on either height.  The blocks of either height are dealt to the XCDs by themselves.
     const unsigned gx = (unsigned)cdiv(g.Ndim - g.n_base, EPI == kEpiSwiglu ? C::BN / 2 : C::BN);
-    const unsigned tall = (unsigned)full * gx, rest = tall % kRound, shorts = (unsigned)(all - full) * gx;
-    const unsigned cut = 2 * rest + shorts <= kRound ? rest : 0u, whole = tall - cut;
+    const unsigned tall = (unsigned)full * gx, shorts = (unsigned)(all - full) * gx;
+    const unsigned cut = plan::tiles_cut(tall, shorts), whole = tall - cut;
     const unsigned first_short = (whole + kXcds - 1) / kXcds * kXcds;
     if (blockIdx.x >= first_short) {
       const unsigned at = dealt(blockIdx.x - first_short, 2 * cut + shorts);
@@ -941,7 +938,7 @@ int launch(const GemmArgs& g, hipStream_t s) {
   if (SETS) total *= g.n_sets;
   if (total <= 0) return SPES_OK;
   total = (total + kXcds - 1) / kXcds * kXcds;
-  if (C::BM != CH::BM) total += kXcds + kRound / 2;       // two kinds of tiles: rounded up twice, and up to half a round of them cut in two
+  if (C::BM != CH::BM) total += kXcds + plan::kRound / 2;       // two kinds of tiles: rounded up twice, and up to half a round of them cut in two
   hipLaunchKernelGGL((gemm_mfma_kernel<MODE, EPI, A_KC, B_KC, SETS, C, CH>), dim3((unsigned)total), dim3(256), 0, s, g);
   return hipGetLastError() == hipSuccess ? SPES_OK : SPES_EHIP;
 }

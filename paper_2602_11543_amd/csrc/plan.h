@@ -22,6 +22,14 @@ inline long set_grid_tiles(const int* rows, const int* cols, int n_sets, int bm,
   return most;
 }
 
+// Full tiles of a launch that run as pairs of half-height ones (asked on the device, where the counts are known): a last round of them that is
+// at most half full, where the pairs and the launch's half-height tiles still are one round.  That costs 0.65 of a full round instead of a
+// whole one; beyond one round they are two, 1.3.  A launch of up to 128 full tiles has no others left.
+constexpr unsigned kRound = 256;      // tiles that run at once, one per CU
+constexpr unsigned tiles_cut(unsigned full, unsigned half_height) {
+  return 2 * (full % kRound) + half_height <= kRound ? full % kRound : 0u;
+}
+
 // Columns of a ragged-row GEMM on full tiles that run as a launch of their own, on half-width tiles: a last column tile
 // that is at most half full.
 inline int column_tail(int ndim) {

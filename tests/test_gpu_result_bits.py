@@ -41,12 +41,14 @@ def _equal_tokens(kw, n_base, device):
 
 
 # Long contractions and experts with several row tiles: 64-, 128- and 256-row ones (those with a half-height last tile, with a column
-# tail and on half-width tiles as well), and both tiles of fp32 layers.
+# tail and on half-width tiles as well: launches of few tiles, which run at half the height), launches with both whole tiles and such that are
+# cut in two, and both tiles of fp32 layers.
 SKEWED = dict(bias="normal", bias_scale=2.0)
 POSITIONS = [
     (dict(T=384, d=1032, M=8, f=776, k=1, dtype="bf16", **SKEWED), 96, 64), (dict(T=192, d=2048, M=8, f=1024, k=2, dtype="bf16", **SKEWED), 64, 64),
     (dict(T=760, d=1032, M=8, f=392, k=1, dtype="bf16", **SKEWED), 190, 128),
     (dict(T=1800, d=1024, M=8, f=968, k=2, dtype="bf16"), 450, 256), (dict(T=1803, d=1032, M=8, f=1024, k=1, dtype="bf16", **SKEWED), 401, 256),
+    (dict(T=4452, d=184, M=1, f=4040, k=1, dtype="bf16"), 100, 256),
     (dict(T=290, d=520, M=8, f=264, k=2), 70, 32), (dict(T=4100, d=264, M=8, f=520, k=4), 1000, 64),
 ]
 

@@ -7,6 +7,7 @@ from test_gpu_layer import _full_parity
 
 pytestmark = pytest.mark.gpu
 
+# (256-row tiles in launches of up to 128 of them run as pairs of half-height ones; test_gpu_gemm_loop.py has larger ones)
 # case, rows per tile, and how full tiles cut the columns of the down projection: a tail of that many columns on half-width
 # tiles, half-width tiles throughout, or full ones (test_plan.py checks both)
 CASES = [

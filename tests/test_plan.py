@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from test_gpu_gemm_f32 import CASES as F32_CASES
+from test_gpu_gemm_loop import FULL_HEIGHT
 from test_gpu_result_bits import MASKS, POSITIONS
 from test_gpu_large_f32 import BEYOND
 from test_gpu_row_tiles import CASES
@@ -20,6 +21,7 @@ long set_grid_tiles(const int* m, const int* n, int sets, int bm, int bn) { retu
 int wgrad_small_tiles(long full, long small, int mean, int most) { return plan::wgrad_small_tiles(full, small, mean, most); }
 int row_tile(long rows, int experts, int d, int f) { return plan::row_tile(rows, experts, d, f); }
 int rowdot_parts(int n, int row_tile, int est) { return plan::rowdot_parts(n, row_tile, est); }
+unsigned tiles_cut(unsigned full, unsigned half_height) { return plan::tiles_cut(full, half_height); }
 int column_tail(int n) { return plan::column_tail(n); }
 int few_tiles_narrow(int n, int est) { return plan::few_tiles_narrow(n, est); }
 int f32_row_tile(long rows, int experts, int d, int f) { return plan::f32_row_tile(rows, experts, d, f); }
@@ -117,6 +119,39 @@ def test_the_layer_cases_take_the_tiles_they_are_for(plan, kw, rows, down):
 def test_the_position_cases_take_the_tiles_they_are_for(plan, kw, n_base, rows):
     rule = plan.row_tile if kw.get("dtype") == "bf16" else plan.f32_row_tile
     assert rule(kw["T"] * kw["k"], kw["M"], kw["d"], kw["f"]) == rows
+
+
+def test_tiles_cut(plan):
+    for full, half, want in ((0, 9, 0), (1, 0, 1), (128, 0, 128), (129, 0, 0), (128, 1, 0), (100, 56, 100), (100, 57, 0), (256, 0, 0),
+                             (257, 254, 1), (257, 255, 0), (384, 0, 128), (385, 0, 0)):
+        assert plan.tiles_cut(full, half) == want, (full, half)
+
+
+def _whole(plan, rows, cols, width):
+    """Tiles of one expert's `rows` rows and of `cols` columns that are left at full height."""
+    gx, full, half = -(-cols // width), rows // 256 + (rows % 256 > 128), int(0 < rows % 256 <= 128)
+    return full * gx - plan.tiles_cut(full * gx, half * gx)
+
+
+@pytest.mark.parametrize("T,d,f,whole,tails", FULL_HEIGHT)
+def test_the_full_height_cases_have_whole_tiles(plan, T, d, f, whole, tails):
+    assert plan.row_tile(T, 1, d, f) == 256
+    got, got_tails = [_whole(plan, T, f, 128)], []
+    for n in (f, d):
+        tail = plan.column_tail(n)
+        got.append(_whole(plan, T, n - tail, 128 if not tail and plan.few_tiles_narrow(n, T // 256 + 1) else 256))
+        got_tails.append(_whole(plan, T, tail, 128) if tail else 0)
+    assert (tuple(got), tuple(got_tails)) == (whole, tails)
+
+
+def test_a_position_case_has_both_heights_in_one_launch(plan):
+    both = [kw for kw, _, rows in POSITIONS if rows == 256 and kw["M"] == 1]
+    assert both
+    for kw in both:
+        T, f = kw["T"], kw["f"]
+        for width in (128, 256):          # gate + up, SwiGLU backward
+            full = (T // 256 + (T % 256 > 128)) * -(-f // width)
+            assert 0 < _whole(plan, T, f, width) < full and not plan.column_tail(f) and not plan.few_tiles_narrow(f, T // 256 + 1)
 
 
 @pytest.mark.parametrize("kw,numbers", MASKS)
