@@ -636,10 +636,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, uint4* const smem, 
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(DS_AHEAD * 3) : "memory");      // no load may still write the LDS that the epilogue uses
   }
   // fp32 store epilogue: lanes along the columns, four of them per lane.  When the result is added to what is there,
-  // the old values of a whole 32-row slab are requested before the previous slab is stored (see load_ab: a load behind
-  // a store waits for that store, and one load, add, store chain per two rows would be 64 round trips a tile; with the
-  // three matrices in one launch this took a step of gradient accumulation at 4096 tokens, 2048 x 2048, 8 of 32 experts
-  // from 1619 to 1471 us).  Only launches over operand sets add; the others keep neither the registers nor the code of it,
+  // the old values of a whole 32-row slab are requested before the previous slab is stored (loads and stores share one counter,
+  // which counts them off in order: a load behind a store waits for that store, and one load, add, store chain per two rows would be
+  // 64 round trips a tile; with the three matrices in one launch this took a step of gradient accumulation at 4096 tokens, 2048 x 2048, 8 of 32
+  // experts from 1619 to 1471 us).  Only launches over operand sets add; the others keep neither the registers nor the code of it,
   // with which the down projection and the router GEMMs took 1 to 7 % longer (32768 tokens 4096 x 1408: 2955 -> 2923,
   // 77 -> 72 and 105 -> 102 us)
   constexpr int F_CPR = ECOLS / 4, F_RPI = 64 / F_CPR, F_NST = 32 / F_RPI;

@@ -40,9 +40,10 @@ inline int column_tail(int ndim) {
 // Few tiles: a launch costs its number of rounds of 256 concurrent tiles, the last of them partly empty.  Half-width
 // tiles cost 0.6 of a full one each and fill the rounds better; they are taken where that arithmetic says so (a layer
 // of a few thousand tokens), never for a launch of many rounds.  est_tiles: expected number of row tiles (0: unknown).
-// Step relative to full tiles throughout, mean (range) over 2129 cells of widths that are multiples of 256: 0.89 (0.81 to 1.09) where the
-// rule takes half-width tiles for either width, 0.97 (0.82 to 1.08) where for one; half-width ones for both cost 1.09 (1.00 to 1.16)
-// where it takes none.  (Full tiles as they were before the last round of them was cut in two where it is at most half full.)
+// Step relative to full tiles throughout, mean (range of 96 %) over 7457 cells of widths that are multiples of 256, random layers under even,
+// normal and Gumbel load: 0.95 (0.84 to 1.11) where the rule takes half-width tiles for both widths, 1.01 (0.91 to 1.11) where for one; half-width
+// ones for both cost 1.10 (1.02 to 1.16) where it takes none.  The arithmetic counts whole rounds, and since a last round of full tiles may be
+// cut (tiles_cut) it lies off where that happens: where one width takes half-width tiles, 0.94 up to 64 full tiles, 1.00 up to 128, but 1.03 at 257 to 384.
 inline bool few_tiles_narrow(int ndim, int est_tiles) {
   if (est_tiles <= 0 || ndim % kFullCols != 0) return false;
   const long full = (long)est_tiles * (ndim / kFullCols);
@@ -53,33 +54,33 @@ inline bool few_tiles_narrow(int ndim, int est_tiles) {
 // Rows per tile of the ragged-row GEMMs.  A 256-row tile of an expert with a few dozen rows computes padding, one block
 // per CU, while the weights it streams are the only work that is needed; 64- and 128-row tiles run two blocks per CU
 // (all but the 128-row SwiGLU one), take any width in 128-column tiles and fill the chip with fewer rows.  They feed
-// fewer MFMAs per byte read, so full tiles win again once experts fill them.  The lines were drawn with an earlier main loop (operands
-// through registers, no half-height last tiles).  Us of a whole step with 256 / 128 / 64 rows, at a mean of n rows per expert, even
-// load, with the present one:
-//   32 experts of 2048 x 2048   n = 20: 605 / 609 / 590   n = 60: 557 / 568 / 597   n = 112: 629 / 711 / 794
-//   64 experts of 1408 x 1408   n = 40: 621 / 557 / 506   n = 96: 684 / 625 / 633   n = 112: 708 / 643 / 687
-//   16 experts of 4096 x 2048   n = 40: 547 / 551 / 563   n = 80: 571 / 581 / 646   n = 112: 582 / 594 / 652
+// fewer MFMAs per byte read, so full tiles win again once experts fill them.  Us of a whole step with 256 / 128 / 64 rows, at a mean of n rows
+// per expert, even load, top-4 (2 of 8 experts):
+//   32 experts of 2048 x 2048   n = 20: 587 / 588 / 565   n = 60: 537 / 546 / 577   n = 112: 592 / 683 / 767
+//   64 experts of 1408 x 1408   n = 40: 589 / 506 / 485   n = 96: 656 / 596 / 603   n = 112: 666 / 622 / 662
+//   16 experts of 4096 x 2048   n = 40: 519 / 524 / 538   n = 80: 549 / 558 / 614   n = 112: 559 / 570 / 626
 // A short contraction is mostly prologue and epilogue, which two blocks per CU overlap, and the line of 64 rows lies higher:
-//   16 experts of 768 x 2048    n = 128: 207 / 196 / 178  n = 256: 262 / 249 / 247  n = 320: 287 / 275 / 289
-//   64 experts of 512 x 352     n = 192: 197 / 150 / 158  n = 512: 310 / 268 / 276
+//   16 experts of 768 x 2048    n = 128: 174 / 177 / 157  n = 256: 223 / 216 / 220  n = 320: 256 / 239 / 259
+//   64 experts of 512 x 352     n = 192: 146 / 132 / 140  n = 512: 262 / 234 / 242
 // (the down projection contracts over d_ff: measured up to d_ff = 4 d_model) -- as long as the launch is short of blocks.
 // Many full tiles overlap nothing less by themselves, and the longer the contraction, the fewer are many:
-//   48 experts of 384 x 1536    n = 192 (720 tiles): 408 / 311 / 291    48 of 768 x 2048 (960) 524 / 577 / 597
-//   64 experts of 768 x 1024    n = 192 (640 tiles): 365 / 397 / 424    64 of 704 x 2560, n = 224 (1760) 781 / 902 / 1034
+//   48 experts of 384 x 1536    n = 192 (720 tiles): 328 / 260 / 253    48 of 768 x 2048 (960) 481 / 545 / 559
+//   64 experts of 768 x 1024    n = 192 (640 tiles): 331 / 361 / 395    64 of 704 x 2560, n = 224 (1760) 744 / 855 / 983
 // From there on 64-row tiles end at 64 rows; 128-row ones go on as far as some more tiles (48 experts of 704 x 2752,
-// n = 104, 946 tiles: 552 / 541 / 551), or wherever full tiles pay a second launch for a column tail (64 experts of
-// 640 x 1280, n = 224: 498 / 472 / 507).
+// n = 104, 946 tiles: 499 / 512 / 523), or wherever full tiles pay a second launch for a column tail (64 experts of
+// 640 x 1280, n = 224: 446 / 439 / 467).
 // Above its line of 64 rows a narrow layer takes 128 where two or three rounds of 256 concurrent full tiles would end
-// in one that is partly and at most 0.6 full: 24 experts of 768 x 768 at n = 562 (1.1 rounds) 266 / 251 / 261.  (The half-height last
-// tiles shorten such a round by themselves: at 2.5 rounds, 16 experts of 768 x 2048, n = 512, full tiles are now ahead, 359 / 372 / 392.)
-// A round that is full, or nearly, keeps full tiles: n = 384 at 768 x 2048 (2.0) 298 / 310 / 325; only the shortest contractions gain
-// under any load (8 experts of 512 x 2048, n = 900, 2.0: 251 / 238 / 247).
-// The load is not known here; an uneven one moves every line.  Over 10622 cells of the present loop (24 fixed and 3517 random shapes
-// under even, normal and Gumbel load) the choice takes 0.84 of the time of full tiles on average, is more than 2 % slower than they are
-// in 171 (at worst 22 %), and at least 10 % off the best height in 1928.  Most of those are wide layers beyond the line of 96 rows, where
-// 128-row tiles took 0.86 of the choice's time up to 192 rows, 0.93 up to 256 and 0.96 up to 512, and 1.06 beyond.  (All of these figures are
-// from before a last round of full tiles that is at most half full ran on half-height ones, which is what 128-row tiles gained there: 175
-// rows of 4096 x 1408 or 125 of 2048 x 1024 in each of 8 experts, a step 0.81 and 0.84 of its time before.)
+// in one that is partly and at most 0.6 full: 24 experts of 768 x 768 at n = 562 (1.1 rounds) 223 / 218 / 230, 16 of 768 x 2048 at n = 512
+// (2.5 rounds) 321 / 309 / 350.  Also where that round would be cut in two (tiles_cut): over the 432 cells of this rule 0.94 of full tiles,
+// 0.92 with two rounds and 0.96 with three, faster by 2 % or more in 298 and slower in 46.  (Top-2 in place of top-4, 4096 tokens of that 768
+// x 2048 layer with its optimizer step are one of the others: 441 / 445.)
+// A round that is full, or nearly, keeps full tiles: n = 384 at 768 x 2048 (2.0) 264 / 265 / 289; the shortest contractions
+// (d_model up to 640) take 128, which is within 2 % now (8 experts of 512 x 2048, n = 900, 2.0: 205 / 209 / 214).
+// The load is not known here; an uneven one moves every line.  Over 24032 cells (24 fixed and 7987 random shapes under even, normal and Gumbel
+// load) the choice takes 0.88 of the time of full tiles on average, is more than 2 % slower than they are in 858 (at worst 36 %), and at
+// least 10 % off the best height in 3260.  Most of those are wide layers beyond the line of 96 rows, where 128-row tiles take 0.93 of the
+// choice's time up to 192 rows (0.81 where full tiles are fewer than 128, 1.03 where they are more than 1024), 0.98 up to 256, 1.02 up to 512 and
+// 1.09 beyond.
 inline int row_tile(long rows, int n_experts, int d_model, int d_ff) {
   if (rows <= 48L * n_experts) return kQuarterRows;
   const bool narrow = d_model <= 896 && d_ff <= 4L * d_model;
