@@ -28,7 +28,8 @@
  *    bf16 with round-to-nearest-even on every store); every accumulation is fp32.
  *    Router logits, gates and all weight gradients are fp32 in both modes.
  *  - Results are reproducible bit for bit.  Within a call, rows with equal operands
- *    get equal bits wherever they stand.
+ *    get equal bits wherever they stand: copies of a token, and a token's rows at
+ *    experts that are copies of one another.
  */
 #ifndef SPES_H_
 #define SPES_H_
